@@ -114,8 +114,7 @@ struct Workspace {
   int32_t* topk_idx; float* topk_w;
   int32_t *group_ws, *group_off, *sorted_token, *pair_pos;
   float* x_ss;                        // [T][4] sums of squares of the row quarters (norm of short calls, Act::ss)
-  int32_t *item_expert, *item_tile;   // (expert, row tile) list of the grouped GEMMs of long calls
-  int max_items;
+  GroupItems items;                   // (expert, row tile) list of the grouped GEMMs of long calls
   h16_t* x_lm;      // [S, d]
   float* lm_part;    // [S][tiles][4]
   size_t bytes;
@@ -124,7 +123,26 @@ struct Workspace {
 constexpr int SCORE_ROWS = 256;      // rows per LM-head pass of rollout_score_chunk
 constexpr int ATTN_WGS_MAX = 1024;   // decode attention grid limit (plan arrays are sized for it)
 
-int plane_rows(int T) { return T <= 256 ? gemm_max_splits() * T : T; }
+// Calls of more than 256 tokens on two-term bf16 activations carry them in rows and take the long-call GEMMs.
+bool long_call(const rlx_model_config& c, int T) { return T > 256 && c.activation_split && c.dtype == RLX_DTYPE_BF16; }
+// ... and so do LM heads of more than 128 rows
+bool rows_lmhead(const rlx_model_config& c, int rows) { return rows > 128 && c.activation_split && c.dtype == RLX_DTYPE_BF16; }
+Act call_act(const rlx_model_config& c, h16_t* p, int T, int K, bool rows) {
+  return rows ? make_act_rows(p, T, K) : make_act(p, T, K, c.activation_split ? 2 : 1, c.dtype);
+}
+
+// Split-K planes per token of an output of up to d_model features (the o and down projections, the router) and of the
+// wider q|k|v: sixteen in short calls; in long ones as many as keep the planes under 16384 (8192) rows, at most eight
+// (four), and two (one) however long the call.
+int long_planes(int T, bool wide) {
+  const int most = wide ? 4 : 8, n = (wide ? 8192 : 16384) / T, least = wide ? 1 : 2;
+  return n > most ? most : (n < least ? least : n);
+}
+size_t plane_rows(int T, bool wide) {   // an upper bound that does not fall as T grows
+  if (T <= 256) return (size_t)gemm_max_splits() * T;
+  const size_t most = (wide ? 4 : 8) * (size_t)T, cap = wide ? 8192 : 16384, least = (wide ? 1 : 2) * (size_t)T;
+  return least > cap ? least : (most < cap ? most : cap);
+}
 
 // carve the workspace; with base == nullptr only the size is computed
 Workspace carve(const rlx_model_config& c, char* base, int S, int T, int max_blocks) {
@@ -151,23 +169,27 @@ Workspace carve(const rlx_model_config& c, char* base, int S, int T, int max_blo
   w.meta.rope_cs = (float2*)take((size_t)T * (c.head_dim / 2) * sizeof(float2));
   w.h = (float*)take((size_t)T * c.d_model * 4);
   const int PL = c.activation_split ? 2 : 1;
-  w.xb = (h16_t*)take(frag_act_elems(T, c.d_model, PL) * 2);
+  auto act_bytes = [&](int rows, int K, bool in_rows) {
+    const size_t frag = frag_act_elems(rows, K, PL) * 2, r = in_rows ? act_rows_elems(rows, K) * 2 : 0;
+    return frag > r ? frag : r;
+  };
+  const bool lng = long_call(c, T);
+  w.xb = (h16_t*)take(act_bytes(T, c.d_model, lng));
   w.x_ss = (float*)take((size_t)T * NORM_PARTS * 4);
-  w.router = c.n_experts ? (float*)take((size_t)plane_rows(T) * c.n_experts * 4) : nullptr;
-  w.qkv = (float*)take((size_t)plane_rows(T) * qkv_dim * 4);
+  w.router = c.n_experts ? (float*)take(plane_rows(T, false) * c.n_experts * 4) : nullptr;
+  w.qkv = (float*)take(plane_rows(T, true) * qkv_dim * 4);
   w.q = (h16_t*)take((size_t)PL * T * qdim * 2);
-  w.ob = (h16_t*)take(frag_act_elems(T, qdim, PL) * 2);
+  w.ob = (h16_t*)take(act_bytes(T, qdim, lng));
   w.attn_part = (float*)take((size_t)ATTN_WGS_MAX * 2 * (c.n_q_heads / c.n_kv_heads) * (c.head_dim + 4) * 4);
   w.attn_prefix = (int32_t*)take((size_t)(S + 1) * 4);
   w.attn_wg_seq = (int32_t*)take((size_t)ATTN_WGS_MAX * 4);
   w.attn_hdr = (int32_t*)take(4 * 4);
   w.attn_seq_part = (float*)take((size_t)S * c.n_q_heads * (c.head_dim + 4) * 4);
   w.attn_pre_part = (float*)take((size_t)shared_prefix_max_tiles(S, c.n_kv_heads) * SP_COLS * (c.head_dim + 4) * 4);
-  // o / down planes: up to 16 per token for short calls, two for long ones (gemm_plan_splits_long)
-  w.planes = (float*)take((size_t)(T <= 256 ? plane_rows(T) : 2 * T) * c.d_model * 4);
+  w.planes = (float*)take(plane_rows(T, false) * c.d_model * 4);   // of the o and down projections
   if (c.n_experts) {
     const size_t P = (size_t)T * c.top_k;
-    w.act = (h16_t*)take(frag_act_elems((int)P, c.d_ff_expert, PL) * 2);
+    w.act = (h16_t*)take(act_bytes((int)P, c.d_ff_expert, lng));
     w.moe_y = (float*)take(P * c.d_model * 4);
     w.topk_idx = (int32_t*)take(P * 4);
     w.topk_w = (float*)take(P * 4);
@@ -175,14 +197,17 @@ Workspace carve(const rlx_model_config& c, char* base, int S, int T, int max_blo
     w.group_off = (int32_t*)take((size_t)(c.n_experts + 1) * 4);
     w.sorted_token = (int32_t*)take(P * 4);
     w.pair_pos = (int32_t*)take(P * 4);
-    w.max_items = (int)(P / 256) + c.n_experts;       // tiles of 256 rows: at most one partial tile per expert
-    w.item_expert = (int32_t*)take((size_t)w.max_items * 4);
-    w.item_tile = (int32_t*)take((size_t)w.max_items * 4);
+    w.items.tile_rows = gemm_long_item_rows((int)((P + c.n_experts - 1) / c.n_experts));
+    w.items.max_items = (int)(P / w.items.tile_rows) + c.n_experts;   // at most one partial tile per expert
+    const size_t item_room = (P / 64 + c.n_experts) * 4;              // of the smallest tile: does not fall as T grows
+    w.items.expert = (int32_t*)take(item_room);
+    w.items.tile = (int32_t*)take(item_room);
+    w.items.count = (int32_t*)take(4);
   } else {
-    w.act = (h16_t*)take(frag_act_elems(T, c.d_ff, PL) * 2);
+    w.act = (h16_t*)take(act_bytes(T, c.d_ff, lng));
   }
   const int lm_rows = S > SCORE_ROWS ? S : SCORE_ROWS;   // sampled rows of a call, or one block of scored rows
-  w.x_lm = (h16_t*)take(frag_act_elems(lm_rows, c.d_model, PL) * 2);
+  w.x_lm = (h16_t*)take(act_bytes(lm_rows, c.d_model, rows_lmhead(c, lm_rows)));
   w.lm_part = (float*)take((size_t)lm_rows * lmhead_tiles(c.vocab) * 4 * 4);
   w.bytes = off;
   return w;
@@ -214,8 +239,9 @@ int run_layers(const rlx_model* m, h16_t* pool, int64_t n_blocks, const Workspac
   const bool small = T <= 256;
   const int PL = c.activation_split ? 2 : 1;
   const int FMT = c.dtype;
-  Act xb = make_act(w.xb, T, d, PL, FMT);
-  const Act ob = make_act(w.ob, T, qdim, PL, FMT);
+  const bool lng = long_call(c, T);
+  Act xb = call_act(c, w.xb, T, d, lng);
+  const Act ob = call_act(c, w.ob, T, qdim, lng);
   const RowAct qb = {w.q, (size_t)T * qdim, qdim, PL, FMT};
 
   RLX_HIP(embed_tokens(m->embed, c.vocab, d, io.tokens, io.input_embeds, T, w.h, FMT, st));
@@ -225,15 +251,19 @@ int run_layers(const rlx_model* m, h16_t* pool, int64_t n_blocks, const Workspac
   // MoE decode batches: the gate/up GEMM reads the routing table itself and publishes the grouping (no grouping launch)
   const int rows_per_expert = c.n_experts ? (int)(((long long)T * c.top_k + c.n_experts - 1) / c.n_experts) : 0;
   const bool routed = c.n_experts && small && gemm_routed_form(c.n_experts, c.d_ff_expert, xb, T * c.top_k, rows_per_expert);
-  // long calls: the grouped GEMMs run over the list of (expert, row tile) items that the grouping pass writes
-  const int item_rows = (c.n_experts && !small && moe_group_lists_items(T, c.top_k))
-                            ? gemm_grouped_item_rows(c.n_experts, c.d_ff_expert, d, xb, T * c.top_k, rows_per_expert) : 0;
   // short calls: the norm runs as four workgroups per row and leaves the row's common factor to the GEMMs that read
   // xb (q|k|v, gate/up, router); not for fp16 (unnormalised rows would strain its range) and not where the grouped
   // gate/up goes through a row list
   if (small && FMT == DT_BF16 && rmsnorm_in_parts(d) && (c.n_experts == 0 || routed)) { xb.ss = w.x_ss; xb.eps = c.rms_eps; }
-  const GroupItems items = {w.item_expert, w.item_tile, w.max_items};
-  const GroupItems* itp = item_rows == 256 ? &items : nullptr;
+  // y = x W^T into `y`: split-K planes that the next kernel adds
+  auto planes_of = [&](int N, int K, bool wide) {
+    if (small) return gemm_plan_splits(N, K, T, gemm_max_splits(), m->n_units, PL, FMT);
+    return lng ? gemm_long_splits(N, K, T, long_planes(T, wide), m->n_units) : 1;
+  };
+  auto store = [&](const LinearW& lw, const Act& x, float* y, int splits, bool wide) {
+    return lng ? gemm_long_store(lw, x, T, y, lw.N, long_planes(T, wide), m->n_units, st)
+               : gemm_store(lw, x, T, y, lw.N, splits, st);
+  };
   auto norm = [&](const h16_t* gain, const int32_t* rows, int n_rows, const Act& x, float* xf) -> hipError_t {
     NormArgs a = {};
     a.h = w.h; a.gain = gain; a.d = d; a.T = n_rows; a.T_total = T; a.eps = c.rms_eps; a.rows = rows;
@@ -251,8 +281,8 @@ int run_layers(const rlx_model* m, h16_t* pool, int64_t n_blocks, const Workspac
     wqkv.seg[1] = m->wk[l]; wqkv.rows[1] = kvdim;
     wqkv.seg[2] = m->wv[l]; wqkv.rows[2] = kvdim;
     wqkv.N = qkv_dim; wqkv.K = d;
-    const int s_qkv = small ? gemm_plan_splits(qkv_dim, d, T, gemm_max_splits(), m->n_units, PL, FMT) : 1;
-    RLX_LAUNCH(RLX_K_QKV, gemm_store(wqkv, xb, T, w.qkv, qkv_dim, s_qkv, st));
+    const int s_qkv = planes_of(qkv_dim, d, true);
+    RLX_LAUNCH(RLX_K_QKV, store(wqkv, xb, w.qkv, s_qkv, true));
 
     h16_t* pool_layer = pool + (size_t)l * n_blocks * block_elems(c);
     RopeArgs r = {};
@@ -286,40 +316,53 @@ int run_layers(const rlx_model* m, h16_t* pool, int64_t n_blocks, const Workspac
       RLX_LAUNCH(RLX_K_ATTN, attention_prefill(at, st));
     }
 
-    const int s_o = small ? gemm_plan_splits(d, qdim, T, gemm_max_splits(), m->n_units, PL, FMT)
-                          : gemm_plan_splits_long(d, T, xb.planes, xb.dtype, m->n_units);
-    RLX_LAUNCH(RLX_K_OPROJ, gemm_store(linear1(m->wo[l], d, qdim), ob, T, w.planes, d, s_o, st));
+    const int s_o = planes_of(d, qdim, false);
+    RLX_LAUNCH(RLX_K_OPROJ, store(linear1(m->wo[l], d, qdim), ob, w.planes, s_o, false));
     pend_planes = w.planes; pend_n = s_o;
 
     RLX_LAUNCH(RLX_K_NORM, norm(m->ffn_norm[l], nullptr, T, xb, nullptr));
     if (c.n_experts == 0) {
-      const Act act = make_act(w.act, T, c.d_ff, PL, FMT);
-      RLX_LAUNCH(RLX_K_GATEUP, gemm_swiglu(m->w_gate_up[l], c.d_ff, d, xb, T, act, st));
-      const int s_d = small ? gemm_plan_splits(d, c.d_ff, T, gemm_max_splits(), m->n_units, PL, FMT)
-                            : gemm_plan_splits_long(d, T, xb.planes, xb.dtype, m->n_units);
-      RLX_LAUNCH(RLX_K_DOWN, gemm_store(linear1(m->w_down[l], d, c.d_ff), act, T, w.planes, d, s_d, st));
+      const Act act = call_act(c, w.act, T, c.d_ff, lng);
+      RLX_LAUNCH(RLX_K_GATEUP, lng ? gemm_long_swiglu(m->w_gate_up[l], c.d_ff, d, xb, T, act, m->n_units, st)
+                                   : gemm_swiglu(m->w_gate_up[l], c.d_ff, d, xb, T, act, st));
+      const int s_d = planes_of(d, c.d_ff, false);
+      RLX_LAUNCH(RLX_K_DOWN, store(linear1(m->w_down[l], d, c.d_ff), act, w.planes, s_d, false));
       pend_planes = w.planes; pend_n = s_d;
     } else {
-      const int s_r = small ? gemm_plan_splits(c.n_experts, d, T, gemm_max_splits(), m->n_units, PL, FMT) : 1;
-      RLX_LAUNCH(RLX_K_ROUTER, gemm_store(linear1(m->w_router[l], c.n_experts, d), xb, T, w.router, c.n_experts, s_r, st));
+      const int s_r = planes_of(c.n_experts, d, false);
+      RLX_LAUNCH(RLX_K_ROUTER, store(linear1(m->w_router[l], c.n_experts, d), xb, w.router, s_r, false));
       RouterArgs ra = {};
       ra.logits = w.router; ra.n_planes = s_r; ra.T = T; ra.E = c.n_experts; ra.top_k = c.top_k;
       ra.topk_idx = w.topk_idx; ra.topk_w = w.topk_w; ra.routing_out = io.out_routing; ra.layer = l;
       ra.n_layers = c.n_layers; ra.tok_live = w.meta.tok_live; ra.replay_idx = io.replay_routing;
-      RLX_LAUNCH(RLX_K_GROUP, moe_route(ra, w.group_off, w.sorted_token, w.pair_pos, w.group_ws, !routed, itp ? item_rows : 0,
-                                         w.max_items, w.item_expert, w.item_tile, st));
-      const Act act = make_act(w.act, T * c.top_k, c.d_ff_expert, PL, FMT);
-      if (routed)
+      RLX_LAUNCH(RLX_K_GROUP, moe_route(ra, w.group_off, w.sorted_token, w.pair_pos, w.group_ws, !routed,
+                                         lng ? &w.items : nullptr, st));
+      const Act act = call_act(c, w.act, T * c.top_k, c.d_ff_expert, lng);
+      if (lng)
+        RLX_LAUNCH(RLX_K_GATEUP, gemm_long_grouped_swiglu(m->w_gate_up[l], c.d_ff_expert, d, xb, w.sorted_token, w.group_off,
+                                                          act, w.items, st));
+      else if (routed)
         RLX_LAUNCH(RLX_K_GATEUP, gemm_routed_swiglu(m->w_gate_up[l], c.n_experts, c.d_ff_expert, d, xb, w.topk_idx,
                                                     T * c.top_k, c.top_k, T, act, w.group_off, w.pair_pos, st));
       else
         RLX_LAUNCH(RLX_K_GATEUP, gemm_grouped_swiglu(m->w_gate_up[l], c.n_experts, c.d_ff_expert, d, xb,
-                                                     w.sorted_token, w.group_off, T, rows_per_expert, act, itp, st));
-      RLX_LAUNCH(RLX_K_DOWN, gemm_grouped_store(m->w_down[l], c.n_experts, d, c.d_ff_expert, act, w.group_off, T,
-                                                rows_per_expert, w.moe_y, itp, st));
+                                                     w.sorted_token, w.group_off, T, rows_per_expert, act, st));
+      if (lng)
+        RLX_LAUNCH(RLX_K_DOWN, gemm_long_grouped_store(m->w_down[l], d, c.d_ff_expert, act, w.group_off, w.moe_y, w.items, st));
+      else
+        RLX_LAUNCH(RLX_K_DOWN, gemm_grouped_store(m->w_down[l], c.n_experts, d, c.d_ff_expert, act, w.group_off, T,
+                                                  rows_per_expert, w.moe_y, st));
       pend_moe = true;
     }
   }
+
+  auto lmhead = [&](const Act& x, int rows, float* logits, const uint64_t* seeds, const int32_t* sample_pos,
+                    const int32_t* row_seq, bool draw) {
+    return x.pitch ? gemm_long_lmhead(m->lm_head, c.vocab, d, x, rows, logits, w.lm_part, seeds, io.temperature, sample_pos,
+                                      row_seq, draw, m->n_units, st)
+                   : gemm_lmhead(m->lm_head, c.vocab, d, x, rows, logits, w.lm_part, seeds, io.temperature, sample_pos, row_seq,
+                                 draw, st);
+  };
 
   if (io.score) {
     // every position is scored: final norm + LM head (log-sum-exp partials only, no draw) + target logit, in
@@ -327,11 +370,10 @@ int run_layers(const rlx_model* m, h16_t* pool, int64_t n_blocks, const Workspac
     const float* pp = pend_planes; const int pn = pend_n; const bool pm = pend_moe;
     for (int r0 = 0; r0 < T; r0 += SCORE_ROWS) {
       const int n = T - r0 < SCORE_ROWS ? T - r0 : SCORE_ROWS;
-      const Act x_lm = make_act(w.x_lm, n, d, PL, FMT);
+      const Act x_lm = call_act(c, w.x_lm, n, d, rows_lmhead(c, n));
       pend_planes = pp; pend_n = pn; pend_moe = pm;
       RLX_HIP(norm(m->final_norm, w.meta.tok_iota + r0, n, x_lm, nullptr));
-      RLX_LAUNCH(RLX_K_LMHEAD, gemm_lmhead(m->lm_head, c.vocab, d, x_lm, n, nullptr, w.lm_part, nullptr, io.temperature,
-                                           nullptr, w.meta.tok_seq + r0, false, st));
+      RLX_LAUNCH(RLX_K_LMHEAD, lmhead(x_lm, n, nullptr, nullptr, nullptr, w.meta.tok_seq + r0, false));
       FinalizeArgs f = {};
       f.n_rows = n; f.n_tiles = lmhead_tiles(c.vocab); f.vocab = c.vocab; f.d = d;
       f.part = w.lm_part; f.x = x_lm; f.w_lm = m->lm_head;
@@ -344,10 +386,9 @@ int run_layers(const rlx_model* m, h16_t* pool, int64_t n_blocks, const Workspac
 
   // final norm of the rows that emit a token, LM head with fused log-sum-exp / Gumbel-max partials
   const int S = io.n_seqs;
-  const Act x_lm = make_act(w.x_lm, S, d, PL, FMT);
+  const Act x_lm = call_act(c, w.x_lm, S, d, rows_lmhead(c, S));
   RLX_HIP(norm(m->final_norm, w.meta.sample_row, S, x_lm, nullptr));
-  RLX_LAUNCH(RLX_K_LMHEAD, gemm_lmhead(m->lm_head, c.vocab, d, x_lm, S, io.out_logits, w.lm_part, io.seeds,
-                                       io.temperature, w.meta.sample_pos, nullptr, true, st));
+  RLX_LAUNCH(RLX_K_LMHEAD, lmhead(x_lm, S, io.out_logits, io.seeds, w.meta.sample_pos, nullptr, true));
   FinalizeArgs f = {};
   f.n_rows = S; f.n_tiles = lmhead_tiles(c.vocab); f.vocab = c.vocab; f.d = d;
   f.part = w.lm_part; f.x = x_lm; f.w_lm = m->lm_head;

@@ -372,7 +372,7 @@ __global__ __launch_bounds__(256) void attn_decode_merge_kernel(AttnDecodeArgs a
   constexpr int PS = HD + 4;
   const int seq = blockIdx.x / a.Hkv, kvh = blockIdx.x % a.Hkv;
   const int lane = threadIdx.x;
-  const int group = a.Hq / a.Hkv, PL = a.o.planes, mtiles = a.o.mtiles();
+  const int group = a.Hq / a.Hkv, PL = a.o.planes;
   const int np = a.unit_prefix[seq + 1] - a.unit_prefix[seq];
   const Shares sh = load_shares(a.plan_hdr);
   const int xs = a.Hkv * a.unit_prefix[seq] + kvh * np;
@@ -435,14 +435,14 @@ __global__ __launch_bounds__(256) void attn_decode_merge_kernel(AttnDecodeArgs a
     h16_t hi[8], lo[8];
 #pragma unroll
     for (int e = 0; e < 8; ++e) split_h16(l > 0.f ? o[e] / l : 0.f, hi[e], lo[e], a.o.dtype);
-    h16_t* dst = a.o.p + frag_act_offset(seq, (kvh * group + j) * HD + d0, 0, mtiles, PL);
+    h16_t* dst = a.o.p + a.o.group_offset(seq, (kvh * group + j) * HD + d0);
     u32x4 pk = {(uint32_t)hi[0] | ((uint32_t)hi[1] << 16), (uint32_t)hi[2] | ((uint32_t)hi[3] << 16),
                 (uint32_t)hi[4] | ((uint32_t)hi[5] << 16), (uint32_t)hi[6] | ((uint32_t)hi[7] << 16)};
     *reinterpret_cast<u32x4*>(dst) = pk;
     if (PL == 2) {
       u32x4 pk2 = {(uint32_t)lo[0] | ((uint32_t)lo[1] << 16), (uint32_t)lo[2] | ((uint32_t)lo[3] << 16),
                    (uint32_t)lo[4] | ((uint32_t)lo[5] << 16), (uint32_t)lo[6] | ((uint32_t)lo[7] << 16)};
-      *reinterpret_cast<u32x4*>(dst + 512) = pk2;
+      *reinterpret_cast<u32x4*>(dst + a.o.small_terms()) = pk2;
     }
   }
 }

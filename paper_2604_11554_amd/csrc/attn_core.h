@@ -174,7 +174,6 @@ template <int HD, int NCT, int PL, int FMT>
 __device__ __forceinline__ void store_column(const WaveState<HD, NCT>& st, int c, const Act& o, int trow, int head,
                                              int g) {
   const float inv = st.l[c] > 0.f ? 1.f / st.l[c] : 0.f;
-  const int mtiles = o.mtiles();
 #pragma unroll
   for (int dt = 0; dt < HD / 16; ++dt) {
     f32x4 v = st.o[c][dt] * inv;
@@ -182,12 +181,12 @@ __device__ __forceinline__ void store_column(const WaveState<HD, NCT>& st, int c
 #pragma unroll
     for (int j = 0; j < 4; ++j) split_h16<FMT>(v[j], hi[j], lo[j]);
     const int col = head * HD + 16 * dt + 4 * g;   // feature index of the output projection's K
-    h16_t* dst = o.p + frag_act_offset(trow, col & ~7, 0, mtiles, PL) + (col & 7);
+    h16_t* dst = o.p + o.group_offset(trow, col & ~7) + (col & 7);
     u32x2 p = {(uint32_t)hi[0] | ((uint32_t)hi[1] << 16), (uint32_t)hi[2] | ((uint32_t)hi[3] << 16)};
     *reinterpret_cast<u32x2*>(dst) = p;
     if (PL == 2) {
       u32x2 p2 = {(uint32_t)lo[0] | ((uint32_t)lo[1] << 16), (uint32_t)lo[2] | ((uint32_t)lo[3] << 16)};
-      *reinterpret_cast<u32x2*>(dst + 512) = p2;
+      *reinterpret_cast<u32x2*>(dst + o.small_terms()) = p2;
     }
   }
 }

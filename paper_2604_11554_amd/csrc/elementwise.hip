@@ -126,17 +126,16 @@ __global__ __launch_bounds__(256) void rmsnorm_kernel(NormArgs a) {
     // stream is left alone.  Uniform over the workgroup, before any barrier.
     for (int i = threadIdx.x; i < nv; i += 256) {
       const int k = 4 * i;
-      h16_t* xo = a.x.p + frag_act_offset(r, k & ~7, 0, a.x.mtiles(), a.x.planes) + (k & 7);
+      h16_t* xo = a.x.p + a.x.group_offset(r, k & ~7) + (k & 7);
       const u32x2 z = {0u, 0u};
       *reinterpret_cast<u32x2*>(xo) = z;
-      if (a.x.planes == 2) *reinterpret_cast<u32x2*>(xo + 512) = z;
+      if (a.x.planes == 2) *reinterpret_cast<u32x2*>(xo + a.x.small_terms()) = z;
       if (a.xf) *reinterpret_cast<f32x4*>(a.xf + (size_t)r * a.d + 4 * i) = f32x4{0.f, 0.f, 0.f, 0.f};
     }
     return;
   }
   float* hrow = a.h + (size_t)t * a.d;
   const bool adding = (a.add != nullptr) || (a.moe_y != nullptr);
-  const int mtiles = a.x.mtiles();
   const bool single = nv <= 256 * NV;
   const int dt = a.x.dtype;
   f32x4 keep[NV];
@@ -224,12 +223,12 @@ __global__ __launch_bounds__(256) void rmsnorm_kernel(NormArgs a) {
 #pragma unroll
       for (int e = 0; e < 4; ++e) split_h16(o[e], hi[e], lo[e], dt);
       const int k = 4 * i;
-      h16_t* xo = a.x.p + frag_act_offset(r, k & ~7, 0, mtiles, a.x.planes) + (k & 7);
+      h16_t* xo = a.x.p + a.x.group_offset(r, k & ~7) + (k & 7);
       u32x2 pk = {(uint32_t)hi[0] | ((uint32_t)hi[1] << 16), (uint32_t)hi[2] | ((uint32_t)hi[3] << 16)};
       *reinterpret_cast<u32x2*>(xo) = pk;
       if (a.x.planes == 2) {
         u32x2 pk2 = {(uint32_t)lo[0] | ((uint32_t)lo[1] << 16), (uint32_t)lo[2] | ((uint32_t)lo[3] << 16)};
-        *reinterpret_cast<u32x2*>(xo + 512) = pk2;
+        *reinterpret_cast<u32x2*>(xo + a.x.small_terms()) = pk2;
       }
       if (a.xf) *reinterpret_cast<f32x4*>(a.xf + (size_t)r * a.d + 4 * i) = o;
     }
@@ -368,7 +367,7 @@ __global__ __launch_bounds__(256) void qk_rope_append_kernel(RopeArgs a) {
   }
 }
 
-// Long calls (one plane): the kernel above spends its time issuing instructions for two elements per lane, so here
+// Long calls: the kernel above spends its time issuing instructions for two elements per lane, so here
 // 16 lanes share a head and a wave takes four heads of NT tokens.  Lane j of a head owns the pairs j + 16 k
 // (k < HD / 32): summing its squares as (k = 0 with 2) + (1 with 3) and then across the 16 lanes is the butterfly
 // of the 64-lane form with its first two levels done locally, and every other operation is per element, so both
@@ -410,10 +409,26 @@ __global__ __launch_bounds__(256) void qk_rope_append_wide_kernel(RopeArgs a) {
     const float* src = a.qkv + ((size_t)tc[i] * n_heads + hc) * HD;
 #pragma unroll
     for (int k = 0; k < PPL; ++k) {
-      x0[i][k] = src[j + 16 * k];
-      x1[i][k] = src[j + 16 * k + half];
+      x0[i][k] = 0.f + src[j + 16 * k];              // the plane sum of the 64-lane form
+      x1[i][k] = 0.f + src[j + 16 * k + half];
       cs[i][k] = a.rope_cs[(size_t)tc[i] * half + j + 16 * k];
     }
+  }
+  for (int p = 1; p < a.n_planes; ++p) {             // further split-K planes, added in plane order
+    const float* plane = a.qkv + (size_t)p * a.T * n_heads * HD;
+    float v0[NT][PPL], v1[NT][PPL];
+#pragma unroll
+    for (int i = 0; i < NT; ++i)
+#pragma unroll
+      for (int k = 0; k < PPL; ++k) {
+        const float* src = plane + ((size_t)tc[i] * n_heads + hc) * HD;
+        v0[i][k] = src[j + 16 * k];
+        v1[i][k] = src[j + 16 * k + half];
+      }
+#pragma unroll
+    for (int i = 0; i < NT; ++i)
+#pragma unroll
+      for (int k = 0; k < PPL; ++k) { x0[i][k] += v0[i][k]; x1[i][k] += v1[i][k]; }
   }
   int64_t blk[NT];
 #pragma unroll
@@ -433,8 +448,8 @@ __global__ __launch_bounds__(256) void qk_rope_append_wide_kernel(RopeArgs a) {
     float u0[PPL], u1[PPL], p[PPL];
 #pragma unroll
     for (int k = 0; k < PPL; ++k) {
-      u0[k] = 0.f + x0[i][k];                      // the plane sum of the 64-lane form with one plane
-      u1[k] = 0.f + x1[i][k];
+      u0[k] = x0[i][k];
+      u1[k] = x1[i][k];
       p[k] = __builtin_fmaf(u1[k], u1[k], u0[k] * u0[k]);
     }
     float ss = PPL == 4 ? (p[0] + p[2]) + (p[1] + p[3]) : p[0] + p[1];
@@ -604,7 +619,7 @@ hipError_t rmsnorm(const NormArgs& a, hipStream_t st) {
 
 hipError_t qk_rope_append(const RopeArgs& a, hipStream_t st) {
   const int n_heads = a.Hq + 2 * a.Hkv;
-  if (a.T > 1024 && a.n_planes == 1 && (a.hd == 128 || a.hd == 64)) {
+  if (a.T > 1024 && (a.hd == 128 || a.hd == 64)) {
     const dim3 grid((n_heads + 15) / 16, (a.T + 3) / 4);
     if (a.hd == 128) hipLaunchKernelGGL((qk_rope_append_wide_kernel<128, 4>), grid, dim3(256), 0, st, a);
     else hipLaunchKernelGGL((qk_rope_append_wide_kernel<64, 4>), grid, dim3(256), 0, st, a);

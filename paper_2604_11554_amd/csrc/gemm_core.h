@@ -1,0 +1,209 @@
+// What the GEMM kernels share: their argument block and their epilogues (plain store, SwiGLU, LM head with fused
+// log-sum-exp and Gumbel-max partials per 32-row weight tile).
+#pragma once
+#include "kernels.h"
+
+namespace rlx {
+
+struct GemmArgs {
+  const h16_t* x;        // fragment-ordered activations [T_x, K], `PL` planes
+  int x_mtiles;           // ceil(T_x / 32)
+  const float* x_ss;      // optional: activation row t lacks the factor rstd(t) of its norm (Act::ss); outputs take it
+  float x_eps;
+  const int32_t* x_rows;  // grouped gate/up: logical row r of the group reads activation row x_rows[r]
+  const h16_t* w[3];     // packed weights, up to three stacked row segments
+  int w_tiles[3];         // 32-row tiles per segment
+  int N, K, T;
+  int ksteps_per_split;   // k-steps (16 wide) per blockIdx.y
+  float* y;               // EPI_STORE: [splits][T][ldy]
+  int ldy;
+  h16_t* act;            // EPI_SWIGLU: fragment-ordered [act_rows, N], `PL` planes
+  int act_mtiles;
+  // LM-head epilogue
+  float* logits;          // optional [T][N]
+  float* part;            // [T][n_tiles][4] = max, sumexp, best score, best index (as float bits)
+  const uint64_t* seeds;
+  const float* temperature;
+  const int32_t* sample_pos;
+  const int32_t* row_seq;     // optional: row t takes its temperature from entry row_seq[t] (scoring: token -> sequence)
+  int draw;                   // 0: no Gumbel-max draw (scoring): the random words are not generated
+  // expert-grouped form: blockIdx.y is the expert, its rows are [group_off[e], group_off[e+1])
+  const int32_t* group_off;
+  size_t w_expert_stride;     // packed elements between consecutive experts' matrices
+  // expert-grouped decode form without a grouping pass: the kernel finds its expert's rows in the routing table itself
+  const int32_t* route_idx;   // [n_pairs] expert of pair p = token * top_k + slot, or null (rows come from group_off)
+  int n_pairs, top_k;
+  int32_t* pub_group_off;     // [E + 1] written by this launch: first row of every expert in expert order
+  int32_t* pub_pair_pos;      // [n_pairs] written by this launch: row of every pair in expert order
+  // long-call form (gemm_long.hip): x is in rows (Act::pitch), and so is act
+  size_t x_pitch, act_pitch;
+  int splits;                 // K ranges of ksteps_per_split k-steps, a plane of y each
+  const int32_t* item_expert; // grouped: expert and row tile of every item, and the number of items (GroupItems)
+  const int32_t* item_tile;
+  const int32_t* n_items;
+};
+
+enum { EPI_STORE = 0, EPI_SWIGLU = 1, EPI_LMHEAD = 2 };
+
+// ---- Philox-4x32-10 (Salmon et al., SC'11), written from the published definition ----
+__device__ __forceinline__ void philox4x32_10(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3, uint32_t k0,
+                                              uint32_t k1, uint32_t (&out)[4]) {
+#pragma unroll
+  for (int r = 0; r < 10; ++r) {
+    uint32_t h0 = __umulhi(0xD2511F53u, c0), l0 = 0xD2511F53u * c0;
+    uint32_t h1 = __umulhi(0xCD9E8D57u, c2), l1 = 0xCD9E8D57u * c2;
+    uint32_t n0 = h1 ^ c1 ^ k0, n2 = h0 ^ c3 ^ k1;
+    c0 = n0; c1 = l1; c2 = n2; c3 = l0;
+    k0 += 0x9E3779B9u; k1 += 0xBB67AE85u;
+  }
+  out[0] = c0; out[1] = c1; out[2] = c2; out[3] = c3;
+}
+
+// Gumbel(0,1) from a 32-bit word: u = (R + 0.5) 2^-32, g = -log(-log u).  The largest values of g, the ones that
+// win the draw, come from u next to 1, so for the upper half of the range -log u is taken from w = 1 - u (exact
+// from the integer): the series w + w^2/2 + w^3/3 + w^4/4 below 2^-6 (relative error w^4/5 < 2e-8), the
+// hardware logarithm of 1 - w above (absolute error ~1e-7 on a value of at least 0.0156).  The hardware
+// logarithm's absolute error of ~1e-7 is also what the other two logarithms carry (their arguments are not near
+// 1 where it would matter, or their result is near 0 where it does not): g is within ~1e-5 of the exact value,
+// three orders below the tolerance on the scores it is added to.  Branch-free: lanes of a wave hold both halves.
+__device__ __forceinline__ float gumbel_from_u32(uint32_t r) {
+  const bool upper = r >= 0x80000000u;
+  const float u = ((float)r + 0.5f) * 2.3283064365386963e-10f;
+  const float w = ((float)(0xFFFFFFFFu - r) + 0.5f) * 2.3283064365386963e-10f;   // 1 - u, meaningful when upper
+  const float series = w * (1.f + w * (0.5f + w * (0.33333334f + w * 0.25f)));
+  const float nl_hi = w < 0.015625f ? series : -__logf(1.f - w);
+  const float nl = upper ? nl_hi : -__logf(u);
+  return -__logf(nl);
+}
+
+// Epilogue of one 32-row weight tile `nt` over token tiles mt0 .. mt0 + MT - 1: lane holds token r32 of each token
+// tile, rows n0 + 8q + 4*half + {0..3}, q = 0..3, of the accumulators.
+// factor that the norm left out of activation row `tok` (Act::ss): the same expression as in the norm kernel
+__device__ __forceinline__ f32x4 row_ss(const GemmArgs& a, int tok) {
+  return *reinterpret_cast<const f32x4*>(a.x_ss + (size_t)NORM_PARTS * tok);
+}
+__device__ __forceinline__ float row_rstd(const GemmArgs& a, const f32x4& p) {
+  return 1.0f / sqrtf(((p[0] + p[1]) + (p[2] + p[3])) / (float)a.K + a.x_eps);
+}
+
+// rs[m]: factor of the lane's activation row in token tile m (row_rstd, or 1), fetched by the caller before its main
+// loop so that the round trip is not spent at the end of the kernel
+template <int MT, int EPI, int PL, int FMT>
+__device__ __forceinline__ void tile_epilogue(const GemmArgs& a, const f32x16 (&acc)[MT], int nt, int n_tiles, int mt0,
+                                              int split, int row_base, int lane, const float (&rs)[MT]) {
+  const int r32 = lane & 31, half = lane >> 5;
+  const int n0 = nt * 32;
+  if (EPI == EPI_STORE) {
+#pragma unroll
+    for (int m = 0; m < MT; ++m) {
+      const int t = (mt0 + m) * 32 + r32;
+      if (t >= a.T) continue;
+      float* dst = a.y + ((size_t)split * a.T + row_base + t) * a.ldy;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int nrow = n0 + 8 * q + 4 * half;
+        f32x4 v = {acc[m][4 * q], acc[m][4 * q + 1], acc[m][4 * q + 2], acc[m][4 * q + 3]};
+        if (a.x_ss) v *= rs[m];
+        if (nrow + 3 < a.N) {
+          *reinterpret_cast<f32x4*>(dst + nrow) = v;
+        } else {
+#pragma unroll
+          for (int j = 0; j < 4; ++j)
+            if (nrow + j < a.N) dst[nrow + j] = v[j];
+        }
+      }
+    }
+  } else if (EPI == EPI_SWIGLU) {
+    // The packed matrix interleaves gate and up: rows 0..15 of a tile are gate rows of features
+    // 16 nt .. 16 nt + 15, rows 16..31 the matching up rows, so a lane holds both halves of a pair
+    // (register groups q and q + 2).  The output feature is the K index of the down projection.
+    const int n_feat = a.N >> 1;
+#pragma unroll
+    for (int m = 0; m < MT; ++m) {
+      const int t = (mt0 + m) * 32 + r32;
+      if (t >= a.T) continue;
+      const int orow = row_base + t;
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+        const int feat = nt * 16 + 8 * q + 4 * half;   // four consecutive features inside one 8-group
+        if (feat >= n_feat) continue;
+        h16_t hi[4], lo[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          float g = acc[m][4 * q + j], u = acc[m][4 * (q + 2) + j];
+          if (a.x_ss) { g *= rs[m]; u *= rs[m]; }
+          split_h16<FMT>(g / (1.f + __expf(-g)) * u, hi[j], lo[j]);
+        }
+        h16_t* dst = a.act + frag_act_offset(orow, feat & ~7, 0, a.act_mtiles, PL) + (feat & 7);
+        u32x2 pk = {(uint32_t)hi[0] | ((uint32_t)hi[1] << 16), (uint32_t)hi[2] | ((uint32_t)hi[3] << 16)};
+        *reinterpret_cast<u32x2*>(dst) = pk;
+        if (PL == 2) {
+          u32x2 pk2 = {(uint32_t)lo[0] | ((uint32_t)lo[1] << 16), (uint32_t)lo[2] | ((uint32_t)lo[3] << 16)};
+          *reinterpret_cast<u32x2*>(dst + 512) = pk2;
+        }
+      }
+    }
+  } else {  // EPI_LMHEAD: per token, reduce this tile's 32 vocabulary rows to (max, sumexp, best, argbest)
+#pragma unroll
+    for (int m = 0; m < MT; ++m) {
+      const int t = (mt0 + m) * 32 + r32;
+      const bool ok = t < a.T;
+      float mx = -INFINITY, se = 0.f, best = -INFINITY;
+      int besti = 0x7FFFFFFF;
+      if (ok) {
+        const float temp = a.temperature[a.row_seq ? a.row_seq[t] : t];
+        const float invt = temp > 0.f ? 1.f / temp : 1.f;
+        const bool draw = a.draw != 0 && temp > 0.f;          // uniform over the launch when draw == 0
+        const uint64_t seed = a.draw ? a.seeds[t] : 0;
+        const uint32_t pos = a.draw ? (uint32_t)a.sample_pos[t] : 0u;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const int nrow = n0 + 8 * q + 4 * half;  // multiple of 4: one Philox block covers the four ids
+          if (nrow >= a.N) continue;
+          uint32_t rnd[4] = {0u, 0u, 0u, 0u};
+          if (a.draw) philox4x32_10((uint32_t)(nrow >> 2), pos, 0u, 0u, (uint32_t)seed, (uint32_t)(seed >> 32), rnd);
+          f32x4 v = {acc[m][4 * q], acc[m][4 * q + 1], acc[m][4 * q + 2], acc[m][4 * q + 3]};
+          if (a.logits) {
+            if (nrow + 3 < a.N) {
+              *reinterpret_cast<f32x4*>(a.logits + (size_t)t * a.N + nrow) = v;
+            } else {
+#pragma unroll
+              for (int j = 0; j < 4; ++j)
+                if (nrow + j < a.N) a.logits[(size_t)t * a.N + nrow + j] = v[j];
+            }
+          }
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            if (nrow + j < a.N) {
+              const float z = v[j] * invt;
+              const float sc = draw ? z + gumbel_from_u32(rnd[j]) : z;
+              if (sc > best) { best = sc; besti = nrow + j; }   // ascending ids: ties keep the smaller one
+              const float nm = fmaxf(mx, z);
+              se = se * __expf(mx - nm) + __expf(z - nm);
+              mx = nm;
+            }
+          }
+        }
+      }
+      // merge the two half-waves (rows 8q+0..3 and 8q+4..7) of the same token
+      const float omx = __shfl_xor(mx, 32, WAVE), ose = __shfl_xor(se, 32, WAVE);
+      const float obest = __shfl_xor(best, 32, WAVE);
+      const int obesti = __shfl_xor(besti, 32, WAVE);
+      if (obest > best || (obest == best && obesti < besti)) { best = obest; besti = obesti; }
+      const float nm = fmaxf(mx, omx);
+      if (nm > -INFINITY) {
+        // fixed operand order (lower half first) so both half-waves compute the same bits
+        const float lo_m = half ? omx : mx, lo_s = half ? ose : se, hi_m = half ? mx : omx, hi_s = half ? se : ose;
+        se = lo_s * (lo_m == -INFINITY ? 0.f : __expf(lo_m - nm)) + hi_s * (hi_m == -INFINITY ? 0.f : __expf(hi_m - nm));
+        mx = nm;
+      }
+      if (ok && half == 0) {
+        float* o = a.part + ((size_t)t * n_tiles + nt) * 4;
+        f32x4 pv = {mx, se, best, __int_as_float(besti)};
+        *reinterpret_cast<f32x4*>(o) = pv;
+      }
+    }
+  }
+}
+
+}  // namespace rlx

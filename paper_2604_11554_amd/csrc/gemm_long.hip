@@ -1,0 +1,439 @@
+// GEMM of long calls (prefill and scoring chunks, LM heads of many rows) on two-term bf16 activations.
+//
+//   y[t, n] = sum_k x[t, k] * W[n, k],  x = hi + lo: two MFMA 32x32x16 per weight fragment and 32 x 32 outputs
+//
+// A workgroup of WR x WT waves computes 128 WR weight rows x 64 WT tokens, a wave 128 x 64 of them (4 weight tiles x 2
+// token tiles: 128 accumulator registers).  Both operands pass through LDS, copied there by the hardware
+// (global_load_lds, 16 bytes per lane, no registers in between), in stages of 32 k, NB stage buffers deep.
+//  - Weights: the packed layout's fragments, 1 KB per copy, read back linearly.
+//  - Activations: rows (Act::pitch): the 32 k of a stage are one 128-byte line of a row (eight 16-byte chunks: per
+//    8 k the large terms, then the small ones), so any list of rows can be gathered a full line at a time; a copy
+//    takes eight rows.  In LDS row r's chunk c sits in slot c ^ ((r >> 1) & 7) of the row's 128 bytes (the copy picks
+//    the chunk per lane), which spreads the 16 rows that a fragment read touches at a time over all 64 banks.
+// What bounds it: the matrix cores under the card's power limit (the same loop without copies and LDS reads runs at
+// 1.57-1.67 PFLOP/s on random data and at 2.07 on zeros) and the copies: issued in a burst after the barrier they
+// hold up the waves' own products, so they are spread over the stage, two per eight products.  Measured at 32 768
+// tokens, K 2560, N 6144: 1.24 PFLOP/s (both terms counted) with the burst, 1.31 spread; stores of 16 bytes per lane
+// to 32 rows at a time 1.33, of 128-byte lines (the store form swaps the operands, so that lanes run along n) 1.36.
+// Per accumulator the products come in the order of the skinny form (k ascending, small term first).
+#include <mutex>
+
+#include "gemm_core.h"
+
+namespace rlx {
+namespace {
+
+// One copy of 64 x 16 bytes: lane i's 16 bytes at `g` -> LDS address lds + 16 i.  The wait state between the write of
+// m0 and its use is the assembler's to place, hence the s_nop.  No register is written by the copy.
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"   // m0 as a clobber: "reserved register"
+__device__ __forceinline__ void copy_to_lds(const void* g, uint32_t lds) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds), "v"(g) : "memory", "m0");
+}
+#pragma clang diagnostic pop
+// Waits until at most N of this wave's copies are in flight and its LDS reads are done, then for the other waves.
+template <int N>
+__device__ __forceinline__ void wait_copies_and_barrier() {
+  asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory");
+}
+
+template <int WR, int WT, int NB>
+struct LongTiling {
+  static constexpr int WAVES = WR * WT, ROWS = 128 * WR, TOKENS = 64 * WT;
+  static constexpr int WFR = 8 * WR, XFR = 8 * WT;                 // KB of weights and of activations per stage
+  static constexpr int STAGE = (WFR + XFR) * 1024;
+  static constexpr int PW = WFR / WAVES, PX = XFR / WAVES, P = PW + PX;   // copies per wave and stage
+  static constexpr int LDS_BYTES = NB * STAGE;
+  static_assert(WFR % WAVES == 0 && XFR % WAVES == 0, "the waves share a stage's copies evenly");
+};
+
+__device__ __forceinline__ uint32_t pack_bf16(float a, float b) {   // round to nearest even, a in the low half
+  typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+  const bf16x2 v = {(__bf16)a, (__bf16)b};
+  return __builtin_bit_cast(uint32_t, v);
+}
+
+// grid: 8 * ceil(tiles / 8) workgroups, tiles = splits x weight tiles x (token tiles, or items of the list).  The ids go
+// round robin over the eight XCDs, so XCD x takes every eighth id; each takes one contiguous eighth of the tiles, whose
+// order keeps the tiles in flight on an XCD close: `band` token tiles, then the next weight tile.
+template <int WR, int WT, int NB, int EPI>
+__global__ __launch_bounds__(64 * WR * WT) __attribute__((amdgpu_waves_per_eu(2, 2))) void gemm_long_kernel(GemmArgs a, int n_wt,
+                                                                                                           int n_tt, int band) {
+  using TL = LongTiling<WR, WT, NB>;
+  constexpr int NW = TL::WAVES, STAGE = TL::STAGE, PW = TL::PW, PX = TL::PX, P = TL::P, WFR = TL::WFR;
+  extern __shared__ __align__(16) unsigned char lds_raw[];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int r32 = lane & 31, half = lane >> 5;
+  const int wr = wave % WR, wt = wave / WR;
+
+  // ---- the workgroup's tile ----
+  if (a.item_expert) { n_tt = min(a.n_items[0], n_tt); band = 1; }
+  const int per_split = n_wt * n_tt, tiles = per_split * a.splits;
+  int id;
+  {
+    const int xcd = blockIdx.x & 7, j = blockIdx.x >> 3;
+    const int base = tiles >> 3, extra = tiles & 7;
+    if (j >= base + (xcd < extra ? 1 : 0)) return;   // uniform over the workgroup, before any barrier
+    id = xcd * base + min(xcd, extra) + j;
+  }
+  const int split = id / per_split;
+  id -= split * per_split;
+  const int b0 = id / (band * n_wt) * band, h = min(band, n_tt - b0), in_band = id - b0 * n_wt;
+  const int tw = in_band / h;
+  int tt = b0 + in_band % h;
+  int row_base = 0;
+  if (a.item_expert) {
+    const int e = a.item_expert[tt];
+    tt = a.item_tile[tt];
+    row_base = a.group_off[e];
+    a.T = a.group_off[e + 1] - row_base;
+    a.w[0] += (size_t)e * a.w_expert_stride;
+  }
+
+  // ---- copies: wave w takes copies w, w + NW, ... of a stage's weights (k-step, tile) and activations (eight rows) ----
+  const int KS = a.K >> 4;
+  const int n_tiles = (a.N + 31) >> 5;
+  const int ks_b = split * a.ksteps_per_split;       // even: the host cuts K between stages
+  const int ks_e = min(ks_b + a.ksteps_per_split, KS);
+  const int n_st = (ks_e - ks_b) >> 1;               // whole stages; an odd last k-step is half a stage more
+  const int n_cp = (ks_e - ks_b + 1) >> 1;           // stages to copy
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)lds_raw;
+  const h16_t* wp[PW];
+  int wstep[PW];
+#pragma unroll
+  for (int i = 0; i < PW; ++i) {
+    const int f = wave + NW * i, j = f % (4 * WR);
+    int lt = tw * 4 * WR + j;
+    wstep[i] = 1;
+    if (lt >= n_tiles) { lt = 0; wstep[i] = 0; }     // no such tile: one cached block, its products are never stored
+    const h16_t* base = a.w[0];
+    if (lt >= a.w_tiles[0]) {
+      lt -= a.w_tiles[0];
+      base = a.w[1];
+      if (lt >= a.w_tiles[1]) { lt -= a.w_tiles[1]; base = a.w[2]; }
+    }
+    wp[i] = base + packed_tile_offset(lt, KS) + lane * 8;
+  }
+  // a token row past the end reads the group's first row: a row only reaches its own outputs, which are not stored
+  const h16_t* xp[PX];
+#pragma unroll
+  for (int i = 0; i < PX; ++i) {
+    const int r = 8 * (wave + NW * i) + (lane >> 3);
+    int t = tt * TL::TOKENS + r;
+    if (t >= a.T) t = 0;
+    const int row = a.x_rows ? a.x_rows[row_base + t] : row_base + t;
+    xp[i] = a.x + (size_t)row * a.x_pitch + (size_t)ks_b * 32 + (size_t)(((lane & 7) ^ ((r >> 1) & 7)) * 8);
+  }
+  auto copy_one = [&](int i, int s, int buf) {       // stages past the end repeat the last one: counts stay the same
+    const int sc = min(s, n_cp - 1);
+    const uint32_t dst = lds0 + buf * STAGE;
+    if (i < PW) {
+      const int f = wave + NW * i;
+      const int ks = min(ks_b + 2 * sc + f / (4 * WR), KS - 1);   // the missing half of an odd last stage: any block
+      copy_to_lds(wp[i] + (size_t)(ks * wstep[i]) * W_KSTRIDE, dst + f * 1024);
+    } else {
+      copy_to_lds(xp[i - PW] + (size_t)sc * 64, dst + (WFR + wave + NW * (i - PW)) * 1024);
+    }
+  };
+
+  f32x16 acc[4][2];
+#pragma unroll
+  for (int j = 0; j < 4; ++j)
+#pragma unroll
+    for (int m = 0; m < 2; ++m)
+#pragma unroll
+      for (int q = 0; q < 16; ++q) acc[j][m][q] = 0.f;
+
+  // ---- fragments from LDS ----
+  const unsigned char* w_rd = lds_raw + 4 * wr * 1024 + lane * 16;
+  const unsigned char* x_rd[4];                      // by (k-step, term) of the stage
+#pragma unroll
+  for (int c = 0; c < 4; ++c) {
+    const int chunk = ((c >> 1) * 2 + half) * 2 + (c & 1);
+    x_rd[c] = lds_raw + WFR * 1024 + (wt * 64 + r32) * 128 + ((chunk ^ ((r32 >> 1) & 7)) * 16);
+  }
+  auto read_w = [&](int buf, int kk, h16x8 (&w)[4]) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) w[j] = *reinterpret_cast<const u32x4*>(w_rd + buf * STAGE + (kk * 4 * WR + j) * 1024);
+  };
+  auto read_x = [&](int buf, int kk, int p, h16x8 (&x)[2]) {
+#pragma unroll
+    for (int m = 0; m < 2; ++m) x[m] = *reinterpret_cast<const u32x4*>(x_rd[kk * 2 + p] + buf * STAGE + m * 4096);
+  };
+  // half a phase: the store form swaps the operands, so that lanes run along n and registers along the tokens
+  auto products = [&](const h16x8 (&w)[4], const h16x8 (&x)[2], int hf) {
+#pragma unroll
+    for (int j = 2 * hf; j < 2 * hf + 2; ++j)
+#pragma unroll
+      for (int m = 0; m < 2; ++m)
+        acc[j][m] = EPI == EPI_STORE ? mfma_32x32x16<DT_BF16>(x[m], w[j], acc[j][m]) : mfma_32x32x16<DT_BF16>(w[j], x[m], acc[j][m]);
+  };
+  // copies of slot k (0..5): those of the stage NB - 1 ahead, into the buffer that the last barrier released
+  constexpr int AHEAD = NB - 1;
+  auto slot = [&](int k, int s, int fbuf) {
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int i = 0; i < P; ++i)
+      if (i * 6 / P == k) copy_one(i, s + AHEAD, fbuf);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+
+#pragma unroll
+  for (int s = 0; s < AHEAD; ++s)
+#pragma unroll
+    for (int i = 0; i < P; ++i) copy_one(i, s, s);
+  wait_copies_and_barrier<(AHEAD - 1) * P>();
+  const int tok0 = tt * TL::TOKENS + wt * 64;        // the wave's first token (of its group)
+  int buf = 0, fbuf = AHEAD;
+  if (tok0 >= a.T) {
+    // all of the wave's tokens lie past the last row: it only copies, and leaves its SIMD to the waves beside it
+    for (int s = 0; s < n_st; ++s) {
+#pragma unroll
+      for (int i = 0; i < P; ++i) copy_one(i, s + AHEAD, fbuf);
+      wait_copies_and_barrier<(AHEAD - 1) * P>();
+      fbuf = fbuf + 1 == NB ? 0 : fbuf + 1;
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    return;
+  }
+  h16x8 w0[4], w1[4], xa[2], xb[2];
+  read_w(0, 0, w0);
+  read_x(0, 0, 1, xa);
+  __builtin_amdgcn_sched_barrier(0);
+  for (int s = 0; s < n_st; ++s) {
+    const int nbuf = buf + 1 == NB ? 0 : buf + 1;
+    read_x(buf, 0, 0, xb);
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_setprio(1);
+    products(w0, xa, 0);                             // k-step 0, small term
+    slot(0, s, fbuf);
+    products(w0, xa, 1);
+    slot(1, s, fbuf);
+    read_w(buf, 1, w1);
+    read_x(buf, 1, 1, xa);
+    __builtin_amdgcn_sched_barrier(0);
+    products(w0, xb, 0);                             // k-step 0, large term
+    slot(2, s, fbuf);
+    products(w0, xb, 1);
+    slot(3, s, fbuf);
+    read_x(buf, 1, 0, xb);
+    __builtin_amdgcn_sched_barrier(0);
+    products(w1, xa, 0);                             // k-step 1, small term
+    slot(4, s, fbuf);
+    products(w1, xa, 1);
+    slot(5, s, fbuf);
+    __builtin_amdgcn_s_setprio(0);
+    wait_copies_and_barrier<(AHEAD - 1) * P>();      // stage s + 1 is in LDS; nobody reads stage s from here on
+    read_w(nbuf, 0, w0);
+    read_x(nbuf, 0, 1, xa);
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_setprio(1);
+    products(w1, xb, 0);                             // k-step 1, large term
+    products(w1, xb, 1);
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_setprio(0);
+    buf = nbuf;
+    fbuf = fbuf + 1 == NB ? 0 : fbuf + 1;
+  }
+  if (n_cp > n_st) {                                 // the last k-step of an odd K: w0 and xa are its first fragments
+    read_x(buf, 0, 0, xb);
+    products(w0, xa, 0);
+    products(w0, xa, 1);
+    products(w0, xb, 0);
+    products(w0, xb, 1);
+  }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // no copy may outlive the workgroup's LDS
+
+  const int nt0 = tw * 4 * WR + 4 * wr;              // the wave's first weight tile
+  if (EPI == EPI_STORE) {
+    // lane = weight row r32 of a tile, register q = token 8 (q / 4) + 4 half + q % 4
+    float* y = a.y + ((size_t)split * a.T + row_base + tok0) * a.ldy + (size_t)nt0 * 32 + r32;
+#pragma unroll
+    for (int m = 0; m < 2; ++m)
+#pragma unroll
+      for (int q = 0; q < 16; ++q) {
+        const int t = m * 32 + 8 * (q >> 2) + 4 * half + (q & 3);
+        if (tok0 + t >= a.T) continue;
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          if ((nt0 + j) * 32 + r32 < a.N) y[(size_t)t * a.ldy + 32 * j] = acc[j][m][q];
+      }
+  } else if (EPI == EPI_SWIGLU) {
+    // rows 0..15 of a tile are gate rows, 16..31 the matching up rows: lane (token r32, half) holds features
+    // 8 g + 4 half + {0..3}, g = 0, 1, of the tile's sixteen.  The halves trade a group, so that each ends up with
+    // eight consecutive features and stores 16 bytes of large terms and 16 of small ones, side by side.
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int nt = nt0 + j;
+      if (nt >= n_tiles) continue;
+#pragma unroll
+      for (int m = 0; m < 2; ++m) {
+        uint32_t hi[2][2], lo[2][2];
+#pragma unroll
+        for (int g = 0; g < 2; ++g) {
+          float v[4];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const float gt = acc[j][m][4 * g + e], up = acc[j][m][4 * (g + 2) + e];
+            v[e] = gt / (1.f + __expf(-gt)) * up;
+          }
+#pragma unroll
+          for (int e = 0; e < 2; ++e) {
+            hi[g][e] = pack_bf16(v[2 * e], v[2 * e + 1]);
+            lo[g][e] = pack_bf16(v[2 * e] - __uint_as_float(hi[g][e] << 16), v[2 * e + 1] - __uint_as_float(hi[g][e] & 0xFFFF0000u));
+          }
+        }
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {                // upper half of group 0 <-> lower half of group 1
+          const auto h2 = __builtin_amdgcn_permlane32_swap(hi[0][e], hi[1][e], false, false);
+          const auto l2 = __builtin_amdgcn_permlane32_swap(lo[0][e], lo[1][e], false, false);
+          hi[0][e] = h2[0]; hi[1][e] = h2[1];
+          lo[0][e] = l2[0]; lo[1][e] = l2[1];
+        }
+        const int t = tok0 + m * 32 + r32;
+        if (t < a.T) {
+          h16_t* dst = a.act + (size_t)(row_base + t) * a.act_pitch + (size_t)(nt * 2 + half) * 16;
+          *reinterpret_cast<u32x4*>(dst) = u32x4{hi[0][0], hi[0][1], hi[1][0], hi[1][1]};
+          *reinterpret_cast<u32x4*>(dst + 8) = u32x4{lo[0][0], lo[0][1], lo[1][0], lo[1][1]};
+        }
+      }
+    }
+  } else {
+    const float one[2] = {1.f, 1.f};
+    const int mt0 = tok0 >> 5;
+    // written out, not a loop: accumulators indexed at run time would move to scratch memory
+    if (nt0 < n_tiles) tile_epilogue<2, EPI, 2, DT_BF16>(a, acc[0], nt0, n_tiles, mt0, 0, 0, lane, one);
+    if (nt0 + 1 < n_tiles) tile_epilogue<2, EPI, 2, DT_BF16>(a, acc[1], nt0 + 1, n_tiles, mt0, 0, 0, lane, one);
+    if (nt0 + 2 < n_tiles) tile_epilogue<2, EPI, 2, DT_BF16>(a, acc[2], nt0 + 2, n_tiles, mt0, 0, 0, lane, one);
+    if (nt0 + 3 < n_tiles) tile_epilogue<2, EPI, 2, DT_BF16>(a, acc[3], nt0 + 3, n_tiles, mt0, 0, 0, lane, one);
+  }
+}
+
+template <int WR, int WT, int NB, int EPI>
+void launch_form(const GemmArgs& a, int n_wt, int n_tt, int band, hipStream_t st) {
+  using TL = LongTiling<WR, WT, NB>;
+  static std::once_flag attr_once;                   // raise the dynamic LDS limit once per instantiation, from any thread
+  std::call_once(attr_once, [] {
+    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_long_kernel<WR, WT, NB, EPI>),
+                              hipFuncAttributeMaxDynamicSharedMemorySize, TL::LDS_BYTES);
+  });
+  const long tiles = (long)n_wt * n_tt * a.splits;
+  hipLaunchKernelGGL((gemm_long_kernel<WR, WT, NB, EPI>), dim3((unsigned)((tiles + 7) / 8 * 8)), dim3(64 * TL::WAVES),
+                     TL::LDS_BYTES, st, a, n_wt, n_tt, band);
+}
+
+template <int EPI>
+void launch_long(const GemmArgs& a, int form, int n_items, hipStream_t st) {
+  const int n_tiles = (a.N + 31) / 32;
+  auto tt = [&](int tokens) { return n_items ? n_items : (a.T + tokens - 1) / tokens; };
+  auto wt = [&](int rows) { return (n_tiles * 32 + rows - 1) / rows; };
+  if (form == LONG_512x128) launch_form<4, 2, 3, EPI>(a, wt(512), tt(128), 4, st);
+  else if (form == LONG_256x128) launch_form<2, 2, 4, EPI>(a, wt(256), tt(128), 8, st);
+  else launch_form<4, 1, 2, EPI>(a, wt(512), tt(64), 8, st);
+}
+
+// ---- which form, and into how many planes K is cut ----
+// Both dense forms put one workgroup on a compute unit: 512 x 128 (eight waves, three stages) has the better rate,
+// 256 x 128 (four waves, four stages) half the step in size, and what decides at a few hundred to a few thousand
+// tokens is how well the number of workgroups fits the units.  A launch takes about rounds x (c + p x stages) with
+// rounds = ceil(workgroups / units); c and p were fitted to a sweep over the two model shapes (N 2048..19456, K
+// 2048..9728), 260..16 384 tokens and 1..8 planes, where the form and plane count it picks are the best of the sweep
+// or within 7 % of it (one exception: 14 %).  E.g. 1437 tokens, N 2560, K 9728: 512 x 128 whole 329 us, 256 x 128
+// whole 290, 512 x 128 in four planes 121 (130 with the reader's extra planes).  A plane costs its write and read.
+struct LongPlan { int form, splits; };
+static LongPlan plan_long(int N, int K, int T, int max_splits, int n_units) {
+  const int stages = (K / 16 + 1) / 2;
+  LongPlan best = {LONG_512x128, 1};
+  float best_us = 1e30f;
+  for (int s = 1; s <= max_splits; ++s) {
+    const int per = (stages + s - 1) / s;
+    if (s > 1 && ((s - 1) * per >= stages || per < 8)) continue;   // no empty split, no split of a few stages
+    const long wg_t = (long)((T + 127) / 128) * s;
+    const long r512 = (wg_t * ((N + 511) / 512) + n_units - 1) / n_units;
+    const long r256 = (wg_t * ((N + 255) / 256) + n_units - 1) / n_units;
+    const float planes_us = (float)(s - 1) * (float)T * (float)N * 1.5e-6f;
+    const float t512 = (float)r512 * (10.f + 1.35f * (float)per) + planes_us;
+    const float t256 = (float)r256 * (11.f + 0.78f * (float)per) + planes_us;
+    if (t512 < best_us) { best_us = t512; best = {LONG_512x128, s}; }
+    if (t256 < best_us) { best_us = t256; best = {LONG_256x128, s}; }
+  }
+  return best;
+}
+
+// Expert-grouped products: 128 rows per tile, or 64 where an expert is not expected to get more than 48 (30B-A3B shape,
+// gate/up + down: 32 rows per expert 250 us with tiles of 128, 235 with 64; 64 rows 293 / 350; 1024 rows 2255 / 2476).
+// Over the same list, 256 weight rows x 128 took 3 to 40 % longer than 512 x 128 everywhere.
+static int grouped_form(int tile_rows) { return tile_rows == 64 ? LONG_512x64 : LONG_512x128; }
+
+}  // namespace
+
+int gemm_long_item_rows(int expected_rows) { return expected_rows <= 48 ? 64 : 128; }
+
+int gemm_long_splits(int N, int K, int T, int max_splits, int n_units) { return plan_long(N, K, T, max_splits, n_units).splits; }
+
+static void fill_long(GemmArgs& a, const Act& x, int N, int K, int T) {
+  a.x = x.p; a.x_pitch = x.pitch;
+  a.N = N; a.K = K; a.T = T;
+  a.ksteps_per_split = (K / 16 + 1) / 2 * 2;
+  a.splits = 1;
+}
+
+hipError_t gemm_long_store(const LinearW& w, const Act& x, int T, float* y, int ldy, int max_splits, int n_units,
+                           hipStream_t st) {
+  const LongPlan plan = plan_long(w.N, w.K, T, max_splits, n_units);
+  GemmArgs a = {};
+  fill_long(a, x, w.N, w.K, T);
+  for (int i = 0; i < 3; ++i) { a.w[i] = w.seg[i]; a.w_tiles[i] = (w.rows[i] + 31) / 32; }
+  a.splits = plan.splits;
+  a.ksteps_per_split = ((w.K / 16 + 1) / 2 + plan.splits - 1) / plan.splits * 2;
+  a.y = y; a.ldy = ldy;
+  launch_long<EPI_STORE>(a, plan.form, 0, st);
+  return hipGetLastError();
+}
+
+hipError_t gemm_long_swiglu(const h16_t* w_gate_up, int F, int K, const Act& x, int T, const Act& act, int n_units,
+                            hipStream_t st) {
+  GemmArgs a = {};
+  fill_long(a, x, 2 * F, K, T);
+  a.w[0] = w_gate_up; a.w_tiles[0] = F / 16;
+  a.act = act.p; a.act_pitch = act.pitch;
+  launch_long<EPI_SWIGLU>(a, plan_long(2 * F, K, T, 1, n_units).form, 0, st);
+  return hipGetLastError();
+}
+
+hipError_t gemm_long_grouped_swiglu(const h16_t* w_gate_up, int F, int K, const Act& x, const int32_t* x_rows,
+                                    const int32_t* group_off, const Act& act, const GroupItems& items, hipStream_t st) {
+  GemmArgs a = {};
+  fill_long(a, x, 2 * F, K, 0);
+  a.x_rows = x_rows;
+  a.w[0] = w_gate_up; a.w_tiles[0] = F / 16; a.w_expert_stride = packed_weight_elems(2 * F, K);
+  a.act = act.p; a.act_pitch = act.pitch;
+  a.group_off = group_off; a.item_expert = items.expert; a.item_tile = items.tile; a.n_items = items.count;
+  launch_long<EPI_SWIGLU>(a, grouped_form(items.tile_rows), items.max_items, st);
+  return hipGetLastError();
+}
+
+hipError_t gemm_long_grouped_store(const h16_t* w, int N, int K, const Act& x, const int32_t* group_off, float* y,
+                                   const GroupItems& items, hipStream_t st) {
+  GemmArgs a = {};
+  fill_long(a, x, N, K, 0);
+  a.w[0] = w; a.w_tiles[0] = (N + 31) / 32; a.w_expert_stride = packed_weight_elems(N, K);
+  a.y = y; a.ldy = N;
+  a.group_off = group_off; a.item_expert = items.expert; a.item_tile = items.tile; a.n_items = items.count;
+  launch_long<EPI_STORE>(a, grouped_form(items.tile_rows), items.max_items, st);
+  return hipGetLastError();
+}
+
+hipError_t gemm_long_lmhead(const h16_t* w_lm, int V, int K, const Act& x, int T, float* logits, float* part,
+                            const uint64_t* seeds, const float* temperature, const int32_t* sample_pos,
+                            const int32_t* row_seq, bool draw, int n_units, hipStream_t st) {
+  GemmArgs a = {};
+  fill_long(a, x, V, K, T);
+  a.w[0] = w_lm; a.w_tiles[0] = (V + 31) / 32;
+  a.logits = logits; a.part = part; a.seeds = seeds; a.temperature = temperature; a.sample_pos = sample_pos;
+  a.row_seq = row_seq; a.draw = draw ? 1 : 0;
+  launch_long<EPI_LMHEAD>(a, plan_long(V, K, T, 1, n_units).form, 0, st);
+  return hipGetLastError();
+}
+
+}  // namespace rlx

@@ -31,13 +31,30 @@ struct Act {
   int T, K, planes, dtype;
   float* ss;
   float eps;
+  // 0: fragment order.  Otherwise the matrix is in rows, `pitch` elements apart (two-term bf16 of long calls): the 8
+  // large terms of features 8 i .. 8 i + 7 at element 16 i of the row, their small terms at 16 i + 8, so that 32
+  // features are one 128-byte line and any list of rows can be read by whole lines.
+  size_t pitch;
   __host__ __device__ int mtiles() const { return (T + 31) / 32; }
+  // offset of the 8-element group (t, k .. k + 7), k a multiple of 8, of the large terms ...
+  __host__ __device__ size_t group_offset(int t, int k) const {
+    return pitch ? (size_t)t * pitch + 2 * (size_t)k : frag_act_offset(t, k, 0, mtiles(), planes);
+  }
+  // ... and from there to the same group of the small terms
+  __host__ __device__ int small_terms() const { return pitch ? 8 : 512; }
 };
 constexpr int NORM_PARTS = 4;
 inline Act make_act(h16_t* p, int T, int K, int planes, int dtype) {
-  Act a = {p, T, K, planes, dtype, nullptr, 0.f};
+  Act a = {p, T, K, planes, dtype, nullptr, 0.f, 0};
   return a;
 }
+// Row pitch: whole lines, an odd number of them, so that the rows' lines at one k fall on different cache channels.
+inline size_t row_pitch(int K) { return (size_t)(((K + 31) / 32) | 1) * 64; }
+inline Act make_act_rows(h16_t* p, int T, int K) {
+  Act a = {p, T, K, 2, DT_BF16, nullptr, 0.f, row_pitch(K)};
+  return a;
+}
+inline size_t act_rows_elems(size_t T, int K) { return T * row_pitch(K); }
 // Row-major variant [planes][T, ld] (queries of the attention kernel).
 struct RowAct {
   h16_t* p;
@@ -51,8 +68,6 @@ void gemm_set_units(int n_units);   // compute units of the device (sizes the ch
 // number of split-K planes for y[T <= 256, N] = x W^T on a device with n_units compute units; the activations come
 // as `planes` terms of format `dtype`
 int gemm_plan_splits(int N, int K, int T, int max_splits, int n_units, int planes, int dtype);
-// planes (1 or 2) for a call of more than 256 tokens: 2 where halving K lets the 256 x 256 form fill the device twice
-int gemm_plan_splits_long(int N, int T, int planes, int dtype, int n_units);
 // y[split][t][n] (fp32, leading dimension ldy); weights packed (common.h), activations in fragment order
 hipError_t gemm_store(const LinearW& w, const Act& x, int T, float* y, int ldy, int splits, hipStream_t st);
 // act[t][f] = silu(x Wg^T) * (x Wu^T); w_gate_up is the interleaved packed pair (pack_gate_up)
@@ -65,17 +80,11 @@ hipError_t gemm_lmhead(const h16_t* w_lm, int V, int K, const Act& x, int T, flo
                        const int32_t* row_seq, bool draw, hipStream_t st);
 // expert-grouped forms: rows [group_off[e], group_off[e+1]) belong to expert e = blockIdx.y; max_rows bounds the rows
 // of one expert, expected_rows (pairs / experts) picks the token-tile height
-// items (optional, large-batch form only: gemm_grouped_item_rows() > 0): the list of (expert, row tile) pairs from
-// moe_route; the grid then runs over the list instead of over (expert, tile index up to max_rows)
-struct GroupItems { const int32_t* expert; const int32_t* tile; int max_items; };
-// rows per tile of the form the grouped GEMMs take for this call if it can run over an item list, else 0
-int gemm_grouped_item_rows(int E, int F, int N, const Act& x, int n_pairs, int expected_rows);
 hipError_t gemm_grouped_swiglu(const h16_t* w_gate_up, int E, int F, int K, const Act& x, const int32_t* x_rows,
                                const int32_t* group_off, int max_rows, int expected_rows, const Act& act,
-                               const GroupItems* items, hipStream_t st);
+                               hipStream_t st);
 hipError_t gemm_grouped_store(const h16_t* w, int E, int N, int K, const Act& x,
-                              const int32_t* group_off, int max_rows, int expected_rows, float* y,
-                              const GroupItems* items, hipStream_t st);
+                              const int32_t* group_off, int max_rows, int expected_rows, float* y, hipStream_t st);
 
 // routed form of the gate/up GEMM (decode batches, two-term bf16): the kernel finds its expert's (token, slot) pairs
 // in the routing table route_idx[n_pairs] itself, so no grouping pass runs before it; it writes act in expert order
@@ -84,6 +93,25 @@ bool gemm_routed_form(int E, int F, const Act& x, int n_pairs, int expected_rows
 hipError_t gemm_routed_swiglu(const h16_t* w_gate_up, int E, int F, int K, const Act& x, const int32_t* route_idx,
                               int n_pairs, int top_k, int max_rows, const Act& act, int32_t* group_off,
                               int32_t* pair_pos, hipStream_t st);
+
+// ---- gemm_long.hip: the same products for long calls on two-term bf16 activations in rows (Act::pitch) ----
+enum { LONG_512x128 = 0, LONG_256x128, LONG_512x64 };   // weight rows x tokens of a workgroup
+// y[split][t][n]: K cut into gemm_long_splits() planes (at most max_splits)
+int gemm_long_splits(int N, int K, int T, int max_splits, int n_units);
+hipError_t gemm_long_store(const LinearW& w, const Act& x, int T, float* y, int ldy, int max_splits, int n_units,
+                           hipStream_t st);
+hipError_t gemm_long_swiglu(const h16_t* w_gate_up, int F, int K, const Act& x, int T, const Act& act, int n_units,
+                            hipStream_t st);
+// list of (expert, tile of tile_rows of the expert's rows) items that moe_route writes; count is on the device
+struct GroupItems { int32_t *expert, *tile, *count; int max_items, tile_rows; };
+int gemm_long_item_rows(int expected_rows);   // tile_rows for experts that expect this many rows
+hipError_t gemm_long_grouped_swiglu(const h16_t* w_gate_up, int F, int K, const Act& x, const int32_t* x_rows,
+                                    const int32_t* group_off, const Act& act, const GroupItems& items, hipStream_t st);
+hipError_t gemm_long_grouped_store(const h16_t* w, int N, int K, const Act& x, const int32_t* group_off, float* y,
+                                   const GroupItems& items, hipStream_t st);
+hipError_t gemm_long_lmhead(const h16_t* w_lm, int V, int K, const Act& x, int T, float* logits, float* part,
+                            const uint64_t* seeds, const float* temperature, const int32_t* sample_pos,
+                            const int32_t* row_seq, bool draw, int n_units, hipStream_t st);
 
 // ---- elementwise.hip ----
 struct TokenMeta {        // per packed token, built on the device at the start of a call
@@ -234,13 +262,10 @@ struct RouterArgs {
 // workgroups for long ones, which pass through `seg_ws` (moe_group_workspace_words() int32 words)
 size_t moe_group_workspace_words();
 // group = false: only the top-k launch (the routed gate/up GEMM reads topk_idx itself and publishes the grouping).
-// Long lists (moe_group_lists_items) with tile_rows > 0: item_expert / item_tile[max_items] receive the list of
-// (expert, tile of tile_rows rows) pairs that have rows, experts ascending, the rest marked -1; max_items must be at
-// least T * top_k / tile_rows + E.
-bool moe_group_lists_items(int T, int top_k);
+// items (optional): receives the list of (expert, tile) pairs that have rows, experts ascending, and their number;
+// max_items must be at least T * top_k / tile_rows + E.
 hipError_t moe_route(const RouterArgs& a, int32_t* group_off, int32_t* sorted_token, int32_t* pair_pos,
-                     int32_t* seg_ws, bool group, int tile_rows, int max_items, int32_t* item_expert,
-                     int32_t* item_tile, hipStream_t st);
+                     int32_t* seg_ws, bool group, const GroupItems* items, hipStream_t st);
 
 // ---- sampling.hip ----
 struct FinalizeArgs {

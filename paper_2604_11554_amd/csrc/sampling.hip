@@ -77,7 +77,6 @@ __global__ __launch_bounds__(256) void sample_finalize_kernel(FinalizeArgs a) {
 
   // logit of the emitted token: the same 16-bit operands as the LM-head tiles, fp32 accumulate
   // (eight consecutive k are one 16-byte group in both layouts; a thread's loads of a round go out together)
-  const int mtiles = a.x.mtiles();
   const int dt = a.x.dtype;
   const int ng = a.d >> 3;
   float acc = 0.f;
@@ -87,9 +86,9 @@ __global__ __launch_bounds__(256) void sample_finalize_kernel(FinalizeArgs a) {
     for (int u = 0; u < 2; ++u) {
       const int gi = g0 + u * 256 + (int)threadIdx.x;
       const int k = 8 * (gi < ng ? gi : ng - 1);
-      const h16_t* x = a.x.p + frag_act_offset(r, k, 0, mtiles, a.x.planes);
+      const h16_t* x = a.x.p + a.x.group_offset(r, k);
       xh[u] = load_h16x8(x);
-      xl[u] = a.x.planes == 2 ? load_h16x8(x + 512) : zero_h16x8();
+      xl[u] = a.x.planes == 2 ? load_h16x8(x + a.x.small_terms()) : zero_h16x8();
       wv[u] = load_h16x8(a.w_lm + packed_weight_offset(tok, k, a.d));
     }
 #pragma unroll

@@ -1,0 +1,65 @@
+"""Calls of more than 256 tokens take GEMM forms of their own (activations in rows, tiles of 128 or 64 tokens, K cut into
+planes where the tiles leave the device idle).  They are compared with the same tokens handed over in calls of at most
+256, which take the short-call forms: same products, sums in another grouping."""
+import numpy as np
+import pytest
+
+import rollout_inputs as RI
+
+pytestmark = pytest.mark.gpu
+
+# widths at the edges of the tiles: K = 688 and 2064 have an odd number of 16-wide k-steps, N = 2056 / 24 experts and the
+# vocabulary are no multiple of a weight tile, 2064 is long enough to be cut into planes
+SHAPES = {
+    "tiny_dense": RI.TINY_DENSE,
+    "wide_dense": RI.TINY_DENSE.replace(d_model=528, d_ff=2064, vocab=2056, n_q_heads=8, n_kv_heads=1, qk_norm=True),
+    "tiny_moe": RI.TINY_MOE.replace(n_experts=24, vocab=2056),
+}
+# tokens of every sequence: just past the limit, around the 64- and 128-token tiles, a few hundred ragged ones
+LENGTHS = {"257": [257], "320": [64, 1, 255], "385": [129, 256], "ragged": [256, 31, 200, 97, 1, 250, 255, 118]}
+
+
+@pytest.mark.parametrize("lengths", sorted(LENGTHS))
+@pytest.mark.parametrize("name", sorted(SHAPES))
+def test_long_calls_equal_the_same_tokens_in_short_calls(name, lengths):
+    import paper_2604_11554_amd as pkg
+    from paper_2604_11554_amd import synthetic
+
+    s = SHAPES[name]
+    lens = LENGTHS[lengths]
+    model = synthetic.model_from_shape(s, 3)
+    rng = np.random.default_rng(11)
+    toks = [rng.integers(0, s.vocab - 2, n).astype(np.int32) for n in lens]
+    rows = list(range(len(lens)))
+    blocks = [(n + 31) // 16 for n in lens]
+
+    def engine():
+        eng = pkg.RolloutEngine(model, n_blocks=sum(blocks), max_seqs=len(lens), max_chunk_tokens=sum(lens),
+                                max_blocks_per_seq=max(blocks))
+        for i in rows:
+            eng.add_sequence(i, reserve_tokens=16 * blocks[i])
+        return eng
+
+    long_eng, short_eng = engine(), engine()
+    out = long_eng.prefill(rows, toks, want_logits=True, want_routing=True)
+    lp, _ = (lambda e: e.score(rows, toks, [np.roll(t, -1) for t in toks]))(engine())
+    replay = out.routing.cpu().numpy() if s.is_moe else None
+    offs = np.concatenate([[0], np.cumsum(lens)])
+    logits, lp_short = [], []
+    scorer = engine()
+    for i in rows:                               # one sequence per call: at most 256 tokens, or 200 and then the rest
+        cuts = [0, len(toks[i])] if len(toks[i]) <= 256 else [0, 200, len(toks[i])]
+        for a, b in zip(cuts, cuts[1:]):
+            o = short_eng.prefill([i], [toks[i][a:b]], want_logits=True)
+            scored, _ = scorer.score([i], [toks[i][a:b]], [np.roll(toks[i], -1)[a:b]],
+                                     replay_routing=None if replay is None else [replay[offs[i] + a:offs[i] + b]])
+            lp_short.append(scored.cpu().numpy())
+        logits.append(o.logits.cpu().numpy()[0])
+    dz = np.abs(out.logits.cpu().numpy() - np.stack(logits)).max()
+    dlp = np.abs(lp.cpu().numpy() - np.concatenate(lp_short)).max()
+    # Both sides hold activations to 16 significand bits and round the same keys and values to bf16; sums in another
+    # order (1e-7 relative each) flip the last bit of a few of those (2^-9 of an element).  Logits have unit variance:
+    # the short forms are within 5e-4 of the oracle here, the bar of the project is 0.05.
+    assert dz < 5e-3, dz
+    assert dlp < 5e-3, dlp
+    model.close()
