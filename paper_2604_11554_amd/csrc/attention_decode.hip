@@ -225,8 +225,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     const int key_end = cur.ctx + 1;
     const int pos_col[1] = {cur.ctx};
     auto step = [&](int i, const PageRegs<HD>& pr, bool valid) {
-      pair_step<HD, 1, PL, FMT>(st, pr.k0, pr.k1, pr.vf, qf, 32 * (cur.u0 + i), 32 * (cur.u0 + i) + 16, pr.ok0 && valid,
-                                pr.ok1 && valid, key_end, pos_col, scale, g);
+      const int key0 = 32 * (cur.u0 + i);
+      const bool ok0 = pr.ok0 && valid, ok1 = pr.ok1 && valid;
+      pair_step<HD, 1, PL, FMT>(st, pr.k0, pr.k1, pr.vf, qf, key0, key0 + 16, ok0, ok1, key_end, pos_col,
+                                ok0 && ok1 && key0 + 32 <= key_end, scale, g);
     };
 
     // Two register sets alternate: while one unit is multiplied the next one's pages are in flight.  The loop
@@ -259,18 +261,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     if (cur.seg_end) {
       st.finish_denominators();
       merge_waves<HD, 1>(st, lds_o, lds_ml, wave, lane);
-      if (wave == 0 && col_ok) {
-        const int head = cur.kvh * group + c16;
-        const bool whole = cur.pb == 0 && cur.pe == cur.np;
-        if (whole && cur.u0 == 0) {
-          store_column<HD, 1, PL, FMT>(st, 0, a.o, cur.seq, head, g);
-        } else {                                     // lane holds column c16, rows d = 16 dt + 4 g + {0..3}
-          float* dst = whole ? a.seq_part + (((size_t)cur.seq * a.Hkv + cur.kvh) * group + c16) * PS
-                             : a.part + ((size_t)(w * 2 + (first_seg ? 0 : 1)) * group + c16) * PS;
+      const bool whole = cur.pb == 0 && cur.pe == cur.np;
+      if (wave == 0 && whole && cur.u0 == 0) {
+        store_column<HD, 1, PL, FMT>(st, 0, a.o, cur.seq, cur.kvh * group + c16, g, col_ok);
+      } else if (wave == 0 && col_ok) {                // lane holds column c16, rows d = 16 dt + 4 g + {0..3}
+        float* dst = whole ? a.seq_part + (((size_t)cur.seq * a.Hkv + cur.kvh) * group + c16) * PS
+                           : a.part + ((size_t)(w * 2 + (first_seg ? 0 : 1)) * group + c16) * PS;
 #pragma unroll
-          for (int dt = 0; dt < DT; ++dt) *reinterpret_cast<f32x4*>(dst + 16 * dt + 4 * g) = st.o[0][dt];
-          if (g == 0) { dst[HD] = st.m[0]; dst[HD + 1] = st.l[0]; }
-        }
+        for (int dt = 0; dt < DT; ++dt) *reinterpret_cast<f32x4*>(dst + 16 * dt + 4 * g) = st.o[0][dt];
+        if (g == 0) { dst[HD] = st.m[0]; dst[HD + 1] = st.l[0]; }
       }
       first_seg = false;
     }
@@ -347,7 +346,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         vf[dt] = load_2x4(kp0 + 16 * HD + (size_t)(16 * dt + c16) * 16 + 4 * g,
                           kp1 + 16 * HD + (size_t)(16 * dt + c16) * 16 + 4 * g);
       asm volatile("" ::: "memory");                   // query fragments are re-read from LDS, not kept in registers
-      pair_step<HD, NCT, PL, FMT>(st, k0, k1, vf, qf, 32 * i, 32 * i + 16, ok0, ok1, 0x7FFFFFFF, pos_col, scale, g);
+      pair_step<HD, NCT, PL, FMT>(st, k0, k1, vf, qf, 32 * i, 32 * i + 16, ok0, ok1, 0x7FFFFFFF, pos_col, ok0 && ok1,
+                                  scale, g);
     }
     st.finish_denominators();
     merge_waves<HD, NCT>(st, lds_o, lds_ml, wave, lane);
@@ -395,8 +395,7 @@ __global__ __launch_bounds__(256) void attn_decode_merge_kernel(AttnDecodeArgs a
     auto add = [&](const f32x4& va, const f32x4& vb, float ms, float ls) {
       if (ms == -INFINITY) return;
       const float mn = fmaxf(m, ms);
-      const float aa = (m == -INFINITY) ? 0.f : __expf(m - mn);
-      const float ab = __expf(ms - mn);
+      const float aa = state_weight(m, mn), ab = state_weight(ms, mn);
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         o[e] = o[e] * aa + va[e] * ab;

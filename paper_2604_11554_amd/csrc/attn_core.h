@@ -50,79 +50,132 @@ struct WaveState {
   }
 };
 
-// The K fragments of two pages (tokens j0*16.. and j1*16..), the V^T fragments of the same 32 tokens and
-// the query fragments are in registers; one online-softmax step over these 32 keys.
+// weight of a state with maximum m in a merge whose maximum is `reference`: an empty state weighs nothing
+__device__ __forceinline__ float state_weight(float m, float reference) { return m == -INFINITY ? 0.f : __expf(m - reference); }
+
+// largest value of the four lanes that share a column (lanes 16 apart), by swaps of rows and of halves of the wave
+__device__ __forceinline__ float column_max(float x) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  const float y = fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+  const auto h = __builtin_amdgcn_permlane32_swap(__float_as_uint(y), __float_as_uint(y), false, false);
+  return fmaxf(__uint_as_float(h[0]), __uint_as_float(h[1]));
+}
+
+// One online-softmax step over 32 keys.  The K fragments of two pages (tokens j0*16.. and j1*16..), the V^T fragments of
+// the same 32 tokens and the query fragments are in registers or LDS:
 //   k0/k1[ks]: page rows (lane & 15), features 32 ks + 8 (lane >> 4) .. +8
 //   vf[dt]:    V^T rows 16 dt + (lane & 15), tokens 4 (lane >> 4) .. +4 of page 0 then of page 1
 //   qf(p, c, ks): query fragment of term p, column tile c: column (lane & 15), features 32 ks + 8 (lane >> 4) .. +8
-// A key is visible to column c when its page is valid, key < key_end and key <= pos_col[c].
+template <int HD, int NCT>
+struct Scores { f32x4 a[NCT], b[NCT]; };              // of the keys of page 0 and of page 1: keys 4 (lane >> 4) + {0..3}
+
 template <int HD, int NCT, int PL, int FMT, typename QF>
-__device__ __forceinline__ void pair_step(WaveState<HD, NCT>& st, const h16x8 (&k0)[HD / 32],
-                                          const h16x8 (&k1)[HD / 32], const h16x8 (&vf)[HD / 16], QF qf,
-                                          int key_base0, int key_base1, bool ok0, bool ok1, int key_end,
-                                          const int (&pos_col)[NCT], float scale, int g) {
-  constexpr int DT = HD / 16, KS = HD / 32;
-  f32x4 s0[NCT], s1[NCT];
+__device__ __forceinline__ void qk_step(Scores<HD, NCT>& s, const h16x8 (&k0)[HD / 32], const h16x8 (&k1)[HD / 32], QF qf) {
 #pragma unroll
-  for (int c = 0; c < NCT; ++c) { s0[c] = f32x4{0.f, 0.f, 0.f, 0.f}; s1[c] = f32x4{0.f, 0.f, 0.f, 0.f}; }
+  for (int c = 0; c < NCT; ++c) { s.a[c] = f32x4{0.f, 0.f, 0.f, 0.f}; s.b[c] = f32x4{0.f, 0.f, 0.f, 0.f}; }
 #pragma unroll
-  for (int ks = 0; ks < KS; ++ks)
+  for (int ks = 0; ks < HD / 32; ++ks)
 #pragma unroll
     for (int c = 0; c < NCT; ++c)
 #pragma unroll
       for (int p = PL - 1; p >= 0; --p) {   // small term first
         const h16x8 q = qf(p, c, ks);
-        s0[c] = mfma_16x16x32<FMT>(k0[ks], q, s0[c]);
-        s1[c] = mfma_16x16x32<FMT>(k1[ks], q, s1[c]);
+        s.a[c] = mfma_16x16x32<FMT>(k0[ks], q, s.a[c]);
+        s.b[c] = mfma_16x16x32<FMT>(k1[ks], q, s.b[c]);
       }
+}
 
-  h16x8 pf[PL][NCT];
+// Scaling, and -inf for the keys that a column does not see: a key is visible to column c when its page is valid,
+// key < key_end and key <= pos_col[c]; all_visible (uniform over the wave) says that this holds for every key and column,
+// which all but the last steps of a run can tell.
+template <int HD, int NCT>
+__device__ __forceinline__ void scale_and_mask(Scores<HD, NCT>& s, int key_base0, int key_base1, bool ok0, bool ok1, int key_end,
+                                               const int (&pos_col)[NCT], bool all_visible, float scale, int g) {
 #pragma unroll
-  for (int c = 0; c < NCT; ++c) {
-    float mx = -INFINITY;
+  for (int c = 0; c < NCT; ++c) { s.a[c] *= scale; s.b[c] *= scale; }
+  if (all_visible) return;
+#pragma unroll
+  for (int c = 0; c < NCT; ++c)
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
-      int key0 = key_base0 + 4 * g + v, key1 = key_base1 + 4 * g + v;
-      bool vis0 = ok0 && key0 < key_end && key0 <= pos_col[c];
-      bool vis1 = ok1 && key1 < key_end && key1 <= pos_col[c];
-      s0[c][v] = vis0 ? s0[c][v] * scale : -INFINITY;
-      s1[c][v] = vis1 ? s1[c][v] * scale : -INFINITY;
-      mx = fmaxf(mx, fmaxf(s0[c][v], s1[c][v]));
+      const int key0 = key_base0 + 4 * g + v, key1 = key_base1 + 4 * g + v;
+      if (!(ok0 && key0 < key_end && key0 <= pos_col[c])) s.a[c][v] = -INFINITY;
+      if (!(ok1 && key1 < key_end && key1 <= pos_col[c])) s.b[c][v] = -INFINITY;
     }
-    mx = fmaxf(mx, __shfl_xor(mx, 16, WAVE));
-    mx = fmaxf(mx, __shfl_xor(mx, 32, WAVE));
+}
+
+// The vector arithmetic of a step: per score a subtraction, the exponential, an addition and three operations for its
+// two terms.  (With compares and selects on every score, the 16-bit conversions in integer operations and the maximum
+// through LDS it was about thirty per score, twice the time of the step's 32 matrix products; same bits.)  It leaves
+// the weights as B operands and the factor alpha by which the sums so far have to be multiplied before they go on.
+template <int HD, int NCT, int PL, int FMT>
+__device__ __forceinline__ void softmax_step(WaveState<HD, NCT>& st, const Scores<HD, NCT>& s, h16x8 (&pf)[PL][NCT],
+                                             float (&alpha)[NCT]) {
+#pragma unroll
+  for (int c = 0; c < NCT; ++c) {
+    float mx = fmaxf(fmaxf(fmaxf(s.a[c][0], s.a[c][1]), fmaxf(s.a[c][2], s.a[c][3])),
+                     fmaxf(fmaxf(s.b[c][0], s.b[c][1]), fmaxf(s.b[c][2], s.b[c][3])));
+    mx = column_max(mx);
     const float mn = fmaxf(st.m[c], mx);
-    const float alpha = (st.m[c] == -INFINITY) ? 0.f : __expf(st.m[c] - mn);
+    const float ref = mn == -INFINITY ? 0.f : mn;       // a column that has seen no key: every weight below is 0
+    alpha[c] = __expf(st.m[c] - ref);
     float p0[4], p1[4], ps = 0.f;
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
-      p0[v] = (s0[c][v] == -INFINITY) ? 0.f : __expf(s0[c][v] - mn);
-      p1[v] = (s1[c][v] == -INFINITY) ? 0.f : __expf(s1[c][v] - mn);
+      p0[v] = __expf(s.a[c][v] - ref);
+      p1[v] = __expf(s.b[c][v] - ref);
       ps += p0[v] + p1[v];
     }
-    st.l[c] = st.l[c] * alpha + ps;     // partial over this lane's keys; lane groups are summed at the end
+    st.l[c] = st.l[c] * alpha[c] + ps;  // partial over this lane's keys; lane groups are summed at the end
     st.m[c] = mn;
+    u32x4 ph, pl;
 #pragma unroll
-    for (int dt = 0; dt < DT; ++dt) st.o[c][dt] *= alpha;
-    h16_t ph[8], pl[8];
-#pragma unroll
-    for (int v = 0; v < 4; ++v) { split_h16<FMT>(p0[v], ph[v], pl[v]); split_h16<FMT>(p1[v], ph[4 + v], pl[4 + v]); }
-    u32x4 pk = {(uint32_t)ph[0] | ((uint32_t)ph[1] << 16), (uint32_t)ph[2] | ((uint32_t)ph[3] << 16),
-                (uint32_t)ph[4] | ((uint32_t)ph[5] << 16), (uint32_t)ph[6] | ((uint32_t)ph[7] << 16)};
-    pf[0][c] = __builtin_bit_cast(h16x8, pk);
-    if (PL == 2) {
-      u32x4 pk2 = {(uint32_t)pl[0] | ((uint32_t)pl[1] << 16), (uint32_t)pl[2] | ((uint32_t)pl[3] << 16),
-                   (uint32_t)pl[4] | ((uint32_t)pl[5] << 16), (uint32_t)pl[6] | ((uint32_t)pl[7] << 16)};
-      pf[PL - 1][c] = __builtin_bit_cast(h16x8, pk2);
+    for (int v = 0; v < 2; ++v) {
+      uint32_t h, l = 0;
+      split_pair<FMT, PL>(p0[2 * v], p0[2 * v + 1], h, l);
+      ph[v] = h; pl[v] = l;
+      split_pair<FMT, PL>(p1[2 * v], p1[2 * v + 1], h, l);
+      ph[2 + v] = h; pl[2 + v] = l;
     }
+    pf[0][c] = ph;
+    if (PL == 2) pf[PL - 1][c] = pl;
   }
+}
+
+// (A branch that skips this where no maximum moved cost as many register moves as it saved products, and split the
+// step's instructions into blocks that cannot be interleaved.)
+template <int HD, int NCT>
+__device__ __forceinline__ void rescale(WaveState<HD, NCT>& st, const float (&alpha)[NCT]) {
 #pragma unroll
-  for (int dt = 0; dt < DT; ++dt)
+  for (int c = 0; c < NCT; ++c)
+#pragma unroll
+    for (int dt = 0; dt < HD / 16; ++dt) st.o[c][dt] *= alpha[c];
+}
+
+template <int HD, int NCT, int PL, int FMT>
+__device__ __forceinline__ void pv_step(WaveState<HD, NCT>& st, const h16x8 (&vf)[HD / 16], const h16x8 (&pf)[PL][NCT]) {
+#pragma unroll
+  for (int dt = 0; dt < HD / 16; ++dt)
 #pragma unroll
     for (int c = 0; c < NCT; ++c)
 #pragma unroll
       for (int p = PL - 1; p >= 0; --p)
         st.o[c][dt] = mfma_16x16x32<FMT>(vf[dt], pf[p][c], st.o[c][dt]);
+}
+
+template <int HD, int NCT, int PL, int FMT, typename QF>
+__device__ __forceinline__ void pair_step(WaveState<HD, NCT>& st, const h16x8 (&k0)[HD / 32],
+                                          const h16x8 (&k1)[HD / 32], const h16x8 (&vf)[HD / 16], QF qf,
+                                          int key_base0, int key_base1, bool ok0, bool ok1, int key_end,
+                                          const int (&pos_col)[NCT], bool all_visible, float scale, int g) {
+  Scores<HD, NCT> s;
+  h16x8 pf[PL][NCT];
+  float alpha[NCT];
+  qk_step<HD, NCT, PL, FMT>(s, k0, k1, qf);
+  scale_and_mask<HD, NCT>(s, key_base0, key_base1, ok0, ok1, key_end, pos_col, all_visible, scale, g);
+  softmax_step<HD, NCT, PL, FMT>(st, s, pf, alpha);
+  rescale<HD, NCT>(st, alpha);
+  pv_step<HD, NCT, PL, FMT>(st, vf, pf);
 }
 
 // merge the state held in LDS (written by another wave) into this wave's registers
@@ -132,8 +185,7 @@ __device__ __forceinline__ void merge_from_lds(WaveState<HD, NCT>& st, const flo
   for (int c = 0; c < NCT; ++c) {
     float mb = ml[(c * 2 + 0) * WAVE + lane], lb = ml[(c * 2 + 1) * WAVE + lane];
     float mn = fmaxf(st.m[c], mb);
-    float aa = (st.m[c] == -INFINITY) ? 0.f : __expf(st.m[c] - mn);
-    float ab = (mb == -INFINITY) ? 0.f : __expf(mb - mn);
+    const float aa = state_weight(st.m[c], mn), ab = state_weight(mb, mn);
     st.l[c] = st.l[c] * aa + lb * ab;
     st.m[c] = mn;
 #pragma unroll
@@ -169,24 +221,40 @@ __device__ __forceinline__ void merge_waves(WaveState<HD, NCT>& st, f32x4* lds_o
   if (wave == 0) merge_from_lds<HD, NCT>(st, lds_ml, lds_o, lane);
 }
 
-// normalised column c of `st` -> 16-bit (hi, lo) terms at row `trow`, features head*HD + ..., fragment order
+// Normalised column c of `st` -> 16-bit (hi, lo) terms at row `trow`, features head*HD + ...; every lane of the wave
+// calls it (`store` says whether the lane's column exists).  A lane holds four features of every 16-feature tile; lanes
+// 16 apart trade those of two tiles, so that each stores whole groups of eight: 16 bytes of large terms, 16 of small ones.
 template <int HD, int NCT, int PL, int FMT>
 __device__ __forceinline__ void store_column(const WaveState<HD, NCT>& st, int c, const Act& o, int trow, int head,
-                                             int g) {
+                                             int g, bool store) {
   const float inv = st.l[c] > 0.f ? 1.f / st.l[c] : 0.f;
 #pragma unroll
-  for (int dt = 0; dt < HD / 16; ++dt) {
-    f32x4 v = st.o[c][dt] * inv;
-    h16_t hi[4], lo[4];
+  for (int dt = 0; dt < HD / 16; dt += 2) {
+    uint32_t hi[2][2], lo[2][2];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) split_h16<FMT>(v[j], hi[j], lo[j]);
-    const int col = head * HD + 16 * dt + 4 * g;   // feature index of the output projection's K
-    h16_t* dst = o.p + o.group_offset(trow, col & ~7) + (col & 7);
-    u32x2 p = {(uint32_t)hi[0] | ((uint32_t)hi[1] << 16), (uint32_t)hi[2] | ((uint32_t)hi[3] << 16)};
-    *reinterpret_cast<u32x2*>(dst) = p;
-    if (PL == 2) {
-      u32x2 p2 = {(uint32_t)lo[0] | ((uint32_t)lo[1] << 16), (uint32_t)lo[2] | ((uint32_t)lo[3] << 16)};
-      *reinterpret_cast<u32x2*>(dst + o.small_terms()) = p2;
+    for (int i = 0; i < 2; ++i) {
+      const f32x4 v = st.o[c][dt + i] * inv;
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        uint32_t h, l = 0;
+        split_pair<FMT, PL>(v[2 * j], v[2 * j + 1], h, l);
+        hi[i][j] = h; lo[i][j] = l;
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {                      // odd rows of tile dt <-> even rows of tile dt + 1
+      const auto h2 = __builtin_amdgcn_permlane16_swap(hi[0][j], hi[1][j], false, false);
+      hi[0][j] = h2[0]; hi[1][j] = h2[1];
+      if (PL == 2) {
+        const auto l2 = __builtin_amdgcn_permlane16_swap(lo[0][j], lo[1][j], false, false);
+        lo[0][j] = l2[0]; lo[1][j] = l2[1];
+      }
+    }
+    // rows 0 and 2 of the wave now hold the two groups of tile dt, rows 1 and 3 those of tile dt + 1
+    if (store) {
+      h16_t* dst = o.p + o.group_offset(trow, head * HD + 16 * (dt + (g & 1)) + 8 * (g >> 1));
+      *reinterpret_cast<u32x4*>(dst) = u32x4{hi[0][0], hi[0][1], hi[1][0], hi[1][1]};
+      if (PL == 2) *reinterpret_cast<u32x4*>(dst + o.small_terms()) = u32x4{lo[0][0], lo[0][1], lo[1][0], lo[1][1]};
     }
   }
 }

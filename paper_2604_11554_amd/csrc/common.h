@@ -28,6 +28,14 @@ __device__ __forceinline__ h16_t f32_to_bf16(float f) {
 __device__ __forceinline__ float f16_to_f32(h16_t b) { return (float)__builtin_bit_cast(_Float16, b); }
 __device__ __forceinline__ h16_t f32_to_f16(float f) { return __builtin_bit_cast(h16_t, (_Float16)f); }
 
+// two at once, a in the low half (v_cvt_pk_bf16_f32): the same rounding
+__device__ __forceinline__ uint32_t pack_bf16(float a, float b) {
+  typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+  const bf16x2 v = {(__bf16)a, (__bf16)b};
+  return __builtin_bit_cast(uint32_t, v);
+}
+__device__ __forceinline__ uint32_t pack_f16(float a, float b) { return (uint32_t)f32_to_f16(a) | ((uint32_t)f32_to_f16(b) << 16); }
+
 // format picked at compile time (inner loops) ...
 template <int DT> __device__ __forceinline__ float h16_to_f32(h16_t b) { return DT == DT_F16 ? f16_to_f32(b) : bf16_to_f32(b); }
 template <int DT> __device__ __forceinline__ h16_t f32_to_h16(float f) { return DT == DT_F16 ? f32_to_f16(f) : f32_to_bf16(f); }
@@ -43,6 +51,17 @@ template <int DT> __device__ __forceinline__ void split_h16(float v, h16_t& hi, 
 __device__ __forceinline__ void split_h16(float v, h16_t& hi, h16_t& lo, int dt) {
   hi = f32_to_h16(v, dt);
   lo = f32_to_h16(v - h16_to_f32(hi, dt), dt);
+}
+
+// two values as packed large terms and, if wanted, packed small terms (bit for bit split_h16 of each)
+template <int DT, int PL> __device__ __forceinline__ void split_pair(float a, float b, uint32_t& hi, uint32_t& lo) {
+  if (DT == DT_F16) {
+    hi = pack_f16(a, b);
+    if (PL == 2) lo = pack_f16(a - f16_to_f32((h16_t)(hi & 0xFFFFu)), b - f16_to_f32((h16_t)(hi >> 16)));
+  } else {
+    hi = pack_bf16(a, b);
+    if (PL == 2) lo = pack_bf16(a - __uint_as_float(hi << 16), b - __uint_as_float(hi & 0xFFFF0000u));
+  }
 }
 
 // matrix-core steps on bit-pattern operands

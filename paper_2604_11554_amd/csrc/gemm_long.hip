@@ -19,23 +19,10 @@
 #include <mutex>
 
 #include "gemm_core.h"
+#include "lds_copy.h"
 
 namespace rlx {
 namespace {
-
-// One copy of 64 x 16 bytes: lane i's 16 bytes at `g` -> LDS address lds + 16 i.  The wait state between the write of
-// m0 and its use is the assembler's to place, hence the s_nop.  No register is written by the copy.
-#pragma clang diagnostic push
-#pragma clang diagnostic ignored "-Winline-asm"   // m0 as a clobber: "reserved register"
-__device__ __forceinline__ void copy_to_lds(const void* g, uint32_t lds) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds), "v"(g) : "memory", "m0");
-}
-#pragma clang diagnostic pop
-// Waits until at most N of this wave's copies are in flight and its LDS reads are done, then for the other waves.
-template <int N>
-__device__ __forceinline__ void wait_copies_and_barrier() {
-  asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory");
-}
 
 template <int WR, int WT, int NB>
 struct LongTiling {
@@ -46,12 +33,6 @@ struct LongTiling {
   static constexpr int LDS_BYTES = NB * STAGE;
   static_assert(WFR % WAVES == 0 && XFR % WAVES == 0, "the waves share a stage's copies evenly");
 };
-
-__device__ __forceinline__ uint32_t pack_bf16(float a, float b) {   // round to nearest even, a in the low half
-  typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-  const bf16x2 v = {(__bf16)a, (__bf16)b};
-  return __builtin_bit_cast(uint32_t, v);
-}
 
 // grid: 8 * ceil(tiles / 8) workgroups, tiles = splits x weight tiles x (token tiles, or items of the list).  The ids go
 // round robin over the eight XCDs, so XCD x takes every eighth id; each takes one contiguous eighth of the tiles, whose
@@ -97,7 +78,7 @@ __global__ __launch_bounds__(64 * WR * WT) __attribute__((amdgpu_waves_per_eu(2,
   const int ks_e = min(ks_b + a.ksteps_per_split, KS);
   const int n_st = (ks_e - ks_b) >> 1;               // whole stages; an odd last k-step is half a stage more
   const int n_cp = (ks_e - ks_b + 1) >> 1;           // stages to copy
-  const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)lds_raw;
+  const uint32_t lds0 = lds_address(lds_raw);
   const h16_t* wp[PW];
   int wstep[PW];
 #pragma unroll
@@ -278,10 +259,7 @@ __global__ __launch_bounds__(64 * WR * WT) __attribute__((amdgpu_waves_per_eu(2,
             v[e] = gt / (1.f + __expf(-gt)) * up;
           }
 #pragma unroll
-          for (int e = 0; e < 2; ++e) {
-            hi[g][e] = pack_bf16(v[2 * e], v[2 * e + 1]);
-            lo[g][e] = pack_bf16(v[2 * e] - __uint_as_float(hi[g][e] << 16), v[2 * e + 1] - __uint_as_float(hi[g][e] & 0xFFFF0000u));
-          }
+          for (int e = 0; e < 2; ++e) split_pair<DT_BF16, 2>(v[2 * e], v[2 * e + 1], hi[g][e], lo[g][e]);
         }
 #pragma unroll
         for (int e = 0; e < 2; ++e) {                // upper half of group 0 <-> lower half of group 1
