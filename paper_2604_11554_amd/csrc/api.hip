@@ -131,10 +131,13 @@ Act call_act(const rlx_model_config& c, h16_t* p, int T, int K, bool rows) {
   return rows ? make_act_rows(p, T, K) : make_act(p, T, K, c.activation_split ? 2 : 1, c.dtype);
 }
 
-// Split-K planes per token of an output of up to d_model features (the o and down projections, the router) and of the
-// wider q|k|v: sixteen in short calls; in long ones as many as keep the planes under 16384 (8192) rows, at most eight
-// (four), and two (one) however long the call.
-int long_planes(int T, bool wide) {
+// Split-K planes per token of an output of up to d_model features (the o and down projections) and of the wider q|k|v:
+// sixteen in short calls; in long ones as many as keep the planes under 16384 (8192) rows, at most eight (four), and
+// two (one) however long the call.  Long calls of MoE policies keep their sums whole: the other order of sums would
+// change the last bits of the router's input, which decide near-ties of the routing, and 128 x 128 tiles fill the
+// device there without planes (30B-A3B shape, 2048 tokens: output projection 64 us whole, 63 in two planes).
+int long_planes(const rlx_model_config& c, int T, bool wide) {
+  if (c.n_experts) return 1;
   const int most = wide ? 4 : 8, n = (wide ? 8192 : 16384) / T, least = wide ? 1 : 2;
   return n > most ? most : (n < least ? least : n);
 }
@@ -258,10 +261,10 @@ int run_layers(const rlx_model* m, h16_t* pool, int64_t n_blocks, const Workspac
   // y = x W^T into `y`: split-K planes that the next kernel adds
   auto planes_of = [&](int N, int K, bool wide) {
     if (small) return gemm_plan_splits(N, K, T, gemm_max_splits(), m->n_units, PL, FMT);
-    return lng ? gemm_long_splits(N, K, T, long_planes(T, wide), m->n_units) : 1;
+    return lng ? gemm_long_splits(N, K, T, long_planes(c, T, wide), m->n_units) : 1;
   };
   auto store = [&](const LinearW& lw, const Act& x, float* y, int splits, bool wide) {
-    return lng ? gemm_long_store(lw, x, T, y, lw.N, long_planes(T, wide), m->n_units, st)
+    return lng ? gemm_long_store(lw, x, T, y, lw.N, long_planes(c, T, wide), m->n_units, st)
                : gemm_store(lw, x, T, y, lw.N, splits, st);
   };
   auto norm = [&](const h16_t* gain, const int32_t* rows, int n_rows, const Act& x, float* xf) -> hipError_t {

@@ -2,8 +2,8 @@
 //
 //   y[t, n] = sum_k x[t, k] * W[n, k],  x = hi + lo: two MFMA 32x32x16 per weight fragment and 32 x 32 outputs
 //
-// A workgroup of WR x WT waves computes 128 WR weight rows x 64 WT tokens, a wave 128 x 64 of them (4 weight tiles x 2
-// token tiles: 128 accumulator registers).  Both operands pass through LDS, copied there by the hardware
+// A workgroup of WR x WT waves computes 32 JW WR weight rows x 64 WT tokens, a wave 32 JW x 64 of them (JW weight tiles x
+// 2 token tiles: 32 JW accumulator registers).  Both operands pass through LDS, copied there by the hardware
 // (global_load_lds, 16 bytes per lane, no registers in between), in stages of 32 k, NB stage buffers deep.
 //  - Weights: the packed layout's fragments, 1 KB per copy, read back linearly.
 //  - Activations: rows (Act::pitch): the 32 k of a stage are one 128-byte line of a row (eight 16-byte chunks: per
@@ -24,10 +24,10 @@
 namespace rlx {
 namespace {
 
-template <int WR, int WT, int NB>
+template <int JW, int WR, int WT, int NB>
 struct LongTiling {
-  static constexpr int WAVES = WR * WT, ROWS = 128 * WR, TOKENS = 64 * WT;
-  static constexpr int WFR = 8 * WR, XFR = 8 * WT;                 // KB of weights and of activations per stage
+  static constexpr int WAVES = WR * WT, ROWS = 32 * JW * WR, TOKENS = 64 * WT;
+  static constexpr int WFR = 2 * JW * WR, XFR = 8 * WT;            // KB of weights and of activations per stage
   static constexpr int STAGE = (WFR + XFR) * 1024;
   static constexpr int PW = WFR / WAVES, PX = XFR / WAVES, P = PW + PX;   // copies per wave and stage
   static constexpr int LDS_BYTES = NB * STAGE;
@@ -37,10 +37,10 @@ struct LongTiling {
 // grid: 8 * ceil(tiles / 8) workgroups, tiles = splits x weight tiles x (token tiles, or items of the list).  The ids go
 // round robin over the eight XCDs, so XCD x takes every eighth id; each takes one contiguous eighth of the tiles, whose
 // order keeps the tiles in flight on an XCD close: `band` token tiles, then the next weight tile.
-template <int WR, int WT, int NB, int EPI>
+template <int JW, int WR, int WT, int NB, int EPI>
 __global__ __launch_bounds__(64 * WR * WT) __attribute__((amdgpu_waves_per_eu(2, 2))) void gemm_long_kernel(GemmArgs a, int n_wt,
                                                                                                            int n_tt, int band) {
-  using TL = LongTiling<WR, WT, NB>;
+  using TL = LongTiling<JW, WR, WT, NB>;
   constexpr int NW = TL::WAVES, STAGE = TL::STAGE, PW = TL::PW, PX = TL::PX, P = TL::P, WFR = TL::WFR;
   extern __shared__ __align__(16) unsigned char lds_raw[];
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -83,8 +83,8 @@ __global__ __launch_bounds__(64 * WR * WT) __attribute__((amdgpu_waves_per_eu(2,
   int wstep[PW];
 #pragma unroll
   for (int i = 0; i < PW; ++i) {
-    const int f = wave + NW * i, j = f % (4 * WR);
-    int lt = tw * 4 * WR + j;
+    const int f = wave + NW * i, j = f % (JW * WR);
+    int lt = tw * JW * WR + j;
     wstep[i] = 1;
     if (lt >= n_tiles) { lt = 0; wstep[i] = 0; }     // no such tile: one cached block, its products are never stored
     const h16_t* base = a.w[0];
@@ -110,41 +110,41 @@ __global__ __launch_bounds__(64 * WR * WT) __attribute__((amdgpu_waves_per_eu(2,
     const uint32_t dst = lds0 + buf * STAGE;
     if (i < PW) {
       const int f = wave + NW * i;
-      const int ks = min(ks_b + 2 * sc + f / (4 * WR), KS - 1);   // the missing half of an odd last stage: any block
+      const int ks = min(ks_b + 2 * sc + f / (JW * WR), KS - 1);   // the missing half of an odd last stage: any block
       copy_to_lds(wp[i] + (size_t)(ks * wstep[i]) * W_KSTRIDE, dst + f * 1024);
     } else {
       copy_to_lds(xp[i - PW] + (size_t)sc * 64, dst + (WFR + wave + NW * (i - PW)) * 1024);
     }
   };
 
-  f32x16 acc[4][2];
+  f32x16 acc[JW][2];
 #pragma unroll
-  for (int j = 0; j < 4; ++j)
+  for (int j = 0; j < JW; ++j)
 #pragma unroll
     for (int m = 0; m < 2; ++m)
 #pragma unroll
       for (int q = 0; q < 16; ++q) acc[j][m][q] = 0.f;
 
   // ---- fragments from LDS ----
-  const unsigned char* w_rd = lds_raw + 4 * wr * 1024 + lane * 16;
+  const unsigned char* w_rd = lds_raw + JW * wr * 1024 + lane * 16;
   const unsigned char* x_rd[4];                      // by (k-step, term) of the stage
 #pragma unroll
   for (int c = 0; c < 4; ++c) {
     const int chunk = ((c >> 1) * 2 + half) * 2 + (c & 1);
     x_rd[c] = lds_raw + WFR * 1024 + (wt * 64 + r32) * 128 + ((chunk ^ ((r32 >> 1) & 7)) * 16);
   }
-  auto read_w = [&](int buf, int kk, h16x8 (&w)[4]) {
+  auto read_w = [&](int buf, int kk, h16x8 (&w)[JW]) {
 #pragma unroll
-    for (int j = 0; j < 4; ++j) w[j] = *reinterpret_cast<const u32x4*>(w_rd + buf * STAGE + (kk * 4 * WR + j) * 1024);
+    for (int j = 0; j < JW; ++j) w[j] = *reinterpret_cast<const u32x4*>(w_rd + buf * STAGE + (kk * JW * WR + j) * 1024);
   };
   auto read_x = [&](int buf, int kk, int p, h16x8 (&x)[2]) {
 #pragma unroll
     for (int m = 0; m < 2; ++m) x[m] = *reinterpret_cast<const u32x4*>(x_rd[kk * 2 + p] + buf * STAGE + m * 4096);
   };
   // half a phase: the store form swaps the operands, so that lanes run along n and registers along the tokens
-  auto products = [&](const h16x8 (&w)[4], const h16x8 (&x)[2], int hf) {
+  auto products = [&](const h16x8 (&w)[JW], const h16x8 (&x)[2], int hf) {
 #pragma unroll
-    for (int j = 2 * hf; j < 2 * hf + 2; ++j)
+    for (int j = JW / 2 * hf; j < JW / 2 * (hf + 1); ++j)
 #pragma unroll
       for (int m = 0; m < 2; ++m)
         acc[j][m] = EPI == EPI_STORE ? mfma_32x32x16<DT_BF16>(x[m], w[j], acc[j][m]) : mfma_32x32x16<DT_BF16>(w[j], x[m], acc[j][m]);
@@ -177,7 +177,7 @@ __global__ __launch_bounds__(64 * WR * WT) __attribute__((amdgpu_waves_per_eu(2,
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     return;
   }
-  h16x8 w0[4], w1[4], xa[2], xb[2];
+  h16x8 w0[JW], w1[JW], xa[2], xb[2];
   read_w(0, 0, w0);
   read_x(0, 0, 1, xa);
   __builtin_amdgcn_sched_barrier(0);
@@ -225,7 +225,7 @@ __global__ __launch_bounds__(64 * WR * WT) __attribute__((amdgpu_waves_per_eu(2,
   }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // no copy may outlive the workgroup's LDS
 
-  const int nt0 = tw * 4 * WR + 4 * wr;              // the wave's first weight tile
+  const int nt0 = tw * JW * WR + JW * wr;            // the wave's first weight tile
   if (EPI == EPI_STORE) {
     // lane = weight row r32 of a tile, register q = token 8 (q / 4) + 4 half + q % 4
     float* y = a.y + ((size_t)split * a.T + row_base + tok0) * a.ldy + (size_t)nt0 * 32 + r32;
@@ -236,7 +236,7 @@ __global__ __launch_bounds__(64 * WR * WT) __attribute__((amdgpu_waves_per_eu(2,
         const int t = m * 32 + 8 * (q >> 2) + 4 * half + (q & 3);
         if (tok0 + t >= a.T) continue;
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
+        for (int j = 0; j < JW; ++j)
           if ((nt0 + j) * 32 + r32 < a.N) y[(size_t)t * a.ldy + 32 * j] = acc[j][m][q];
       }
   } else if (EPI == EPI_SWIGLU) {
@@ -244,7 +244,7 @@ __global__ __launch_bounds__(64 * WR * WT) __attribute__((amdgpu_waves_per_eu(2,
     // 8 g + 4 half + {0..3}, g = 0, 1, of the tile's sixteen.  The halves trade a group, so that each ends up with
     // eight consecutive features and stores 16 bytes of large terms and 16 of small ones, side by side.
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
+    for (int j = 0; j < JW; ++j) {
       const int nt = nt0 + j;
       if (nt >= n_tiles) continue;
 #pragma unroll
@@ -282,21 +282,21 @@ __global__ __launch_bounds__(64 * WR * WT) __attribute__((amdgpu_waves_per_eu(2,
     // written out, not a loop: accumulators indexed at run time would move to scratch memory
     if (nt0 < n_tiles) tile_epilogue<2, EPI, 2, DT_BF16>(a, acc[0], nt0, n_tiles, mt0, 0, 0, lane, one);
     if (nt0 + 1 < n_tiles) tile_epilogue<2, EPI, 2, DT_BF16>(a, acc[1], nt0 + 1, n_tiles, mt0, 0, 0, lane, one);
-    if (nt0 + 2 < n_tiles) tile_epilogue<2, EPI, 2, DT_BF16>(a, acc[2], nt0 + 2, n_tiles, mt0, 0, 0, lane, one);
-    if (nt0 + 3 < n_tiles) tile_epilogue<2, EPI, 2, DT_BF16>(a, acc[3], nt0 + 3, n_tiles, mt0, 0, 0, lane, one);
+    if (JW == 4 && nt0 + 2 < n_tiles) tile_epilogue<2, EPI, 2, DT_BF16>(a, acc[JW - 2], nt0 + 2, n_tiles, mt0, 0, 0, lane, one);
+    if (JW == 4 && nt0 + 3 < n_tiles) tile_epilogue<2, EPI, 2, DT_BF16>(a, acc[JW - 1], nt0 + 3, n_tiles, mt0, 0, 0, lane, one);
   }
 }
 
-template <int WR, int WT, int NB, int EPI>
+template <int JW, int WR, int WT, int NB, int EPI>
 void launch_form(const GemmArgs& a, int n_wt, int n_tt, int band, hipStream_t st) {
-  using TL = LongTiling<WR, WT, NB>;
+  using TL = LongTiling<JW, WR, WT, NB>;
   static std::once_flag attr_once;                   // raise the dynamic LDS limit once per instantiation, from any thread
   std::call_once(attr_once, [] {
-    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_long_kernel<WR, WT, NB, EPI>),
+    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_long_kernel<JW, WR, WT, NB, EPI>),
                               hipFuncAttributeMaxDynamicSharedMemorySize, TL::LDS_BYTES);
   });
   const long tiles = (long)n_wt * n_tt * a.splits;
-  hipLaunchKernelGGL((gemm_long_kernel<WR, WT, NB, EPI>), dim3((unsigned)((tiles + 7) / 8 * 8)), dim3(64 * TL::WAVES),
+  hipLaunchKernelGGL((gemm_long_kernel<JW, WR, WT, NB, EPI>), dim3((unsigned)((tiles + 7) / 8 * 8)), dim3(64 * TL::WAVES),
                      TL::LDS_BYTES, st, a, n_wt, n_tt, band);
 }
 
@@ -305,19 +305,21 @@ void launch_long(const GemmArgs& a, int form, int n_items, hipStream_t st) {
   const int n_tiles = (a.N + 31) / 32;
   auto tt = [&](int tokens) { return n_items ? n_items : (a.T + tokens - 1) / tokens; };
   auto wt = [&](int rows) { return (n_tiles * 32 + rows - 1) / rows; };
-  if (form == LONG_512x128) launch_form<4, 2, 3, EPI>(a, wt(512), tt(128), 4, st);
-  else if (form == LONG_256x128) launch_form<2, 2, 4, EPI>(a, wt(256), tt(128), 8, st);
-  else launch_form<4, 1, 2, EPI>(a, wt(512), tt(64), 8, st);
+  if (form == LONG_512x128) launch_form<4, 4, 2, 3, EPI>(a, wt(512), tt(128), 4, st);
+  else if (form == LONG_128x128) launch_form<2, 2, 2, 3, EPI>(a, wt(128), tt(128), 8, st);
+  else launch_form<4, 4, 1, 2, EPI>(a, wt(512), tt(64), 8, st);
 }
 
 // ---- which form, and into how many planes K is cut ----
-// Both dense forms put one workgroup on a compute unit: 512 x 128 (eight waves, three stages) has the better rate,
-// 256 x 128 (four waves, four stages) half the step in size, and what decides at a few hundred to a few thousand
-// tokens is how well the number of workgroups fits the units.  A launch takes about rounds x (c + p x stages) with
-// rounds = ceil(workgroups / units); c and p were fitted to a sweep over the two model shapes (N 2048..19456, K
-// 2048..9728), 260..16 384 tokens and 1..8 planes, where the form and plane count it picks are the best of the sweep
-// or within 7 % of it (one exception: 14 %).  E.g. 1437 tokens, N 2560, K 9728: 512 x 128 whole 329 us, 256 x 128
-// whole 290, 512 x 128 in four planes 121 (130 with the reader's extra planes).  A plane costs its write and read.
+// 512 x 128 (eight waves, one workgroup per unit) has the better rate when the device is full many times over, 128 x 128
+// (four waves, two workgroups per unit) an eighth of its step in size, and what decides at a few hundred to a few thousand
+// tokens is how well the workgroups fit the units.  A launch of 512 x 128 takes about rounds x (10 + 1.4 stages) us,
+// rounds = ceil(workgroups / units); one of 128 x 128 3 + 0.85 stages per two workgroups on every unit, and for the rest
+// 0.44 per stage where a unit gets one of them, 0.85 where some get two; a plane more costs its write and read.  The
+// constants were fitted to a sweep over the two model shapes (N 128..19456, K 2048..9728), 260..8192 tokens and 1, 2 and
+// 4 planes, where the choice is within 10 % of the best of the sweep everywhere and 1 % behind it in the mean.  E.g.
+// 1437 tokens, N 2560, K 9728: 512 x 128 whole 324 us, 128 x 128 whole 135, 512 x 128 in four planes 122; 3000 tokens,
+// N 6144, K 2560: 512 x 128 217 us, 128 x 128 174; 8192 tokens: 375 and 428.  (256 x 128 tiles were never the best.)
 struct LongPlan { int form, splits; };
 static LongPlan plan_long(int N, int K, int T, int max_splits, int n_units) {
   const int stages = (K / 16 + 1) / 2;
@@ -327,20 +329,21 @@ static LongPlan plan_long(int N, int K, int T, int max_splits, int n_units) {
     const int per = (stages + s - 1) / s;
     if (s > 1 && ((s - 1) * per >= stages || per < 8)) continue;   // no empty split, no split of a few stages
     const long wg_t = (long)((T + 127) / 128) * s;
+    const float planes_us = (float)(s - 1) * (float)T * (float)N * 1.1e-6f;
     const long r512 = (wg_t * ((N + 511) / 512) + n_units - 1) / n_units;
-    const long r256 = (wg_t * ((N + 255) / 256) + n_units - 1) / n_units;
-    const float planes_us = (float)(s - 1) * (float)T * (float)N * 1.5e-6f;
-    const float t512 = (float)r512 * (10.f + 1.35f * (float)per) + planes_us;
-    const float t256 = (float)r256 * (11.f + 0.78f * (float)per) + planes_us;
+    const float t512 = (float)r512 * (10.f + 1.4f * (float)per) + planes_us;
     if (t512 < best_us) { best_us = t512; best = {LONG_512x128, s}; }
-    if (t256 < best_us) { best_us = t256; best = {LONG_256x128, s}; }
+    const long w128 = wg_t * ((N + 127) / 128), full = w128 / (2 * n_units), rest = w128 % (2 * n_units);
+    float t128 = 3.f + (float)full * (3.f + 0.85f * (float)per) + planes_us;
+    if (rest) t128 += 3.f + (rest <= n_units ? 0.44f : 0.85f) * (float)per;
+    if (t128 < best_us) { best_us = t128; best = {LONG_128x128, s}; }
   }
   return best;
 }
 
 // Expert-grouped products: 128 rows per tile, or 64 where an expert is not expected to get more than 48 (30B-A3B shape,
 // gate/up + down: 32 rows per expert 250 us with tiles of 128, 235 with 64; 64 rows 293 / 350; 1024 rows 2255 / 2476).
-// Over the same list, 256 weight rows x 128 took 3 to 40 % longer than 512 x 128 everywhere.
+// Over the same list, tiles of 128 or 256 weight rows took up to 25 % longer than those of 512 nearly everywhere.
 static int grouped_form(int tile_rows) { return tile_rows == 64 ? LONG_512x64 : LONG_512x128; }
 
 }  // namespace

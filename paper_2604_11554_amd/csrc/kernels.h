@@ -95,7 +95,7 @@ hipError_t gemm_routed_swiglu(const h16_t* w_gate_up, int E, int F, int K, const
                               int32_t* pair_pos, hipStream_t st);
 
 // ---- gemm_long.hip: the same products for long calls on two-term bf16 activations in rows (Act::pitch) ----
-enum { LONG_512x128 = 0, LONG_256x128, LONG_512x64 };   // weight rows x tokens of a workgroup
+enum { LONG_512x128 = 0, LONG_128x128, LONG_512x64 };   // weight rows x tokens of a workgroup
 // y[split][t][n]: K cut into gemm_long_splits() planes (at most max_splits)
 int gemm_long_splits(int N, int K, int T, int max_splits, int n_units);
 hipError_t gemm_long_store(const LinearW& w, const Act& x, int T, float* y, int ldy, int max_splits, int n_units,
