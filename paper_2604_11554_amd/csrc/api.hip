@@ -120,13 +120,17 @@ struct Workspace {
   size_t bytes;
 };
 
-constexpr int SCORE_ROWS = 256;      // rows per LM-head pass of rollout_score_chunk
+// rows per LM-head pass of rollout_score_chunk: passes of a thousand rows leave a twentieth of the device idle at their end,
+// passes of 256 a quarter (30B-A3B shape, 151 936 x 2048: 256 rows 300 us, 1024 rows 1007); short calls stay with 256
+constexpr int SCORE_ROWS = 1024;
+int score_rows_max(int T) { return T <= 256 ? 256 : (T < SCORE_ROWS ? T : SCORE_ROWS); }
 constexpr int ATTN_WGS_MAX = 1024;   // decode attention grid limit (plan arrays are sized for it)
 
 // Calls of more than 256 tokens on two-term bf16 activations carry them in rows and take the long-call GEMMs.
 bool long_call(const rlx_model_config& c, int T) { return T > 256 && c.activation_split && c.dtype == RLX_DTYPE_BF16; }
-// ... and so do LM heads of more than 128 rows
-bool rows_lmhead(const rlx_model_config& c, int rows) { return rows > 128 && c.activation_split && c.dtype == RLX_DTYPE_BF16; }
+// ... and so do LM heads of more than 64 rows (151 936 x 2560, one draw per row: 96 rows 234 -> 211 us, 256 rows 509 -> 396;
+// 64 rows 153 in the short form, 161 at best in long ones)
+bool rows_lmhead(const rlx_model_config& c, int rows) { return rows > 64 && c.activation_split && c.dtype == RLX_DTYPE_BF16; }
 Act call_act(const rlx_model_config& c, h16_t* p, int T, int K, bool rows) {
   return rows ? make_act_rows(p, T, K) : make_act(p, T, K, c.activation_split ? 2 : 1, c.dtype);
 }
@@ -209,9 +213,9 @@ Workspace carve(const rlx_model_config& c, char* base, int S, int T, int max_blo
   } else {
     w.act = (h16_t*)take(act_bytes(T, c.d_ff, lng));
   }
-  const int lm_rows = S > SCORE_ROWS ? S : SCORE_ROWS;   // sampled rows of a call, or one block of scored rows
+  const int score_rows = score_rows_max(T), lm_rows = S > score_rows ? S : score_rows;   // sampled rows, or a block of scored ones
   w.x_lm = (h16_t*)take(act_bytes(lm_rows, c.d_model, rows_lmhead(c, lm_rows)));
-  w.lm_part = (float*)take((size_t)lm_rows * lmhead_tiles(c.vocab) * 4 * 4);
+  w.lm_part = (float*)take((size_t)lm_rows * ((c.vocab + 31) / 32) * 4 * 4);
   w.bytes = off;
   return w;
 }
@@ -369,16 +373,18 @@ int run_layers(const rlx_model* m, h16_t* pool, int64_t n_blocks, const Workspac
 
   if (io.score) {
     // every position is scored: final norm + LM head (log-sum-exp partials only, no draw) + target logit, in
-    // blocks of SCORE_ROWS rows; each block applies the residual still pending from the last sub-layer to its rows
+    // blocks of rows; each block applies the residual still pending from the last sub-layer to its rows
     const float* pp = pend_planes; const int pn = pend_n; const bool pm = pend_moe;
-    for (int r0 = 0; r0 < T; r0 += SCORE_ROWS) {
-      const int n = T - r0 < SCORE_ROWS ? T - r0 : SCORE_ROWS;
+    const int passes = (T + score_rows_max(T) - 1) / score_rows_max(T);
+    const int per_pass = passes == 1 ? T : ((T + passes - 1) / passes + 127) / 128 * 128;   // whole token tiles
+    for (int r0 = 0; r0 < T; r0 += per_pass) {
+      const int n = T - r0 < per_pass ? T - r0 : per_pass;
       const Act x_lm = call_act(c, w.x_lm, n, d, rows_lmhead(c, n));
       pend_planes = pp; pend_n = pn; pend_moe = pm;
       RLX_HIP(norm(m->final_norm, w.meta.tok_iota + r0, n, x_lm, nullptr));
       RLX_LAUNCH(RLX_K_LMHEAD, lmhead(x_lm, n, nullptr, nullptr, nullptr, w.meta.tok_seq + r0, false));
       FinalizeArgs f = {};
-      f.n_rows = n; f.n_tiles = lmhead_tiles(c.vocab); f.vocab = c.vocab; f.d = d;
+      f.n_rows = n; f.n_parts = lmhead_parts(c.vocab, x_lm); f.vocab = c.vocab; f.d = d;
       f.part = w.lm_part; f.x = x_lm; f.w_lm = m->lm_head;
       f.temperature = io.temperature; f.forced = io.score_targets + r0; f.row_seq = w.meta.tok_seq + r0;
       f.eos = c.eos_token_id; f.pad = c.pad_token_id; f.out_logprobs = io.score_logprobs + r0; f.score = 1;
@@ -393,7 +399,7 @@ int run_layers(const rlx_model* m, h16_t* pool, int64_t n_blocks, const Workspac
   RLX_HIP(norm(m->final_norm, w.meta.sample_row, S, x_lm, nullptr));
   RLX_LAUNCH(RLX_K_LMHEAD, lmhead(x_lm, S, io.out_logits, io.seeds, w.meta.sample_pos, nullptr, true));
   FinalizeArgs f = {};
-  f.n_rows = S; f.n_tiles = lmhead_tiles(c.vocab); f.vocab = c.vocab; f.d = d;
+  f.n_rows = S; f.n_parts = lmhead_parts(c.vocab, x_lm); f.vocab = c.vocab; f.d = d;
   f.part = w.lm_part; f.x = x_lm; f.w_lm = m->lm_head;
   f.temperature = io.temperature; f.max_ctx_len = io.max_ctx_len; f.forced = io.forced;
   f.sample_pos = w.meta.sample_pos; f.sample_on = w.meta.sample_on;

@@ -38,13 +38,15 @@ struct Tiling {
   static constexpr int FRAGS = KC * MT * PL;                                // 1 KB fragments per chunk
   static constexpr int PER_THREAD = FRAGS / GEMM_WAVES;                     // staged by each wave
   static constexpr int LDS_BYTES = 2 * FRAGS * 1024;
+  static_assert(LDS_BYTES >= GEMM_WAVES * MT * 4 * 1024, "the LM-head epilogue's scratch fits");
 };
 
 // ONCE: the launch reads every weight once (a single token tile per weight tile), so the weight loads are marked
 // non-temporal; with several token tiles the later ones find the weights in the caches, and the mark would send
 // them to memory again (decode steps of 129..256 tokens: down projection +10 % with the mark).
+// at least two waves per SIMD: beyond 256 registers only one workgroup would be resident per unit
 template <int MT, int EPI, int PL, int FMT, bool ONCE>
-__global__ __launch_bounds__(GEMM_THREADS) void gemm_skinny_kernel(GemmArgs a) {
+__global__ __launch_bounds__(GEMM_THREADS, 2) void gemm_skinny_kernel(GemmArgs a) {
   using TL = Tiling<MT, PL>;
   constexpr int KC = TL::KC, U = TL::U, FRAGS = TL::FRAGS, PT = TL::PER_THREAD;
   extern __shared__ __align__(16) unsigned char lds_raw[];
@@ -116,6 +118,13 @@ __global__ __launch_bounds__(GEMM_THREADS) void gemm_skinny_kernel(GemmArgs a) {
     ssq[m] = f32x4{1.f, 1.f, 1.f, 1.f};
     if (a.x_ss && !grouped) ssq[m] = row_ss(a, t < a.T ? t : 0);
   }
+  LmRow lm[MT];                                       // LM head: likewise requested first of all ...
+  auto fetch_lm_rows = [&]() {
+#pragma unroll
+    for (int m = 0; m < MT; ++m)
+      if constexpr (EPI == EPI_LMHEAD) lm[m] = lm_row(a, (mt0 + m) * 32 + r32);
+  };
+  if (PL == 2) fetch_lm_rows();                       // ... or last, where 256 registers are taken without them
   __builtin_amdgcn_sched_barrier(0);
   // Fragment i of this wave belongs to the same token tile in every chunk.  With four token tiles the tile is picked
   // here, once, by comparing the wave number with constants, so that the arrays above are only ever indexed by
@@ -254,7 +263,12 @@ __global__ __launch_bounds__(GEMM_THREADS) void gemm_skinny_kernel(GemmArgs a) {
     }
   }
   if (!have_tile) return;
-  tile_epilogue<MT, EPI, PL, FMT>(a, acc, nt, n_tiles, mt0, split, row_base, lane, rs);
+  if (PL != 2) fetch_lm_rows();
+  if constexpr (EPI == EPI_LMHEAD)                   // past the last barrier: the activation chunks are dead
+    lmhead_epilogue<1, MT>(a, reinterpret_cast<f32x4*>(lds) + wave * MT * 4 * WAVE, reinterpret_cast<const f32x16(&)[1][MT]>(acc),
+                           lm, nt, mt0, nt, n_tiles, lane);
+  else
+    tile_epilogue<MT, EPI, PL, FMT>(a, acc, nt, n_tiles, mt0, split, row_base, lane, rs);
 }
 
 // ---- expert-grouped decode form: up to 32 rows per expert, J tile groups per workgroup ----
@@ -691,8 +705,6 @@ hipError_t gemm_routed_swiglu(const h16_t* w_gate_up, int E, int F, int K, const
   if (!launch_expert<EPI_SWIGLU>(a, a.w_tiles[0], E, x, st)) return hipErrorInvalidValue;
   return hipGetLastError();
 }
-
-int lmhead_tiles(int vocab) { return (vocab + 31) / 32; }
 
 hipError_t gemm_lmhead(const h16_t* w_lm, int V, int K, const Act& x, int T, float* logits, float* part,
                        const uint64_t* seeds, const float* temperature, const int32_t* sample_pos,

@@ -21,7 +21,7 @@ struct GemmArgs {
   int act_mtiles;
   // LM-head epilogue
   float* logits;          // optional [T][N]
-  float* part;            // [T][n_tiles][4] = max, sumexp, best score, best index (as float bits)
+  float* part;            // [T][n_parts][4] = max, sumexp, best score, best index (as float bits)
   const uint64_t* seeds;
   const float* temperature;
   const int32_t* sample_pos;
@@ -50,30 +50,30 @@ __device__ __forceinline__ void philox4x32_10(uint32_t c0, uint32_t c1, uint32_t
                                               uint32_t k1, uint32_t (&out)[4]) {
 #pragma unroll
   for (int r = 0; r < 10; ++r) {
-    uint32_t h0 = __umulhi(0xD2511F53u, c0), l0 = 0xD2511F53u * c0;
-    uint32_t h1 = __umulhi(0xCD9E8D57u, c2), l1 = 0xCD9E8D57u * c2;
-    uint32_t n0 = h1 ^ c1 ^ k0, n2 = h0 ^ c3 ^ k1;
-    c0 = n0; c1 = l1; c2 = n2; c3 = l0;
+    uint64_t p0, p1, carry;                          // one instruction for both halves of a product
+    asm("v_mad_u64_u32 %0, %1, %2, %3, 0" : "=v"(p0), "=s"(carry) : "v"(c0), "s"(0xD2511F53u));
+    asm("v_mad_u64_u32 %0, %1, %2, %3, 0" : "=v"(p1), "=s"(carry) : "v"(c2), "s"(0xCD9E8D57u));
+    const uint32_t n0 = (uint32_t)(p1 >> 32) ^ c1 ^ k0, n2 = (uint32_t)(p0 >> 32) ^ c3 ^ k1;
+    c0 = n0; c1 = (uint32_t)p1; c2 = n2; c3 = (uint32_t)p0;
     k0 += 0x9E3779B9u; k1 += 0xBB67AE85u;
   }
   out[0] = c0; out[1] = c1; out[2] = c2; out[3] = c3;
 }
 
 // Gumbel(0,1) from a 32-bit word: u = (R + 0.5) 2^-32, g = -log(-log u).  The largest values of g, the ones that
-// win the draw, come from u next to 1, so for the upper half of the range -log u is taken from w = 1 - u (exact
-// from the integer): the series w + w^2/2 + w^3/3 + w^4/4 below 2^-6 (relative error w^4/5 < 2e-8), the
-// hardware logarithm of 1 - w above (absolute error ~1e-7 on a value of at least 0.0156).  The hardware
-// logarithm's absolute error of ~1e-7 is also what the other two logarithms carry (their arguments are not near
-// 1 where it would matter, or their result is near 0 where it does not): g is within ~1e-5 of the exact value,
-// three orders below the tolerance on the scores it is added to.  Branch-free: lanes of a wave hold both halves.
+// win the draw, come from u next to 1: there (1 - u < 2^-6) -log u is taken from w = 1 - u (exact from the integer) by the
+// series w + w^2/2 + w^3/3 + w^4/4 (relative error w^4/5 < 2e-8), elsewhere by the hardware's base-2 logarithm (absolute
+// error ~1e-7 on a value of at least 0.0156, which is also what the outer logarithm carries): g is within ~1e-5 of the
+// exact value, three orders below the tolerance on the scores it is added to.  Two logarithms and a dozen operations,
+// branch-free; with a third logarithm and branches around them the four draws of a step cost 5 us in a 17 us LM head.
 __device__ __forceinline__ float gumbel_from_u32(uint32_t r) {
-  const bool upper = r >= 0x80000000u;
-  const float u = ((float)r + 0.5f) * 2.3283064365386963e-10f;
-  const float w = ((float)(0xFFFFFFFFu - r) + 0.5f) * 2.3283064365386963e-10f;   // 1 - u, meaningful when upper
-  const float series = w * (1.f + w * (0.5f + w * (0.33333334f + w * 0.25f)));
-  const float nl_hi = w < 0.015625f ? series : -__logf(1.f - w);
-  const float nl = upper ? nl_hi : -__logf(u);
-  return -__logf(nl);
+  constexpr float LN2 = 0.693147182f;
+  const float u = __builtin_fmaf((float)r, 2.3283064365386963e-10f, 1.16415321826934814e-10f);
+  const float w = __builtin_fmaf((float)~r, 2.3283064365386963e-10f, 1.16415321826934814e-10f);   // 1 - u
+  const float series = w * __builtin_fmaf(w, __builtin_fmaf(w, __builtin_fmaf(w, 0.25f, 0.33333334f), 0.5f), 1.f);
+  const float log_u = __builtin_amdgcn_logf(u) * -LN2;           // u >= 2^-33: no subnormal reaches the logarithms
+  const float nl = r >= 0xFC000000u ? series : log_u;
+  return __builtin_amdgcn_logf(nl) * -LN2;
 }
 
 // Epilogue of one 32-row weight tile `nt` over token tiles mt0 .. mt0 + MT - 1: lane holds token r32 of each token
@@ -143,65 +143,94 @@ __device__ __forceinline__ void tile_epilogue(const GemmArgs& a, const f32x16 (&
         }
       }
     }
-  } else {  // EPI_LMHEAD: per token, reduce this tile's 32 vocabulary rows to (max, sumexp, best, argbest)
+  }
+}
+
+// LM-head epilogue of a wave: per token, its 32 JT vocabulary rows (tiles nt0 ..) are reduced to (max, sumexp, best
+// score, its id), record `part` of `n_parts` of the token's row.  The accumulators go through a scratch area in LDS
+// (`scr`: JT * MT * 4 KB of the wave's own), which lets the work on them run as a loop: written out over the registers it
+// was up to 50 KB of straight code per form.  The parts' order of sums differs from a sum id by id, not their precision.
+// What it needs to know of the lane's row is passed in, so that the caller can ask for it early (three dependent fetches
+// at the end of a kernel are three round trips).
+struct LmRow { float temperature; uint64_t seed; uint32_t pos; };
+__device__ __forceinline__ LmRow lm_row(const GemmArgs& a, int t) {
+  const int tc = t < a.T ? t : 0;
+  LmRow r = {a.temperature[a.row_seq ? a.row_seq[tc] : tc], 0ull, 0u};
+  if (a.draw) { r.seed = a.seeds[tc]; r.pos = (uint32_t)a.sample_pos[tc]; }
+  return r;
+}
+template <int JT, int MT>
+__device__ __forceinline__ void lmhead_epilogue(const GemmArgs& a, f32x4* scr, const f32x16 (&acc)[JT][MT], const LmRow (&row)[MT],
+                                                int nt0, int mt0, int part, int n_parts, int lane) {
+  const int r32 = lane & 31, half = lane >> 5;
 #pragma unroll
-    for (int m = 0; m < MT; ++m) {
-      const int t = (mt0 + m) * 32 + r32;
-      const bool ok = t < a.T;
-      float mx = -INFINITY, se = 0.f, best = -INFINITY;
-      int besti = 0x7FFFFFFF;
-      if (ok) {
-        const float temp = a.temperature[a.row_seq ? a.row_seq[t] : t];
-        const float invt = temp > 0.f ? 1.f / temp : 1.f;
-        const bool draw = a.draw != 0 && temp > 0.f;          // uniform over the launch when draw == 0
-        const uint64_t seed = a.draw ? a.seeds[t] : 0;
-        const uint32_t pos = a.draw ? (uint32_t)a.sample_pos[t] : 0u;
+  for (int m = 0; m < MT; ++m)
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const int nrow = n0 + 8 * q + 4 * half;  // multiple of 4: one Philox block covers the four ids
-          if (nrow >= a.N) continue;
-          uint32_t rnd[4] = {0u, 0u, 0u, 0u};
-          if (a.draw) philox4x32_10((uint32_t)(nrow >> 2), pos, 0u, 0u, (uint32_t)seed, (uint32_t)(seed >> 32), rnd);
-          f32x4 v = {acc[m][4 * q], acc[m][4 * q + 1], acc[m][4 * q + 2], acc[m][4 * q + 3]};
-          if (a.logits) {
-            if (nrow + 3 < a.N) {
-              *reinterpret_cast<f32x4*>(a.logits + (size_t)t * a.N + nrow) = v;
-            } else {
+    for (int j = 0; j < JT; ++j)
 #pragma unroll
-              for (int j = 0; j < 4; ++j)
-                if (nrow + j < a.N) a.logits[(size_t)t * a.N + nrow + j] = v[j];
-            }
-          }
+      for (int q = 0; q < 4; ++q)
+        scr[((m * JT + j) * 4 + q) * WAVE + lane] = f32x4{acc[j][m][4 * q], acc[j][m][4 * q + 1], acc[j][m][4 * q + 2], acc[j][m][4 * q + 3]};
 #pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            if (nrow + j < a.N) {
-              const float z = v[j] * invt;
-              const float sc = draw ? z + gumbel_from_u32(rnd[j]) : z;
-              if (sc > best) { best = sc; besti = nrow + j; }   // ascending ids: ties keep the smaller one
-              const float nm = fmaxf(mx, z);
-              se = se * __expf(mx - nm) + __expf(z - nm);
-              mx = nm;
-            }
+  for (int m = 0; m < MT; ++m) {
+    const int t = (mt0 + m) * 32 + r32;
+    const bool ok = t < a.T;
+    float mx = -INFINITY, se = 0.f, best = -INFINITY;
+    int besti = 0x7FFFFFFF;
+    if (ok) {
+      const float temp = row[m].temperature, invt = temp > 0.f ? 1.f / temp : 1.f;
+      const bool draw = a.draw != 0 && temp > 0.f;            // uniform over the launch when draw == 0
+      const uint64_t seed = row[m].seed;
+      const uint32_t pos = row[m].pos;
+#pragma unroll 1
+      for (int i = 0; i < 4 * JT; ++i) {
+        const int nrow = nt0 * 32 + 8 * i + 4 * half;         // multiple of 4: one Philox block covers the four ids
+        if (nrow >= a.N) break;
+        const f32x4 v = scr[(m * JT * 4 + i) * WAVE + lane];
+        if (a.logits) {
+          if (nrow + 3 < a.N) {
+            *reinterpret_cast<f32x4*>(a.logits + (size_t)t * a.N + nrow) = v;
+          } else {
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+              if (nrow + j < a.N) a.logits[(size_t)t * a.N + nrow + j] = v[j];
           }
         }
-      }
-      // merge the two half-waves (rows 8q+0..3 and 8q+4..7) of the same token
-      const float omx = __shfl_xor(mx, 32, WAVE), ose = __shfl_xor(se, 32, WAVE);
-      const float obest = __shfl_xor(best, 32, WAVE);
-      const int obesti = __shfl_xor(besti, 32, WAVE);
-      if (obest > best || (obest == best && obesti < besti)) { best = obest; besti = obesti; }
-      const float nm = fmaxf(mx, omx);
-      if (nm > -INFINITY) {
-        // fixed operand order (lower half first) so both half-waves compute the same bits
-        const float lo_m = half ? omx : mx, lo_s = half ? ose : se, hi_m = half ? mx : omx, hi_s = half ? se : ose;
-        se = lo_s * (lo_m == -INFINITY ? 0.f : __expf(lo_m - nm)) + hi_s * (hi_m == -INFINITY ? 0.f : __expf(hi_m - nm));
+        float z[4], sc[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) z[j] = sc[j] = nrow + j < a.N ? v[j] * invt : -INFINITY;
+        if (a.draw) {
+          uint32_t rnd[4];
+          philox4x32_10((uint32_t)(nrow >> 2), pos, 0u, 0u, (uint32_t)seed, (uint32_t)(seed >> 32), rnd);
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            float noise = gumbel_from_u32(rnd[j]);
+            asm volatile("" : "+v"(noise));                     // computed for all lanes: no branch per id
+            sc[j] = draw ? z[j] + noise : z[j];
+          }
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          if (sc[j] > best) { best = sc[j]; besti = nrow + j; }   // ascending ids: ties keep the smaller one
+        const float nm = fmaxf(mx, fmaxf(fmaxf(z[0], z[1]), fmaxf(z[2], z[3])));
+        se = se * __expf(mx - nm) + ((__expf(z[0] - nm) + __expf(z[1] - nm)) + (__expf(z[2] - nm) + __expf(z[3] - nm)));
         mx = nm;
       }
-      if (ok && half == 0) {
-        float* o = a.part + ((size_t)t * n_tiles + nt) * 4;
-        f32x4 pv = {mx, se, best, __int_as_float(besti)};
-        *reinterpret_cast<f32x4*>(o) = pv;
-      }
+    }
+    // merge the two half-waves (rows 8i+0..3 and 8i+4..7) of the same token
+    const float omx = __shfl_xor(mx, 32, WAVE), ose = __shfl_xor(se, 32, WAVE);
+    const float obest = __shfl_xor(best, 32, WAVE);
+    const int obesti = __shfl_xor(besti, 32, WAVE);
+    if (obest > best || (obest == best && obesti < besti)) { best = obest; besti = obesti; }
+    const float nm = fmaxf(mx, omx);
+    if (nm > -INFINITY) {
+      // fixed operand order (lower half first) so both half-waves compute the same bits
+      const float lo_m = half ? omx : mx, lo_s = half ? ose : se, hi_m = half ? mx : omx, hi_s = half ? se : ose;
+      se = lo_s * (lo_m == -INFINITY ? 0.f : __expf(lo_m - nm)) + hi_s * (hi_m == -INFINITY ? 0.f : __expf(hi_m - nm));
+      mx = nm;
+    }
+    if (ok && half == 0) {
+      const f32x4 pv = {mx, se, best, __int_as_float(besti)};
+      *reinterpret_cast<f32x4*>(a.part + ((size_t)t * n_parts + part) * 4) = pv;
     }
   }
 }

@@ -223,6 +223,8 @@ __global__ __launch_bounds__(64 * WR * WT) __attribute__((amdgpu_waves_per_eu(2,
     products(w0, xb, 0);
     products(w0, xb, 1);
   }
+  LmRow lm[2];
+  if constexpr (EPI == EPI_LMHEAD) { lm[0] = lm_row(a, tok0 + r32); lm[1] = lm_row(a, tok0 + 32 + r32); }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // no copy may outlive the workgroup's LDS
 
   const int nt0 = tw * JW * WR + JW * wr;            // the wave's first weight tile
@@ -277,13 +279,16 @@ __global__ __launch_bounds__(64 * WR * WT) __attribute__((amdgpu_waves_per_eu(2,
       }
     }
   } else {
-    const float one[2] = {1.f, 1.f};
-    const int mt0 = tok0 >> 5;
-    // written out, not a loop: accumulators indexed at run time would move to scratch memory
-    if (nt0 < n_tiles) tile_epilogue<2, EPI, 2, DT_BF16>(a, acc[0], nt0, n_tiles, mt0, 0, 0, lane, one);
-    if (nt0 + 1 < n_tiles) tile_epilogue<2, EPI, 2, DT_BF16>(a, acc[1], nt0 + 1, n_tiles, mt0, 0, 0, lane, one);
-    if (JW == 4 && nt0 + 2 < n_tiles) tile_epilogue<2, EPI, 2, DT_BF16>(a, acc[JW - 2], nt0 + 2, n_tiles, mt0, 0, 0, lane, one);
-    if (JW == 4 && nt0 + 3 < n_tiles) tile_epilogue<2, EPI, 2, DT_BF16>(a, acc[JW - 1], nt0 + 3, n_tiles, mt0, 0, 0, lane, one);
+    // every wave is past its last fragment read once it is past this barrier (waves without tokens have left; a barrier
+    // counts those that run): the stage buffers become the waves' scratch, two weight tiles at a time
+    asm volatile("s_barrier" ::: "memory");
+    f32x4* scr = reinterpret_cast<f32x4*>(lds_raw) + wave * 2 * 2 * 4 * WAVE;
+    static_assert(EPI != EPI_LMHEAD || TL::LDS_BYTES >= NW * 16 * 1024, "the waves' scratch fits");
+    const int n_parts = (n_tiles + 1) / 2;
+#pragma unroll
+    for (int j = 0; j < JW; j += 2)
+      if (nt0 + j < n_tiles)
+        lmhead_epilogue<2, 2>(a, scr, reinterpret_cast<const f32x16(&)[2][2]>(acc[j]), lm, nt0 + j, tok0 >> 5, (nt0 + j) >> 1, n_parts, lane);
   }
 }
 

@@ -72,8 +72,9 @@ int gemm_plan_splits(int N, int K, int T, int max_splits, int n_units, int plane
 hipError_t gemm_store(const LinearW& w, const Act& x, int T, float* y, int ldy, int splits, hipStream_t st);
 // act[t][f] = silu(x Wg^T) * (x Wu^T); w_gate_up is the interleaved packed pair (pack_gate_up)
 hipError_t gemm_swiglu(const h16_t* w_gate_up, int F, int K, const Act& x, int T, const Act& act, hipStream_t st);
-int lmhead_tiles(int vocab);
-// LM head with fused per-tile log-sum-exp and Gumbel-max partials: part[t][tile][4]
+// LM head with fused log-sum-exp and Gumbel-max partials: part[t][lmhead_parts()][4], a part per 32 vocabulary rows, or
+// per 64 in the long-call form
+inline int lmhead_parts(int vocab, const Act& x) { return x.pitch ? (vocab + 63) / 64 : (vocab + 31) / 32; }
 // row_seq (optional): row t reads temperature[row_seq[t]]; draw = false skips the Gumbel-max draw (scoring)
 hipError_t gemm_lmhead(const h16_t* w_lm, int V, int K, const Act& x, int T, float* logits, float* part,
                        const uint64_t* seeds, const float* temperature, const int32_t* sample_pos,
@@ -269,8 +270,8 @@ hipError_t moe_route(const RouterArgs& a, int32_t* group_off, int32_t* sorted_to
 
 // ---- sampling.hip ----
 struct FinalizeArgs {
-  int n_rows, n_tiles, vocab, d;
-  const float* part;          // [n_rows][n_tiles][4]
+  int n_rows, n_parts, vocab, d;
+  const float* part;          // [n_rows][n_parts][4]
   Act x;                      // [planes][n_rows, d] final-normalised hidden
   const h16_t* w_lm;         // [vocab, d] packed, format x.dtype
   const float* temperature; const int32_t* max_ctx_len; const int32_t* forced;

@@ -43,17 +43,17 @@ __global__ __launch_bounds__(256) void sample_finalize_kernel(FinalizeArgs a) {
   // thread t takes tiles t, t + 256, ... (one 16-byte record each, eight loads in flight), merged in
   // ascending order; then a fixed binary tree over the threads
   Part p = {-INFINITY, 0.f, -INFINITY, 0x7FFFFFFF};
-  const f32x4* base = reinterpret_cast<const f32x4*>(a.part + (size_t)r * a.n_tiles * 4);
-  for (int t0 = 0; t0 < a.n_tiles; t0 += 8 * 256) {
+  const f32x4* base = reinterpret_cast<const f32x4*>(a.part + (size_t)r * a.n_parts * 4);
+  for (int t0 = 0; t0 < a.n_parts; t0 += 8 * 256) {
     f32x4 q[8];
 #pragma unroll
     for (int u = 0; u < 8; ++u) {
       const int tile = t0 + u * 256 + (int)threadIdx.x;
-      q[u] = base[tile < a.n_tiles ? tile : a.n_tiles - 1];
+      q[u] = base[tile < a.n_parts ? tile : a.n_parts - 1];
     }
 #pragma unroll
     for (int u = 0; u < 8; ++u)
-      if (t0 + u * 256 + (int)threadIdx.x < a.n_tiles) {
+      if (t0 + u * 256 + (int)threadIdx.x < a.n_parts) {
         Part b = {q[u][0], q[u][1], q[u][2], __float_as_int(q[u][3])};
         p = part_merge(p, b);
       }

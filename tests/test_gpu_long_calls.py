@@ -63,3 +63,35 @@ def test_long_calls_equal_the_same_tokens_in_short_calls(name, lengths):
     assert dz < 5e-3, dz
     assert dlp < 5e-3, dlp
     model.close()
+
+
+@pytest.mark.parametrize("vocab", [2048, 2056, 35])
+@pytest.mark.parametrize("n_rows", [65, 128, 130, 257])
+def test_lm_heads_of_many_rows_draw_what_short_ones_draw(n_rows, vocab):
+    """More than 64 sampled rows take the long-call LM head (records of 64 ids, rows of activations): same draws and
+    log-probabilities as calls of at most 64 rows; 2056 and 35 ids end inside a tile."""
+    import paper_2604_11554_amd as pkg
+    from paper_2604_11554_amd import synthetic
+
+    s = RI.TINY_DENSE.replace(vocab=vocab)
+    model = synthetic.model_from_shape(s, 5)
+    toks = [np.array([i % (vocab - 2)], np.int32) for i in range(n_rows)]
+    sampled, logprobs = [], []
+    for step in (n_rows, 64):
+        got = []
+        for a in range(0, n_rows, step):
+            part = toks[a:a + step]
+            eng = pkg.RolloutEngine(model, n_blocks=len(part), max_seqs=len(part), max_chunk_tokens=len(part),
+                                    max_blocks_per_seq=1)
+            for j in range(len(part)):
+                eng.add_sequence(7000 + a + j, temperature=0.7 if (a + j) % 3 else 0.0, reserve_tokens=16)
+            out = eng.prefill(list(range(len(part))), part, want_sampled=True)
+            got.append((out.sampled.cpu().numpy(), out.logprobs.cpu().numpy()))
+        sampled.append(np.concatenate([g[0] for g in got]))
+        logprobs.append(np.concatenate([g[1] for g in got]))
+    # the logits differ by the order of their sums only (~1e-6): a draw may differ where two scores are that close
+    same = sampled[0] == sampled[1]
+    assert same.mean() >= 0.99, np.nonzero(~same)
+    # log-probabilities of unit-variance logits: 1e-6 of the sums, and up to one flipped last bit of a cached key
+    assert np.abs(logprobs[0] - logprobs[1])[same].max() < 1e-3
+    model.close()
