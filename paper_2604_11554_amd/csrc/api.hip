@@ -126,8 +126,10 @@ constexpr int SCORE_ROWS = 1024;
 int score_rows_max(int T) { return T <= 256 ? 256 : (T < SCORE_ROWS ? T : SCORE_ROWS); }
 constexpr int ATTN_WGS_MAX = 1024;   // decode attention grid limit (plan arrays are sized for it)
 
-// Calls of more than 256 tokens on two-term bf16 activations carry them in rows and take the long-call GEMMs.
-bool long_call(const rlx_model_config& c, int T) { return T > 256 && c.activation_split && c.dtype == RLX_DTYPE_BF16; }
+// Calls of more than 128 tokens (MoE: 256) on two-term bf16 activations carry them in rows and take the long-call GEMMs.
+bool long_call(const rlx_model_config& c, int T) {
+  return T > (c.n_experts ? 256 : 128) && c.activation_split && c.dtype == RLX_DTYPE_BF16;
+}
 // ... and so do LM heads of more than 64 rows (151 936 x 2560, one draw per row: 96 rows 234 -> 211 us, 256 rows 509 -> 396;
 // 64 rows 153 in the short form, 161 at best in long ones)
 bool rows_lmhead(const rlx_model_config& c, int rows) { return rows > 64 && c.activation_split && c.dtype == RLX_DTYPE_BF16; }
@@ -243,10 +245,9 @@ int run_layers(const rlx_model* m, h16_t* pool, int64_t n_blocks, const Workspac
   const rlx_model_config& c = m->cfg;
   const int d = c.d_model, T = io.T;
   const int qdim = c.n_q_heads * c.head_dim, kvdim = c.n_kv_heads * c.head_dim, qkv_dim = qdim + 2 * kvdim;
-  const bool small = T <= 256;
   const int PL = c.activation_split ? 2 : 1;
   const int FMT = c.dtype;
-  const bool lng = long_call(c, T);
+  const bool lng = long_call(c, T), small = T <= 256 && !lng;
   Act xb = call_act(c, w.xb, T, d, lng);
   const Act ob = call_act(c, w.ob, T, qdim, lng);
   const RowAct qb = {w.q, (size_t)T * qdim, qdim, PL, FMT};
