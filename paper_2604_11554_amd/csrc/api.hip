@@ -104,8 +104,8 @@ struct Workspace {
   float* qkv;        // [planes][T, qkv_dim]
   h16_t* q;         // [T, q_dim]
   h16_t* ob;        // [T, q_dim]
-  float* attn_part;  // [attn_wgs][2][Hq/Hkv][hd+4] decode partials of straddling (sequence, KV head) pairs
-  int32_t *attn_prefix, *attn_wg_seq, *attn_hdr;   // decode attention plan
+  float* attn_part;  // [ATTN_SHARES_MAX][2][Hq/Hkv][hd+4] decode partials of straddling (sequence, KV head) pairs
+  int32_t *attn_prefix, *attn_share_seq, *attn_hdr;   // decode attention plan
   float* attn_seq_part;   // [S][Hkv][Hq/Hkv][hd+4] own part of a pair that prefix tiles precede
   float* attn_pre_part;   // [shared_prefix_max_tiles][SP_COLS][hd+4] parts of the shared-prefix tiles
   float* planes;     // split-K planes of the o / down projections
@@ -124,7 +124,7 @@ struct Workspace {
 // passes of 256 a quarter (30B-A3B shape, 151 936 x 2048: 256 rows 300 us, 1024 rows 1007); short calls stay with 256
 constexpr int SCORE_ROWS = 1024;
 int score_rows_max(int T) { return T <= 256 ? 256 : (T < SCORE_ROWS ? T : SCORE_ROWS); }
-constexpr int ATTN_WGS_MAX = 1024;   // decode attention grid limit (plan arrays are sized for it)
+constexpr int ATTN_WGS_MAX = 1024;   // decode attention grid limit
 
 // Calls of more than 128 tokens (MoE: 256) on two-term bf16 activations carry them in rows and take the long-call GEMMs.
 bool long_call(const rlx_model_config& c, int T) {
@@ -186,16 +186,21 @@ Workspace carve(const rlx_model_config& c, char* base, int S, int T, int max_blo
   w.xb = (h16_t*)take(act_bytes(T, c.d_model, lng));
   w.x_ss = (float*)take((size_t)T * NORM_PARTS * 4);
   w.router = c.n_experts ? (float*)take(plane_rows(T, false) * c.n_experts * 4) : nullptr;
-  w.qkv = (float*)take(plane_rows(T, true) * qkv_dim * 4);
   w.q = (h16_t*)take((size_t)PL * T * qdim * 2);
   w.ob = (h16_t*)take(act_bytes(T, qdim, lng));
-  w.attn_part = (float*)take((size_t)ATTN_WGS_MAX * 2 * (c.n_q_heads / c.n_kv_heads) * (c.head_dim + 4) * 4);
   w.attn_prefix = (int32_t*)take((size_t)(S + 1) * 4);
-  w.attn_wg_seq = (int32_t*)take((size_t)ATTN_WGS_MAX * 4);
+  w.attn_share_seq = (int32_t*)take((size_t)ATTN_SHARES_MAX * 4);
   w.attn_hdr = (int32_t*)take(4 * 4);
   w.attn_seq_part = (float*)take((size_t)S * c.n_q_heads * (c.head_dim + 4) * 4);
   w.attn_pre_part = (float*)take((size_t)shared_prefix_max_tiles(S, c.n_kv_heads) * SP_COLS * (c.head_dim + 4) * 4);
-  w.planes = (float*)take(plane_rows(T, false) * c.d_model * 4);   // of the o and down projections
+  // Split-K planes of q|k|v and of the o and down projections.  Both are dead while decode attention runs (its queries
+  // are rotated, the residual has taken the planes up), so its partials lie in the same memory.
+  const size_t planes_at = off;
+  w.qkv = (float*)take(plane_rows(T, true) * qkv_dim * 4);
+  w.planes = (float*)take(plane_rows(T, false) * c.d_model * 4);
+  w.attn_part = w.qkv;
+  const size_t attn_end = planes_at + align_up((size_t)ATTN_SHARES_MAX * 2 * (c.n_q_heads / c.n_kv_heads) * (c.head_dim + 4) * 4);
+  if (off < attn_end) off = attn_end;
   if (c.n_experts) {
     const size_t P = (size_t)T * c.top_k;
     w.act = (h16_t*)take(act_bytes((int)P, c.d_ff_expert, lng));
@@ -307,7 +312,7 @@ int run_layers(const rlx_model* m, h16_t* pool, int64_t n_blocks, const Workspac
       at.q = qb; at.pool_layer = pool_layer; at.n_blocks = n_blocks;
       at.Hq = c.n_q_heads; at.Hkv = c.n_kv_heads; at.hd = c.head_dim;
       at.block_table = io.block_table; at.max_blocks = io.max_blocks; at.ctx_lens = io.ctx_lens;
-      at.n_seqs = io.n_seqs; at.unit_prefix = w.attn_prefix; at.wg_seq = w.attn_wg_seq; at.plan_hdr = w.attn_hdr;
+      at.n_seqs = io.n_seqs; at.unit_prefix = w.attn_prefix; at.share_seq = w.attn_share_seq; at.plan_hdr = w.attn_hdr;
       at.n_wgs = m->attn_wgs; at.part = w.attn_part; at.o = ob;
       at.shared = io.shared_prefix; at.seq_part = w.attn_seq_part; at.pre_part = w.attn_pre_part;
       at.n_prefix_wgs = 2 * m->n_units;
@@ -669,7 +674,7 @@ int rollout_decode_step_shared(const rlx_model* m, void* kv_pool, int64_t n_bloc
   hipStream_t st = (hipStream_t)stream;
   RLX_HIP(meta_decode(w.meta, n_seqs, ctx_lens_inout, finished_inout, m->inv_freq, m->cfg.head_dim, st));
   RLX_HIP(attention_decode_plan(n_seqs, ctx_lens_inout, w.meta.tok_live, m->cfg.n_kv_heads, m->attn_wgs,
-                                (const int32_t*)shared_prefix, w.attn_prefix, w.attn_wg_seq, w.attn_hdr, st));
+                                (const int32_t*)shared_prefix, w.attn_prefix, w.attn_share_seq, w.attn_hdr, st));
   StepIO io = {};
   io.n_seqs = n_seqs; io.T = n_seqs; io.decode = true;
   io.tokens = tokens_inout; io.ctx_lens = ctx_lens_inout; io.ctx_lens_rw = ctx_lens_inout;

@@ -2,14 +2,17 @@
 //
 // One new token per sequence; the 16 MFMA columns of a tile are the query heads of one KV head
 // (group <= 16), so a KV page is read once for all heads of its group.  The work of a step is the
-// sequence of 32-key units of all (sequence, KV head) pairs laid end to end; every workgroup takes a
+// sequence of 32-key units of all (sequence, KV head) pairs laid end to end; every WAVE takes a
 // contiguous share of it, all shares within one unit of each other (the plan is built once per step,
-// contexts being the same for every layer), so the grid is exactly resident (two workgroups per compute unit) and every workgroup streams
-// for the whole kernel instead of paying its start-up and wind-down latency per 256 keys.  Within a
-// share the four waves take units round-robin, each keeping the next unit's pages in flight while it
-// works on the current one.  Where a (sequence, KV head) pair lies inside one share its output is
-// final; where it straddles shares each part leaves (o, m, l) and a small second kernel merges the
-// parts in share order (deterministic).
+// contexts being the same for every layer), on a grid that is exactly resident (two workgroups of four waves per
+// compute unit).  A wave walks its share by itself, the next unit's pages on their way while it works on the current
+// one, the next pair's queries copied into its part of LDS by the hardware; there is no barrier.  Where a (sequence, KV
+// head) pair lies inside one share its output is final; where it straddles shares each part leaves (o, m, l) and a small
+// second kernel merges the parts in share order (deterministic).
+// (With a share per workgroup, its waves taking units in turn, the end of every pair cost a merge of the four waves
+// through LDS, three barriers and a half-idle step.  4B shape, 256 sequences, one layer: 32 to 287 keys each 94 us then,
+// 42 now; 144 keys each 51 and 35; 1024 keys each 182 and 172, 6.2 TB/s.  A lone sequence of 3000 keys: merge 19 us
+// then, of 64 parts by one round trip per four, 5 now.)
 //
 // Shared prompt prefixes (sequences of one sampling group list the same pages for their prompt): the descriptor
 // `shared` names, per sequence, how many leading units are served by prefix tiles instead.  A prefix tile is
@@ -18,6 +21,7 @@
 // responses of a prompt at the 4B shape) instead of once per sequence; the per-sequence kernel starts after the
 // shared units, and the merge kernel adds the prefix parts first.
 #include "attn_core.h"
+#include "lds_copy.h"
 
 namespace rlx {
 namespace {
@@ -57,8 +61,8 @@ __device__ __forceinline__ int shared_units_of(const SharedView& v, int seq, int
   return v.on ? min(max(v.start_unit[seq], 0), ctx / 32) : 0;
 }
 
-// Shares of two sizes: workgroups 0 .. H-1 take CA units each, the others CB = CA - 1, which may be zero (plan
-// header: CA, total, CB, H).
+// Shares of two sizes: 0 .. H-1 take CA units each, the others CB = CA - 1, as long as there are units (plan header: CA,
+// total, CB, H).
 struct Shares {
   int CA, CB, H, U;
   __device__ __forceinline__ int start(int w) const { return w < H ? w * CA : H * CA + (w - H) * CB; }
@@ -76,23 +80,23 @@ struct Run {
 
 template <int HD, int PL, int FMT>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_decode_kernel(AttnDecodeArgs a) {
-  constexpr int DT = HD / 16, KS = HD / 32, PS = HD + 4;
-  __shared__ f32x4 lds_o[2 * DT * WAVE];
-  __shared__ float lds_ml[2 * 2 * WAVE];
-  __shared__ u32x4 lds_q[PL * KS * WAVE];            // query fragments of the current segment, MFMA operand order
+  constexpr int DT = HD / 16, KS = HD / 32, PS = HD + 4, NQ = PL * KS;
+  // query fragments of the wave's current and next pair, MFMA operand order
+  __shared__ u32x4 lds_q[4][2][NQ * WAVE];
 
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int c16 = lane & 15, g = lane >> 4;
   const int group = a.Hq / a.Hkv;
   const bool col_ok = c16 < group;
-  const int w = blockIdx.x;
+  const int w = wave * gridDim.x + blockIdx.x;       // few shares spread over the units
+  if (w >= ATTN_SHARES_MAX) return;
   const Shares sh = load_shares(a.plan_hdr);
   const int U = sh.U;
   int u = sh.start(w);
   const int u_end = min(U, sh.start(w + 1));
-  if (u >= u_end) return;                            // uniform over the workgroup
-  int seq = a.wg_seq[w];
+  if (u >= u_end) return;                            // uniform over the wave
+  int seq = a.share_seq[w];
   const float scale = rsqrtf((float)HD);
   const size_t page = (size_t)2 * 16 * HD;
 
@@ -150,36 +154,26 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     if (jb >= a.max_blocks) t0 = -1;
     if (jb + 64 >= a.max_blocks) t1 = -1;
   };
-  // The waves share the fetch of a segment's query fragments; they stay in LDS (registers hold two units of pages).
-  // The fragments of the next run's pair are requested a whole run ahead (the run generator looks one run ahead
-  // anyway) and only written to LDS at the switch, so that a new segment does not begin with a round trip.
-  constexpr int QPW = (PL * KS + 3) / 4;             // fragments fetched by each wave
-  auto fetch_queries = [&](const Run& r, u32x4 (&q)[QPW]) {
+  // The query fragments of a pair go straight into LDS, a whole run before they are read (the run generator looks one
+  // run ahead anyway).  Columns past the group read some head's queries; their results are never stored.
+  int qsel = 0;
+  auto copy_queries = [&](const Run& r, int sel) {
     const int head = r.kvh * group + (col_ok ? c16 : 0);
+    const uint32_t dst = lds_address(&lds_q[wave][sel][0]);
 #pragma unroll
-    for (int i = 0; i < QPW; ++i) {
-      const int f = min(wave + 4 * i, PL * KS - 1);  // a slot without a fragment repeats the last one; never written
+    for (int f = 0; f < NQ; ++f) {
       const int p = f / KS, ks = f % KS;
-      q[i] = *reinterpret_cast<const u32x4*>(a.q.p + p * a.q.plane + ((size_t)r.seq * a.Hq + head) * HD + 32 * ks + 8 * g);
+      copy_to_lds(a.q.p + p * a.q.plane + ((size_t)r.seq * a.Hq + head) * HD + 32 * ks + 8 * g, dst + f * 1024);
     }
   };
-  auto put_queries = [&](const u32x4 (&q)[QPW]) {
-    const u32x4 z = {0u, 0u, 0u, 0u};
-#pragma unroll
-    for (int i = 0; i < QPW; ++i)
-      if (wave + 4 * i < PL * KS) lds_q[(wave + 4 * i) * WAVE + lane] = col_ok ? q[i] : z;
-  };
-  auto qf = [&](int p, int, int ks) { return __builtin_bit_cast(h16x8, lds_q[(p * KS + ks) * WAVE + lane]); };
+  auto qf = [&](int p, int, int ks) { return __builtin_bit_cast(h16x8, lds_q[wave][qsel][(p * KS + ks) * WAVE + lane]); };
 
   Run cur, nxt;
   next_run(cur);
   if (!cur.valid) return;
   int32_t tb0, tb1, tbn0, tbn1;
   load_window(cur, tb0, tb1);
-  u32x4 qpre[QPW];
-  fetch_queries(cur, qpre);
-  put_queries(qpre);
-  __syncthreads();
+  copy_queries(cur, 0);
 
   // Page loads of unit i of run r (table window t0/t1).  They are unconditional: a slot with no unit behind it
   // (`live` false, i clamped into the run) reads one fixed row of the pool with every lane, which costs cache
@@ -210,61 +204,48 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
       pr.vf[dt] = load_2x4_stream(vp0 + 256 * dt + voff0, vp1 + 256 * dt + voff1);
   };
 
+  constexpr int UNIT_LOADS = 2 * KS + 2 * DT;        // vector loads of one unit
   WaveState<HD, 1> st;
   PageRegs<HD> ra, rb;
-  issue(cur, tb0, tb1, min(cur.lo + wave, cur.hi - 1), cur.lo + wave < cur.hi, ra);
-  bool first_seg = true;
-
-  for (;;) {                                         // one run per iteration; uniform
+  issue(cur, tb0, tb1, cur.lo, true, ra);
+  bool first_seg = true, more = false, fresh = true;
+  int k = cur.lo;
+  auto look_ahead = [&]() {                          // the run after cur: its table window and, for a new pair, its queries
     next_run(nxt);
-    const bool more = nxt.valid;
-    if (!more) nxt = cur;                            // keeps the look-ahead loads below in bounds
+    more = nxt.valid;
+    if (!more) nxt = cur;                            // keeps the look-ahead loads in bounds
     load_window(nxt, tbn0, tbn1);
-    fetch_queries(nxt, qpre);                        // unconditional, like every load of this loop
-    if (cur.seg_start) st.reset();
-    const int key_end = cur.ctx + 1;
-    const int pos_col[1] = {cur.ctx};
-    auto step = [&](int i, const PageRegs<HD>& pr, bool valid) {
-      const int key0 = 32 * (cur.u0 + i);
-      const bool ok0 = pr.ok0 && valid, ok1 = pr.ok1 && valid;
-      pair_step<HD, 1, PL, FMT>(st, pr.k0, pr.k1, pr.vf, qf, key0, key0 + 16, ok0, ok1, key_end, pos_col,
-                                ok0 && ok1 && key0 + 32 <= key_end, scale, g);
-    };
+    if (more && nxt.seg_start) copy_queries(nxt, qsel ^ 1);
+  };
+  look_ahead();
+  st.reset();
 
-    // Two register sets alternate: while one unit is multiplied the next one's pages are in flight.  The loop
-    // body has no branch around a load (a unit index past the wave's last one is clamped and its step masked),
-    // so the hardware counters let each step wait for its own pages only.  The slot after the wave's last unit
-    // fetches its first unit of the next run, so the stream does not drain between runs.
-    const int first = cur.lo + wave;
-    const int n_my = first < cur.hi ? (cur.hi - first + 3) / 4 : 0;
-    const int last = first + 4 * (n_my - 1);
-    const int nfirst = min(nxt.lo + wave, nxt.hi - 1);
-    const bool nlive = more && nxt.lo + wave < nxt.hi;
-    for (int k = 0; k < n_my; k += 2) {
-      const int i = first + 4 * k;
-      issue(cur, tb0, tb1, min(i + 4, last), i + 4 <= last, rb);
-      asm volatile("" ::: "memory");                 // query fragments are re-read from LDS, not kept in registers
-      __builtin_amdgcn_sched_barrier(0);             // the next unit's loads go out before this unit's math
-      step(i, ra, true);
-      {
-        const bool beyond = i + 8 > last;
-        Run rs = cur;
-        if (beyond) rs = nxt;
-        issue(rs, beyond ? tbn0 : tb0, beyond ? tbn1 : tb1, beyond ? nfirst : i + 8, !beyond || nlive, ra);
-      }
-      asm volatile("" ::: "memory");
-      __builtin_amdgcn_sched_barrier(0);
-      step(i + 4, rb, k + 1 < n_my);
+  // One unit: the next one's pages (of this run or the first of the next) are requested into `next`, then the unit in
+  // `now` is multiplied.  There is no branch around the loads, so the hardware counters let a step wait for its own
+  // pages only.  Returns false after the wave's last unit.
+  auto unit = [&](PageRegs<HD>& now, PageRegs<HD>& next) -> bool {
+    const bool last = k + 1 == cur.hi;
+    {
+      Run rs = cur;
+      if (last) rs = nxt;
+      issue(rs, last ? tbn0 : tb0, last ? tbn1 : tb1, last ? nxt.lo : k + 1, !last || more, next);
     }
-    if (n_my == 0) issue(nxt, tbn0, tbn1, nfirst, nlive, ra);   // this wave had no unit in the run
-
+    // the first unit of a pair: its queries were requested before its pages, and those before the loads just issued
+    if (fresh) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(UNIT_LOADS) : "memory");
+    fresh = false;
+    asm volatile("" ::: "memory");                   // query fragments are re-read from LDS, not kept in registers
+    __builtin_amdgcn_sched_barrier(0);               // the next unit's loads go out before this unit's math
+    const int key0 = 32 * (cur.u0 + k), key_end = cur.ctx + 1;
+    const int pos_col[1] = {cur.ctx};
+    pair_step<HD, 1, PL, FMT>(st, now.k0, now.k1, now.vf, qf, key0, key0 + 16, now.ok0, now.ok1, key_end, pos_col,
+                              now.ok0 && now.ok1 && key0 + 32 <= key_end, scale, g);
+    if (!last) { ++k; return true; }
     if (cur.seg_end) {
       st.finish_denominators();
-      merge_waves<HD, 1>(st, lds_o, lds_ml, wave, lane);
       const bool whole = cur.pb == 0 && cur.pe == cur.np;
-      if (wave == 0 && whole && cur.u0 == 0) {
+      if (whole && cur.u0 == 0) {
         store_column<HD, 1, PL, FMT>(st, 0, a.o, cur.seq, cur.kvh * group + c16, g, col_ok);
-      } else if (wave == 0 && col_ok) {                // lane holds column c16, rows d = 16 dt + 4 g + {0..3}
+      } else if (col_ok) {                           // lane holds column c16, rows d = 16 dt + 4 g + {0..3}
         float* dst = whole ? a.seq_part + (((size_t)cur.seq * a.Hkv + cur.kvh) * group + c16) * PS
                            : a.part + ((size_t)(w * 2 + (first_seg ? 0 : 1)) * group + c16) * PS;
 #pragma unroll
@@ -272,12 +253,16 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         if (g == 0) { dst[HD] = st.m[0]; dst[HD + 1] = st.l[0]; }
       }
       first_seg = false;
+      st.reset();
     }
-    if (!more) break;
-    if (nxt.seg_start) put_queries(qpre);            // every wave is past the merge: the old fragments are dead
-    __syncthreads();                                 // new fragments visible; wave 0 is done with the merge buffers
-    cur = nxt; tb0 = tbn0; tb1 = tbn1;
-  }
+    if (!more) return false;
+    if (nxt.seg_start) { qsel ^= 1; fresh = true; }
+    cur = nxt; tb0 = tbn0; tb1 = tbn1; k = cur.lo;
+    look_ahead();
+    return true;
+  };
+  while (unit(ra, rb) && unit(rb, ra)) {}
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // no copy may outlive the workgroup's LDS
 }
 
 // Prefix tiles: workgroup t, t + grid, ... takes tile t of the descriptor.  The NCT x 16 columns are (member, head of
@@ -364,14 +349,19 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   }
 }
 
-// One 64-thread workgroup per (sequence, KV head): inert rows are zeroed; a pair that one share covered and no
-// prefix precedes is already final; otherwise the parts are merged in a fixed order: prefix chunks in key order,
-// then the pair's own part (one share) or parts (share order).
+// One workgroup per (sequence, KV head): inert rows are zeroed; a pair that one share covered and no prefix precedes is
+// already final; otherwise the parts are merged: prefix chunks in key order, then the pair's own part (one share) or
+// parts (share order).  A thread owns eight features of a head; MERGE_GROUPS threads share a slice and take a contiguous
+// quarter of the parts each (a long context of a single sequence is dozens of parts, a round trip per eight of them), the
+// first one the prefix chunks too; their results are merged in order through LDS.  With MERGE_ALONE pairs or more a pair
+// has at most a handful of parts, unless it is far longer than the others: one thread per slice.
+constexpr int MERGE_GROUPS = 4, MERGE_BATCH = 8, MERGE_ALONE = 512;
+constexpr int MERGE_AT_ONCE = MERGE_GROUPS * MERGE_BATCH;
 template <int HD>
-__global__ __launch_bounds__(256) void attn_decode_merge_kernel(AttnDecodeArgs a) {
-  constexpr int PS = HD + 4;
+__global__ __launch_bounds__(1024) void attn_decode_merge_kernel(AttnDecodeArgs a) {
+  constexpr int PS = HD + 4, PB = MERGE_BATCH;
+  extern __shared__ __align__(16) float merge_lds[];   // [MERGE_GROUPS - 1][slices][10]
   const int seq = blockIdx.x / a.Hkv, kvh = blockIdx.x % a.Hkv;
-  const int lane = threadIdx.x;
   const int group = a.Hq / a.Hkv, PL = a.o.planes;
   const int np = a.unit_prefix[seq + 1] - a.unit_prefix[seq];
   const Shares sh = load_shares(a.plan_hdr);
@@ -379,78 +369,111 @@ __global__ __launch_bounds__(256) void attn_decode_merge_kernel(AttnDecodeArgs a
   const int w_first = np ? sh.of_unit(xs) : 0, w_last = np ? sh.of_unit(xs + np - 1) : 0;
   const SharedView sv = shared_view(a.shared, a.n_seqs, a.Hkv);
   const int su = np ? shared_units_of(sv, seq, a.ctx_lens[seq]) : 0;
-  if (np && w_first == w_last && su == 0) return;
+  if (np && w_first == w_last && su == 0) return;      // uniform over the workgroup
   int n_chunks = 0, tile0 = 0, col0 = 0;
   if (su > 0) {
     n_chunks = min(max(sv.n_chunks[seq], 0), SP_MAX_CHUNKS);
     tile0 = max(sv.tile0[seq], 0);
     col0 = min(max(sv.col0[seq], 0), SP_COLS - group);
   }
-  for (int uu = lane; uu < group * HD / 8; uu += (int)blockDim.x) {   // one pass: the block has a thread per slice
-    const int j = uu / (HD / 8), d0 = (uu % (HD / 8)) * 8;
-    float m = -INFINITY, l = 0.f;
-    float o[8];
+  const int slices = group * HD / 8, merge_groups = (int)gridDim.x >= MERGE_ALONE ? 1 : MERGE_GROUPS;
+  const int per_group = (int)blockDim.x / merge_groups;                     // at least `slices`, whole waves
+  const int part_group = (int)threadIdx.x / per_group, uu = (int)threadIdx.x % per_group;
+  const bool mine = uu < slices;
+  const int us = mine ? uu : 0;
+  const int j = us / (HD / 8), d0 = (us % (HD / 8)) * 8;
+  float m = -INFINITY, l = 0.f;
+  float o[8];
 #pragma unroll
-    for (int e = 0; e < 8; ++e) o[e] = 0.f;
-    auto add = [&](const f32x4& va, const f32x4& vb, float ms, float ls) {
-      if (ms == -INFINITY) return;
-      const float mn = fmaxf(m, ms);
-      const float aa = state_weight(m, mn), ab = state_weight(ms, mn);
+  for (int e = 0; e < 8; ++e) o[e] = 0.f;
+  auto add = [&](const f32x4& va, const f32x4& vb, float ms, float ls) {
+    if (ms == -INFINITY) return;
+    const float mn = fmaxf(m, ms);
+    const float aa = state_weight(m, mn), ab = state_weight(ms, mn);
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        o[e] = o[e] * aa + va[e] * ab;
-        o[4 + e] = o[4 + e] * aa + vb[e] * ab;
-      }
-      l = l * aa + ls * ab;
-      m = mn;
-    };
-    auto add_at = [&](const float* p) {
-      add(*reinterpret_cast<const f32x4*>(p + d0), *reinterpret_cast<const f32x4*>(p + d0 + 4), p[HD], p[HD + 1]);
-    };
-    for (int c = 0; c < n_chunks; ++c) {
-      const int t = min(tile0 + c * a.Hkv + kvh, sv.max_tiles - 1);
-      add_at(a.pre_part + ((size_t)t * SP_COLS + col0 + j) * PS);
+    for (int e = 0; e < 4; ++e) {
+      o[e] = o[e] * aa + va[e] * ab;
+      o[4 + e] = o[4 + e] * aa + vb[e] * ab;
     }
-    if (np && w_first == w_last) {
-      add_at(a.seq_part + (((size_t)seq * a.Hkv + kvh) * group + j) * PS);
-    } else if (np) {
-      for (int w0 = w_first; w0 <= w_last; w0 += 4) {
-        f32x4 va[4], vb[4];
-        float ms[4], ls[4];
+    l = l * aa + ls * ab;
+    m = mn;
+  };
+  auto add_at = [&](const float* p) {
+    add(*reinterpret_cast<const f32x4*>(p + d0), *reinterpret_cast<const f32x4*>(p + d0 + 4), p[HD], p[HD + 1]);
+  };
+  const int n_parts = np ? w_last - w_first + 1 : 0;
+  if (part_group == 0 && n_chunks > 0) {
+    f32x4 va[SP_MAX_CHUNKS], vb[SP_MAX_CHUNKS];
+    float ms[SP_MAX_CHUNKS], ls[SP_MAX_CHUNKS];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {                // loads first (clamped), merges after
-          const int wc = w0 + q <= w_last ? w0 + q : w_last;
-          const int slot = xs <= sh.start(wc) ? 0 : 1;   // first segment of its share or not
-          const float* p = a.part + ((size_t)(wc * 2 + slot) * group + j) * PS;
-          va[q] = *reinterpret_cast<const f32x4*>(p + d0);
-          vb[q] = *reinterpret_cast<const f32x4*>(p + d0 + 4);
-          ms[q] = p[HD]; ls[q] = p[HD + 1];
+    for (int c = 0; c < SP_MAX_CHUNKS; ++c) {          // loads first (clamped), merges after
+      const int t = min(tile0 + min(c, n_chunks - 1) * a.Hkv + kvh, sv.max_tiles - 1);
+      const float* p = a.pre_part + ((size_t)t * SP_COLS + col0 + j) * PS;
+      va[c] = *reinterpret_cast<const f32x4*>(p + d0);
+      vb[c] = *reinterpret_cast<const f32x4*>(p + d0 + 4);
+      ms[c] = p[HD]; ls[c] = p[HD + 1];
+    }
+#pragma unroll
+    for (int c = 0; c < SP_MAX_CHUNKS; ++c)
+      if (c < n_chunks) add(va[c], vb[c], ms[c], ls[c]);
+  }
+  if (n_parts == 1) {
+    if (part_group == 0) add_at(a.seq_part + (((size_t)seq * a.Hkv + kvh) * group + j) * PS);
+  } else {
+    // few parts stay with the first group: nothing to gain from dealing them out
+    const int each = n_parts <= PB ? n_parts : (n_parts + merge_groups - 1) / merge_groups;
+    const int p_b = min(n_parts, part_group * each), p_e = min(n_parts, p_b + each);
+    for (int w0 = w_first + p_b; w0 < w_first + p_e; w0 += PB) {
+      f32x4 va[PB], vb[PB];
+      float ms[PB], ls[PB];
+#pragma unroll
+      for (int q = 0; q < PB; ++q) {                   // loads first (clamped), merges after
+        const int wc = min(w0 + q, w_last);
+        const int slot = xs <= sh.start(wc) ? 0 : 1;   // first segment of its share or not
+        const float* p = a.part + ((size_t)(wc * 2 + slot) * group + j) * PS;
+        va[q] = *reinterpret_cast<const f32x4*>(p + d0);
+        vb[q] = *reinterpret_cast<const f32x4*>(p + d0 + 4);
+        ms[q] = p[HD]; ls[q] = p[HD + 1];
+      }
+#pragma unroll
+      for (int q = 0; q < PB; ++q)
+        if (w0 + q < w_first + p_e) add(va[q], vb[q], ms[q], ls[q]);
+    }
+    if (n_parts > PB && merge_groups > 1) {            // uniform over the workgroup
+      float* mine_lds = merge_lds + ((size_t)(part_group - 1) * slices + us) * 10;
+      if (part_group > 0 && mine) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) mine_lds[e] = o[e];
+        mine_lds[8] = m; mine_lds[9] = l;
+      }
+      __syncthreads();
+      if (part_group == 0 && mine)
+        for (int q = 0; q < merge_groups - 1; ++q) {
+          const float* p = merge_lds + ((size_t)q * slices + us) * 10;
+          add(f32x4{p[0], p[1], p[2], p[3]}, f32x4{p[4], p[5], p[6], p[7]}, p[8], p[9]);
         }
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-          if (w0 + q <= w_last) add(va[q], vb[q], ms[q], ls[q]);
-      }
     }
-    h16_t hi[8], lo[8];
+  }
+  if (part_group > 0 || !mine) return;
+  h16_t hi[8], lo[8];
 #pragma unroll
-    for (int e = 0; e < 8; ++e) split_h16(l > 0.f ? o[e] / l : 0.f, hi[e], lo[e], a.o.dtype);
-    h16_t* dst = a.o.p + a.o.group_offset(seq, (kvh * group + j) * HD + d0);
-    u32x4 pk = {(uint32_t)hi[0] | ((uint32_t)hi[1] << 16), (uint32_t)hi[2] | ((uint32_t)hi[3] << 16),
-                (uint32_t)hi[4] | ((uint32_t)hi[5] << 16), (uint32_t)hi[6] | ((uint32_t)hi[7] << 16)};
-    *reinterpret_cast<u32x4*>(dst) = pk;
-    if (PL == 2) {
-      u32x4 pk2 = {(uint32_t)lo[0] | ((uint32_t)lo[1] << 16), (uint32_t)lo[2] | ((uint32_t)lo[3] << 16),
-                   (uint32_t)lo[4] | ((uint32_t)lo[5] << 16), (uint32_t)lo[6] | ((uint32_t)lo[7] << 16)};
-      *reinterpret_cast<u32x4*>(dst + a.o.small_terms()) = pk2;
-    }
+  for (int e = 0; e < 8; ++e) split_h16(l > 0.f ? o[e] / l : 0.f, hi[e], lo[e], a.o.dtype);
+  h16_t* dst = a.o.p + a.o.group_offset(seq, (kvh * group + j) * HD + d0);
+  u32x4 pk = {(uint32_t)hi[0] | ((uint32_t)hi[1] << 16), (uint32_t)hi[2] | ((uint32_t)hi[3] << 16),
+              (uint32_t)hi[4] | ((uint32_t)hi[5] << 16), (uint32_t)hi[6] | ((uint32_t)hi[7] << 16)};
+  *reinterpret_cast<u32x4*>(dst) = pk;
+  if (PL == 2) {
+    u32x4 pk2 = {(uint32_t)lo[0] | ((uint32_t)lo[1] << 16), (uint32_t)lo[2] | ((uint32_t)lo[3] << 16),
+                 (uint32_t)lo[4] | ((uint32_t)lo[5] << 16), (uint32_t)lo[6] | ((uint32_t)lo[7] << 16)};
+    *reinterpret_cast<u32x4*>(dst + a.o.small_terms()) = pk2;
   }
 }
 
 // One workgroup: exclusive prefix of the per-sequence unit counts, the two share sizes, and the sequence in which
 // each share starts.
 __global__ __launch_bounds__(1024) void attn_plan_kernel(int n_seqs, const int32_t* ctx, const uint8_t* live, int Hkv,
-                                                          int n_wgs, const int32_t* shared, int32_t* unit_prefix,
-                                                          int32_t* wg_seq, int32_t* hdr) {
+                                                          int n_shares, const int32_t* shared, int32_t* unit_prefix,
+                                                          int32_t* share_seq, int32_t* hdr) {
   __shared__ int sh[1024];
   __shared__ int carry;
   const int tid = threadIdx.x;
@@ -478,34 +501,34 @@ __global__ __launch_bounds__(1024) void attn_plan_kernel(int n_seqs, const int32
   if (tid == 0) unit_prefix[n_seqs] = per_head;
   __syncthreads();                                   // the prefix is read back below
   const int total = per_head * Hkv;
-  // share sizes differ by at most one unit: the units of the step are dealt out evenly and the first H workgroups
-  // take the remainder, one unit each.  (One size for all, rounded up, left a tenth of the workgroups without work
-  // at the benchmark's contexts; sizes in multiples of four units, so that the four waves of a share get equal
-  // counts, made the longer shares up to a tenth longer than the mean, and the waves' counts are unequal anyway
-  // wherever a pair's boundary falls inside a share.)  With as many (sequence, KV head) pairs as workgroups and
-  // equal contexts a share is exactly a pair: nothing straddles and nothing is left to merge.
-  const int q = total / n_wgs, H = total % n_wgs;
+  // share sizes differ by at most one unit: the units of the step are dealt out evenly and the first H shares take the
+  // remainder, one unit each.  There are at most MERGE_AT_ONCE shares per pair, the
+  // parts that the merge takes in one round trip: a lone sequence would leave it a part per unit otherwise (4B shape, one
+  // sequence of 3000 keys, attention + merge: 2 units per share 15.0 us, 3 14.7, 6 17.3; the limit makes it 3).
+  const int n = max(1, min(min(n_shares, total), MERGE_AT_ONCE * n_seqs * Hkv));
+  const int q = total / n, H = total % n;
   const int CA = q + 1, CB = q;
   if (tid == 0) { hdr[0] = CA; hdr[1] = total; hdr[2] = CB; hdr[3] = H; }
   const Shares shr = Shares{CA, CB, H, total};
-  for (int w = tid; w < n_wgs; w += 1024) {
+  for (int w = tid; w < n_shares; w += 1024) {
     const int u0 = shr.start(w);
     int lo = 0, hi = n_seqs - 1;                     // largest s with Hkv * prefix[s] <= u0
     while (lo < hi) {
       const int mid = (lo + hi + 1) >> 1;
       if (Hkv * unit_prefix[mid] <= u0) lo = mid; else hi = mid - 1;
     }
-    wg_seq[w] = u0 < total ? lo : n_seqs;
+    share_seq[w] = u0 < total ? lo : n_seqs;
   }
 }
 
 }  // namespace
 
 hipError_t attention_decode_plan(int n_seqs, const int32_t* ctx_lens, const uint8_t* tok_live, int Hkv, int n_wgs,
-                                 const int32_t* shared, int32_t* unit_prefix, int32_t* wg_seq, int32_t* hdr,
+                                 const int32_t* shared, int32_t* unit_prefix, int32_t* share_seq, int32_t* hdr,
                                  hipStream_t st) {
-  hipLaunchKernelGGL(attn_plan_kernel, dim3(1), dim3(1024), 0, st, n_seqs, ctx_lens, tok_live, Hkv, n_wgs, shared,
-                     unit_prefix, wg_seq, hdr);
+  const int n_shares = 4 * n_wgs < ATTN_SHARES_MAX ? 4 * n_wgs : ATTN_SHARES_MAX;   // a larger grid leaves waves idle
+  hipLaunchKernelGGL(attn_plan_kernel, dim3(1), dim3(1024), 0, st, n_seqs, ctx_lens, tok_live, Hkv, n_shares, shared,
+                     unit_prefix, share_seq, hdr);
   return hipGetLastError();
 }
 
@@ -613,9 +636,11 @@ hipError_t attention_decode(const AttnDecodeArgs& a, hipStream_t st) {
 hipError_t attention_decode_merge(const AttnDecodeArgs& a, hipStream_t st) {
   dim3 grid(a.n_seqs * a.Hkv);
   const int slices = (a.Hq / a.Hkv) * a.hd / 8;      // 8-feature slices of a pair's heads: at most 16 * 128 / 8 = 256
-  dim3 block((slices + 63) / 64 * 64);
-  if (a.hd == 128) hipLaunchKernelGGL((attn_decode_merge_kernel<128>), grid, block, 0, st, a);
-  else hipLaunchKernelGGL((attn_decode_merge_kernel<64>), grid, block, 0, st, a);
+  const int merge_groups = (int)grid.x >= MERGE_ALONE ? 1 : MERGE_GROUPS;
+  const dim3 block((slices + 63) / 64 * 64 * merge_groups);
+  const size_t lds = (size_t)(merge_groups - 1) * slices * 10 * sizeof(float);
+  if (a.hd == 128) hipLaunchKernelGGL((attn_decode_merge_kernel<128>), grid, block, lds, st, a);
+  else hipLaunchKernelGGL((attn_decode_merge_kernel<64>), grid, block, lds, st, a);
   return hipGetLastError();
 }
 

@@ -200,6 +200,7 @@ struct AttnArgs {            // prefill
 };
 hipError_t attention_prefill(const AttnArgs& a, hipStream_t st);
 
+constexpr int ATTN_SHARES_MAX = 2048;   // decode attention: four waves of two workgroups on 256 compute units
 struct AttnDecodeArgs {      // one new token per sequence: row = sequence slot
   RowAct q;                  // [planes][n_seqs, Hq*hd] rotated queries
   const h16_t* pool_layer;  // this layer's pages (the new token's K and V already appended)
@@ -210,10 +211,10 @@ struct AttnDecodeArgs {      // one new token per sequence: row = sequence slot
   int n_seqs;
   // plan of the step (attention_decode_plan): 32-key units of all (sequence, KV head) pairs end to end
   const int32_t* unit_prefix;  // [n_seqs + 1] exclusive prefix of the per-sequence unit counts (0 for inert rows)
-  const int32_t* wg_seq;       // [n_wgs] sequence in which workgroup w's share starts
-  const int32_t* plan_hdr;     // [4] units per share of the first H workgroups, total units, units per share of the others, H
-  int n_wgs;                   // grid size: shares of the unit sequence
-  float* part;               // [n_wgs][2][Hq/Hkv][hd+4] partial (o, m, l) of a share's first / other straddling pair
+  const int32_t* share_seq;    // [ATTN_SHARES_MAX] sequence in which a share starts
+  const int32_t* plan_hdr;     // [4] units per share of the first H shares, total units, units per share of the others, H
+  int n_wgs;                   // grid size: a share of the unit sequence per wave, at most ATTN_SHARES_MAX
+  float* part;               // [ATTN_SHARES_MAX][2][Hq/Hkv][hd+4] partial (o, m, l) of a share's first / other straddling pair
   Act o;                     // [n_seqs, Hq*hd] in fragment order (input of the output projection)
   // shared prompt prefixes (optional): the first units of a sequence that shares them with others are attended
   // once per group by attention_decode_prefix; the kernels above then start at unit sp.start_unit[seq]
@@ -240,7 +241,7 @@ inline size_t shared_prefix_words(int n_seqs, int Hkv) {
 // fills `words` (shared_prefix_words entries) from per-sequence group leaders and shared page counts (host arrays)
 void shared_prefix_build(int n_seqs, int Hq, int Hkv, const int32_t* leader, const int32_t* shared_pages, int32_t* words);
 hipError_t attention_decode_plan(int n_seqs, const int32_t* ctx_lens, const uint8_t* tok_live, int Hkv, int n_wgs,
-                                 const int32_t* shared, int32_t* unit_prefix, int32_t* wg_seq, int32_t* hdr,
+                                 const int32_t* shared, int32_t* unit_prefix, int32_t* share_seq, int32_t* hdr,
                                  hipStream_t st);
 hipError_t attention_decode_prefix(const AttnDecodeArgs& a, hipStream_t st);   // no-op without a descriptor
 hipError_t attention_decode(const AttnDecodeArgs& a, hipStream_t st);

@@ -1,0 +1,41 @@
+"""Decode attention merges the parts of a (sequence, KV head) pair with several threads per output where a call has few
+pairs and with one where it has many (512 pairs and up).  One long sequence, cut into dozens of parts, is decoded alone and
+among hundreds of short ones."""
+import numpy as np
+import pytest
+import torch
+
+import rollout_inputs as RI
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("keys", [40, 1023, 3000])
+def test_a_long_sequence_among_many_short_ones(keys):
+    import paper_2604_11554_amd as pkg
+    from paper_2604_11554_amd import synthetic
+
+    s = RI.TINY_DENSE
+    n = (512 + s.n_kv_heads - 1) // s.n_kv_heads
+    model = synthetic.model_from_shape(s, 3)
+    long = np.random.default_rng(5).integers(0, s.vocab - 2, keys).astype(np.int32)
+    logits = []
+    for short in (0, n - 1):
+        toks = [long] + [long[:1 + i % 3] for i in range(short)]
+        rows = list(range(len(toks)))
+        blocks = [(t.size + 2 + 15) // 16 for t in toks]
+        eng = pkg.RolloutEngine(model, n_blocks=sum(blocks), max_seqs=len(toks), max_chunk_tokens=keys + 3 * len(toks),
+                                max_blocks_per_seq=max(blocks))
+        for i in rows:
+            eng.add_sequence(i, reserve_tokens=16 * blocks[i])
+        eng.prefill([0], [long], forced=[int(long[0])])
+        if short:
+            eng.prefill(rows[1:], toks[1:], forced=[int(long[0])] * short)
+        out = eng.decode_step(forced=torch.full((len(toks),), int(long[0]), dtype=torch.int32, device="cuda"), want_logits=True)
+        logits.append(out.logits.cpu().numpy())
+    # the same products; sums in another grouping (other GEMM forms and parts) flip the last bit of a few bf16 keys and
+    # values (2^-9 of an element) of unit-variance logits: the bar of the calls compared form against form
+    assert np.isfinite(logits[1]).all()
+    d = np.abs(logits[0][0] - logits[1][0]).max()
+    assert d < 5e-3, d
+    model.close()
