@@ -264,10 +264,11 @@ int run_layers(const rlx_model* m, h16_t* pool, int64_t n_blocks, const Workspac
   // MoE decode batches: the gate/up GEMM reads the routing table itself and publishes the grouping (no grouping launch)
   const int rows_per_expert = c.n_experts ? (int)(((long long)T * c.top_k + c.n_experts - 1) / c.n_experts) : 0;
   const bool routed = c.n_experts && small && gemm_routed_form(c.n_experts, c.d_ff_expert, xb, T * c.top_k, rows_per_expert);
-  // short calls: the norm runs as four workgroups per row and leaves the row's common factor to the GEMMs that read
-  // xb (q|k|v, gate/up, router); not for fp16 (unnormalised rows would strain its range) and not where the grouped
+  // calls of up to 256 tokens: the norm runs as four workgroups per row (256 rows of 2560: 6.4 us; in one 8.9) and leaves
+  // the row's common factor to the GEMMs that read xb (q|k|v, gate/up, router), which also keeps rows that two bf16 terms
+  // hold exactly (embeddings) exact; not for fp16 (unnormalised rows would strain its range) and not where the grouped
   // gate/up goes through a row list
-  if (small && FMT == DT_BF16 && rmsnorm_in_parts(d) && (c.n_experts == 0 || routed)) { xb.ss = w.x_ss; xb.eps = c.rms_eps; }
+  if (T <= 256 && FMT == DT_BF16 && rmsnorm_in_parts(d) && (c.n_experts == 0 || routed)) { xb.ss = w.x_ss; xb.eps = c.rms_eps; }
   // y = x W^T into `y`: split-K planes that the next kernel adds
   auto planes_of = [&](int N, int K, bool wide) {
     if (small) return gemm_plan_splits(N, K, T, gemm_max_splits(), m->n_units, PL, FMT);

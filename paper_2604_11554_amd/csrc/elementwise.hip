@@ -300,12 +300,12 @@ __global__ __launch_bounds__(256) void rmsnorm_part_kernel(NormArgs a) {
 #pragma unroll
   for (int e = 0; e < 4; ++e) split_h16(o[e], hi[e], lo[e], dt);
   const int k = 4 * i;
-  h16_t* xo = a.x.p + frag_act_offset(t, k & ~7, 0, a.x.mtiles(), a.x.planes) + (k & 7);
+  h16_t* xo = a.x.p + a.x.group_offset(t, k & ~7) + (k & 7);
   u32x2 pk = {(uint32_t)hi[0] | ((uint32_t)hi[1] << 16), (uint32_t)hi[2] | ((uint32_t)hi[3] << 16)};
   *reinterpret_cast<u32x2*>(xo) = pk;
   if (a.x.planes == 2) {
     u32x2 pk2 = {(uint32_t)lo[0] | ((uint32_t)lo[1] << 16), (uint32_t)lo[2] | ((uint32_t)lo[3] << 16)};
-    *reinterpret_cast<u32x2*>(xo + 512) = pk2;
+    *reinterpret_cast<u32x2*>(xo + a.x.small_terms()) = pk2;
   }
 }
 

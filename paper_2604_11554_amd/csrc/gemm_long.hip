@@ -223,6 +223,15 @@ __global__ __launch_bounds__(64 * WR * WT) __attribute__((amdgpu_waves_per_eu(2,
     products(w0, xb, 0);
     products(w0, xb, 1);
   }
+  // factors that the norm left to this kernel (Act::ss): the lane's tokens r32 and 32 + r32
+  float rs[2] = {1.f, 1.f};
+  if (EPI != EPI_LMHEAD && a.x_ss) {
+#pragma unroll
+    for (int m = 0; m < 2; ++m) {
+      const int t = tok0 + m * 32 + r32;
+      rs[m] = row_rstd(a, row_ss(a, t < a.T ? t : 0));
+    }
+  }
   LmRow lm[2];
   if constexpr (EPI == EPI_LMHEAD) { lm[0] = lm_row(a, tok0 + r32); lm[1] = lm_row(a, tok0 + 32 + r32); }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // no copy may outlive the workgroup's LDS
@@ -236,10 +245,11 @@ __global__ __launch_bounds__(64 * WR * WT) __attribute__((amdgpu_waves_per_eu(2,
 #pragma unroll
       for (int q = 0; q < 16; ++q) {
         const int t = m * 32 + 8 * (q >> 2) + 4 * half + (q & 3);
+        const float f = a.x_ss ? __shfl(rs[m], t & 31, WAVE) : 1.f;
         if (tok0 + t >= a.T) continue;
 #pragma unroll
         for (int j = 0; j < JW; ++j)
-          if ((nt0 + j) * 32 + r32 < a.N) y[(size_t)t * a.ldy + 32 * j] = acc[j][m][q];
+          if ((nt0 + j) * 32 + r32 < a.N) y[(size_t)t * a.ldy + 32 * j] = acc[j][m][q] * f;
       }
   } else if (EPI == EPI_SWIGLU) {
     // rows 0..15 of a tile are gate rows, 16..31 the matching up rows: lane (token r32, half) holds features
@@ -257,7 +267,7 @@ __global__ __launch_bounds__(64 * WR * WT) __attribute__((amdgpu_waves_per_eu(2,
           float v[4];
 #pragma unroll
           for (int e = 0; e < 4; ++e) {
-            const float gt = acc[j][m][4 * g + e], up = acc[j][m][4 * (g + 2) + e];
+            const float gt = acc[j][m][4 * g + e] * rs[m], up = acc[j][m][4 * (g + 2) + e] * rs[m];
             v[e] = gt / (1.f + __expf(-gt)) * up;
           }
 #pragma unroll
@@ -358,7 +368,7 @@ int gemm_long_item_rows(int expected_rows) { return expected_rows <= 48 ? 64 : 1
 int gemm_long_splits(int N, int K, int T, int max_splits, int n_units) { return plan_long(N, K, T, max_splits, n_units).splits; }
 
 static void fill_long(GemmArgs& a, const Act& x, int N, int K, int T) {
-  a.x = x.p; a.x_pitch = x.pitch;
+  a.x = x.p; a.x_pitch = x.pitch; a.x_ss = x.ss; a.x_eps = x.eps;
   a.N = N; a.K = K; a.T = T;
   a.ksteps_per_split = (K / 16 + 1) / 2 * 2;
   a.splits = 1;
