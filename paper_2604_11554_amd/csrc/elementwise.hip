@@ -368,15 +368,20 @@ __global__ __launch_bounds__(256) void qk_rope_append_kernel(RopeArgs a) {
 }
 
 // Long calls: the kernel above spends its time issuing instructions for two elements per lane, so here
-// 16 lanes share a head and a wave takes four heads of NT tokens.  Lane j of a head owns the pairs j + 16 k
-// (k < HD / 32): summing its squares as (k = 0 with 2) + (1 with 3) and then across the 16 lanes is the butterfly
-// of the 64-lane form with its first two levels done locally, and every other operation is per element, so both
-// kernels give the same bits.  Neighbouring lanes exchange codes so that the 16-bit results leave as 32-bit stores.
+// 16 lanes share a head and a wave takes four heads of NT tokens.  Lane j of a head owns the HD / 32 consecutive pairs
+// from PPL j on: 16-byte loads, 8-byte stores.  Its squares are summed in the order of the 64-lane butterfly (pair L with
+// L ^ 32, then ^ 16, ... ^ 1: the lanes' bits first, the place inside a lane last), and every other operation is per
+// element, so both kernels give the same bits.  Values are stored transposed, [hd][16]: four tokens in neighbouring slots
+// leave as one 8-byte store per feature, two as one of 4 (2-byte stores alone touched a 32-byte sector per value).
+// 32 565 tokens of the 4B shape: 440 us with 4-byte loads and stores and 2-byte values, 364 now (4.0 TB/s); 16 384 of the
+// 30B-A3B shape 200 and 146.
 template <int HD, int NT>
 __global__ __launch_bounds__(256) void qk_rope_append_wide_kernel(RopeArgs a) {
   constexpr int half = HD / 2, PPL = HD / 32;
+  typedef float fv __attribute__((ext_vector_type(PPL)));
+  typedef uint32_t uv __attribute__((ext_vector_type(PPL / 2)));
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int j = lane & 15, odd = lane & 1;
+  const int j = lane & 15, first = PPL * j;         // first pair of the lane
   const int dt = a.q_out.dtype;
   const int n_heads = a.Hq + 2 * a.Hkv;
   const int h = (blockIdx.x * 4 + wave) * 4 + (lane >> 4);
@@ -389,13 +394,13 @@ __global__ __launch_bounds__(256) void qk_rope_append_wide_kernel(RopeArgs a) {
   float g0[PPL], g1[PPL];
 #pragma unroll
   for (int k = 0; k < PPL; ++k) {
-    g0[k] = normed ? h16_to_f32(gain[j + 16 * k], dt) : 1.f;
-    g1[k] = normed ? h16_to_f32(gain[j + 16 * k + half], dt) : 1.f;
+    g0[k] = normed ? h16_to_f32(gain[first + k], dt) : 1.f;
+    g1[k] = normed ? h16_to_f32(gain[first + k + half], dt) : 1.f;
   }
   int tc[NT], pos[NT], seq[NT];
   bool live[NT];
-  float x0[NT][PPL], x1[NT][PPL];
-  float2 cs[NT][PPL];
+  fv x0[NT], x1[NT];
+  float cs[NT][2 * PPL];
 #pragma unroll
   for (int i = 0; i < NT; ++i) {
     const int t = blockIdx.y * NT + i;
@@ -407,28 +412,24 @@ __global__ __launch_bounds__(256) void qk_rope_append_wide_kernel(RopeArgs a) {
 #pragma unroll
   for (int i = 0; i < NT; ++i) {
     const float* src = a.qkv + ((size_t)tc[i] * n_heads + hc) * HD;
+    x0[i] = 0.f + *reinterpret_cast<const fv*>(src + first);   // the plane sum of the 64-lane form
+    x1[i] = 0.f + *reinterpret_cast<const fv*>(src + first + half);
+    const fv* c = reinterpret_cast<const fv*>(a.rope_cs + (size_t)tc[i] * half + first);
+    const fv ca = c[0], cb = c[1];
 #pragma unroll
-    for (int k = 0; k < PPL; ++k) {
-      x0[i][k] = 0.f + src[j + 16 * k];              // the plane sum of the 64-lane form
-      x1[i][k] = 0.f + src[j + 16 * k + half];
-      cs[i][k] = a.rope_cs[(size_t)tc[i] * half + j + 16 * k];
-    }
+    for (int k = 0; k < PPL; ++k) { cs[i][k] = ca[k]; cs[i][PPL + k] = cb[k]; }
   }
   for (int p = 1; p < a.n_planes; ++p) {             // further split-K planes, added in plane order
     const float* plane = a.qkv + (size_t)p * a.T * n_heads * HD;
-    float v0[NT][PPL], v1[NT][PPL];
+    fv v0[NT], v1[NT];
 #pragma unroll
-    for (int i = 0; i < NT; ++i)
+    for (int i = 0; i < NT; ++i) {
+      const float* src = plane + ((size_t)tc[i] * n_heads + hc) * HD + first;
+      v0[i] = *reinterpret_cast<const fv*>(src);
+      v1[i] = *reinterpret_cast<const fv*>(src + half);
+    }
 #pragma unroll
-      for (int k = 0; k < PPL; ++k) {
-        const float* src = plane + ((size_t)tc[i] * n_heads + hc) * HD;
-        v0[i][k] = src[j + 16 * k];
-        v1[i][k] = src[j + 16 * k + half];
-      }
-#pragma unroll
-    for (int i = 0; i < NT; ++i)
-#pragma unroll
-      for (int k = 0; k < PPL; ++k) { x0[i][k] += v0[i][k]; x1[i][k] += v1[i][k]; }
+    for (int i = 0; i < NT; ++i) { x0[i] += v0[i]; x1[i] += v1[i]; }
   }
   int64_t blk[NT];
 #pragma unroll
@@ -445,56 +446,87 @@ __global__ __launch_bounds__(256) void qk_rope_append_wide_kernel(RopeArgs a) {
     const int t = blockIdx.y * NT + i;
     if (t >= a.T) break;                           // uniform over the workgroup
     const int slot = pos[i] & 15;
-    float u0[PPL], u1[PPL], p[PPL];
+    float p[PPL];
 #pragma unroll
-    for (int k = 0; k < PPL; ++k) {
-      u0[k] = x0[i][k];
-      u1[k] = x1[i][k];
-      p[k] = __builtin_fmaf(u1[k], u1[k], u0[k] * u0[k]);
+    for (int k = 0; k < PPL; ++k) p[k] = __builtin_fmaf(x1[i][k], x1[i][k], x0[i][k] * x0[i][k]);
+    // the lanes of a head trade sums until each holds the total of one of its PPL places, then add the places up
+    const bool b3 = j & 8, b2 = j & 4;
+    float ss;
+    if constexpr (PPL == 4) {
+      const float s0 = (b3 ? p[2] : p[0]) + __shfl_xor(b3 ? p[0] : p[2], 8, WAVE);
+      const float s1 = (b3 ? p[3] : p[1]) + __shfl_xor(b3 ? p[1] : p[3], 8, WAVE);
+      ss = (b2 ? s1 : s0) + __shfl_xor(b2 ? s0 : s1, 4, WAVE);
+    } else {
+      ss = (b3 ? p[1] : p[0]) + __shfl_xor(b3 ? p[0] : p[1], 8, WAVE);
+      ss += __shfl_xor(ss, 4, WAVE);
     }
-    float ss = PPL == 4 ? (p[0] + p[2]) + (p[1] + p[3]) : p[0] + p[1];
-#pragma unroll
-    for (int o = 8; o > 0; o >>= 1) ss += __shfl_xor(ss, o, WAVE);
+    ss += __shfl_xor(ss, 2, WAVE);
+    ss += __shfl_xor(ss, 1, WAVE);
+    ss += __shfl_xor(ss, 8, WAVE);
+    if constexpr (PPL == 4) ss += __shfl_xor(ss, 4, WAVE);
     const float rstd = 1.0f / sqrtf(ss / (float)HD + a.eps);
-    uint32_t mine[PPL], theirs[PPL];               // (large | small << 16) codes: mine to store, theirs to hand over
+    if (!head_ok || !(is_q || is_k)) continue;
+    h16_t* dst = nullptr;
+    if (is_q) dst = a.q_out.p + ((size_t)t * a.Hq + hc) * HD;
+    else if (blk[i] >= 0) dst = a.pool_layer + (((size_t)blk[i] * a.Hkv + (hc - a.Hq)) * 2) * 16 * HD + (size_t)slot * HD;
+    if (!dst) continue;
+    uv hi0, lo0, hi1, lo1;
+#pragma unroll
+    for (int k = 0; k < PPL; k += 2) {
+      float y0[2], y1[2];
+#pragma unroll
+      for (int e = 0; e < 2; ++e) {
+        float v0 = x0[i][k + e], v1 = x1[i][k + e];
+        if (normed) { v0 = v0 * rstd * g0[k + e]; v1 = v1 * rstd * g1[k + e]; }
+        const float c = cs[i][2 * (k + e)], sn = cs[i][2 * (k + e) + 1];
+        y0[e] = __builtin_fmaf(v0, c, -(v1 * sn));
+        y1[e] = __builtin_fmaf(v1, c, v0 * sn);
+      }
+      uint32_t h, l = 0;
+      if (dt == DT_F16) split_pair<DT_F16, 2>(y0[0], y0[1], h, l); else split_pair<DT_BF16, 2>(y0[0], y0[1], h, l);
+      hi0[k / 2] = h; lo0[k / 2] = l;
+      if (dt == DT_F16) split_pair<DT_F16, 2>(y1[0], y1[1], h, l); else split_pair<DT_BF16, 2>(y1[0], y1[1], h, l);
+      hi1[k / 2] = h; lo1[k / 2] = l;
+    }
+    *reinterpret_cast<uv*>(dst + first) = hi0;
+    *reinterpret_cast<uv*>(dst + first + half) = hi1;
+    if (is_q && a.q_out.planes == 2) {
+      *reinterpret_cast<uv*>(dst + first + a.q_out.plane) = lo0;
+      *reinterpret_cast<uv*>(dst + first + half + a.q_out.plane) = lo1;
+    }
+  }
+  if (is_q || is_k || !head_ok) return;
+  // value heads
+  const int kvh = hc - a.Hq - a.Hkv;
+  auto pack = [&](float u, float v) { return dt == DT_F16 ? pack_f16(u, v) : pack_bf16(u, v); };
+  auto next = [&](int i) { return blk[i] >= 0 && blk[i + 1] == blk[i] && pos[i + 1] == pos[i] + 1; };   // same page, next slot
+  static_assert(NT == 4, "the group of four below");
+  if ((pos[0] & 3) == 0 && next(0) && next(1) && next(2)) {
+    h16_t* dst = a.pool_layer + (((size_t)blk[0] * a.Hkv + kvh) * 2 + 1) * 16 * HD + (pos[0] & 15);
 #pragma unroll
     for (int k = 0; k < PPL; ++k) {
-      float v0 = u0[k], v1 = u1[k];
-      if (normed) { v0 = v0 * rstd * g0[k]; v1 = v1 * rstd * g1[k]; }
-      float y0 = v0, y1 = v1;
-      if (is_q || is_k) {
-        y0 = __builtin_fmaf(v0, cs[i][k].x, -(v1 * cs[i][k].y));
-        y1 = __builtin_fmaf(v1, cs[i][k].x, v0 * cs[i][k].y);
-      }
-      h16_t h0, l0 = 0, h1, l1 = 0;
-      if (is_q) { split_h16(y0, h0, l0, dt); split_h16(y1, h1, l1, dt); }
-      else { h0 = f32_to_h16(y0, dt); h1 = f32_to_h16(y1, dt); }
-      const uint32_t c0 = (uint32_t)h0 | ((uint32_t)l0 << 16), c1 = (uint32_t)h1 | ((uint32_t)l1 << 16);
-      mine[k] = odd ? c1 : c0;                     // even lanes store the first half, odd lanes the second
-      theirs[k] = __shfl_xor(odd ? c0 : c1, 1, WAVE);
+      *reinterpret_cast<u32x2*>(dst + (size_t)(first + k) * 16) = u32x2{pack(x0[0][k], x0[1][k]), pack(x0[2][k], x0[3][k])};
+      *reinterpret_cast<u32x2*>(dst + (size_t)(first + k + half) * 16) = u32x2{pack(x1[0][k], x1[1][k]), pack(x1[2][k], x1[3][k])};
     }
-    if (!head_ok) continue;
-    if (is_q || is_k) {
-      h16_t* dst = nullptr;
-      if (is_q) dst = a.q_out.p + ((size_t)t * a.Hq + hc) * HD;
-      else if (blk[i] >= 0) dst = a.pool_layer + (((size_t)blk[i] * a.Hkv + (hc - a.Hq)) * 2) * 16 * HD + (size_t)slot * HD;
-      if (dst) {
+    return;
+  }
+  bool done = false;                                // token i went out with token i - 1
 #pragma unroll
-        for (int k = 0; k < PPL; ++k) {
-          // even lane j: elements (j, j + 1) + 16 k of the first half; odd lane j: (j - 1, j) + 16 k of the second
-          const uint32_t lo_lane = odd ? theirs[k] : mine[k], hi_lane = odd ? mine[k] : theirs[k];
-          h16_t* d = dst + (odd ? half + j - 1 : j) + 16 * k;
-          *reinterpret_cast<uint32_t*>(d) = (lo_lane & 0xFFFFu) | (hi_lane << 16);
-          if (is_q && a.q_out.planes == 2)
-            *reinterpret_cast<uint32_t*>(d + a.q_out.plane) = (lo_lane >> 16) | (hi_lane & 0xFFFF0000u);
-        }
-      }
-    } else if (blk[i] >= 0) {                      // value head: stored transposed, [hd][16]
-      h16_t* dst = a.pool_layer + (((size_t)blk[i] * a.Hkv + (hc - a.Hq - a.Hkv)) * 2 + 1) * 16 * HD;
+  for (int i = 0; i < NT; ++i) {
+    if (done || blk[i] < 0) { done = false; continue; }
+    h16_t* dst = a.pool_layer + (((size_t)blk[i] * a.Hkv + kvh) * 2 + 1) * 16 * HD + (pos[i] & 15);
+    if (i + 1 < NT && (pos[i] & 1) == 0 && next(i)) {
+      done = true;
 #pragma unroll
       for (int k = 0; k < PPL; ++k) {
-        dst[(size_t)(j + 16 * k) * 16 + slot] = f32_to_h16(u0[k], dt);
-        dst[(size_t)(j + 16 * k + half) * 16 + slot] = f32_to_h16(u1[k], dt);
+        *reinterpret_cast<uint32_t*>(dst + (size_t)(first + k) * 16) = pack(x0[i][k], x0[(i + 1) % NT][k]);
+        *reinterpret_cast<uint32_t*>(dst + (size_t)(first + k + half) * 16) = pack(x1[i][k], x1[(i + 1) % NT][k]);
+      }
+    } else {
+#pragma unroll
+      for (int k = 0; k < PPL; ++k) {
+        dst[(size_t)(first + k) * 16] = f32_to_h16(x0[i][k], dt);
+        dst[(size_t)(first + k + half) * 16] = f32_to_h16(x1[i][k], dt);
       }
     }
   }

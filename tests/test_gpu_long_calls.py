@@ -95,3 +95,34 @@ def test_lm_heads_of_many_rows_draw_what_short_ones_draw(n_rows, vocab):
     # log-probabilities of unit-variance logits: 1e-6 of the sums, and up to one flipped last bit of a cached key
     assert np.abs(logprobs[0] - logprobs[1])[same].max() < 1e-3
     model.close()
+
+
+@pytest.mark.parametrize("head_dim", [64, 128])
+def test_values_of_tokens_at_any_slot_are_appended_alike(head_dim):
+    """Calls above 1024 tokens store the values of four tokens in neighbouring slots of a page together, of two, or one
+    by one: sequences that begin at every slot remainder, in one call of 1222 tokens and in two of fewer."""
+    import torch
+
+    import paper_2604_11554_amd as pkg
+    from paper_2604_11554_amd import synthetic
+
+    s = RI.TINY_DENSE.replace(name="tiny_rope", n_q_heads=2 * 64 // head_dim, n_kv_heads=1, head_dim=head_dim, qk_norm=True)
+    before, lens = [0, 1, 2, 3, 5, 16, 17, 30], [301, 1, 2, 3, 258, 7, 350, 300]
+    rng = np.random.default_rng(4)
+    toks = [rng.integers(0, s.vocab - 2, b + n).astype(np.int32) for b, n in zip(before, lens)]
+    model = synthetic.model_from_shape(s, 3)
+    pools = []
+    for calls in ([range(8)], [range(5), range(5, 8)]):
+        eng = pkg.RolloutEngine(model, n_blocks=192, max_seqs=8, max_chunk_tokens=2048, max_blocks_per_seq=32)
+        for i in range(8):
+            eng.add_sequence(i, reserve_tokens=16 * 20 + 64)
+        for i in range(1, 8):
+            eng.prefill([i], [toks[i][:before[i]]], sample_last=[False])
+        for rows in calls:
+            eng.prefill(list(rows), [toks[i][before[i]:] for i in rows], sample_last=[False] * len(rows))
+        torch.cuda.synchronize()
+        pools.append(eng.kv_pool.view(torch.int16).cpu().numpy().copy())
+    layer0 = 192 * 2 * 16 * head_dim             # the first layer's inputs are the same bits in both
+    assert (pools[0][:layer0] != 0).sum() >= sum(map(len, toks)) * head_dim
+    assert np.array_equal(pools[0][:layer0], pools[1][:layer0])
+    model.close()
