@@ -61,14 +61,24 @@ __device__ __forceinline__ int shared_units_of(const SharedView& v, int seq, int
   return v.on ? min(max(v.start_unit[seq], 0), ctx / 32) : 0;
 }
 
-// Shares of two sizes: 0 .. H-1 take CA units each, the others CB = CA - 1, as long as there are units (plan header: CA,
-// total, CB, H).
+// The unit sequence is cut into groups of two sizes, 0 .. H-1 of CA units and the others of CB = CA - 1 as long as there are
+// units, and every group into four shares, one per wave (plan header: CA, total, CB, H, spread).  Where there is a group
+// for every workgroup its shares are that workgroup's waves; fewer groups are spread over all workgroups (`spread`).
 struct Shares {
-  int CA, CB, H, U;
-  __device__ __forceinline__ int start(int w) const { return w < H ? w * CA : H * CA + (w - H) * CB; }
-  __device__ __forceinline__ int of_unit(int x) const { return x < H * CA ? x / CA : H + (x - H * CA) / max(CB, 1); }
+  int CA, CB, H, U, spread;
+  __device__ __forceinline__ int group_start(int b) const { return b < H ? b * CA : H * CA + (b - H) * CB; }
+  __device__ __forceinline__ int group_units(int b) const { return b < H ? CA : CB; }
+  __device__ __forceinline__ int start(int w) const { return group_start(w >> 2) + ((group_units(w >> 2) * (w & 3)) >> 2); }
+  __device__ __forceinline__ int of_unit(int x) const {   // x < U
+    const int b = x < H * CA ? x / CA : H + (x - H * CA) / max(CB, 1);
+    return 4 * b + (4 * (x - group_start(b)) + 3) / max(group_units(b), 1);
+  }
+  // whether the workgroup of group b holds exactly the `np` units from `xs` on, a whole pair: its waves merge it themselves
+  __device__ __forceinline__ bool whole_pair(int b, int xs, int np) const {
+    return !spread && np >= 4 && group_start(b) == xs && group_units(b) == np;
+  }
 };
-__device__ __forceinline__ Shares load_shares(const int32_t* hdr) { return Shares{hdr[0], hdr[2], hdr[3], hdr[1]}; }
+__device__ __forceinline__ Shares load_shares(const int32_t* hdr) { return Shares{hdr[0], hdr[2], hdr[3], hdr[1], hdr[4]}; }
 
 struct Run {
   int seq, kvh, ctx, np;     // np: units of the whole pair, counted from unit u0 of the sequence
@@ -89,14 +99,19 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   const int c16 = lane & 15, g = lane >> 4;
   const int group = a.Hq / a.Hkv;
   const bool col_ok = c16 < group;
-  const int w = wave * gridDim.x + blockIdx.x;       // few shares spread over the units
-  if (w >= ATTN_SHARES_MAX) return;
   const Shares sh = load_shares(a.plan_hdr);
+  const int w = sh.spread ? wave * gridDim.x + blockIdx.x : 4 * blockIdx.x + wave;
+  if (w >= ATTN_SHARES_MAX) return;
   const int U = sh.U;
   int u = sh.start(w);
   const int u_end = min(U, sh.start(w + 1));
   if (u >= u_end) return;                            // uniform over the wave
   int seq = a.share_seq[w];
+  bool pair_here = false;                            // the workgroup's shares are one whole pair (uniform over it)
+  if (!sh.spread && seq < a.n_seqs) {
+    const int p0 = a.unit_prefix[seq], np = a.unit_prefix[seq + 1] - p0, xs = sh.group_start(blockIdx.x);
+    pair_here = np > 0 && (xs - a.Hkv * p0) % np == 0 && sh.whole_pair(blockIdx.x, xs, np);
+  }
   const float scale = rsqrtf((float)HD);
   const size_t page = (size_t)2 * 16 * HD;
 
@@ -240,7 +255,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     pair_step<HD, 1, PL, FMT>(st, now.k0, now.k1, now.vf, qf, key0, key0 + 16, now.ok0, now.ok1, key_end, pos_col,
                               now.ok0 && now.ok1 && key0 + 32 <= key_end, scale, g);
     if (!last) { ++k; return true; }
-    if (cur.seg_end) {
+    if (cur.seg_end && !pair_here) {
       st.finish_denominators();
       const bool whole = cur.pb == 0 && cur.pe == cur.np;
       if (whole && cur.u0 == 0) {
@@ -263,6 +278,22 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   };
   while (unit(ra, rb) && unit(rb, ra)) {}
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // no copy may outlive the workgroup's LDS
+  if (!pair_here) return;
+  st.finish_denominators();
+  __syncthreads();                                   // the queries' LDS becomes the merge buffers
+  f32x4* lds_o = reinterpret_cast<f32x4*>(&lds_q[0][0][0]);
+  float* lds_ml = reinterpret_cast<float*>(lds_o + 2 * DT * WAVE);
+  static_assert(sizeof(lds_q) >= (2 * DT * 16 + 2 * 2 * 4) * WAVE, "the merge buffers fit");
+  merge_waves<HD, 1>(st, lds_o, lds_ml, wave, lane);
+  if (wave != 0) return;
+  if (cur.u0 == 0) {
+    store_column<HD, 1, PL, FMT>(st, 0, a.o, cur.seq, cur.kvh * group + c16, g, col_ok);
+  } else if (col_ok) {
+    float* dst = a.seq_part + (((size_t)cur.seq * a.Hkv + cur.kvh) * group + c16) * PS;
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt) *reinterpret_cast<f32x4*>(dst + 16 * dt + 4 * g) = st.o[0][dt];
+    if (g == 0) { dst[HD] = st.m[0]; dst[HD + 1] = st.l[0]; }
+  }
 }
 
 // Prefix tiles: workgroup t, t + grid, ... takes tile t of the descriptor.  The NCT x 16 columns are (member, head of
@@ -366,7 +397,8 @@ __global__ __launch_bounds__(1024) void attn_decode_merge_kernel(AttnDecodeArgs 
   const int np = a.unit_prefix[seq + 1] - a.unit_prefix[seq];
   const Shares sh = load_shares(a.plan_hdr);
   const int xs = a.Hkv * a.unit_prefix[seq] + kvh * np;
-  const int w_first = np ? sh.of_unit(xs) : 0, w_last = np ? sh.of_unit(xs + np - 1) : 0;
+  const int w_first = np ? sh.of_unit(xs) : 0;
+  const int w_last = np && !sh.whole_pair(w_first >> 2, xs, np) ? sh.of_unit(xs + np - 1) : w_first;
   const SharedView sv = shared_view(a.shared, a.n_seqs, a.Hkv);
   const int su = np ? shared_units_of(sv, seq, a.ctx_lens[seq]) : 0;
   if (np && w_first == w_last && su == 0) return;      // uniform over the workgroup
@@ -437,7 +469,7 @@ __global__ __launch_bounds__(1024) void attn_decode_merge_kernel(AttnDecodeArgs 
       }
 #pragma unroll
       for (int q = 0; q < PB; ++q)
-        if (w0 + q < w_first + p_e) add(va[q], vb[q], ms[q], ls[q]);
+        if (w0 + q < w_first + p_e && sh.start(w0 + q) < sh.start(w0 + q + 1)) add(va[q], vb[q], ms[q], ls[q]);
     }
     if (n_parts > PB && merge_groups > 1) {            // uniform over the workgroup
       float* mine_lds = merge_lds + ((size_t)(part_group - 1) * slices + us) * 10;
@@ -472,7 +504,7 @@ __global__ __launch_bounds__(1024) void attn_decode_merge_kernel(AttnDecodeArgs 
 // One workgroup: exclusive prefix of the per-sequence unit counts, the two share sizes, and the sequence in which
 // each share starts.
 __global__ __launch_bounds__(1024) void attn_plan_kernel(int n_seqs, const int32_t* ctx, const uint8_t* live, int Hkv,
-                                                          int n_shares, const int32_t* shared, int32_t* unit_prefix,
+                                                          int n_wgs, int n_shares, const int32_t* shared, int32_t* unit_prefix,
                                                           int32_t* share_seq, int32_t* hdr) {
   __shared__ int sh[1024];
   __shared__ int carry;
@@ -501,15 +533,15 @@ __global__ __launch_bounds__(1024) void attn_plan_kernel(int n_seqs, const int32
   if (tid == 0) unit_prefix[n_seqs] = per_head;
   __syncthreads();                                   // the prefix is read back below
   const int total = per_head * Hkv;
-  // share sizes differ by at most one unit: the units of the step are dealt out evenly and the first H shares take the
-  // remainder, one unit each.  There are at most MERGE_AT_ONCE shares per pair, the
-  // parts that the merge takes in one round trip: a lone sequence would leave it a part per unit otherwise (4B shape, one
-  // sequence of 3000 keys, attention + merge: 2 units per share 15.0 us, 3 14.7, 6 17.3; the limit makes it 3).
-  const int n = max(1, min(min(n_shares, total), MERGE_AT_ONCE * n_seqs * Hkv));
+  // Group sizes differ by at most one unit, and so do the shares: the units of the step are dealt out evenly.  There are
+  // at most MERGE_AT_ONCE shares per pair, the parts that the merge takes in one round trip: a lone sequence would leave it
+  // a part per unit otherwise (4B shape, one sequence of 3000 keys, attention + merge: 2 units per share 15.0 us, 3 14.7,
+  // 6 17.3; the limit makes it 3).  With as many pairs as workgroups and equal contexts a group is exactly a pair.
+  const int n = max(1, min(min(n_shares / 4, total / 4), MERGE_AT_ONCE / 4 * n_seqs * Hkv));
   const int q = total / n, H = total % n;
-  const int CA = q + 1, CB = q;
-  if (tid == 0) { hdr[0] = CA; hdr[1] = total; hdr[2] = CB; hdr[3] = H; }
-  const Shares shr = Shares{CA, CB, H, total};
+  const int CA = q + 1, CB = q, spread = n < n_wgs;
+  if (tid == 0) { hdr[0] = CA; hdr[1] = total; hdr[2] = CB; hdr[3] = H; hdr[4] = spread; }
+  const Shares shr = Shares{CA, CB, H, total, spread};
   for (int w = tid; w < n_shares; w += 1024) {
     const int u0 = shr.start(w);
     int lo = 0, hi = n_seqs - 1;                     // largest s with Hkv * prefix[s] <= u0
@@ -527,7 +559,7 @@ hipError_t attention_decode_plan(int n_seqs, const int32_t* ctx_lens, const uint
                                  const int32_t* shared, int32_t* unit_prefix, int32_t* share_seq, int32_t* hdr,
                                  hipStream_t st) {
   const int n_shares = 4 * n_wgs < ATTN_SHARES_MAX ? 4 * n_wgs : ATTN_SHARES_MAX;   // a larger grid leaves waves idle
-  hipLaunchKernelGGL(attn_plan_kernel, dim3(1), dim3(1024), 0, st, n_seqs, ctx_lens, tok_live, Hkv, n_shares, shared,
+  hipLaunchKernelGGL(attn_plan_kernel, dim3(1), dim3(1024), 0, st, n_seqs, ctx_lens, tok_live, Hkv, n_wgs, n_shares, shared,
                      unit_prefix, share_seq, hdr);
   return hipGetLastError();
 }

@@ -39,3 +39,30 @@ def test_a_long_sequence_among_many_short_ones(keys):
     d = np.abs(logits[0][0] - logits[1][0]).max()
     assert d < 5e-3, d
     model.close()
+
+
+@pytest.mark.parametrize("keys", [97, 130, 2200])
+def test_pairs_that_are_exactly_a_workgroup(keys):
+    """With as many workgroups as pairs and equal contexts the four waves of a workgroup share one pair and merge it
+    themselves (four units at least: 97 keys are the fewest); other grids cut the same pairs elsewhere."""
+    import paper_2604_11554_amd as pkg
+    from paper_2604_11554_amd import synthetic
+
+    s, n = RI.TINY_DENSE, 3
+    model = synthetic.model_from_shape(s, 3)
+    rng = np.random.default_rng(6)
+    toks = [rng.integers(0, s.vocab - 2, keys - 1).astype(np.int32) for _ in range(n)]
+    logits = []
+    for grid in (n * s.n_kv_heads, n * s.n_kv_heads + 1, 1, 512):
+        model.set_attention_grid(grid)
+        blocks = (keys + 17) // 16
+        eng = pkg.RolloutEngine(model, n_blocks=n * blocks, max_seqs=n, max_chunk_tokens=n * keys, max_blocks_per_seq=blocks)
+        for i in range(n):
+            eng.add_sequence(i, reserve_tokens=16 * blocks)
+        eng.prefill(list(range(n)), toks, forced=[1] * n)
+        out = eng.decode_step(forced=torch.ones(n, dtype=torch.int32, device="cuda"), want_logits=True)
+        logits.append(out.logits.cpu().numpy())
+    # one layer's sums in another grouping: as above
+    assert np.isfinite(logits[0]).all()
+    assert max(np.abs(z - logits[0]).max() for z in logits[1:]) < 5e-3
+    model.close()
