@@ -452,6 +452,8 @@ __global__ __launch_bounds__(1024) void attn_decode_merge_kernel(AttnDecodeArgs 
   if (n_parts == 1) {
     if (part_group == 0) add_at(a.seq_part + (((size_t)seq * a.Hkv + kvh) * group + j) * PS);
   } else {
+    const int slot0 = xs <= sh.start(w_first) ? 0 : 1;
+    const bool gaps = sh.CA <= 4;                      // shares may be empty in a step of fewer than four units
     // few parts stay with the first group: nothing to gain from dealing them out
     const int each = n_parts <= PB ? n_parts : (n_parts + merge_groups - 1) / merge_groups;
     const int p_b = min(n_parts, part_group * each), p_e = min(n_parts, p_b + each);
@@ -461,7 +463,7 @@ __global__ __launch_bounds__(1024) void attn_decode_merge_kernel(AttnDecodeArgs 
 #pragma unroll
       for (int q = 0; q < PB; ++q) {                   // loads first (clamped), merges after
         const int wc = min(w0 + q, w_last);
-        const int slot = xs <= sh.start(wc) ? 0 : 1;   // first segment of its share or not
+        const int slot = wc == w_first ? slot0 : 0;    // first segment of its share or not
         const float* p = a.part + ((size_t)(wc * 2 + slot) * group + j) * PS;
         va[q] = *reinterpret_cast<const f32x4*>(p + d0);
         vb[q] = *reinterpret_cast<const f32x4*>(p + d0 + 4);
@@ -469,7 +471,7 @@ __global__ __launch_bounds__(1024) void attn_decode_merge_kernel(AttnDecodeArgs 
       }
 #pragma unroll
       for (int q = 0; q < PB; ++q)
-        if (w0 + q < w_first + p_e && sh.start(w0 + q) < sh.start(w0 + q + 1)) add(va[q], vb[q], ms[q], ls[q]);
+        if (w0 + q < w_first + p_e && (!gaps || sh.start(w0 + q) < sh.start(w0 + q + 1))) add(va[q], vb[q], ms[q], ls[q]);
     }
     if (n_parts > PB && merge_groups > 1) {            // uniform over the workgroup
       float* mine_lds = merge_lds + ((size_t)(part_group - 1) * slices + us) * 10;
