@@ -7,8 +7,10 @@
 // contexts being the same for every layer), on a grid that is exactly resident (two workgroups of four waves per
 // compute unit).  A wave walks its share by itself, the next unit's pages on their way while it works on the current
 // one, the next pair's queries copied into its part of LDS by the hardware; there is no barrier.  Where a (sequence, KV
-// head) pair lies inside one share its output is final; where it straddles shares each part leaves (o, m, l) and a small
-// second kernel merges the parts in share order (deterministic).
+// head) pair lies inside one share its output is final; where a workgroup's four shares are exactly one pair (equal
+// contexts, as many pairs as workgroups) they are merged through LDS at the end (30B-A3B shape, 128 sequences: 16.41 ->
+// 16.10 ms per step against the merge kernel); elsewhere each part leaves (o, m, l) and a small second kernel merges the
+// parts in share order (deterministic).
 // (With a share per workgroup, its waves taking units in turn, the end of every pair cost a merge of the four waves
 // through LDS, three barriers and a half-idle step.  4B shape, 256 sequences, one layer: 32 to 287 keys each 94 us then,
 // 42 now; 144 keys each 51 and 35; 1024 keys each 182 and 172, 6.2 TB/s.  A lone sequence of 3000 keys: merge 19 us
