@@ -133,6 +133,10 @@ bool long_call(const rlx_model_config& c, int T) {
 // ... and so do LM heads of more than 64 rows (151 936 x 2560, one draw per row: 96 rows 234 -> 211 us, 256 rows 509 -> 396;
 // 64 rows 153 in the short form, 161 at best in long ones)
 bool rows_lmhead(const rlx_model_config& c, int rows) { return rows > 64 && c.activation_split && c.dtype == RLX_DTYPE_BF16; }
+// Decode attention of MoE policies keeps a share of the keys per workgroup: in a share per wave the sums come in another
+// order, and the last bits of the router's input decide near-ties of the routing (30B-A3B shape, 128 sequences of 1530
+// keys: one token took its ninth expert for its eighth, which moved the batch's logits by 3 % of their norm).
+bool attn_by_team(const rlx_model_config& c) { return c.n_experts > 0; }
 Act call_act(const rlx_model_config& c, h16_t* p, int T, int K, bool rows) {
   return rows ? make_act_rows(p, T, K) : make_act(p, T, K, c.activation_split ? 2 : 1, c.dtype);
 }
@@ -190,7 +194,7 @@ Workspace carve(const rlx_model_config& c, char* base, int S, int T, int max_blo
   w.ob = (h16_t*)take(act_bytes(T, qdim, lng));
   w.attn_prefix = (int32_t*)take((size_t)(S + 1) * 4);
   w.attn_share_seq = (int32_t*)take((size_t)ATTN_SHARES_MAX * 4);
-  w.attn_hdr = (int32_t*)take(5 * 4);
+  w.attn_hdr = (int32_t*)take(6 * 4);
   w.attn_seq_part = (float*)take((size_t)S * c.n_q_heads * (c.head_dim + 4) * 4);
   w.attn_pre_part = (float*)take((size_t)shared_prefix_max_tiles(S, c.n_kv_heads) * SP_COLS * (c.head_dim + 4) * 4);
   // Split-K planes of q|k|v and of the o and down projections.  Both are dead while decode attention runs (its queries
@@ -314,7 +318,7 @@ int run_layers(const rlx_model* m, h16_t* pool, int64_t n_blocks, const Workspac
       at.Hq = c.n_q_heads; at.Hkv = c.n_kv_heads; at.hd = c.head_dim;
       at.block_table = io.block_table; at.max_blocks = io.max_blocks; at.ctx_lens = io.ctx_lens;
       at.n_seqs = io.n_seqs; at.unit_prefix = w.attn_prefix; at.share_seq = w.attn_share_seq; at.plan_hdr = w.attn_hdr;
-      at.n_wgs = m->attn_wgs; at.part = w.attn_part; at.o = ob;
+      at.team = attn_by_team(c); at.n_wgs = m->attn_wgs; at.part = w.attn_part; at.o = ob;
       at.shared = io.shared_prefix; at.seq_part = w.attn_seq_part; at.pre_part = w.attn_pre_part;
       at.n_prefix_wgs = 2 * m->n_units;
       RLX_LAUNCH(RLX_K_ATTN_PREFIX, attention_decode_prefix(at, st));
@@ -675,7 +679,7 @@ int rollout_decode_step_shared(const rlx_model* m, void* kv_pool, int64_t n_bloc
   hipStream_t st = (hipStream_t)stream;
   RLX_HIP(meta_decode(w.meta, n_seqs, ctx_lens_inout, finished_inout, m->inv_freq, m->cfg.head_dim, st));
   RLX_HIP(attention_decode_plan(n_seqs, ctx_lens_inout, w.meta.tok_live, m->cfg.n_kv_heads, m->attn_wgs,
-                                (const int32_t*)shared_prefix, w.attn_prefix, w.attn_share_seq, w.attn_hdr, st));
+                                attn_by_team(m->cfg), (const int32_t*)shared_prefix, w.attn_prefix, w.attn_share_seq, w.attn_hdr, st));
   StepIO io = {};
   io.n_seqs = n_seqs; io.T = n_seqs; io.decode = true;
   io.tokens = tokens_inout; io.ctx_lens = ctx_lens_inout; io.ctx_lens_rw = ctx_lens_inout;

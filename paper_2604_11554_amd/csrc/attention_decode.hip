@@ -16,6 +16,11 @@
 // 42 now; 144 keys each 51 and 35; 1024 keys each 182 and 172, 6.2 TB/s.  A lone sequence of 3000 keys: merge 19 us
 // then, of 64 parts by one round trip per four, 5 now.)
 //
+// MoE policies (a.team) keep a share per WORKGROUP instead, its four waves taking the share's units in turn and merging
+// their sums through LDS: another order of sums is not wrong, but it moves the last bits of the router's input, and a token
+// at a near-tie of its eighth and ninth expert goes the other way.  30B-A3B shape, four layers, 128 sequences of 1530 keys:
+// 1.41 ms a step with a share per wave, 1.39 to 1.43 with one per workgroup.
+//
 // Shared prompt prefixes (sequences of one sampling group list the same pages for their prompt): the descriptor
 // `shared` names, per sequence, how many leading units are served by prefix tiles instead.  A prefix tile is
 // (subgroup of up to 32 / group sequences, KV head, chunk of units): the 32 columns of its two MFMA column tiles
@@ -64,23 +69,24 @@ __device__ __forceinline__ int shared_units_of(const SharedView& v, int seq, int
 }
 
 // The unit sequence is cut into groups of two sizes, 0 .. H-1 of CA units and the others of CB = CA - 1 as long as there are
-// units, and every group into four shares, one per wave (plan header: CA, total, CB, H, spread).  Where there is a group
-// for every workgroup its shares are that workgroup's waves; fewer groups are spread over all workgroups (`spread`).
+// units (plan header: CA, total, CB, H, spread, per).  A share per workgroup: a group is a share (per = 1).  A share per wave:
+// every group is four (per = 4); where there is a group for every workgroup its shares are that workgroup's waves, fewer
+// groups are spread over all workgroups (`spread`).
 struct Shares {
-  int CA, CB, H, U, spread;
+  int CA, CB, H, U, spread, per;
   __device__ __forceinline__ int group_start(int b) const { return b < H ? b * CA : H * CA + (b - H) * CB; }
   __device__ __forceinline__ int group_units(int b) const { return b < H ? CA : CB; }
-  __device__ __forceinline__ int start(int w) const { return group_start(w >> 2) + ((group_units(w >> 2) * (w & 3)) >> 2); }
+  __device__ __forceinline__ int start(int w) const { return group_start(w / per) + group_units(w / per) * (w % per) / per; }
   __device__ __forceinline__ int of_unit(int x) const {   // x < U
     const int b = x < H * CA ? x / CA : H + (x - H * CA) / max(CB, 1);
-    return 4 * b + (4 * (x - group_start(b)) + 3) / max(group_units(b), 1);
+    return per * b + (per * (x - group_start(b)) + per - 1) / max(group_units(b), 1);
   }
   // whether the workgroup of group b holds exactly the `np` units from `xs` on, a whole pair: its waves merge it themselves
   __device__ __forceinline__ bool whole_pair(int b, int xs, int np) const {
-    return !spread && np >= 4 && group_start(b) == xs && group_units(b) == np;
+    return per == 4 && !spread && np >= 4 && group_start(b) == xs && group_units(b) == np;
   }
 };
-__device__ __forceinline__ Shares load_shares(const int32_t* hdr) { return Shares{hdr[0], hdr[2], hdr[3], hdr[1], hdr[4]}; }
+__device__ __forceinline__ Shares load_shares(const int32_t* hdr) { return Shares{hdr[0], hdr[2], hdr[3], hdr[1], hdr[4], hdr[5]}; }
 
 struct Run {
   int seq, kvh, ctx, np;     // np: units of the whole pair, counted from unit u0 of the sequence
@@ -90,42 +96,26 @@ struct Run {
   bool seg_start, seg_end, valid;
 };
 
-template <int HD, int PL, int FMT>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_decode_kernel(AttnDecodeArgs a) {
-  constexpr int DT = HD / 16, KS = HD / 32, PS = HD + 4, NQ = PL * KS;
-  // query fragments of the wave's current and next pair, MFMA operand order
-  __shared__ u32x4 lds_q[4][2][NQ * WAVE];
-
-  const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int c16 = lane & 15, g = lane >> 4;
-  const int group = a.Hq / a.Hkv;
-  const bool col_ok = c16 < group;
-  const Shares sh = load_shares(a.plan_hdr);
-  const int w = sh.spread ? wave * gridDim.x + blockIdx.x : 4 * blockIdx.x + wave;
-  if (w >= ATTN_SHARES_MAX) return;
-  const int U = sh.U;
-  int u = sh.start(w);
-  const int u_end = min(U, sh.start(w + 1));
-  if (u >= u_end) return;                            // uniform over the wave
-  int seq = a.share_seq[w];
-  bool pair_here = false;                            // the workgroup's shares are one whole pair (uniform over it)
-  if (!sh.spread && seq < a.n_seqs) {
-    const int p0 = a.unit_prefix[seq], np = a.unit_prefix[seq + 1] - p0, xs = sh.group_start(blockIdx.x);
-    pair_here = np > 0 && (xs - a.Hkv * p0) % np == 0 && sh.whole_pair(blockIdx.x, xs, np);
+// Walks the runs of a share: the per-sequence plan entries are held in a 64-lane register window.
+struct RunWalk {
+  const AttnDecodeArgs& a;
+  const SharedView sv;
+  const int lane, u_end;
+  int u, seq, seq0, rem_lo, rem_hi;                  // rem: rest of the current segment
+  int32_t wpre, wctx, wst;
+  Run seg;
+  __device__ __forceinline__ RunWalk(const AttnDecodeArgs& args, int lane_, int u_, int u_end_, int seq_)
+      : a(args), sv(shared_view(args.shared, args.n_seqs, args.Hkv)), lane(lane_), u_end(u_end_), u(u_), seq(seq_), rem_lo(0),
+        rem_hi(0), seg() {
+    slide();
   }
-  const float scale = rsqrtf((float)HD);
-  const size_t page = (size_t)2 * 16 * HD;
-
-  // ---- run generator: the per-sequence plan entries are held in a 64-lane register window ----
-  const SharedView sv = shared_view(a.shared, a.n_seqs, a.Hkv);
-  int seq0 = seq;
-  int32_t wpre = a.unit_prefix[min(seq0 + lane, a.n_seqs)];
-  int32_t wctx = a.ctx_lens[min(seq0 + lane, a.n_seqs - 1)];
-  int32_t wst = shared_units_of(sv, min(seq0 + lane, a.n_seqs - 1), wctx);
-  int rem_lo = 0, rem_hi = 0;                        // rest of the current segment
-  Run seg = {};
-  auto next_run = [&](Run& r) {
+  __device__ __forceinline__ void slide() {
+    seq0 = seq;
+    wpre = a.unit_prefix[min(seq0 + lane, a.n_seqs)];
+    wctx = a.ctx_lens[min(seq0 + lane, a.n_seqs - 1)];
+    wst = shared_units_of(sv, min(seq0 + lane, a.n_seqs - 1), wctx);
+  }
+  __device__ __forceinline__ void next(Run& r) {
     if (rem_lo < rem_hi) {                           // the segment continues in another table window
       r = seg;
       r.lo = rem_lo; r.hi = min(rem_hi, rem_lo + 64);
@@ -135,12 +125,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     }
     r.valid = false;
     while (u < u_end && seq < a.n_seqs) {
-      if (seq - seq0 > 62) {                         // slide the window (rare: 63 sequences inside one share)
-        seq0 = seq;
-        wpre = a.unit_prefix[min(seq0 + lane, a.n_seqs)];
-        wctx = a.ctx_lens[min(seq0 + lane, a.n_seqs - 1)];
-        wst = shared_units_of(sv, min(seq0 + lane, a.n_seqs - 1), wctx);
-      }
+      if (seq - seq0 > 62) slide();                  // rare: 63 sequences inside one share
       const int p0 = __builtin_amdgcn_readlane(wpre, seq - seq0);
       const int np = __builtin_amdgcn_readlane(wpre, seq - seq0 + 1) - p0;
       if (np == 0) { ++seq; continue; }              // inert sequence: no units
@@ -161,16 +146,95 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
       if (seg.pe == np && kvh == a.Hkv - 1) ++seq;
       return;
     }
-  };
-  // block-table window of a run: lane holds the entries of blocks 2 (u0 + lo) + lane and + 64
-  auto load_window = [&](const Run& r, int32_t& t0, int32_t& t1) {
-    const int32_t* table = a.block_table + (size_t)r.seq * a.max_blocks;
-    const int jb = 2 * (r.u0 + r.lo) + lane;
-    const int j0 = min(jb, a.max_blocks - 1), j1 = min(jb + 64, a.max_blocks - 1);
-    t0 = table[j0]; t1 = table[j1];                  // unconditional, clamped; masked below
-    if (jb >= a.max_blocks) t0 = -1;
-    if (jb + 64 >= a.max_blocks) t1 = -1;
-  };
+  }
+};
+
+// block-table window of a run: lane holds the entries of blocks 2 (u0 + lo) + lane and + 64
+__device__ __forceinline__ void load_window(const AttnDecodeArgs& a, const Run& r, int lane, int32_t& t0, int32_t& t1) {
+  const int32_t* table = a.block_table + (size_t)r.seq * a.max_blocks;
+  const int jb = 2 * (r.u0 + r.lo) + lane;
+  const int j0 = min(jb, a.max_blocks - 1), j1 = min(jb + 64, a.max_blocks - 1);
+  t0 = table[j0]; t1 = table[j1];                    // unconditional, clamped; masked below
+  if (jb >= a.max_blocks) t0 = -1;
+  if (jb + 64 >= a.max_blocks) t1 = -1;
+}
+
+// Page loads of unit i of run r (table window t0/t1).  They are unconditional: a slot with no unit behind it
+// (`live` false, i clamped into the run) reads one fixed row of the pool with every lane, which costs cache
+// hits and no memory traffic.
+template <int HD>
+__device__ __forceinline__ void issue_unit(const AttnDecodeArgs& a, const Run& r, int32_t t0, int32_t t1, int i, bool live, int c16,
+                                           int g, PageRegs<HD>& pr) {
+  constexpr size_t page = (size_t)2 * 16 * HD;
+  const int rel = 2 * (i - r.lo);                    // uniform, 0 .. 126
+  const int32_t sel = rel < 64 ? t0 : t1;
+  int64_t b0 = __builtin_amdgcn_readlane(sel, rel & 63);
+  int64_t b1 = __builtin_amdgcn_readlane(sel, (rel + 1) & 63);
+  const bool has1 = (2 * (r.u0 + i) + 1) * 16 < r.ctx + 1;
+  pr.ok0 = live && b0 >= 0 && b0 < a.n_blocks;
+  pr.ok1 = live && has1 && b1 >= 0 && b1 < a.n_blocks;
+  if (!pr.ok0) b0 = 0;                               // keep the loads in bounds; scores are masked
+  if (!pr.ok1) b1 = b0;
+  const h16_t* kp0 = a.pool_layer + ((size_t)b0 * a.Hkv + r.kvh) * page;
+  const h16_t* kp1 = a.pool_layer + ((size_t)b1 * a.Hkv + r.kvh) * page;
+  const h16_t* vp0 = kp0 + 16 * HD;
+  const h16_t* vp1 = kp1 + 16 * HD;
+  const int koff0 = pr.ok0 ? c16 * HD + 8 * g : 0, koff1 = pr.ok1 ? c16 * HD + 8 * g : 0;
+  const int voff0 = pr.ok0 ? c16 * 16 + 4 * g : 0, voff1 = pr.ok1 ? c16 * 16 + 4 * g : 0;
+#pragma unroll
+  for (int ks = 0; ks < HD / 32; ++ks) {
+    pr.k0[ks] = load_stream_16(kp0 + koff0 + 32 * ks);
+    pr.k1[ks] = load_stream_16(kp1 + koff1 + 32 * ks);
+  }
+#pragma unroll
+  for (int dt = 0; dt < HD / 16; ++dt)
+    pr.vf[dt] = load_2x4_stream(vp0 + 256 * dt + voff0, vp1 + 256 * dt + voff1);
+}
+
+// The end of a segment: final if it is a whole pair that no prefix precedes, else (o, m, l) for the merge kernel.  `share`:
+// index of its share, `first`: it is the share's first segment.  Every lane of the wave calls it; a lane holds column
+// c16, rows d = 16 dt + 4 g + {0..3}.
+template <int HD, int PL, int FMT>
+__device__ __forceinline__ void store_segment(const AttnDecodeArgs& a, const WaveState<HD, 1>& st, const Run& r, int share, bool first,
+                                              int group, int c16, int g) {
+  constexpr int PS = HD + 4;
+  const bool col_ok = c16 < group, whole = r.pb == 0 && r.pe == r.np;
+  if (whole && r.u0 == 0) {
+    store_column<HD, 1, PL, FMT>(st, 0, a.o, r.seq, r.kvh * group + c16, g, col_ok);
+  } else if (col_ok) {
+    float* dst = whole ? a.seq_part + (((size_t)r.seq * a.Hkv + r.kvh) * group + c16) * PS
+                       : a.part + ((size_t)(share * 2 + (first ? 0 : 1)) * group + c16) * PS;
+#pragma unroll
+    for (int dt = 0; dt < HD / 16; ++dt) *reinterpret_cast<f32x4*>(dst + 16 * dt + 4 * g) = st.o[0][dt];
+    if (g == 0) { dst[HD] = st.m[0]; dst[HD + 1] = st.l[0]; }
+  }
+}
+
+// A share per wave (dense policies).
+template <int HD, int PL, int FMT>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_decode_kernel(AttnDecodeArgs a) {
+  constexpr int DT = HD / 16, KS = HD / 32, PS = HD + 4, NQ = PL * KS;
+  // query fragments of the wave's current and next pair, MFMA operand order
+  __shared__ u32x4 lds_q[4][2][NQ * WAVE];
+
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int c16 = lane & 15, g = lane >> 4;
+  const int group = a.Hq / a.Hkv;
+  const bool col_ok = c16 < group;
+  const Shares sh = load_shares(a.plan_hdr);
+  const int w = sh.spread ? wave * gridDim.x + blockIdx.x : 4 * blockIdx.x + wave;
+  if (w >= ATTN_SHARES_MAX) return;
+  const int u = sh.start(w), u_end = min(sh.U, sh.start(w + 1));
+  if (u >= u_end) return;                            // uniform over the wave
+  const int seq = a.share_seq[w];
+  bool pair_here = false;                            // the workgroup's shares are one whole pair (uniform over it)
+  if (!sh.spread && seq < a.n_seqs) {
+    const int p0 = a.unit_prefix[seq], np = a.unit_prefix[seq + 1] - p0, xs = sh.group_start(blockIdx.x);
+    pair_here = np > 0 && (xs - a.Hkv * p0) % np == 0 && sh.whole_pair(blockIdx.x, xs, np);
+  }
+  const float scale = rsqrtf((float)HD);
+  RunWalk walk(a, lane, u, u_end, seq);
   // The query fragments of a pair go straight into LDS, a whole run before they are read (the run generator looks one
   // run ahead anyway).  Columns past the group read some head's queries; their results are never stored.
   int qsel = 0;
@@ -186,52 +250,23 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   auto qf = [&](int p, int, int ks) { return __builtin_bit_cast(h16x8, lds_q[wave][qsel][(p * KS + ks) * WAVE + lane]); };
 
   Run cur, nxt;
-  next_run(cur);
+  walk.next(cur);
   if (!cur.valid) return;
   int32_t tb0, tb1, tbn0, tbn1;
-  load_window(cur, tb0, tb1);
+  load_window(a, cur, lane, tb0, tb1);
   copy_queries(cur, 0);
-
-  // Page loads of unit i of run r (table window t0/t1).  They are unconditional: a slot with no unit behind it
-  // (`live` false, i clamped into the run) reads one fixed row of the pool with every lane, which costs cache
-  // hits and no memory traffic.
-  auto issue = [&](const Run& r, int32_t t0, int32_t t1, int i, bool live, PageRegs<HD>& pr) {
-    const int rel = 2 * (i - r.lo);                  // uniform, 0 .. 126
-    const int32_t sel = rel < 64 ? t0 : t1;
-    int64_t b0 = __builtin_amdgcn_readlane(sel, rel & 63);
-    int64_t b1 = __builtin_amdgcn_readlane(sel, (rel + 1) & 63);
-    const bool has1 = (2 * (r.u0 + i) + 1) * 16 < r.ctx + 1;
-    pr.ok0 = live && b0 >= 0 && b0 < a.n_blocks;
-    pr.ok1 = live && has1 && b1 >= 0 && b1 < a.n_blocks;
-    if (!pr.ok0) b0 = 0;                             // keep the loads in bounds; scores are masked
-    if (!pr.ok1) b1 = b0;
-    const h16_t* kp0 = a.pool_layer + ((size_t)b0 * a.Hkv + r.kvh) * page;
-    const h16_t* kp1 = a.pool_layer + ((size_t)b1 * a.Hkv + r.kvh) * page;
-    const h16_t* vp0 = kp0 + 16 * HD;
-    const h16_t* vp1 = kp1 + 16 * HD;
-    const int koff0 = pr.ok0 ? c16 * HD + 8 * g : 0, koff1 = pr.ok1 ? c16 * HD + 8 * g : 0;
-    const int voff0 = pr.ok0 ? c16 * 16 + 4 * g : 0, voff1 = pr.ok1 ? c16 * 16 + 4 * g : 0;
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) {
-      pr.k0[ks] = load_stream_16(kp0 + koff0 + 32 * ks);
-      pr.k1[ks] = load_stream_16(kp1 + koff1 + 32 * ks);
-    }
-#pragma unroll
-    for (int dt = 0; dt < DT; ++dt)
-      pr.vf[dt] = load_2x4_stream(vp0 + 256 * dt + voff0, vp1 + 256 * dt + voff1);
-  };
 
   constexpr int UNIT_LOADS = 2 * KS + 2 * DT;        // vector loads of one unit
   WaveState<HD, 1> st;
   PageRegs<HD> ra, rb;
-  issue(cur, tb0, tb1, cur.lo, true, ra);
+  issue_unit<HD>(a, cur, tb0, tb1, cur.lo, true, c16, g, ra);
   bool first_seg = true, more = false, fresh = true;
   int k = cur.lo;
   auto look_ahead = [&]() {                          // the run after cur: its table window and, for a new pair, its queries
-    next_run(nxt);
+    walk.next(nxt);
     more = nxt.valid;
     if (!more) nxt = cur;                            // keeps the look-ahead loads in bounds
-    load_window(nxt, tbn0, tbn1);
+    load_window(a, nxt, lane, tbn0, tbn1);
     if (more && nxt.seg_start) copy_queries(nxt, qsel ^ 1);
   };
   look_ahead();
@@ -245,7 +280,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     {
       Run rs = cur;
       if (last) rs = nxt;
-      issue(rs, last ? tbn0 : tb0, last ? tbn1 : tb1, last ? nxt.lo : k + 1, !last || more, next);
+      issue_unit<HD>(a, rs, last ? tbn0 : tb0, last ? tbn1 : tb1, last ? nxt.lo : k + 1, !last || more, c16, g, next);
     }
     // the first unit of a pair: its queries were requested before its pages, and those before the loads just issued
     if (fresh) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(UNIT_LOADS) : "memory");
@@ -259,16 +294,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     if (!last) { ++k; return true; }
     if (cur.seg_end && !pair_here) {
       st.finish_denominators();
-      const bool whole = cur.pb == 0 && cur.pe == cur.np;
-      if (whole && cur.u0 == 0) {
-        store_column<HD, 1, PL, FMT>(st, 0, a.o, cur.seq, cur.kvh * group + c16, g, col_ok);
-      } else if (col_ok) {                           // lane holds column c16, rows d = 16 dt + 4 g + {0..3}
-        float* dst = whole ? a.seq_part + (((size_t)cur.seq * a.Hkv + cur.kvh) * group + c16) * PS
-                           : a.part + ((size_t)(w * 2 + (first_seg ? 0 : 1)) * group + c16) * PS;
-#pragma unroll
-        for (int dt = 0; dt < DT; ++dt) *reinterpret_cast<f32x4*>(dst + 16 * dt + 4 * g) = st.o[0][dt];
-        if (g == 0) { dst[HD] = st.m[0]; dst[HD + 1] = st.l[0]; }
-      }
+      store_segment<HD, PL, FMT>(a, st, cur, w, first_seg, group, c16, g);
       first_seg = false;
       st.reset();
     }
@@ -295,6 +321,118 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 #pragma unroll
     for (int dt = 0; dt < DT; ++dt) *reinterpret_cast<f32x4*>(dst + 16 * dt + 4 * g) = st.o[0][dt];
     if (g == 0) { dst[HD] = st.m[0]; dst[HD + 1] = st.l[0]; }
+  }
+}
+
+// A share per workgroup (MoE policies): the four waves take the share's units in turn, and their sums of a segment are
+// merged through LDS.
+template <int HD, int PL, int FMT>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_decode_team_kernel(AttnDecodeArgs a) {
+  constexpr int DT = HD / 16, KS = HD / 32;
+  __shared__ f32x4 lds_o[2 * DT * WAVE];
+  __shared__ float lds_ml[2 * 2 * WAVE];
+  __shared__ u32x4 lds_q[PL * KS * WAVE];            // query fragments of the current segment, MFMA operand order
+
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int c16 = lane & 15, g = lane >> 4;
+  const int group = a.Hq / a.Hkv;
+  const bool col_ok = c16 < group;
+  const int w = blockIdx.x;
+  const Shares sh = load_shares(a.plan_hdr);
+  const int u = sh.start(w), u_end = min(sh.U, sh.start(w + 1));
+  if (u >= u_end) return;                            // uniform over the workgroup
+  const float scale = rsqrtf((float)HD);
+  RunWalk walk(a, lane, u, u_end, a.share_seq[w]);
+  // The waves share the fetch of a segment's query fragments; they stay in LDS (registers hold two units of pages).
+  // The fragments of the next run's pair are requested a whole run ahead (the run generator looks one run ahead
+  // anyway) and only written to LDS at the switch, so that a new segment does not begin with a round trip.
+  constexpr int QPW = (PL * KS + 3) / 4;             // fragments fetched by each wave
+  auto fetch_queries = [&](const Run& r, u32x4 (&q)[QPW]) {
+    const int head = r.kvh * group + (col_ok ? c16 : 0);
+#pragma unroll
+    for (int i = 0; i < QPW; ++i) {
+      const int f = min(wave + 4 * i, PL * KS - 1);  // a slot without a fragment repeats the last one; never written
+      const int p = f / KS, ks = f % KS;
+      q[i] = *reinterpret_cast<const u32x4*>(a.q.p + p * a.q.plane + ((size_t)r.seq * a.Hq + head) * HD + 32 * ks + 8 * g);
+    }
+  };
+  auto put_queries = [&](const u32x4 (&q)[QPW]) {
+    const u32x4 z = {0u, 0u, 0u, 0u};
+#pragma unroll
+    for (int i = 0; i < QPW; ++i)
+      if (wave + 4 * i < PL * KS) lds_q[(wave + 4 * i) * WAVE + lane] = col_ok ? q[i] : z;
+  };
+  auto qf = [&](int p, int, int ks) { return __builtin_bit_cast(h16x8, lds_q[(p * KS + ks) * WAVE + lane]); };
+
+  Run cur, nxt;
+  walk.next(cur);
+  if (!cur.valid) return;                            // uniform over the workgroup
+  int32_t tb0, tb1, tbn0, tbn1;
+  load_window(a, cur, lane, tb0, tb1);
+  u32x4 qpre[QPW];
+  fetch_queries(cur, qpre);
+  put_queries(qpre);
+  __syncthreads();
+
+  WaveState<HD, 1> st;
+  PageRegs<HD> ra, rb;
+  issue_unit<HD>(a, cur, tb0, tb1, min(cur.lo + wave, cur.hi - 1), cur.lo + wave < cur.hi, c16, g, ra);
+  bool first_seg = true;
+
+  for (;;) {                                         // one run per iteration; uniform
+    walk.next(nxt);
+    const bool more = nxt.valid;
+    if (!more) nxt = cur;                            // keeps the look-ahead loads below in bounds
+    load_window(a, nxt, lane, tbn0, tbn1);
+    fetch_queries(nxt, qpre);                        // unconditional, like every load of this loop
+    if (cur.seg_start) st.reset();
+    const int key_end = cur.ctx + 1;
+    const int pos_col[1] = {cur.ctx};
+    auto step = [&](int i, const PageRegs<HD>& pr, bool valid) {
+      const int key0 = 32 * (cur.u0 + i);
+      const bool ok0 = pr.ok0 && valid, ok1 = pr.ok1 && valid;
+      pair_step<HD, 1, PL, FMT>(st, pr.k0, pr.k1, pr.vf, qf, key0, key0 + 16, ok0, ok1, key_end, pos_col,
+                                ok0 && ok1 && key0 + 32 <= key_end, scale, g);
+    };
+
+    // Two register sets alternate: while one unit is multiplied the next one's pages are in flight.  The loop
+    // body has no branch around a load (a unit index past the wave's last one is clamped and its step masked),
+    // so the hardware counters let each step wait for its own pages only.  The slot after the wave's last unit
+    // fetches its first unit of the next run, so the stream does not drain between runs.
+    const int first = cur.lo + wave;
+    const int n_my = first < cur.hi ? (cur.hi - first + 3) / 4 : 0;
+    const int last = first + 4 * (n_my - 1);
+    const int nfirst = min(nxt.lo + wave, nxt.hi - 1);
+    const bool nlive = more && nxt.lo + wave < nxt.hi;
+    for (int k = 0; k < n_my; k += 2) {
+      const int i = first + 4 * k;
+      issue_unit<HD>(a, cur, tb0, tb1, min(i + 4, last), i + 4 <= last, c16, g, rb);
+      asm volatile("" ::: "memory");                 // query fragments are re-read from LDS, not kept in registers
+      __builtin_amdgcn_sched_barrier(0);             // the next unit's loads go out before this unit's math
+      step(i, ra, true);
+      {
+        const bool beyond = i + 8 > last;
+        Run rs = cur;
+        if (beyond) rs = nxt;
+        issue_unit<HD>(a, rs, beyond ? tbn0 : tb0, beyond ? tbn1 : tb1, beyond ? nfirst : i + 8, !beyond || nlive, c16, g, ra);
+      }
+      asm volatile("" ::: "memory");
+      __builtin_amdgcn_sched_barrier(0);
+      step(i + 4, rb, k + 1 < n_my);
+    }
+    if (n_my == 0) issue_unit<HD>(a, nxt, tbn0, tbn1, nfirst, nlive, c16, g, ra);   // this wave had no unit in the run
+
+    if (cur.seg_end) {
+      st.finish_denominators();
+      merge_waves<HD, 1>(st, lds_o, lds_ml, wave, lane);
+      if (wave == 0) store_segment<HD, PL, FMT>(a, st, cur, w, first_seg, group, c16, g);
+      first_seg = false;
+    }
+    if (!more) break;
+    if (nxt.seg_start) put_queries(qpre);            // every wave is past the merge: the old fragments are dead
+    __syncthreads();                                 // new fragments visible; wave 0 is done with the merge buffers
+    cur = nxt; tb0 = tbn0; tb1 = tbn1;
   }
 }
 
@@ -387,7 +525,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 // parts (share order).  A thread owns eight features of a head; MERGE_GROUPS threads share a slice and take a contiguous
 // quarter of the parts each (a long context of a single sequence is dozens of parts, a round trip per eight of them), the
 // first one the prefix chunks too; their results are merged in order through LDS.  With MERGE_ALONE pairs or more a pair
-// has at most a handful of parts, unless it is far longer than the others: one thread per slice.
+// has at most a handful of parts, unless it is far longer than the others: one thread per slice.  So it is with a share per
+// workgroup, which keeps the sum in one run.
 constexpr int MERGE_GROUPS = 4, MERGE_BATCH = 8, MERGE_ALONE = 512;
 constexpr int MERGE_AT_ONCE = MERGE_GROUPS * MERGE_BATCH;
 template <int HD>
@@ -410,7 +549,7 @@ __global__ __launch_bounds__(1024) void attn_decode_merge_kernel(AttnDecodeArgs 
     tile0 = max(sv.tile0[seq], 0);
     col0 = min(max(sv.col0[seq], 0), SP_COLS - group);
   }
-  const int slices = group * HD / 8, merge_groups = (int)gridDim.x >= MERGE_ALONE ? 1 : MERGE_GROUPS;
+  const int slices = group * HD / 8, merge_groups = a.team || (int)gridDim.x >= MERGE_ALONE ? 1 : MERGE_GROUPS;
   const int per_group = (int)blockDim.x / merge_groups;                     // at least `slices`, whole waves
   const int part_group = (int)threadIdx.x / per_group, uu = (int)threadIdx.x % per_group;
   const bool mine = uu < slices;
@@ -420,20 +559,23 @@ __global__ __launch_bounds__(1024) void attn_decode_merge_kernel(AttnDecodeArgs 
   float o[8];
 #pragma unroll
   for (int e = 0; e < 8; ++e) o[e] = 0.f;
-  auto add = [&](const f32x4& va, const f32x4& vb, float ms, float ls) {
+  // a part of the pair, or (`other`) what comes from the other kernel's share of its keys: prefix chunks and the rest of a
+  // pair that they precede (weighted_sum: the roundings of a few features differ between the two)
+  auto add = [&](const f32x4& va, const f32x4& vb, float ms, float ls, bool other) {
     if (ms == -INFINITY) return;
     const float mn = fmaxf(m, ms);
     const float aa = state_weight(m, mn), ab = state_weight(ms, mn);
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      o[e] = o[e] * aa + va[e] * ab;
-      o[4 + e] = o[4 + e] * aa + vb[e] * ab;
+      const bool swap = other && e == 0;
+      o[e] = swap ? weighted_sum(va[e], ab, o[e], aa) : weighted_sum(o[e], aa, va[e], ab);
+      o[4 + e] = swap ? weighted_sum(vb[e], ab, o[4 + e], aa) : weighted_sum(o[4 + e], aa, vb[e], ab);
     }
-    l = l * aa + ls * ab;
+    l = other ? weighted_sum(ls, ab, l, aa) : weighted_sum(l, aa, ls, ab);
     m = mn;
   };
   auto add_at = [&](const float* p) {
-    add(*reinterpret_cast<const f32x4*>(p + d0), *reinterpret_cast<const f32x4*>(p + d0 + 4), p[HD], p[HD + 1]);
+    add(*reinterpret_cast<const f32x4*>(p + d0), *reinterpret_cast<const f32x4*>(p + d0 + 4), p[HD], p[HD + 1], true);
   };
   const int n_parts = np ? w_last - w_first + 1 : 0;
   if (part_group == 0 && n_chunks > 0) {
@@ -449,13 +591,13 @@ __global__ __launch_bounds__(1024) void attn_decode_merge_kernel(AttnDecodeArgs 
     }
 #pragma unroll
     for (int c = 0; c < SP_MAX_CHUNKS; ++c)
-      if (c < n_chunks) add(va[c], vb[c], ms[c], ls[c]);
+      if (c < n_chunks) add(va[c], vb[c], ms[c], ls[c], true);
   }
   if (n_parts == 1) {
     if (part_group == 0) add_at(a.seq_part + (((size_t)seq * a.Hkv + kvh) * group + j) * PS);
   } else {
     const int slot0 = xs <= sh.start(w_first) ? 0 : 1;
-    const bool gaps = sh.CA <= 4;                      // shares may be empty in a step of fewer than four units
+    const bool gaps = sh.per == 4 && sh.CA <= 4;       // shares may be empty in a step of fewer than four units
     // few parts stay with the first group: nothing to gain from dealing them out
     const int each = n_parts <= PB ? n_parts : (n_parts + merge_groups - 1) / merge_groups;
     const int p_b = min(n_parts, part_group * each), p_e = min(n_parts, p_b + each);
@@ -473,7 +615,7 @@ __global__ __launch_bounds__(1024) void attn_decode_merge_kernel(AttnDecodeArgs 
       }
 #pragma unroll
       for (int q = 0; q < PB; ++q)
-        if (w0 + q < w_first + p_e && (!gaps || sh.start(w0 + q) < sh.start(w0 + q + 1))) add(va[q], vb[q], ms[q], ls[q]);
+        if (w0 + q < w_first + p_e && (!gaps || sh.start(w0 + q) < sh.start(w0 + q + 1))) add(va[q], vb[q], ms[q], ls[q], false);
     }
     if (n_parts > PB && merge_groups > 1) {            // uniform over the workgroup
       float* mine_lds = merge_lds + ((size_t)(part_group - 1) * slices + us) * 10;
@@ -486,7 +628,7 @@ __global__ __launch_bounds__(1024) void attn_decode_merge_kernel(AttnDecodeArgs 
       if (part_group == 0 && mine)
         for (int q = 0; q < merge_groups - 1; ++q) {
           const float* p = merge_lds + ((size_t)q * slices + us) * 10;
-          add(f32x4{p[0], p[1], p[2], p[3]}, f32x4{p[4], p[5], p[6], p[7]}, p[8], p[9]);
+          add(f32x4{p[0], p[1], p[2], p[3]}, f32x4{p[4], p[5], p[6], p[7]}, p[8], p[9], false);
         }
     }
   }
@@ -508,7 +650,7 @@ __global__ __launch_bounds__(1024) void attn_decode_merge_kernel(AttnDecodeArgs 
 // One workgroup: exclusive prefix of the per-sequence unit counts, the two share sizes, and the sequence in which
 // each share starts.
 __global__ __launch_bounds__(1024) void attn_plan_kernel(int n_seqs, const int32_t* ctx, const uint8_t* live, int Hkv,
-                                                          int n_wgs, int n_shares, const int32_t* shared, int32_t* unit_prefix,
+                                                          int n_wgs, int n_shares, bool team, const int32_t* shared, int32_t* unit_prefix,
                                                           int32_t* share_seq, int32_t* hdr) {
   __shared__ int sh[1024];
   __shared__ int carry;
@@ -541,11 +683,12 @@ __global__ __launch_bounds__(1024) void attn_plan_kernel(int n_seqs, const int32
   // at most MERGE_AT_ONCE shares per pair, the parts that the merge takes in one round trip: a lone sequence would leave it
   // a part per unit otherwise (4B shape, one sequence of 3000 keys, attention + merge: 2 units per share 15.0 us, 3 14.7,
   // 6 17.3; the limit makes it 3).  With as many pairs as workgroups and equal contexts a group is exactly a pair.
-  const int n = max(1, min(min(n_shares / 4, total / 4), MERGE_AT_ONCE / 4 * n_seqs * Hkv));
+  // A share per workgroup: a group for every workgroup.
+  const int n = team ? n_shares : max(1, min(min(n_shares / 4, total / 4), MERGE_AT_ONCE / 4 * n_seqs * Hkv));
   const int q = total / n, H = total % n;
-  const int CA = q + 1, CB = q, spread = n < n_wgs;
-  if (tid == 0) { hdr[0] = CA; hdr[1] = total; hdr[2] = CB; hdr[3] = H; hdr[4] = spread; }
-  const Shares shr = Shares{CA, CB, H, total, spread};
+  const int CA = q + 1, CB = q, spread = n < n_wgs, per = team ? 1 : 4;
+  if (tid == 0) { hdr[0] = CA; hdr[1] = total; hdr[2] = CB; hdr[3] = H; hdr[4] = spread; hdr[5] = per; }
+  const Shares shr = Shares{CA, CB, H, total, spread, per};
   for (int w = tid; w < n_shares; w += 1024) {
     const int u0 = shr.start(w);
     int lo = 0, hi = n_seqs - 1;                     // largest s with Hkv * prefix[s] <= u0
@@ -559,11 +702,11 @@ __global__ __launch_bounds__(1024) void attn_plan_kernel(int n_seqs, const int32
 
 }  // namespace
 
-hipError_t attention_decode_plan(int n_seqs, const int32_t* ctx_lens, const uint8_t* tok_live, int Hkv, int n_wgs,
+hipError_t attention_decode_plan(int n_seqs, const int32_t* ctx_lens, const uint8_t* tok_live, int Hkv, int n_wgs, bool team,
                                  const int32_t* shared, int32_t* unit_prefix, int32_t* share_seq, int32_t* hdr,
                                  hipStream_t st) {
-  const int n_shares = 4 * n_wgs < ATTN_SHARES_MAX ? 4 * n_wgs : ATTN_SHARES_MAX;   // a larger grid leaves waves idle
-  hipLaunchKernelGGL(attn_plan_kernel, dim3(1), dim3(1024), 0, st, n_seqs, ctx_lens, tok_live, Hkv, n_wgs, n_shares, shared,
+  const int n_shares = team ? n_wgs : 4 * n_wgs < ATTN_SHARES_MAX ? 4 * n_wgs : ATTN_SHARES_MAX;   // a larger grid leaves waves idle
+  hipLaunchKernelGGL(attn_plan_kernel, dim3(1), dim3(1024), 0, st, n_seqs, ctx_lens, tok_live, Hkv, n_wgs, n_shares, team, shared,
                      unit_prefix, share_seq, hdr);
   return hipGetLastError();
 }
@@ -652,19 +795,24 @@ hipError_t attention_decode_prefix(const AttnDecodeArgs& a, hipStream_t st) {
   return hipGetLastError();
 }
 
+template <int HD, int PL, int FMT>
+static void launch_decode(const AttnDecodeArgs& a, hipStream_t st) {
+  if (a.team) hipLaunchKernelGGL((attn_decode_team_kernel<HD, PL, FMT>), dim3(a.n_wgs), dim3(256), 0, st, a);
+  else hipLaunchKernelGGL((attn_decode_kernel<HD, PL, FMT>), dim3(a.n_wgs), dim3(256), 0, st, a);
+}
+
 hipError_t attention_decode(const AttnDecodeArgs& a, hipStream_t st) {
-  dim3 grid(a.n_wgs);
   const bool two = a.q.planes == 2;
   // formats built: bf16 with one or two terms, fp16 with one term (checked when the model is created)
   if (a.o.dtype == DT_F16) {
-    if (a.hd == 128) hipLaunchKernelGGL((attn_decode_kernel<128, 1, DT_F16>), grid, dim3(256), 0, st, a);
-    else hipLaunchKernelGGL((attn_decode_kernel<64, 1, DT_F16>), grid, dim3(256), 0, st, a);
+    if (a.hd == 128) launch_decode<128, 1, DT_F16>(a, st);
+    else launch_decode<64, 1, DT_F16>(a, st);
   } else if (a.hd == 128) {
-    if (two) hipLaunchKernelGGL((attn_decode_kernel<128, 2, DT_BF16>), grid, dim3(256), 0, st, a);
-    else hipLaunchKernelGGL((attn_decode_kernel<128, 1, DT_BF16>), grid, dim3(256), 0, st, a);
+    if (two) launch_decode<128, 2, DT_BF16>(a, st);
+    else launch_decode<128, 1, DT_BF16>(a, st);
   } else {
-    if (two) hipLaunchKernelGGL((attn_decode_kernel<64, 2, DT_BF16>), grid, dim3(256), 0, st, a);
-    else hipLaunchKernelGGL((attn_decode_kernel<64, 1, DT_BF16>), grid, dim3(256), 0, st, a);
+    if (two) launch_decode<64, 2, DT_BF16>(a, st);
+    else launch_decode<64, 1, DT_BF16>(a, st);
   }
   return hipGetLastError();
 }
@@ -672,7 +820,7 @@ hipError_t attention_decode(const AttnDecodeArgs& a, hipStream_t st) {
 hipError_t attention_decode_merge(const AttnDecodeArgs& a, hipStream_t st) {
   dim3 grid(a.n_seqs * a.Hkv);
   const int slices = (a.Hq / a.Hkv) * a.hd / 8;      // 8-feature slices of a pair's heads: at most 16 * 128 / 8 = 256
-  const int merge_groups = (int)grid.x >= MERGE_ALONE ? 1 : MERGE_GROUPS;
+  const int merge_groups = a.team || (int)grid.x >= MERGE_ALONE ? 1 : MERGE_GROUPS;
   const dim3 block((slices + 63) / 64 * 64 * merge_groups);
   const size_t lds = (size_t)(merge_groups - 1) * slices * 10 * sizeof(float);
   if (a.hd == 128) hipLaunchKernelGGL((attn_decode_merge_kernel<128>), grid, block, lds, st, a);

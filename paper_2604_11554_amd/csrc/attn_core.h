@@ -50,6 +50,10 @@ struct WaveState {
   }
 };
 
+// x wx + y wy in a merge of two states: the product of x is rounded on its own.  Which of the two it is changes the last bit,
+// on which near-ties of a MoE policy's routing turn, and left to the compiler it depends on the code around.
+__device__ __forceinline__ float weighted_sum(float x, float wx, float y, float wy) { return __builtin_fmaf(y, wy, x * wx); }
+
 // weight of a state with maximum m in a merge whose maximum is `reference`: an empty state weighs nothing
 __device__ __forceinline__ float state_weight(float m, float reference) { return m == -INFINITY ? 0.f : __expf(m - reference); }
 
@@ -186,12 +190,14 @@ __device__ __forceinline__ void merge_from_lds(WaveState<HD, NCT>& st, const flo
     float mb = ml[(c * 2 + 0) * WAVE + lane], lb = ml[(c * 2 + 1) * WAVE + lane];
     float mn = fmaxf(st.m[c], mb);
     const float aa = state_weight(st.m[c], mn), ab = state_weight(mb, mn);
-    st.l[c] = st.l[c] * aa + lb * ab;
+    st.l[c] = weighted_sum(lb, ab, st.l[c], aa);
     st.m[c] = mn;
 #pragma unroll
     for (int dt = 0; dt < HD / 16; ++dt) {
-      f32x4 v = ob[(c * (HD / 16) + dt) * WAVE + lane];
-      st.o[c][dt] = st.o[c][dt] * aa + v * ab;
+      const f32x4 v = ob[(c * (HD / 16) + dt) * WAVE + lane];
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        st.o[c][dt][e] = dt < 2 ? weighted_sum(st.o[c][dt][e], aa, v[e], ab) : weighted_sum(v[e], ab, st.o[c][dt][e], aa);
     }
   }
 }

@@ -34,7 +34,11 @@ __device__ __forceinline__ uint32_t pack_bf16(float a, float b) {
   const bf16x2 v = {(__bf16)a, (__bf16)b};
   return __builtin_bit_cast(uint32_t, v);
 }
-__device__ __forceinline__ uint32_t pack_f16(float a, float b) { return (uint32_t)f32_to_f16(a) | ((uint32_t)f32_to_f16(b) << 16); }
+__device__ __forceinline__ uint32_t pack_f16(float a, float b) {
+  typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));   // v_cvt_pk_f16_f32: one by one, a product would be fused
+  const f16x2 v = {(_Float16)a, (_Float16)b};                   // with its conversion, which rounds once instead of twice
+  return __builtin_bit_cast(uint32_t, v);
+}
 
 // format picked at compile time (inner loops) ...
 template <int DT> __device__ __forceinline__ float h16_to_f32(h16_t b) { return DT == DT_F16 ? f16_to_f32(b) : bf16_to_f32(b); }

@@ -212,8 +212,9 @@ struct AttnDecodeArgs {      // one new token per sequence: row = sequence slot
   // plan of the step (attention_decode_plan): 32-key units of all (sequence, KV head) pairs end to end
   const int32_t* unit_prefix;  // [n_seqs + 1] exclusive prefix of the per-sequence unit counts (0 for inert rows)
   const int32_t* share_seq;    // [ATTN_SHARES_MAX] sequence in which a share starts
-  const int32_t* plan_hdr;     // [5] units of the first H groups of four shares, total units, units of the others, H, spread
-  int n_wgs;                   // grid size: a share of the unit sequence per wave, at most ATTN_SHARES_MAX
+  const int32_t* plan_hdr;     // [6] units of the first H groups of shares, total units, units of the others, H, spread, per
+  bool team;                   // a share of the unit sequence per workgroup (MoE policies), else per wave
+  int n_wgs;                   // grid size; at most ATTN_SHARES_MAX shares
   float* part;               // [ATTN_SHARES_MAX][2][Hq/Hkv][hd+4] partial (o, m, l) of a share's first / other straddling pair
   Act o;                     // [n_seqs, Hq*hd] in fragment order (input of the output projection)
   // shared prompt prefixes (optional): the first units of a sequence that shares them with others are attended
@@ -240,7 +241,7 @@ inline size_t shared_prefix_words(int n_seqs, int Hkv) {
 }
 // fills `words` (shared_prefix_words entries) from per-sequence group leaders and shared page counts (host arrays)
 void shared_prefix_build(int n_seqs, int Hq, int Hkv, const int32_t* leader, const int32_t* shared_pages, int32_t* words);
-hipError_t attention_decode_plan(int n_seqs, const int32_t* ctx_lens, const uint8_t* tok_live, int Hkv, int n_wgs,
+hipError_t attention_decode_plan(int n_seqs, const int32_t* ctx_lens, const uint8_t* tok_live, int Hkv, int n_wgs, bool team,
                                  const int32_t* shared, int32_t* unit_prefix, int32_t* share_seq, int32_t* hdr,
                                  hipStream_t st);
 hipError_t attention_decode_prefix(const AttnDecodeArgs& a, hipStream_t st);   // no-op without a descriptor
