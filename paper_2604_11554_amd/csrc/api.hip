@@ -194,7 +194,7 @@ Workspace carve(const rlx_model_config& c, char* base, int S, int T, int max_blo
   w.ob = (h16_t*)take(act_bytes(T, qdim, lng));
   w.attn_prefix = (int32_t*)take((size_t)(S + 1) * 4);
   w.attn_share_seq = (int32_t*)take((size_t)ATTN_SHARES_MAX * 4);
-  w.attn_hdr = (int32_t*)take(6 * 4);
+  w.attn_hdr = (int32_t*)take(4 * 4);
   w.attn_seq_part = (float*)take((size_t)S * c.n_q_heads * (c.head_dim + 4) * 4);
   w.attn_pre_part = (float*)take((size_t)shared_prefix_max_tiles(S, c.n_kv_heads) * SP_COLS * (c.head_dim + 4) * 4);
   // Split-K planes of q|k|v and of the o and down projections.  Both are dead while decode attention runs (its queries

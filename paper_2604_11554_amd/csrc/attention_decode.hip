@@ -7,10 +7,11 @@
 // contexts being the same for every layer), on a grid that is exactly resident (two workgroups of four waves per
 // compute unit).  A wave walks its share by itself, the next unit's pages on their way while it works on the current
 // one, the next pair's queries copied into its part of LDS by the hardware; there is no barrier.  Where a (sequence, KV
-// head) pair lies inside one share its output is final; where a workgroup's four shares are exactly one pair (equal
-// contexts, as many pairs as workgroups) they are merged through LDS at the end (30B-A3B shape, 128 sequences: 16.41 ->
-// 16.10 ms per step against the merge kernel); elsewhere each part leaves (o, m, l) and a small second kernel merges the
-// parts in share order (deterministic).
+// head) pair lies inside one share its output is final; elsewhere each part leaves (o, m, l) and a small second kernel
+// merges the parts in share order (deterministic).
+// (Shares in fours, merged by their workgroup where they were exactly one pair -- equal contexts, as many pairs as
+// workgroups: 4B shape, eight layers, 64 sequences of 1024 keys each 1160 us against 1200, but 64 of 769 to 1525 keys 1253
+// against 1243, dense_b64's steps 5.39 ms against 5.34, and steps of few keys got shares of two units in series.)
 // (With a share per workgroup, its waves taking units in turn, the end of every pair cost a merge of the four waves
 // through LDS, three barriers and a half-idle step.  4B shape, 256 sequences, one layer: 32 to 287 keys each 94 us then,
 // 42 now; 144 keys each 51 and 35; 1024 keys each 182 and 172, 6.2 TB/s.  A lone sequence of 3000 keys: merge 19 us
@@ -68,25 +69,14 @@ __device__ __forceinline__ int shared_units_of(const SharedView& v, int seq, int
   return v.on ? min(max(v.start_unit[seq], 0), ctx / 32) : 0;
 }
 
-// The unit sequence is cut into groups of two sizes, 0 .. H-1 of CA units and the others of CB = CA - 1 as long as there are
-// units (plan header: CA, total, CB, H, spread, per).  A share per workgroup: a group is a share (per = 1).  A share per wave:
-// every group is four (per = 4); where there is a group for every workgroup its shares are that workgroup's waves, fewer
-// groups are spread over all workgroups (`spread`).
+// Shares of two sizes: 0 .. H-1 take CA units each, the others CB = CA - 1 as long as there are units (plan header: CA,
+// total, CB, H).
 struct Shares {
-  int CA, CB, H, U, spread, per;
-  __device__ __forceinline__ int group_start(int b) const { return b < H ? b * CA : H * CA + (b - H) * CB; }
-  __device__ __forceinline__ int group_units(int b) const { return b < H ? CA : CB; }
-  __device__ __forceinline__ int start(int w) const { return group_start(w / per) + group_units(w / per) * (w % per) / per; }
-  __device__ __forceinline__ int of_unit(int x) const {   // x < U
-    const int b = x < H * CA ? x / CA : H + (x - H * CA) / max(CB, 1);
-    return per * b + (per * (x - group_start(b)) + per - 1) / max(group_units(b), 1);
-  }
-  // whether the workgroup of group b holds exactly the `np` units from `xs` on, a whole pair: its waves merge it themselves
-  __device__ __forceinline__ bool whole_pair(int b, int xs, int np) const {
-    return per == 4 && !spread && np >= 4 && group_start(b) == xs && group_units(b) == np;
-  }
+  int CA, CB, H, U;
+  __device__ __forceinline__ int start(int w) const { return w < H ? w * CA : H * CA + (w - H) * CB; }
+  __device__ __forceinline__ int of_unit(int x) const { return x < H * CA ? x / CA : H + (x - H * CA) / max(CB, 1); }   // x < U
 };
-__device__ __forceinline__ Shares load_shares(const int32_t* hdr) { return Shares{hdr[0], hdr[2], hdr[3], hdr[1], hdr[4], hdr[5]}; }
+__device__ __forceinline__ Shares load_shares(const int32_t* hdr) { return Shares{hdr[0], hdr[2], hdr[3], hdr[1]}; }
 
 struct Run {
   int seq, kvh, ctx, np;     // np: units of the whole pair, counted from unit u0 of the sequence
@@ -213,7 +203,7 @@ __device__ __forceinline__ void store_segment(const AttnDecodeArgs& a, const Wav
 // A share per wave (dense policies).
 template <int HD, int PL, int FMT>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_decode_kernel(AttnDecodeArgs a) {
-  constexpr int DT = HD / 16, KS = HD / 32, PS = HD + 4, NQ = PL * KS;
+  constexpr int KS = HD / 32, NQ = PL * KS;
   // query fragments of the wave's current and next pair, MFMA operand order
   __shared__ u32x4 lds_q[4][2][NQ * WAVE];
 
@@ -222,19 +212,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   const int c16 = lane & 15, g = lane >> 4;
   const int group = a.Hq / a.Hkv;
   const bool col_ok = c16 < group;
-  const Shares sh = load_shares(a.plan_hdr);
-  const int w = sh.spread ? wave * gridDim.x + blockIdx.x : 4 * blockIdx.x + wave;
+  const int w = wave * gridDim.x + blockIdx.x;       // few shares spread over the units
   if (w >= ATTN_SHARES_MAX) return;
+  const Shares sh = load_shares(a.plan_hdr);
   const int u = sh.start(w), u_end = min(sh.U, sh.start(w + 1));
   if (u >= u_end) return;                            // uniform over the wave
-  const int seq = a.share_seq[w];
-  bool pair_here = false;                            // the workgroup's shares are one whole pair (uniform over it)
-  if (!sh.spread && seq < a.n_seqs) {
-    const int p0 = a.unit_prefix[seq], np = a.unit_prefix[seq + 1] - p0, xs = sh.group_start(blockIdx.x);
-    pair_here = np > 0 && (xs - a.Hkv * p0) % np == 0 && sh.whole_pair(blockIdx.x, xs, np);
-  }
   const float scale = rsqrtf((float)HD);
-  RunWalk walk(a, lane, u, u_end, seq);
+  RunWalk walk(a, lane, u, u_end, a.share_seq[w]);
   // The query fragments of a pair go straight into LDS, a whole run before they are read (the run generator looks one
   // run ahead anyway).  Columns past the group read some head's queries; their results are never stored.
   int qsel = 0;
@@ -256,7 +240,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   load_window(a, cur, lane, tb0, tb1);
   copy_queries(cur, 0);
 
-  constexpr int UNIT_LOADS = 2 * KS + 2 * DT;        // vector loads of one unit
+  constexpr int UNIT_LOADS = 2 * KS + 2 * (HD / 16); // vector loads of one unit
   WaveState<HD, 1> st;
   PageRegs<HD> ra, rb;
   issue_unit<HD>(a, cur, tb0, tb1, cur.lo, true, c16, g, ra);
@@ -292,7 +276,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     pair_step<HD, 1, PL, FMT>(st, now.k0, now.k1, now.vf, qf, key0, key0 + 16, now.ok0, now.ok1, key_end, pos_col,
                               now.ok0 && now.ok1 && key0 + 32 <= key_end, scale, g);
     if (!last) { ++k; return true; }
-    if (cur.seg_end && !pair_here) {
+    if (cur.seg_end) {
       st.finish_denominators();
       store_segment<HD, PL, FMT>(a, st, cur, w, first_seg, group, c16, g);
       first_seg = false;
@@ -306,22 +290,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   };
   while (unit(ra, rb) && unit(rb, ra)) {}
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // no copy may outlive the workgroup's LDS
-  if (!pair_here) return;
-  st.finish_denominators();
-  __syncthreads();                                   // the queries' LDS becomes the merge buffers
-  f32x4* lds_o = reinterpret_cast<f32x4*>(&lds_q[0][0][0]);
-  float* lds_ml = reinterpret_cast<float*>(lds_o + 2 * DT * WAVE);
-  static_assert(sizeof(lds_q) >= (2 * DT * 16 + 2 * 2 * 4) * WAVE, "the merge buffers fit");
-  merge_waves<HD, 1>(st, lds_o, lds_ml, wave, lane);
-  if (wave != 0) return;
-  if (cur.u0 == 0) {
-    store_column<HD, 1, PL, FMT>(st, 0, a.o, cur.seq, cur.kvh * group + c16, g, col_ok);
-  } else if (col_ok) {
-    float* dst = a.seq_part + (((size_t)cur.seq * a.Hkv + cur.kvh) * group + c16) * PS;
-#pragma unroll
-    for (int dt = 0; dt < DT; ++dt) *reinterpret_cast<f32x4*>(dst + 16 * dt + 4 * g) = st.o[0][dt];
-    if (g == 0) { dst[HD] = st.m[0]; dst[HD + 1] = st.l[0]; }
-  }
 }
 
 // A share per workgroup (MoE policies): the four waves take the share's units in turn, and their sums of a segment are
@@ -538,8 +506,7 @@ __global__ __launch_bounds__(1024) void attn_decode_merge_kernel(AttnDecodeArgs 
   const int np = a.unit_prefix[seq + 1] - a.unit_prefix[seq];
   const Shares sh = load_shares(a.plan_hdr);
   const int xs = a.Hkv * a.unit_prefix[seq] + kvh * np;
-  const int w_first = np ? sh.of_unit(xs) : 0;
-  const int w_last = np && !sh.whole_pair(w_first >> 2, xs, np) ? sh.of_unit(xs + np - 1) : w_first;
+  const int w_first = np ? sh.of_unit(xs) : 0, w_last = np ? sh.of_unit(xs + np - 1) : 0;
   const SharedView sv = shared_view(a.shared, a.n_seqs, a.Hkv);
   const int su = np ? shared_units_of(sv, seq, a.ctx_lens[seq]) : 0;
   if (np && w_first == w_last && su == 0) return;      // uniform over the workgroup
@@ -597,7 +564,6 @@ __global__ __launch_bounds__(1024) void attn_decode_merge_kernel(AttnDecodeArgs 
     if (part_group == 0) add_at(a.seq_part + (((size_t)seq * a.Hkv + kvh) * group + j) * PS);
   } else {
     const int slot0 = xs <= sh.start(w_first) ? 0 : 1;
-    const bool gaps = sh.per == 4 && sh.CA <= 4;       // shares may be empty in a step of fewer than four units
     // few parts stay with the first group: nothing to gain from dealing them out
     const int each = n_parts <= PB ? n_parts : (n_parts + merge_groups - 1) / merge_groups;
     const int p_b = min(n_parts, part_group * each), p_e = min(n_parts, p_b + each);
@@ -615,7 +581,7 @@ __global__ __launch_bounds__(1024) void attn_decode_merge_kernel(AttnDecodeArgs 
       }
 #pragma unroll
       for (int q = 0; q < PB; ++q)
-        if (w0 + q < w_first + p_e && (!gaps || sh.start(w0 + q) < sh.start(w0 + q + 1))) add(va[q], vb[q], ms[q], ls[q], false);
+        if (w0 + q < w_first + p_e) add(va[q], vb[q], ms[q], ls[q], false);
     }
     if (n_parts > PB && merge_groups > 1) {            // uniform over the workgroup
       float* mine_lds = merge_lds + ((size_t)(part_group - 1) * slices + us) * 10;
@@ -650,7 +616,7 @@ __global__ __launch_bounds__(1024) void attn_decode_merge_kernel(AttnDecodeArgs 
 // One workgroup: exclusive prefix of the per-sequence unit counts, the two share sizes, and the sequence in which
 // each share starts.
 __global__ __launch_bounds__(1024) void attn_plan_kernel(int n_seqs, const int32_t* ctx, const uint8_t* live, int Hkv,
-                                                          int n_wgs, int n_shares, bool team, const int32_t* shared, int32_t* unit_prefix,
+                                                          int n_shares, bool team, const int32_t* shared, int32_t* unit_prefix,
                                                           int32_t* share_seq, int32_t* hdr) {
   __shared__ int sh[1024];
   __shared__ int carry;
@@ -679,16 +645,15 @@ __global__ __launch_bounds__(1024) void attn_plan_kernel(int n_seqs, const int32
   if (tid == 0) unit_prefix[n_seqs] = per_head;
   __syncthreads();                                   // the prefix is read back below
   const int total = per_head * Hkv;
-  // Group sizes differ by at most one unit, and so do the shares: the units of the step are dealt out evenly.  There are
-  // at most MERGE_AT_ONCE shares per pair, the parts that the merge takes in one round trip: a lone sequence would leave it
-  // a part per unit otherwise (4B shape, one sequence of 3000 keys, attention + merge: 2 units per share 15.0 us, 3 14.7,
-  // 6 17.3; the limit makes it 3).  With as many pairs as workgroups and equal contexts a group is exactly a pair.
-  // A share per workgroup: a group for every workgroup.
-  const int n = team ? n_shares : max(1, min(min(n_shares / 4, total / 4), MERGE_AT_ONCE / 4 * n_seqs * Hkv));
+  // Share sizes differ by at most one unit: the units of the step are dealt out evenly and the first H shares take the
+  // remainder, one unit each.  A share per wave is never empty, and there are at most MERGE_AT_ONCE of them per pair, the parts
+  // that the merge takes in one round trip: a lone sequence would leave it a part per unit otherwise (4B shape, one
+  // sequence of 3000 keys, attention + merge: 2 units per share 15.0 us, 3 14.7, 6 17.3; the limit makes it 3).
+  const int n = team ? n_shares : max(1, min(min(n_shares, total), MERGE_AT_ONCE * n_seqs * Hkv));
   const int q = total / n, H = total % n;
-  const int CA = q + 1, CB = q, spread = n < n_wgs, per = team ? 1 : 4;
-  if (tid == 0) { hdr[0] = CA; hdr[1] = total; hdr[2] = CB; hdr[3] = H; hdr[4] = spread; hdr[5] = per; }
-  const Shares shr = Shares{CA, CB, H, total, spread, per};
+  const int CA = q + 1, CB = q;
+  if (tid == 0) { hdr[0] = CA; hdr[1] = total; hdr[2] = CB; hdr[3] = H; }
+  const Shares shr = Shares{CA, CB, H, total};
   for (int w = tid; w < n_shares; w += 1024) {
     const int u0 = shr.start(w);
     int lo = 0, hi = n_seqs - 1;                     // largest s with Hkv * prefix[s] <= u0
@@ -705,9 +670,9 @@ __global__ __launch_bounds__(1024) void attn_plan_kernel(int n_seqs, const int32
 hipError_t attention_decode_plan(int n_seqs, const int32_t* ctx_lens, const uint8_t* tok_live, int Hkv, int n_wgs, bool team,
                                  const int32_t* shared, int32_t* unit_prefix, int32_t* share_seq, int32_t* hdr,
                                  hipStream_t st) {
-  const int n_shares = team ? n_wgs : 4 * n_wgs < ATTN_SHARES_MAX ? 4 * n_wgs : ATTN_SHARES_MAX;   // a larger grid leaves waves idle
-  hipLaunchKernelGGL(attn_plan_kernel, dim3(1), dim3(1024), 0, st, n_seqs, ctx_lens, tok_live, Hkv, n_wgs, n_shares, team, shared,
-                     unit_prefix, share_seq, hdr);
+  const int waves = 4 * n_wgs < ATTN_SHARES_MAX ? 4 * n_wgs : ATTN_SHARES_MAX;   // a larger grid leaves waves idle
+  hipLaunchKernelGGL(attn_plan_kernel, dim3(1), dim3(1024), 0, st, n_seqs, ctx_lens, tok_live, Hkv, team ? n_wgs : waves, team,
+                     shared, unit_prefix, share_seq, hdr);
   return hipGetLastError();
 }
 

@@ -212,7 +212,7 @@ struct AttnDecodeArgs {      // one new token per sequence: row = sequence slot
   // plan of the step (attention_decode_plan): 32-key units of all (sequence, KV head) pairs end to end
   const int32_t* unit_prefix;  // [n_seqs + 1] exclusive prefix of the per-sequence unit counts (0 for inert rows)
   const int32_t* share_seq;    // [ATTN_SHARES_MAX] sequence in which a share starts
-  const int32_t* plan_hdr;     // [6] units of the first H groups of shares, total units, units of the others, H, spread, per
+  const int32_t* plan_hdr;     // [4] units of the first H shares, total units, units of the others, H
   bool team;                   // a share of the unit sequence per workgroup (MoE policies), else per wave
   int n_wgs;                   // grid size; at most ATTN_SHARES_MAX shares
   float* part;               // [ATTN_SHARES_MAX][2][Hq/Hkv][hd+4] partial (o, m, l) of a share's first / other straddling pair

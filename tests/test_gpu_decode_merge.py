@@ -43,8 +43,8 @@ def test_a_long_sequence_among_many_short_ones(keys):
 
 @pytest.mark.parametrize("keys", [97, 130, 2200])
 def test_pairs_that_are_exactly_a_workgroup(keys):
-    """With as many workgroups as pairs and equal contexts the four waves of a workgroup share one pair and merge it
-    themselves (four units at least: 97 keys are the fewest); other grids cut the same pairs elsewhere."""
+    """With as many workgroups as pairs and equal contexts every pair is cut into as many shares as a workgroup has waves;
+    other grids cut the same pairs elsewhere, or not at all."""
     import paper_2604_11554_amd as pkg
     from paper_2604_11554_amd import synthetic
 
