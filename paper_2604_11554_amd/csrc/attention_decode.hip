@@ -490,17 +490,21 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 
 // One workgroup per (sequence, KV head): inert rows are zeroed; a pair that one share covered and no prefix precedes is
 // already final; otherwise the parts are merged: prefix chunks in key order, then the pair's own part (one share) or
-// parts (share order).  A thread owns eight features of a head; MERGE_GROUPS threads share a slice and take a contiguous
-// quarter of the parts each (a long context of a single sequence is dozens of parts, a round trip per eight of them), the
-// first one the prefix chunks too; their results are merged in order through LDS.  With MERGE_ALONE pairs or more a pair
-// has at most a handful of parts, unless it is far longer than the others: one thread per slice.  So it is with a share per
-// workgroup, which keeps the sum in one run.
-constexpr int MERGE_GROUPS = 4, MERGE_BATCH = 8, MERGE_ALONE = 512;
-constexpr int MERGE_AT_ONCE = MERGE_GROUPS * MERGE_BATCH;
-template <int HD>
-__global__ __launch_bounds__(1024) void attn_decode_merge_kernel(AttnDecodeArgs a) {
+// parts (share order).  A thread owns eight features of a head; GROUPS threads share a slice and take a contiguous run of
+// the parts each, a round trip per MERGE_BATCH of them, the first one the prefix chunks too; their results are merged in
+// order through LDS.
+//  - Shares per workgroup (MoE): one thread per slice, which keeps the sum in one run.
+//  - Fewer than MERGE_MANY pairs: four.  The parts of the few pairs are many (a long context is dozens).
+//  - More: two.  Most pairs have a handful of parts, and waves that find nothing to do cost too (2048 pairs, four instead
+//    of one: 9.5 -> 12.7 us), but a sequence far longer than the others has hundreds.  4B shape, eight layers, 63 sequences
+//    of 100 keys and one of 30 000 (198 parts): 1328 us with one thread per slice, 1195 with two, 1145 with four;
+//    dense_b64's steps 5.36, 5.35 and 5.37 ms; 256 sequences in groups of eight 9.26, 9.24 and 9.25 ms.
+constexpr int MERGE_GROUPS_MAX = 4, MERGE_BATCH = 8, MERGE_MANY = 512;
+constexpr int MERGE_AT_ONCE = MERGE_GROUPS_MAX * MERGE_BATCH;
+template <int HD, int GROUPS>
+__global__ __launch_bounds__(256 * GROUPS) void attn_decode_merge_kernel(AttnDecodeArgs a) {
   constexpr int PS = HD + 4, PB = MERGE_BATCH;
-  extern __shared__ __align__(16) float merge_lds[];   // [MERGE_GROUPS - 1][slices][10]
+  extern __shared__ __align__(16) float merge_lds[];   // [GROUPS - 1][slices][10]
   const int seq = blockIdx.x / a.Hkv, kvh = blockIdx.x % a.Hkv;
   const int group = a.Hq / a.Hkv, PL = a.o.planes;
   const int np = a.unit_prefix[seq + 1] - a.unit_prefix[seq];
@@ -516,8 +520,8 @@ __global__ __launch_bounds__(1024) void attn_decode_merge_kernel(AttnDecodeArgs 
     tile0 = max(sv.tile0[seq], 0);
     col0 = min(max(sv.col0[seq], 0), SP_COLS - group);
   }
-  const int slices = group * HD / 8, merge_groups = a.team || (int)gridDim.x >= MERGE_ALONE ? 1 : MERGE_GROUPS;
-  const int per_group = (int)blockDim.x / merge_groups;                     // at least `slices`, whole waves
+  const int slices = group * HD / 8;
+  const int per_group = (int)blockDim.x / GROUPS;                           // at least `slices`, whole waves
   const int part_group = (int)threadIdx.x / per_group, uu = (int)threadIdx.x % per_group;
   const bool mine = uu < slices;
   const int us = mine ? uu : 0;
@@ -565,7 +569,7 @@ __global__ __launch_bounds__(1024) void attn_decode_merge_kernel(AttnDecodeArgs 
   } else {
     const int slot0 = xs <= sh.start(w_first) ? 0 : 1;
     // few parts stay with the first group: nothing to gain from dealing them out
-    const int each = n_parts <= PB ? n_parts : (n_parts + merge_groups - 1) / merge_groups;
+    const int each = n_parts <= PB ? n_parts : (n_parts + GROUPS - 1) / GROUPS;
     const int p_b = min(n_parts, part_group * each), p_e = min(n_parts, p_b + each);
     for (int w0 = w_first + p_b; w0 < w_first + p_e; w0 += PB) {
       f32x4 va[PB], vb[PB];
@@ -583,7 +587,7 @@ __global__ __launch_bounds__(1024) void attn_decode_merge_kernel(AttnDecodeArgs 
       for (int q = 0; q < PB; ++q)
         if (w0 + q < w_first + p_e) add(va[q], vb[q], ms[q], ls[q], false);
     }
-    if (n_parts > PB && merge_groups > 1) {            // uniform over the workgroup
+    if (GROUPS > 1 && n_parts > PB) {                  // uniform over the workgroup
       float* mine_lds = merge_lds + ((size_t)(part_group - 1) * slices + us) * 10;
       if (part_group > 0 && mine) {
 #pragma unroll
@@ -592,7 +596,7 @@ __global__ __launch_bounds__(1024) void attn_decode_merge_kernel(AttnDecodeArgs 
       }
       __syncthreads();
       if (part_group == 0 && mine)
-        for (int q = 0; q < merge_groups - 1; ++q) {
+        for (int q = 0; q < GROUPS - 1; ++q) {
           const float* p = merge_lds + ((size_t)q * slices + us) * 10;
           add(f32x4{p[0], p[1], p[2], p[3]}, f32x4{p[4], p[5], p[6], p[7]}, p[8], p[9], false);
         }
@@ -619,16 +623,18 @@ __global__ __launch_bounds__(1024) void attn_plan_kernel(int n_seqs, const int32
                                                           int n_shares, bool team, const int32_t* shared, int32_t* unit_prefix,
                                                           int32_t* share_seq, int32_t* hdr) {
   __shared__ int sh[1024];
-  __shared__ int carry;
+  __shared__ int carry, n_live;
   const int tid = threadIdx.x;
   const SharedView sv = shared_view(shared, n_seqs, Hkv);
-  if (tid == 0) carry = 0;
+  if (tid == 0) carry = n_live = 0;
   __syncthreads();
   for (int base = 0; base < n_seqs; base += 1024) {
     const int i = base + tid;
     // units of the sequence's own pairs: those after the ones that prefix tiles serve
     const int v = (i < n_seqs && live[i]) ? (ctx[i] + 1 + 31) / 32 - shared_units_of(sv, i, ctx[i]) : 0;
     sh[tid] = v;
+    const int live_here = __popcll(__ballot(v > 0));
+    if ((tid & 63) == 0 && live_here) atomicAdd(&n_live, live_here);
     __syncthreads();
     for (int o = 1; o < 1024; o <<= 1) {
       const int t = tid >= o ? sh[tid - o] : 0;
@@ -646,10 +652,11 @@ __global__ __launch_bounds__(1024) void attn_plan_kernel(int n_seqs, const int32
   __syncthreads();                                   // the prefix is read back below
   const int total = per_head * Hkv;
   // Share sizes differ by at most one unit: the units of the step are dealt out evenly and the first H shares take the
-  // remainder, one unit each.  A share per wave is never empty, and there are at most MERGE_AT_ONCE of them per pair, the parts
-  // that the merge takes in one round trip: a lone sequence would leave it a part per unit otherwise (4B shape, one
-  // sequence of 3000 keys, attention + merge: 2 units per share 15.0 us, 3 14.7, 6 17.3; the limit makes it 3).
-  const int n = team ? n_shares : max(1, min(min(n_shares, total), MERGE_AT_ONCE * n_seqs * Hkv));
+  // remainder, one unit each.  A share per wave is never empty, and there are on average at most MERGE_AT_ONCE of them per
+  // live pair, the parts that the merge takes in one round trip: a lone sequence would leave it a part per unit otherwise
+  // (4B shape, one sequence of 3000 keys, attention + merge: 2 units per share 15.0 us, 3 14.7, 6 17.3; the limit makes
+  // it 3).  A pair far longer than the others has more parts than the average.
+  const int n = team ? n_shares : max(1, min(min(n_shares, total), MERGE_AT_ONCE * n_live * Hkv));
   const int q = total / n, H = total % n;
   const int CA = q + 1, CB = q;
   if (tid == 0) { hdr[0] = CA; hdr[1] = total; hdr[2] = CB; hdr[3] = H; }
@@ -782,14 +789,20 @@ hipError_t attention_decode(const AttnDecodeArgs& a, hipStream_t st) {
   return hipGetLastError();
 }
 
+template <int HD>
+static void launch_merge(const AttnDecodeArgs& a, hipStream_t st) {
+  const dim3 grid(a.n_seqs * a.Hkv);
+  const int slices = (a.Hq / a.Hkv) * HD / 8;        // 8-feature slices of a pair's heads: at most 16 * 128 / 8 = 256
+  const int threads = (slices + 63) / 64 * 64;
+  auto lds = [&](int groups) { return (size_t)(groups - 1) * slices * 10 * sizeof(float); };
+  if (a.team) hipLaunchKernelGGL((attn_decode_merge_kernel<HD, 1>), grid, dim3(threads), lds(1), st, a);
+  else if ((int)grid.x >= MERGE_MANY) hipLaunchKernelGGL((attn_decode_merge_kernel<HD, 2>), grid, dim3(threads * 2), lds(2), st, a);
+  else hipLaunchKernelGGL((attn_decode_merge_kernel<HD, MERGE_GROUPS_MAX>), grid, dim3(threads * MERGE_GROUPS_MAX), lds(MERGE_GROUPS_MAX), st, a);
+}
+
 hipError_t attention_decode_merge(const AttnDecodeArgs& a, hipStream_t st) {
-  dim3 grid(a.n_seqs * a.Hkv);
-  const int slices = (a.Hq / a.Hkv) * a.hd / 8;      // 8-feature slices of a pair's heads: at most 16 * 128 / 8 = 256
-  const int merge_groups = a.team || (int)grid.x >= MERGE_ALONE ? 1 : MERGE_GROUPS;
-  const dim3 block((slices + 63) / 64 * 64 * merge_groups);
-  const size_t lds = (size_t)(merge_groups - 1) * slices * 10 * sizeof(float);
-  if (a.hd == 128) hipLaunchKernelGGL((attn_decode_merge_kernel<128>), grid, block, lds, st, a);
-  else hipLaunchKernelGGL((attn_decode_merge_kernel<64>), grid, block, lds, st, a);
+  if (a.hd == 128) launch_merge<128>(a, st);
+  else launch_merge<64>(a, st);
   return hipGetLastError();
 }
 

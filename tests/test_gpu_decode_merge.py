@@ -1,6 +1,6 @@
-"""Decode attention merges the parts of a (sequence, KV head) pair with several threads per output where a call has few
-pairs and with one where it has many (512 pairs and up).  One long sequence, cut into dozens of parts, is decoded alone and
-among hundreds of short ones."""
+"""Decode attention merges the parts of a (sequence, KV head) pair with four threads per output where a call has few
+pairs and with two where it has many (512 pairs and up).  One long sequence, cut into dozens of parts, is decoded alone, among
+hundreds of short ones and among hundreds of finished ones; pairs of equal length are cut by several grids."""
 import numpy as np
 import pytest
 import torch
@@ -9,13 +9,17 @@ import rollout_inputs as RI
 
 pytestmark = pytest.mark.gpu
 
+HEADS = {64: RI.TINY_DENSE, 128: RI.TINY_DENSE.replace(head_dim=128, n_q_heads=4, n_kv_heads=1)}
 
+
+@pytest.mark.parametrize("head_dim", sorted(HEADS))
+@pytest.mark.parametrize("others", ["short", "finished"])
 @pytest.mark.parametrize("keys", [40, 1023, 3000])
-def test_a_long_sequence_among_many_short_ones(keys):
+def test_a_long_sequence_among_many_others(keys, others, head_dim):
     import paper_2604_11554_amd as pkg
     from paper_2604_11554_amd import synthetic
 
-    s = RI.TINY_DENSE
+    s = HEADS[head_dim]
     n = (512 + s.n_kv_heads - 1) // s.n_kv_heads
     model = synthetic.model_from_shape(s, 3)
     long = np.random.default_rng(5).integers(0, s.vocab - 2, keys).astype(np.int32)
@@ -31,24 +35,27 @@ def test_a_long_sequence_among_many_short_ones(keys):
         eng.prefill([0], [long], forced=[int(long[0])])
         if short:
             eng.prefill(rows[1:], toks[1:], forced=[int(long[0])] * short)
+        if others == "finished":
+            eng.finished[1:len(toks)] = 1
         out = eng.decode_step(forced=torch.full((len(toks),), int(long[0]), dtype=torch.int32, device="cuda"), want_logits=True)
         logits.append(out.logits.cpu().numpy())
     # the same products; sums in another grouping (other GEMM forms and parts) flip the last bit of a few bf16 keys and
     # values (2^-9 of an element) of unit-variance logits: the bar of the calls compared form against form
-    assert np.isfinite(logits[1]).all()
+    assert np.isfinite(logits[1][:1 if others == "finished" else None]).all()
     d = np.abs(logits[0][0] - logits[1][0]).max()
     assert d < 5e-3, d
     model.close()
 
 
+@pytest.mark.parametrize("head_dim", sorted(HEADS))
 @pytest.mark.parametrize("keys", [97, 130, 2200])
-def test_pairs_that_are_exactly_a_workgroup(keys):
+def test_pairs_that_are_exactly_a_workgroup(keys, head_dim):
     """With as many workgroups as pairs and equal contexts every pair is cut into as many shares as a workgroup has waves;
     other grids cut the same pairs elsewhere, or not at all."""
     import paper_2604_11554_amd as pkg
     from paper_2604_11554_amd import synthetic
 
-    s, n = RI.TINY_DENSE, 3
+    s, n = HEADS[head_dim], 3
     model = synthetic.model_from_shape(s, 3)
     rng = np.random.default_rng(6)
     toks = [rng.integers(0, s.vocab - 2, keys - 1).astype(np.int32) for _ in range(n)]
