@@ -240,7 +240,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   load_window(a, cur, lane, tb0, tb1);
   copy_queries(cur, 0);
 
-  constexpr int UNIT_LOADS = 2 * KS + 2 * (HD / 16); // vector loads of one unit
   WaveState<HD, 1> st;
   PageRegs<HD> ra, rb;
   issue_unit<HD>(a, cur, tb0, tb1, cur.lo, true, c16, g, ra);
@@ -266,8 +265,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
       if (last) rs = nxt;
       issue_unit<HD>(a, rs, last ? tbn0 : tb0, last ? tbn1 : tb1, last ? nxt.lo : k + 1, !last || more, c16, g, next);
     }
-    // the first unit of a pair: its queries were requested before its pages, and those before the loads just issued
-    if (fresh) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(UNIT_LOADS) : "memory");
+    // The first unit of a pair: its queries were requested before its pages, and loads return in order, so the queries are
+    // in LDS once the first of the pages is in its registers, which this statement asks of the compiler.
+    if (fresh) asm volatile("" : "+v"(now.k0[0])::"memory");
     fresh = false;
     asm volatile("" ::: "memory");                   // query fragments are re-read from LDS, not kept in registers
     __builtin_amdgcn_sched_barrier(0);               // the next unit's loads go out before this unit's math
