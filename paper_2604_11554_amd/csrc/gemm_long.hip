@@ -234,7 +234,8 @@ __global__ __launch_bounds__(64 * WR * WT) __attribute__((amdgpu_waves_per_eu(2,
   }
   LmRow lm[2];
   if constexpr (EPI == EPI_LMHEAD) { lm[0] = lm_row(a, tok0 + r32); lm[1] = lm_row(a, tok0 + 32 + r32); }
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // no copy may outlive the workgroup's LDS
+  // no copy may outlive the workgroup's LDS, and no fragment read of the last k-step the barrier of the LM head below
+  asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
 
   const int nt0 = tw * JW * WR + JW * wr;            // the wave's first weight tile
   if (EPI == EPI_STORE) {
@@ -289,8 +290,8 @@ __global__ __launch_bounds__(64 * WR * WT) __attribute__((amdgpu_waves_per_eu(2,
       }
     }
   } else {
-    // every wave is past its last fragment read once it is past this barrier (waves without tokens have left; a barrier
-    // counts those that run): the stage buffers become the waves' scratch, two weight tiles at a time
+    // every wave's copies and fragment reads are complete once it is past this barrier (waves without tokens have left; a
+    // barrier counts those that run): the stage buffers become the waves' scratch, two weight tiles at a time
     asm volatile("s_barrier" ::: "memory");
     f32x4* scr = reinterpret_cast<f32x4*>(lds_raw) + wave * 2 * 2 * 4 * WAVE;
     static_assert(EPI != EPI_LMHEAD || TL::LDS_BYTES >= NW * 16 * 1024, "the waves' scratch fits");

@@ -65,15 +65,16 @@ def test_long_calls_equal_the_same_tokens_in_short_calls(name, lengths):
     model.close()
 
 
-@pytest.mark.parametrize("vocab", [2048, 2056, 35])
+@pytest.mark.parametrize("vocab,d_model", [(2048, 256), (2056, 256), (35, 256), (2056, 272)])
 @pytest.mark.parametrize("n_rows", [65, 128, 130, 257])
-def test_lm_heads_of_many_rows_draw_what_short_ones_draw(n_rows, vocab):
+def test_lm_heads_of_many_rows_draw_what_short_ones_draw(n_rows, vocab, d_model):
     """More than 64 sampled rows take the long-call LM head (records of 64 ids, rows of activations): same draws and
-    log-probabilities as calls of at most 64 rows; 2056 and 35 ids end inside a tile."""
+    log-probabilities as calls of at most 64 rows; 2056 and 35 ids end inside a tile, 272 has an odd number of k-steps: the
+    last one is read from LDS right before the epilogue takes the stage buffers."""
     import paper_2604_11554_amd as pkg
     from paper_2604_11554_amd import synthetic
 
-    s = RI.TINY_DENSE.replace(vocab=vocab)
+    s = RI.TINY_DENSE.replace(vocab=vocab, d_model=d_model)
     model = synthetic.model_from_shape(s, 5)
     toks = [np.array([i % (vocab - 2)], np.int32) for i in range(n_rows)]
     sampled, logprobs = [], []
