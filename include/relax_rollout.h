@@ -305,8 +305,10 @@ RLX_API int rollout_decode_step(const rlx_model* m, void* kv_pool, int64_t n_blo
  * loaded there until the process ends; the call allocates nothing, frees nothing and does not synchronise.
  * Arguments and results are those of rollout_decode_step without workspace / workspace_bytes; the model's device
  * must be the current device (as for every call).
- *   RLX_ENOMEM  the step needs more scratch than the array holds (rlx_workspace_bytes(m, n_seqs, n_seqs, ...) >
- *               RLX_STATIC_WORKSPACE_BYTES): nothing is enqueued; use rollout_decode_step with a workspace.
+ *   RLX_ENOMEM  the step needs more scratch than the array holds: nothing is enqueued; use rollout_decode_step with a
+ *               workspace.  A step with rlx_workspace_bytes(m, n_seqs, n_seqs, ...) <= RLX_STATIC_WORKSPACE_BYTES fits; a
+ *               larger one may (that figure covers all smaller steps too).  Dense steps of more than 128 sequences that
+ *               do not fit otherwise cut their matrix products along K fewer times, another order of the same sums.
  * All calls on one GPU share that GPU's array: two calls of this entry point whose work overlaps in time on the
  * same GPU (different streams, or different threads) race on it and give undefined results; calls on one stream
  * are ordered and safe.  The array keeps the previous call's contents; no call depends on them.

@@ -127,12 +127,12 @@ int score_rows_max(int T) { return T <= 256 ? 256 : (T < SCORE_ROWS ? T : SCORE_
 constexpr int ATTN_WGS_MAX = 1024;   // decode attention grid limit
 
 // Calls of more than 128 tokens (MoE: 256) on two-term bf16 activations carry them in rows and take the long-call GEMMs.
-bool long_call(const rlx_model_config& c, int T) {
-  return T > (c.n_experts ? 256 : 128) && c.activation_split && c.dtype == RLX_DTYPE_BF16;
-}
+bool two_term(const rlx_model_config& c) { return c.activation_split && c.dtype == RLX_DTYPE_BF16; }
+int short_tokens(const rlx_model_config& c) { return two_term(c) && !c.n_experts ? 128 : 256; }   // of the calls that split K in up to 16
+bool long_call(const rlx_model_config& c, int T) { return T > short_tokens(c) && two_term(c); }
 // ... and so do LM heads of more than 64 rows (151 936 x 2560, one draw per row: 96 rows 234 -> 211 us, 256 rows 509 -> 396;
 // 64 rows 153 in the short form, 161 at best in long ones)
-bool rows_lmhead(const rlx_model_config& c, int rows) { return rows > 64 && c.activation_split && c.dtype == RLX_DTYPE_BF16; }
+bool rows_lmhead(const rlx_model_config& c, int rows) { return rows > 64 && two_term(c); }
 // Decode attention of MoE policies keeps a share of the keys per workgroup: in a share per wave the sums come in another
 // order, and the last bits of the router's input decide near-ties of the routing (30B-A3B shape, 128 sequences of 1530
 // keys: one token took its ninth expert for its eighth, which moved the batch's logits by 3 % of their norm).
@@ -141,24 +141,40 @@ Act call_act(const rlx_model_config& c, h16_t* p, int T, int K, bool rows) {
   return rows ? make_act_rows(p, T, K) : make_act(p, T, K, c.activation_split ? 2 : 1, c.dtype);
 }
 
-// Split-K planes per token of an output of up to d_model features (the o and down projections) and of the wider q|k|v:
-// sixteen in short calls; in long ones as many as keep the planes under 16384 (8192) rows, at most eight (four), and
-// two (one) however long the call.  Long calls of MoE policies keep their sums whole: the other order of sums would
-// change the last bits of the router's input, which decide near-ties of the routing, and 128 x 128 tiles fill the
-// device there without planes (30B-A3B shape, 2048 tokens: output projection 64 us whole, 63 in two planes).
-int long_planes(const rlx_model_config& c, int T, bool wide) {
+// Split-K planes per token of an output of up to d_model features (the o and down projections) and of the wider q|k|v in
+// long calls: as many as keep the planes under 16384 (8192) rows, at most eight (four), and two (one) however long the
+// call.  Long calls of MoE policies keep their sums whole: the other order of sums would change the last bits of the
+// router's input, which decide near-ties of the routing, and 128 x 128 tiles fill the device there without planes (30B-A3B
+// shape, 2048 tokens: output projection 64 us whole, 63 in two planes).  `lean`: two (one) at any length, for calls that
+// would not fit their scratch otherwise.
+int long_planes(const rlx_model_config& c, int T, bool wide, bool lean) {
   if (c.n_experts) return 1;
   const int most = wide ? 4 : 8, n = (wide ? 8192 : 16384) / T, least = wide ? 1 : 2;
-  return n > most ? most : (n < least ? least : n);
+  return lean || n < least ? least : (n > most ? most : n);
 }
-size_t plane_rows(int T, bool wide) {   // an upper bound that does not fall as T grows
-  if (T <= 256) return (size_t)gemm_max_splits() * T;
-  const size_t most = (wide ? 4 : 8) * (size_t)T, cap = wide ? 8192 : 16384, least = (wide ? 1 : 2) * (size_t)T;
-  return least > cap ? least : (most < cap ? most : cap);
+// rows of the planes of a call of T tokens: sixteen per token in short calls, one in longer ones that carry one term
+size_t plane_rows(const rlx_model_config& c, int T, bool wide, bool lean) {
+  if (T <= short_tokens(c)) return (size_t)gemm_max_splits() * T;
+  return (size_t)(two_term(c) ? long_planes(c, T, wide, lean) : 1) * T;
+}
+// ... and at most of a call of up to T tokens
+size_t plane_rows_up_to(const rlx_model_config& c, int T, bool wide) {
+  const size_t shrt = (size_t)gemm_max_splits() * (T < short_tokens(c) ? T : short_tokens(c));
+  size_t lng = (size_t)T;
+  if (two_term(c) && !c.n_experts) {
+    const size_t most = (wide ? 4 : 8) * lng, cap = wide ? 8192 : 16384, least = (wide ? 1 : 2) * lng;
+    lng = least > cap ? least : (most < cap ? most : cap);
+  }
+  return shrt > lng ? shrt : lng;
 }
 
-// carve the workspace; with base == nullptr only the size is computed
-Workspace carve(const rlx_model_config& c, char* base, int S, int T, int max_blocks) {
+// Carve the workspace; with base == nullptr only the size is computed.  S sequences; T: the larger of S and the number of
+// tokens; `planes`: rows of the split-K planes, narrow and wide.
+struct PlaneRows { size_t narrow, wide; };
+PlaneRows call_planes(const rlx_model_config& c, int tokens, bool lean = false) {
+  return {plane_rows(c, tokens, false, lean), plane_rows(c, tokens, true, lean)};
+}
+Workspace carve(const rlx_model_config& c, char* base, int S, int T, const PlaneRows& planes) {
   Workspace w = {};
   size_t off = 0;
   auto take = [&](size_t bytes) {
@@ -189,7 +205,7 @@ Workspace carve(const rlx_model_config& c, char* base, int S, int T, int max_blo
   const bool lng = long_call(c, T);
   w.xb = (h16_t*)take(act_bytes(T, c.d_model, lng));
   w.x_ss = (float*)take((size_t)T * NORM_PARTS * 4);
-  w.router = c.n_experts ? (float*)take(plane_rows(T, false) * c.n_experts * 4) : nullptr;
+  w.router = c.n_experts ? (float*)take(planes.narrow * c.n_experts * 4) : nullptr;
   w.q = (h16_t*)take((size_t)PL * T * qdim * 2);
   w.ob = (h16_t*)take(act_bytes(T, qdim, lng));
   w.attn_prefix = (int32_t*)take((size_t)(S + 1) * 4);
@@ -200,8 +216,8 @@ Workspace carve(const rlx_model_config& c, char* base, int S, int T, int max_blo
   // Split-K planes of q|k|v and of the o and down projections.  Both are dead while decode attention runs (its queries
   // are rotated, the residual has taken the planes up), so its partials lie in the same memory.
   const size_t planes_at = off;
-  w.qkv = (float*)take(plane_rows(T, true) * qkv_dim * 4);
-  w.planes = (float*)take(plane_rows(T, false) * c.d_model * 4);
+  w.qkv = (float*)take(planes.wide * qkv_dim * 4);
+  w.planes = (float*)take(planes.narrow * c.d_model * 4);
   w.attn_part = w.qkv;
   const size_t attn_end = planes_at + align_up((size_t)ATTN_SHARES_MAX * 2 * (c.n_q_heads / c.n_kv_heads) * (c.head_dim + 4) * 4);
   if (off < attn_end) off = attn_end;
@@ -226,7 +242,8 @@ Workspace carve(const rlx_model_config& c, char* base, int S, int T, int max_blo
   }
   const int score_rows = score_rows_max(T), lm_rows = S > score_rows ? S : score_rows;   // sampled rows, or a block of scored ones
   w.x_lm = (h16_t*)take(act_bytes(lm_rows, c.d_model, rows_lmhead(c, lm_rows)));
-  w.lm_part = (float*)take((size_t)lm_rows * ((c.vocab + 31) / 32) * 4 * 4);
+  // a part per 64 ids in the form of many rows, per 32 in that of up to 64: there are at least 256 rows here
+  w.lm_part = (float*)take((size_t)lm_rows * (two_term(c) ? (c.vocab + 63) / 64 : (c.vocab + 31) / 32) * 4 * 4);
   w.bytes = off;
   return w;
 }
@@ -247,6 +264,7 @@ struct StepIO {
   bool score; const int32_t* score_targets; float* score_logprobs;
   const int32_t* replay_routing;   // optional [T, n_layers, top_k]
   const int32_t* shared_prefix;    // decode only, optional descriptor of shared prompt prefixes
+  bool lean;                       // as few split-K planes as a long call can do with (long_planes)
 };
 
 int run_layers(const rlx_model* m, h16_t* pool, int64_t n_blocks, const Workspace& w, const StepIO& io,
@@ -276,10 +294,10 @@ int run_layers(const rlx_model* m, h16_t* pool, int64_t n_blocks, const Workspac
   // y = x W^T into `y`: split-K planes that the next kernel adds
   auto planes_of = [&](int N, int K, bool wide) {
     if (small) return gemm_plan_splits(N, K, T, gemm_max_splits(), m->n_units, PL, FMT);
-    return lng ? gemm_long_splits(N, K, T, long_planes(c, T, wide), m->n_units) : 1;
+    return lng ? gemm_long_splits(N, K, T, long_planes(c, T, wide, io.lean), m->n_units) : 1;
   };
   auto store = [&](const LinearW& lw, const Act& x, float* y, int splits, bool wide) {
-    return lng ? gemm_long_store(lw, x, T, y, lw.N, long_planes(c, T, wide), m->n_units, st)
+    return lng ? gemm_long_store(lw, x, T, y, lw.N, long_planes(c, T, wide, io.lean), m->n_units, st)
                : gemm_store(lw, x, T, y, lw.N, splits, st);
   };
   auto norm = [&](const h16_t* gain, const int32_t* rows, int n_rows, const Act& x, float* xf) -> hipError_t {
@@ -468,6 +486,36 @@ int install_weights(rlx_model* m, const rlx_weights* wt) {
   return RLX_OK;
 }
 
+int decode_step(const rlx_model* m, void* kv_pool, int64_t n_blocks, void* workspace, size_t workspace_bytes, int32_t n_seqs,
+                int32_t* tokens_inout, int32_t* ctx_lens_inout, const int32_t* block_table, int32_t max_blocks_per_seq,
+                const uint64_t* seeds, const float* temperature, const int32_t* max_ctx_len, uint8_t* finished_inout,
+                const int32_t* forced_tokens, float* out_logprobs, int32_t* out_sampled, int32_t* out_routing,
+                float* out_logits, const void* shared_prefix, bool lean, void* stream) {
+  int rc = check_common(m, kv_pool, n_blocks, workspace, n_seqs, max_blocks_per_seq);
+  if (rc) return rc;
+  if (n_seqs == 0) return RLX_OK;                         // an empty step: nothing to enqueue, no array is read
+  if (!tokens_inout || !ctx_lens_inout || !block_table || !seeds || !temperature || !max_ctx_len ||
+      !finished_inout || !out_logprobs)
+    return fail(RLX_EINVAL, "NULL array argument");
+  if (shared_prefix && !aligned16(shared_prefix)) return fail(RLX_EINVAL, "shared_prefix must be 16-byte aligned");
+  Workspace w = carve(m->cfg, (char*)workspace, n_seqs, n_seqs, call_planes(m->cfg, n_seqs, lean));
+  if (w.bytes > workspace_bytes)
+    return fail(RLX_ENOMEM, "workspace too small: need %zu bytes, have %zu", w.bytes, workspace_bytes);
+  hipStream_t st = (hipStream_t)stream;
+  RLX_HIP(meta_decode(w.meta, n_seqs, ctx_lens_inout, finished_inout, m->inv_freq, m->cfg.head_dim, st));
+  RLX_HIP(attention_decode_plan(n_seqs, ctx_lens_inout, w.meta.tok_live, m->cfg.n_kv_heads, m->attn_wgs,
+                                attn_by_team(m->cfg), (const int32_t*)shared_prefix, w.attn_prefix, w.attn_share_seq, w.attn_hdr, st));
+  StepIO io = {};
+  io.n_seqs = n_seqs; io.T = n_seqs; io.decode = true;
+  io.tokens = tokens_inout; io.ctx_lens = ctx_lens_inout; io.ctx_lens_rw = ctx_lens_inout;
+  io.block_table = block_table; io.max_blocks = max_blocks_per_seq;
+  io.seeds = seeds; io.temperature = temperature; io.max_ctx_len = max_ctx_len; io.forced = forced_tokens;
+  io.out_tokens = tokens_inout; io.out_logprobs = out_logprobs; io.finished = finished_inout;
+  io.out_sampled = out_sampled; io.out_routing = m->cfg.n_experts ? out_routing : nullptr; io.out_logits = out_logits;
+  io.shared_prefix = (const int32_t*)shared_prefix; io.lean = lean;
+  return run_layers(m, (h16_t*)kv_pool, n_blocks, w, io, st);
+}
+
 }  // namespace
 
 extern "C" {
@@ -579,13 +627,8 @@ int rlx_workspace_bytes(const rlx_model* m, int32_t max_seqs, int32_t max_tokens
                         size_t* bytes_out) {
   if (!m || !bytes_out || max_seqs <= 0 || max_tokens < max_seqs || max_blocks_per_seq <= 0)
     return fail(RLX_EINVAL, "bad argument (need 0 < max_seqs <= max_tokens, max_blocks_per_seq > 0)");
-  // calls with at most 256 tokens keep up to 16 split-K planes per token, longer ones a single plane: the
-  // need is monotonic in the token count on either side of that switch, not across it
-  size_t b = carve(m->cfg, nullptr, max_seqs, max_tokens, max_blocks_per_seq).bytes;
-  if (max_tokens > 256) {
-    const size_t b2 = carve(m->cfg, nullptr, max_seqs < 256 ? max_seqs : 256, 256, max_blocks_per_seq).bytes;
-    if (b2 > b) b = b2;
-  }
+  const PlaneRows planes = {plane_rows_up_to(m->cfg, max_tokens, false), plane_rows_up_to(m->cfg, max_tokens, true)};
+  const size_t b = carve(m->cfg, nullptr, max_seqs, max_tokens, planes).bytes;   // no buffer gets smaller as a call grows
   *bytes_out = b;
   return RLX_OK;
 }
@@ -615,7 +658,7 @@ int rollout_prefill_chunk(const rlx_model* m, void* kv_pool, int64_t n_blocks, v
     return fail(RLX_EINVAL, "NULL array argument");
   if (input_embeds && !aligned16(input_embeds)) return fail(RLX_EINVAL, "input_embeds not 16-byte aligned");
   const int T = total_tokens > n_seqs ? total_tokens : n_seqs;
-  Workspace w = carve(m->cfg, (char*)workspace, n_seqs, T, max_blocks_per_seq);
+  Workspace w = carve(m->cfg, (char*)workspace, n_seqs, T, call_planes(m->cfg, total_tokens));
   if (w.bytes > workspace_bytes)
     return fail(RLX_ENOMEM, "workspace too small: need %zu bytes, have %zu", w.bytes, workspace_bytes);
   hipStream_t st = (hipStream_t)stream;
@@ -644,7 +687,7 @@ int rollout_score_chunk(const rlx_model* m, void* kv_pool, int64_t n_blocks, voi
     return fail(RLX_EINVAL, "NULL array argument");
   if (input_embeds && !aligned16(input_embeds)) return fail(RLX_EINVAL, "input_embeds not 16-byte aligned");
   const int T = total_tokens > n_seqs ? total_tokens : n_seqs;
-  Workspace w = carve(m->cfg, (char*)workspace, n_seqs, T, max_blocks_per_seq);
+  Workspace w = carve(m->cfg, (char*)workspace, n_seqs, T, call_planes(m->cfg, total_tokens));
   if (w.bytes > workspace_bytes)
     return fail(RLX_ENOMEM, "workspace too small: need %zu bytes, have %zu", w.bytes, workspace_bytes);
   hipStream_t st = (hipStream_t)stream;
@@ -666,29 +709,9 @@ int rollout_decode_step_shared(const rlx_model* m, void* kv_pool, int64_t n_bloc
                                const float* temperature, const int32_t* max_ctx_len, uint8_t* finished_inout,
                                const int32_t* forced_tokens, float* out_logprobs, int32_t* out_sampled,
                                int32_t* out_routing, float* out_logits, const void* shared_prefix, void* stream) {
-  int rc = check_common(m, kv_pool, n_blocks, workspace, n_seqs, max_blocks_per_seq);
-  if (rc) return rc;
-  if (n_seqs == 0) return RLX_OK;                         // an empty step: nothing to enqueue, no array is read
-  if (!tokens_inout || !ctx_lens_inout || !block_table || !seeds || !temperature || !max_ctx_len ||
-      !finished_inout || !out_logprobs)
-    return fail(RLX_EINVAL, "NULL array argument");
-  if (shared_prefix && !aligned16(shared_prefix)) return fail(RLX_EINVAL, "shared_prefix must be 16-byte aligned");
-  Workspace w = carve(m->cfg, (char*)workspace, n_seqs, n_seqs, max_blocks_per_seq);
-  if (w.bytes > workspace_bytes)
-    return fail(RLX_ENOMEM, "workspace too small: need %zu bytes, have %zu", w.bytes, workspace_bytes);
-  hipStream_t st = (hipStream_t)stream;
-  RLX_HIP(meta_decode(w.meta, n_seqs, ctx_lens_inout, finished_inout, m->inv_freq, m->cfg.head_dim, st));
-  RLX_HIP(attention_decode_plan(n_seqs, ctx_lens_inout, w.meta.tok_live, m->cfg.n_kv_heads, m->attn_wgs,
-                                attn_by_team(m->cfg), (const int32_t*)shared_prefix, w.attn_prefix, w.attn_share_seq, w.attn_hdr, st));
-  StepIO io = {};
-  io.n_seqs = n_seqs; io.T = n_seqs; io.decode = true;
-  io.tokens = tokens_inout; io.ctx_lens = ctx_lens_inout; io.ctx_lens_rw = ctx_lens_inout;
-  io.block_table = block_table; io.max_blocks = max_blocks_per_seq;
-  io.seeds = seeds; io.temperature = temperature; io.max_ctx_len = max_ctx_len; io.forced = forced_tokens;
-  io.out_tokens = tokens_inout; io.out_logprobs = out_logprobs; io.finished = finished_inout;
-  io.out_sampled = out_sampled; io.out_routing = m->cfg.n_experts ? out_routing : nullptr; io.out_logits = out_logits;
-  io.shared_prefix = (const int32_t*)shared_prefix;
-  return run_layers(m, (h16_t*)kv_pool, n_blocks, w, io, st);
+  return decode_step(m, kv_pool, n_blocks, workspace, workspace_bytes, n_seqs, tokens_inout, ctx_lens_inout, block_table,
+                     max_blocks_per_seq, seeds, temperature, max_ctx_len, finished_inout, forced_tokens, out_logprobs,
+                     out_sampled, out_routing, out_logits, shared_prefix, false, stream);
 }
 
 int rollout_decode_step(const rlx_model* m, void* kv_pool, int64_t n_blocks, void* workspace, size_t workspace_bytes,
@@ -713,16 +736,17 @@ int rollout_decode_step_static(const rlx_model* m, void* kv_pool, int64_t n_bloc
   if (n_seqs < 0 || n_seqs > (1 << 16)) return fail(RLX_EINVAL, "n_seqs %d out of range", n_seqs);
   if (max_blocks_per_seq <= 0 || max_blocks_per_seq > (1 << 20))
     return fail(RLX_EINVAL, "max_blocks_per_seq %d out of range", max_blocks_per_seq);
-  const size_t need = n_seqs ? carve(m->cfg, nullptr, n_seqs, n_seqs, max_blocks_per_seq).bytes : 0;
+  size_t need = n_seqs ? carve(m->cfg, nullptr, n_seqs, n_seqs, call_planes(m->cfg, n_seqs)).bytes : 0;
+  const bool lean = need > (size_t)RLX_STATIC_WORKSPACE_BYTES;
+  if (lean) need = carve(m->cfg, nullptr, n_seqs, n_seqs, call_planes(m->cfg, n_seqs, true)).bytes;
   if (need > (size_t)RLX_STATIC_WORKSPACE_BYTES)
     return fail(RLX_ENOMEM, "rollout_decode_step_static: a step of %d sequences of this model needs %zu bytes of "
                 "scratch, the fixed array holds %zu; use rollout_decode_step with a workspace of your own", n_seqs,
                 need, (size_t)RLX_STATIC_WORKSPACE_BYTES);
   if (!m->static_ws) return fail(RLX_EHIP, "rollout_decode_step_static: the fixed scratch array has no address");
-  return rollout_decode_step_shared(m, kv_pool, n_blocks, m->static_ws, (size_t)RLX_STATIC_WORKSPACE_BYTES, n_seqs,
-                                    tokens_inout, ctx_lens_inout, block_table, max_blocks_per_seq, seeds, temperature,
-                                    max_ctx_len, finished_inout, forced_tokens, out_logprobs, out_sampled, out_routing,
-                                    out_logits, nullptr, stream);
+  return decode_step(m, kv_pool, n_blocks, m->static_ws, (size_t)RLX_STATIC_WORKSPACE_BYTES, n_seqs, tokens_inout,
+                     ctx_lens_inout, block_table, max_blocks_per_seq, seeds, temperature, max_ctx_len, finished_inout,
+                     forced_tokens, out_logprobs, out_sampled, out_routing, out_logits, nullptr, lean, stream);
 }
 
 int rlx_shared_prefix_bytes(const rlx_model* m, int32_t n_seqs, size_t* bytes_out) {
