@@ -501,20 +501,26 @@ void launch_one_form(const GemmArgs& a, dim3 grid, hipStream_t st) {
 }
 
 // Several token tiles (grid z) share a weight tile only in the store form at 64 tokens per tile (two-group calls) and
-// in the 128-token forms; an expert group with more rows than a tile is rare enough to keep the streaming mark.
+// in the 128-token forms, of which SwiGLU on two terms has no more than one (longer dense calls take the long-call form);
+// an expert group with more rows than a tile is rare enough to keep the streaming mark.
 template <int MT, int EPI, int PL, int FMT>
 void launch_one(const GemmArgs& a, dim3 grid, hipStream_t st) {
-  constexpr bool shared_tiles_possible = MT == 4 || (MT == 2 && EPI == EPI_STORE);
+  constexpr bool shared_tiles_possible = (MT == 4 && !(EPI == EPI_SWIGLU && PL == 2)) || (MT == 2 && EPI == EPI_STORE);
   if (shared_tiles_possible && grid.z > 1 && a.group_off == nullptr) launch_one_form<MT, EPI, PL, FMT, !shared_tiles_possible>(a, grid, st);
   else launch_one_form<MT, EPI, PL, FMT, true>(a, grid, st);
 }
 
-// formats built: bf16 activations as one or two terms, fp16 activations as one term
+// formats built: bf16 activations as one or two terms, fp16 activations as one term; LM heads of more than 64 rows on two
+// terms take the long-call form (gemm_lmhead refuses them)
 template <int MT, int EPI>
 void launch_fmt(const GemmArgs& a, dim3 grid, const Act& x, hipStream_t st) {
-  if (x.dtype == DT_F16) launch_one<MT, EPI, 1, DT_F16>(a, grid, st);
-  else if (x.planes == 2) launch_one<MT, EPI, 2, DT_BF16>(a, grid, st);
-  else launch_one<MT, EPI, 1, DT_BF16>(a, grid, st);
+  if (x.dtype == DT_F16) {
+    launch_one<MT, EPI, 1, DT_F16>(a, grid, st);
+  } else if (x.planes == 2) {
+    if constexpr (!(MT == 4 && EPI == EPI_LMHEAD)) launch_one<MT, EPI, 2, DT_BF16>(a, grid, st);
+  } else {
+    launch_one<MT, EPI, 1, DT_BF16>(a, grid, st);
+  }
 }
 
 template <int EPI>
@@ -710,6 +716,7 @@ hipError_t gemm_lmhead(const h16_t* w_lm, int V, int K, const Act& x, int T, flo
                        const uint64_t* seeds, const float* temperature, const int32_t* sample_pos,
                        const int32_t* row_seq, bool draw, hipStream_t st) {
   if (x.ss) return hipErrorInvalidValue;              // the LM-head epilogue takes finished rows only
+  if (x.planes == 2 && pick_mt(T) == 4) return hipErrorInvalidValue;
   GemmArgs a = {};
   fill_x(a, x);
   a.w[0] = w_lm; a.w_tiles[0] = (V + 31) / 32;

@@ -323,7 +323,7 @@ void launch_long(const GemmArgs& a, int form, int n_items, hipStream_t st) {
   auto wt = [&](int rows) { return (n_tiles * 32 + rows - 1) / rows; };
   if (form == LONG_512x128) launch_form<4, 4, 2, 3, EPI>(a, wt(512), tt(128), 4, st);
   else if (form == LONG_128x128) launch_form<2, 2, 2, 3, EPI>(a, wt(128), tt(128), 8, st);
-  else launch_form<4, 4, 1, 2, EPI>(a, wt(512), tt(64), 8, st);
+  else if constexpr (EPI != EPI_LMHEAD) launch_form<4, 4, 1, 2, EPI>(a, wt(512), tt(64), 8, st);   // grouped only
 }
 
 // ---- which form, and into how many planes K is cut ----
