@@ -291,13 +291,18 @@ int run_layers(const rlx_model* m, h16_t* pool, int64_t n_blocks, const Workspac
   // hold exactly (embeddings) exact; not for fp16 (unnormalised rows would strain its range) and not where the grouped
   // gate/up goes through a row list
   if (T <= 256 && FMT == DT_BF16 && rmsnorm_in_parts(d) && (c.n_experts == 0 || routed)) { xb.ss = w.x_ss; xb.eps = c.rms_eps; }
-  // y = x W^T into `y`: split-K planes that the next kernel adds
+  // y = x W^T into `y`: split-K planes that the next kernel adds.  q|k|v of long calls of up to 256 tokens (decode batches) comes
+  // in all the planes it may have: keys and values are rounded to 16 bits right after, and with longer sums more of them
+  // get the neighbouring code (K 2560, of six million values 1908 with the two planes that are fastest, 1573 with four, 1490
+  // in short calls; logits of 256 rows, four layers: 2.5e-5 of their norm off a 64-bit computation with two, 2.3e-5 with
+  // four and in the short form; eight layers, 129 rows: 1500 -> 1520 us a step, 256 rows 1910 both).
+  const bool fine_qkv = T <= 256;
   auto planes_of = [&](int N, int K, bool wide) {
     if (small) return gemm_plan_splits(N, K, T, gemm_max_splits(), m->n_units, PL, FMT);
-    return lng ? gemm_long_splits(N, K, T, long_planes(c, T, wide, io.lean), m->n_units) : 1;
+    return lng ? gemm_long_splits(N, K, T, long_planes(c, T, wide, io.lean), m->n_units, wide && fine_qkv) : 1;
   };
   auto store = [&](const LinearW& lw, const Act& x, float* y, int splits, bool wide) {
-    return lng ? gemm_long_store(lw, x, T, y, lw.N, long_planes(c, T, wide, io.lean), m->n_units, st)
+    return lng ? gemm_long_store(lw, x, T, y, lw.N, long_planes(c, T, wide, io.lean), m->n_units, wide && fine_qkv, st)
                : gemm_store(lw, x, T, y, lw.N, splits, st);
   };
   auto norm = [&](const h16_t* gain, const int32_t* rows, int n_rows, const Act& x, float* xf) -> hipError_t {

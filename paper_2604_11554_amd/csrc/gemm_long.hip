@@ -337,13 +337,15 @@ void launch_long(const GemmArgs& a, int form, int n_items, hipStream_t st) {
 // 1437 tokens, N 2560, K 9728: 512 x 128 whole 324 us, 128 x 128 whole 135, 512 x 128 in four planes 122; 3000 tokens,
 // N 6144, K 2560: 512 x 128 217 us, 128 x 128 174; 8192 tokens: 375 and 428.  (256 x 128 tiles were never the best.)
 struct LongPlan { int form, splits; };
-static LongPlan plan_long(int N, int K, int T, int max_splits, int n_units) {
+// `finest`: as many planes as there may be, in the form that is faster with them.
+static LongPlan plan_long(int N, int K, int T, int max_splits, int n_units, bool finest) {
   const int stages = (K / 16 + 1) / 2;
   LongPlan best = {LONG_512x128, 1};
   float best_us = 1e30f;
   for (int s = 1; s <= max_splits; ++s) {
     const int per = (stages + s - 1) / s;
     if (s > 1 && ((s - 1) * per >= stages || per < 8)) continue;   // no empty split, no split of a few stages
+    if (finest) best_us = 1e30f;
     const long wg_t = (long)((T + 127) / 128) * s;
     const float planes_us = (float)(s - 1) * (float)T * (float)N * 1.1e-6f;
     const long r512 = (wg_t * ((N + 511) / 512) + n_units - 1) / n_units;
@@ -366,7 +368,9 @@ static int grouped_form(int tile_rows) { return tile_rows == 64 ? LONG_512x64 : 
 
 int gemm_long_item_rows(int expected_rows) { return expected_rows <= 48 ? 64 : 128; }
 
-int gemm_long_splits(int N, int K, int T, int max_splits, int n_units) { return plan_long(N, K, T, max_splits, n_units).splits; }
+int gemm_long_splits(int N, int K, int T, int max_splits, int n_units, bool finest) {
+  return plan_long(N, K, T, max_splits, n_units, finest).splits;
+}
 
 static void fill_long(GemmArgs& a, const Act& x, int N, int K, int T) {
   a.x = x.p; a.x_pitch = x.pitch; a.x_ss = x.ss; a.x_eps = x.eps;
@@ -375,9 +379,9 @@ static void fill_long(GemmArgs& a, const Act& x, int N, int K, int T) {
   a.splits = 1;
 }
 
-hipError_t gemm_long_store(const LinearW& w, const Act& x, int T, float* y, int ldy, int max_splits, int n_units,
+hipError_t gemm_long_store(const LinearW& w, const Act& x, int T, float* y, int ldy, int max_splits, int n_units, bool finest,
                            hipStream_t st) {
-  const LongPlan plan = plan_long(w.N, w.K, T, max_splits, n_units);
+  const LongPlan plan = plan_long(w.N, w.K, T, max_splits, n_units, finest);
   GemmArgs a = {};
   fill_long(a, x, w.N, w.K, T);
   for (int i = 0; i < 3; ++i) { a.w[i] = w.seg[i]; a.w_tiles[i] = (w.rows[i] + 31) / 32; }
@@ -394,7 +398,7 @@ hipError_t gemm_long_swiglu(const h16_t* w_gate_up, int F, int K, const Act& x, 
   fill_long(a, x, 2 * F, K, T);
   a.w[0] = w_gate_up; a.w_tiles[0] = F / 16;
   a.act = act.p; a.act_pitch = act.pitch;
-  launch_long<EPI_SWIGLU>(a, plan_long(2 * F, K, T, 1, n_units).form, 0, st);
+  launch_long<EPI_SWIGLU>(a, plan_long(2 * F, K, T, 1, n_units, false).form, 0, st);
   return hipGetLastError();
 }
 
@@ -429,7 +433,7 @@ hipError_t gemm_long_lmhead(const h16_t* w_lm, int V, int K, const Act& x, int T
   a.w[0] = w_lm; a.w_tiles[0] = (V + 31) / 32;
   a.logits = logits; a.part = part; a.seeds = seeds; a.temperature = temperature; a.sample_pos = sample_pos;
   a.row_seq = row_seq; a.draw = draw ? 1 : 0;
-  launch_long<EPI_LMHEAD>(a, plan_long(V, K, T, 1, n_units).form, 0, st);
+  launch_long<EPI_LMHEAD>(a, plan_long(V, K, T, 1, n_units, false).form, 0, st);
   return hipGetLastError();
 }
 

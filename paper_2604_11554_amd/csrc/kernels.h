@@ -97,9 +97,9 @@ hipError_t gemm_routed_swiglu(const h16_t* w_gate_up, int E, int F, int K, const
 
 // ---- gemm_long.hip: the same products for long calls on two-term bf16 activations in rows (Act::pitch) ----
 enum { LONG_512x128 = 0, LONG_128x128, LONG_512x64 };   // weight rows x tokens of a workgroup
-// y[split][t][n]: K cut into gemm_long_splits() planes (at most max_splits)
-int gemm_long_splits(int N, int K, int T, int max_splits, int n_units);
-hipError_t gemm_long_store(const LinearW& w, const Act& x, int T, float* y, int ldy, int max_splits, int n_units,
+// y[split][t][n]: K cut into gemm_long_splits() planes, at most max_splits: the fastest number, or the largest (`finest`)
+int gemm_long_splits(int N, int K, int T, int max_splits, int n_units, bool finest);
+hipError_t gemm_long_store(const LinearW& w, const Act& x, int T, float* y, int ldy, int max_splits, int n_units, bool finest,
                            hipStream_t st);
 hipError_t gemm_long_swiglu(const h16_t* w_gate_up, int F, int K, const Act& x, int T, const Act& act, int n_units,
                             hipStream_t st);

@@ -127,3 +127,41 @@ def test_values_of_tokens_at_any_slot_are_appended_alike(head_dim):
     assert (pools[0][:layer0] != 0).sum() >= sum(map(len, toks)) * head_dim
     assert np.array_equal(pools[0][:layer0], pools[1][:layer0])
     model.close()
+
+
+def test_values_of_calls_of_129_to_256_tokens_are_as_exact_as_those_of_short_calls():
+    """Values are rounded to 16 bits as q|k|v leaves them, so its sums decide how many of them get the neighbouring code.
+    Against a product in 64 bits: a call of 256 tokens may have no more such codes than the same tokens in calls of 64,
+    which cut K finer than time alone would ask of the longer call (half a million values per call, twelve calls)."""
+    import torch
+
+    import paper_2604_11554_amd as pkg
+    from paper_2604_11554_amd import synthetic
+
+    s = RI.TINY_DENSE.replace(n_layers=1, d_model=2560, n_q_heads=16, n_kv_heads=16, head_dim=128, d_ff=16, vocab=2048)
+    tensor = synthetic.device_random_tensor(s, 3)
+    model = synthetic.device_random_model(s, 3)
+    f64 = torch.float64
+    h = tensor(-1, "embed").to(f64)
+    x = h / torch.sqrt((h * h).mean(-1, keepdim=True) + s.rms_eps) * tensor(0, "attn_norm").to(f64)
+    want = (x @ tensor(0, "wv").to(f64).t()).to(torch.bfloat16)
+    n, off = 256, {256: 0, 64: 0}
+    for call in range(12):
+        toks = np.random.default_rng(call).choice(s.vocab - 2, n, replace=False).astype(np.int32)
+        for per in off:
+            eng = pkg.RolloutEngine(model, n_blocks=n, max_seqs=n, max_chunk_tokens=n, max_blocks_per_seq=1)
+            for i in range(n):
+                eng.add_sequence(i, reserve_tokens=1)
+            for a in range(0, n, per):
+                eng.prefill(list(range(a, a + per)), [toks[i:i + 1] for i in range(a, a + per)], sample_last=[False] * per)
+            pages = eng.kv_pool.view(torch.bfloat16).view(n, s.n_kv_heads, 2, 16 * s.head_dim)
+            got = pages[eng.block_table[:n, 0].long(), :, 1].view(n, s.kv_dim, 16)[:, :, 0]
+            ref = want[torch.from_numpy(toks).long().to(got.device)]
+            assert bool(((got.float() - ref.float()).abs() <= 2.0 ** -7 * ref.float().abs() + 1e-5).all())
+            off[per] += int((got != ref).sum())
+    # of six million values about 1500 each; the square root is the scatter of the count.  (In two ranges of K instead of four:
+    # a quarter more.)
+    print("codes off", off)
+    assert off[64] > 500, off
+    assert off[256] <= 1.05 * off[64] + 3 * off[64] ** 0.5, off
+    model.close()
