@@ -1,6 +1,7 @@
-"""Calls of more than 256 tokens take GEMM forms of their own (activations in rows, tiles of 128 or 64 tokens, K cut into
-planes where the tiles leave the device idle).  They are compared with the same tokens handed over in calls of at most
-256, which take the short-call forms: same products, sums in another grouping."""
+"""Long calls take GEMM forms of their own (activations in rows, tiles of 128 or 64 tokens, K cut into planes where the tiles
+leave the device idle): the layers' products from 129 tokens on in dense policies and from 257 in MoE ones, LM heads and
+scoring from 65 rows on.  They are compared with the same tokens handed over in calls of at most 64, all of whose products
+take the short forms: the same products, sums in another grouping."""
 import numpy as np
 import pytest
 
@@ -15,8 +16,8 @@ SHAPES = {
     "wide_dense": RI.TINY_DENSE.replace(d_model=528, d_ff=2064, vocab=2056, n_q_heads=8, n_kv_heads=1, qk_norm=True),
     "tiny_moe": RI.TINY_MOE.replace(n_experts=24, vocab=2056),
 }
-# tokens of every sequence: just past the limit, around the 64- and 128-token tiles, a few hundred ragged ones
-LENGTHS = {"257": [257], "320": [64, 1, 255], "385": [129, 256], "ragged": [256, 31, 200, 97, 1, 250, 255, 118]}
+# tokens of every sequence: just past the limits, around the 64- and 128-token tiles, a few hundred ragged ones
+LENGTHS = {"129": [129], "130": [2, 128], "257": [257], "320": [64, 1, 255], "385": [129, 256], "ragged": [256, 31, 200, 97, 1, 250, 255, 118]}
 
 
 @pytest.mark.parametrize("lengths", sorted(LENGTHS))
@@ -47,9 +48,9 @@ def test_long_calls_equal_the_same_tokens_in_short_calls(name, lengths):
     offs = np.concatenate([[0], np.cumsum(lens)])
     logits, lp_short = [], []
     scorer = engine()
-    for i in rows:                               # one sequence per call: at most 256 tokens, or 200 and then the rest
-        cuts = [0, len(toks[i])] if len(toks[i]) <= 256 else [0, 200, len(toks[i])]
-        for a, b in zip(cuts, cuts[1:]):
+    for i in rows:                               # one sequence per call, at most 64 tokens at a time
+        for a in range(0, len(toks[i]), 64):
+            b = min(a + 64, len(toks[i]))
             o = short_eng.prefill([i], [toks[i][a:b]], want_logits=True)
             scored, _ = scorer.score([i], [toks[i][a:b]], [np.roll(toks[i], -1)[a:b]],
                                      replay_routing=None if replay is None else [replay[offs[i] + a:offs[i] + b]])
