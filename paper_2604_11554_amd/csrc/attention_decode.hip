@@ -34,16 +34,12 @@
 namespace rlx {
 namespace {
 
-
 template <int HD>
 struct PageRegs {
   h16x8 k0[HD / 32], k1[HD / 32], vf[HD / 16];
   bool ok0, ok1;
 };
 
-// A run: up to 64 consecutive units of one (sequence, KV head) inside this workgroup's share (64 units = one
-// register window of the block table).  A segment -- the part of a pair that lies in the share -- is one or
-// more runs; the online softmax state lives across the runs of a segment.  All fields are wave-uniform.
 // Views into the shared-prefix descriptor (kernels.h); `on` is false when there is none or it was built for
 // another batch size, and every index read from it is clamped by its user.
 struct SharedView {
@@ -78,6 +74,9 @@ struct Shares {
 };
 __device__ __forceinline__ Shares load_shares(const int32_t* hdr) { return Shares{hdr[0], hdr[2], hdr[3], hdr[1]}; }
 
+// A run: up to 64 consecutive units of one (sequence, KV head) inside a share (64 units = one register window of the
+// block table).  A segment -- the part of a pair that lies in the share -- is one or more runs; the online softmax state
+// lives across the runs of a segment.  All fields are wave-uniform.
 struct Run {
   int seq, kvh, ctx, np;     // np: units of the whole pair, counted from unit u0 of the sequence
   int u0;                    // units before this pair's first one (served by prefix tiles)

@@ -6,7 +6,7 @@
 namespace rlx {
 
 struct GemmArgs {
-  const h16_t* x;        // fragment-ordered activations [T_x, K], `PL` planes
+  const h16_t* x;        // activations [T_x, K]: `PL` terms in fragment order, or rows of two (x_pitch)
   int x_mtiles;           // ceil(T_x / 32)
   const float* x_ss;      // optional: activation row t lacks the factor rstd(t) of its norm (Act::ss); outputs take it
   float x_eps;
@@ -17,7 +17,7 @@ struct GemmArgs {
   int ksteps_per_split;   // k-steps (16 wide) per blockIdx.y
   float* y;               // EPI_STORE: [splits][T][ldy]
   int ldy;
-  h16_t* act;            // EPI_SWIGLU: fragment-ordered [act_rows, N], `PL` planes
+  h16_t* act;            // EPI_SWIGLU: [act_rows, N / 2], like x (act_pitch)
   int act_mtiles;
   // LM-head epilogue
   float* logits;          // optional [T][N]
@@ -76,8 +76,6 @@ __device__ __forceinline__ float gumbel_from_u32(uint32_t r) {
   return __builtin_amdgcn_logf(nl) * -LN2;
 }
 
-// Epilogue of one 32-row weight tile `nt` over token tiles mt0 .. mt0 + MT - 1: lane holds token r32 of each token
-// tile, rows n0 + 8q + 4*half + {0..3}, q = 0..3, of the accumulators.
 // factor that the norm left out of activation row `tok` (Act::ss): the same expression as in the norm kernel
 __device__ __forceinline__ f32x4 row_ss(const GemmArgs& a, int tok) {
   return *reinterpret_cast<const f32x4*>(a.x_ss + (size_t)NORM_PARTS * tok);
@@ -86,6 +84,8 @@ __device__ __forceinline__ float row_rstd(const GemmArgs& a, const f32x4& p) {
   return 1.0f / sqrtf(((p[0] + p[1]) + (p[2] + p[3])) / (float)a.K + a.x_eps);
 }
 
+// Epilogue of one 32-row weight tile `nt` over token tiles mt0 .. mt0 + MT - 1: lane holds token r32 of each token
+// tile, rows n0 + 8q + 4*half + {0..3}, q = 0..3, of the accumulators.
 // rs[m]: factor of the lane's activation row in token tile m (row_rstd, or 1), fetched by the caller before its main
 // loop so that the round trip is not spent at the end of the kernel
 template <int MT, int EPI, int PL, int FMT>
