@@ -73,3 +73,33 @@ def test_pairs_that_are_exactly_a_workgroup(keys, head_dim):
     assert np.isfinite(logits[0]).all()
     assert max(np.abs(z - logits[0]).max() for z in logits[1:]) < 5e-3
     model.close()
+
+
+@pytest.mark.parametrize("shape", ["tiny_dense", "tiny_moe"])
+def test_groups_of_equal_own_length_on_any_grid(shape):
+    """Members of a sampling group whose own keys are equally many: the grid decides whether a pair lies in one share (its
+    own part then goes beside the prefix chunks) or in several.  Every grid equals plain attention without the descriptor."""
+    import paper_2604_11554_amd as pkg
+    from paper_2604_11554_amd import synthetic
+
+    s = {"tiny_dense": RI.TINY_DENSE, "tiny_moe": RI.TINY_MOE}[shape]
+    model = synthetic.model_from_shape(s, 3)
+    rng = np.random.default_rng(8)
+    prompt = rng.integers(0, s.vocab - 2, 200).astype(np.int32)
+    own = [rng.integers(0, s.vocab - 2, 130).astype(np.int32) for _ in range(3)]
+    logits = []
+    for grid, share in ((512, False), (1, True), (3, True), (3 * s.n_kv_heads, True), (12 * s.n_kv_heads, True), (512, True)):
+        model.set_attention_grid(grid)
+        eng = pkg.RolloutEngine(model, n_blocks=120, max_seqs=3, max_chunk_tokens=512, max_blocks_per_seq=24)
+        eng.share_prefix_attention = share
+        lead = eng.add_sequence(1, reserve_tokens=340)
+        eng.prefill([lead], [prompt], sample_last=[False])
+        rows = [lead] + [eng.fork(lead, 2 + i, reserve_tokens=340) for i in range(2)]
+        eng.prefill(rows, own, forced=[5] * 3)
+        out = eng.decode_step(forced=torch.full((3,), 7, dtype=torch.int32, device="cuda"), want_logits=True)
+        logits.append(out.logits.cpu().numpy())
+    # one step's sums in another grouping, as above
+    assert np.isfinite(logits[0]).all()
+    assert max(np.abs(z - logits[0]).max() for z in logits[1:]) < 5e-3
+    assert any(not np.array_equal(z, logits[0]) for z in logits[1:])     # the descriptor was used
+    model.close()

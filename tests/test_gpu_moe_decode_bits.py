@@ -25,6 +25,8 @@ CASES = {
     "pairs_are_shares": (TWO_KV, "bf16", [150] * 6, 1, 12),     # as many workgroups as pairs of equal length
     "few_shares": (RI.TINY_MOE, "bf16", [40, 350, 3, 900], 1, 3),
     "many_rows": (RI.TINY_MOE, "bf16", [1 + 7 * (i % 13) for i in range(70)], 1, 0),
+    "rows_200": (RI.TINY_MOE, "bf16", [1 + i % 40 for i in range(200)], 1, 0),   # GEMMs of 129 to 256 tokens
+    "rows_300": (TWO_KV, "bf16", [1 + i % 40 for i in range(300)], 1, 0),        # ... and of more: activations in rows
     "groups": (RI.TINY_MOE, "bf16", [75, 300, 20], 3, 0),
 }
 STEPS = 4
