@@ -297,11 +297,15 @@ int run_layers(const rlx_model* m, h16_t* pool, int64_t n_blocks, const Workspac
   // in short calls; logits of 256 rows, four layers: 2.5e-5 of their norm off a 64-bit computation with two, 2.3e-5 with
   // four and in the short form; eight layers, 129 rows: 1500 -> 1520 us a step, 256 rows 1910 both).
   const bool fine_qkv = T <= 256;
+  // dense policies only: MoE decode keeps its sums in the order that its routing was recorded with
+  const bool flow = small && c.n_experts == 0 && gemm_flow_store_form(T, PL, FMT);
   auto planes_of = [&](int N, int K, bool wide) {
+    if (flow) return gemm_flow_splits(N, K, T, gemm_max_splits(), m->n_units, PL);
     if (small) return gemm_plan_splits(N, K, T, gemm_max_splits(), m->n_units, PL, FMT);
     return lng ? gemm_long_splits(N, K, T, long_planes(c, T, wide, io.lean), m->n_units, wide && fine_qkv) : 1;
   };
   auto store = [&](const LinearW& lw, const Act& x, float* y, int splits, bool wide) {
+    if (flow) return gemm_flow_store(lw, x, T, y, lw.N, gemm_max_splits(), m->n_units, st);
     return lng ? gemm_long_store(lw, x, T, y, lw.N, long_planes(c, T, wide, io.lean), m->n_units, wide && fine_qkv, st)
                : gemm_store(lw, x, T, y, lw.N, splits, st);
   };
@@ -365,6 +369,8 @@ int run_layers(const rlx_model* m, h16_t* pool, int64_t n_blocks, const Workspac
     if (c.n_experts == 0) {
       const Act act = call_act(c, w.act, T, c.d_ff, lng);
       RLX_LAUNCH(RLX_K_GATEUP, lng ? gemm_long_swiglu(m->w_gate_up[l], c.d_ff, d, xb, T, act, m->n_units, st)
+                               : gemm_flow_swiglu_form(c.d_ff, T, m->n_units, PL, FMT)
+                                   ? gemm_flow_swiglu(m->w_gate_up[l], c.d_ff, d, xb, T, act, m->n_units, st)
                                    : gemm_swiglu(m->w_gate_up[l], c.d_ff, d, xb, T, act, st));
       const int s_d = planes_of(d, c.d_ff, false);
       RLX_LAUNCH(RLX_K_DOWN, store(linear1(m->w_down[l], d, c.d_ff), act, w.planes, s_d, false));

@@ -1,0 +1,311 @@
+// GEMM of short calls of dense policies (decode steps, chunks of up to 128 tokens): a wave walks its own part of K alone.
+//
+//   y[t, n] = sum_k x[t, k] * W[n, k]        fp32 accumulate
+//
+// A workgroup of four waves owns RT tiles of 16 weight rows and all NT tiles of 16 tokens over its K range, and deals the k-steps
+// (32 wide, MFMA 16x16x32) to its waves in turn.  A wave loads the weight and activation fragments of its steps from global
+// memory straight into registers, D steps ahead: every byte enters the compute unit once, nothing passes through LDS and no
+// barrier couples the waves while they stream.  At the end their sums are added through LDS in wave order.
+// What bounds it: with one token tile the weights at the card's rate, with many the ~45 bytes/ns that a compute unit takes in,
+// weights and activations together, so the tile is chosen for equal bytes on every unit: 16-row tiles cut the 4B shape's gate/up
+// into 244 workgroups of 80 rows where 32-row tiles left 152 of 128 rows.  Two steps ahead are enough (four waves x 13 KB), and
+// more were slower everywhere but in the smallest form (us at 45 tokens, D = 2 / 3 / 4: gate/up 22.5 / 23.0 / 22.9, down
+// 12.8 / 14.1 / 14.3, o 7.7 / 8.1 / 8.5); eight waves with D = 1 or 2 the same or slower.
+// us per launch at the 4B shape, the skinny form -> this one (bf16 in two terms, weights from memory):
+//   tokens          1             45            64            96            128
+//   gate/up   24.2 -> 17.7  29.7 -> 22.6  32.0 -> 25.4  53.1 -> 31.6  54.8 -> 38.0
+//   q|k|v      9.8 ->  7.5  10.9 -> 10.4  11.5 -> 11.9  17.5 -> 15.4  (17.9 -> 19.2)   with two fifths fewer planes
+//   o          7.1 ->  5.7   9.3 ->  7.7   9.8 ->  8.6  12.8 -> 11.2  (13.4 -> 14.0)
+//   down      12.7 ->  9.8  15.4 -> 12.8  15.8 -> 14.5  24.5 -> 19.1  (25.2 -> 23.4)
+#include <mutex>
+
+#include "gemm_core.h"
+
+namespace rlx {
+namespace {
+
+constexpr int FLOW_WAVES = 4;
+constexpr int FLOW_RT_MANY = 5;                      // row tiles per workgroup at most beside more than four token tiles (registers)
+
+template <int RT, int NT, int PL>
+struct FlowTiling {
+  static constexpr int TILES = RT * NT, LOADS = RT + NT * PL;
+  static constexpr int D = LOADS <= 4 ? 4 : 2;                             // steps loaded ahead
+  static constexpr int NR = TILES <= 32 ? FLOW_WAVES : FLOW_WAVES / 2;     // waves whose sums are in LDS at a time
+  static constexpr int LDS_BYTES = TILES * NR * 1024 + 16 * NT * 4;
+};
+
+// Loads by buffer descriptor: uniform base, uniform offset of the step, 32-bit lane offset.  A lane whose offset lies past the
+// descriptor's end reads zeros and touches no memory, which serves steps past the end, the missing half of an odd last step
+// and token rows past the last one.
+constexpr uint32_t NOWHERE = 0x80000000u;            // past the end of every descriptor
+typedef __amdgpu_buffer_rsrc_t Desc;
+__device__ __forceinline__ Desc make_desc(const void* p, uint32_t bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, (int)bytes, 0x00027000);
+}
+template <int AUX>
+__device__ __forceinline__ u32x4 desc_load(Desc d, uint32_t lane, uint32_t step) {
+  return __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(d, (int)lane, (int)step, AUX));
+}
+
+template <int RT, int NT, int PL, int FMT, int EPI>
+__global__ __launch_bounds__(64 * FLOW_WAVES, 1) void gemm_flow_kernel(GemmArgs a) {
+  using TL = FlowTiling<RT, NT, PL>;
+  constexpr int D = TL::D, NW = FLOW_WAVES, NR = TL::NR, NONTEMPORAL = 2;
+  extern __shared__ __align__(16) unsigned char lds_raw[];
+  f32x4* red = reinterpret_cast<f32x4*>(lds_raw);    // [tile][NR][lane]
+  float* rs_lds = reinterpret_cast<float*>(lds_raw + TL::TILES * NR * 1024);
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int c16 = lane & 15, kg = lane >> 4;
+  const int split = blockIdx.y;
+  const int KS = a.K >> 4, n_half = ((a.N + 31) >> 5) * 2;   // 16-wide k-steps; row tiles
+  const int ht0 = blockIdx.x * RT;
+
+  // ---- this wave's steps: s_b + wave, + 4, ... below s_e; an odd last 16 k is a step whose second half is missing ----
+  const int s_b = split * a.ksteps_per_split, s_e = min(s_b + a.ksteps_per_split, (KS + 1) >> 1);
+  const int n = (s_e - s_b - wave + NW - 1) / NW;    // may be 0
+
+  // ---- addresses ----
+  Desc wd[RT];
+#pragma unroll
+  for (int r = 0; r < RT; ++r) {
+    const int ht = min(ht0 + r, n_half - 1);         // a row tile past the end repeats the last one and is never stored
+    int lt = ht >> 1;
+    const h16_t* base = a.w[0];
+    if (lt >= a.w_tiles[0]) {
+      lt -= a.w_tiles[0];
+      base = a.w[1];
+      if (lt >= a.w_tiles[1]) { lt -= a.w_tiles[1]; base = a.w[2]; }
+    }
+    wd[r] = make_desc(base + packed_tile_offset(lt, KS) + (EPI == EPI_SWIGLU ? 8 : 16) * (ht & 1) * 8, NOWHERE - 1);
+  }
+  const Desc xd = make_desc(a.x, NOWHERE - 1);
+  // row of the tile that the lane holds: 16 consecutive ones, or eight gate rows and the eight up rows that go with them
+  const int wrow = EPI == EPI_SWIGLU ? c16 + (c16 & 8) : c16;
+  const uint32_t x_kstride = (uint32_t)a.x_mtiles * PL * 1024;           // bytes of 16 k of the activations
+  const uint32_t w_lane = (uint32_t)(wrow + 32 * (kg & 1)) * 16 + (uint32_t)(kg >> 1) * (W_KSTRIDE * 2);
+  uint32_t x_lane[NT];
+#pragma unroll
+  for (int t = 0; t < NT; ++t) {
+    const int tok = 16 * t + c16;
+    x_lane[t] = (uint32_t)(tok >> 5) * (PL * 1024) + (uint32_t)((tok & 31) + 32 * (kg & 1)) * 16 + (uint32_t)(kg >> 1) * x_kstride;
+    if (tok >= a.T) x_lane[t] = NOWHERE;
+  }
+  // the rows' factors (Act::ss) are requested first of all and settled behind the first steps' loads
+  f32x4 ssq = {1.f, 1.f, 1.f, 1.f};
+  const bool scaled = a.x_ss != nullptr;
+  if (scaled) ssq = row_ss(a, min((int)threadIdx.x, a.T - 1));
+  __builtin_amdgcn_sched_barrier(0);
+
+  struct Step { u32x4 w[RT], x[NT * PL]; };
+  auto load = [&](int i, Step& d) {
+    const int s = s_b + wave + NW * i;
+    const uint32_t gone = (s >= s_e || (2 * s + 1 >= KS && kg >= 2)) ? NOWHERE : 0u;
+    const uint32_t ws = (uint32_t)s * (2 * W_KSTRIDE * 2), xs = (uint32_t)s * 2 * x_kstride;
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+      for (int p = 0; p < PL; ++p) d.x[t * PL + p] = desc_load<0>(xd, x_lane[t] | gone, xs + p * 1024);
+#pragma unroll
+    for (int r = 0; r < RT; ++r) d.w[r] = desc_load<NONTEMPORAL>(wd[r], w_lane | gone, ws);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  f32x4 acc[RT][NT];
+#pragma unroll
+  for (int r = 0; r < RT; ++r)
+#pragma unroll
+    for (int t = 0; t < NT; ++t) acc[r][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+  Step st[D];
+#pragma unroll
+  for (int d = 0; d < D; ++d) load(d, st[d]);
+  float rstd = 1.f;
+  if (scaled) rstd = row_rstd(a, ssq);
+  asm volatile("" : "+v"(rstd));
+  __builtin_amdgcn_sched_barrier(0);
+  for (int i = 0; i < n; i += D)
+#pragma unroll
+    for (int d = 0; d < D; ++d) {
+#pragma unroll
+      for (int p = PL - 1; p >= 0; --p)              // small term first
+#pragma unroll
+        for (int r = 0; r < RT; ++r)
+#pragma unroll
+          for (int t = 0; t < NT; ++t) acc[r][t] = mfma_16x16x32<FMT>(st[d].w[r], st[d].x[t * PL + p], acc[r][t]);
+      __builtin_amdgcn_sched_barrier(0);
+      load(i + D + d, st[d]);
+    }
+
+  // ---- the waves' sums, tile by tile in wave order ----
+  if (scaled && (int)threadIdx.x < 16 * NT) rs_lds[threadIdx.x] = rstd;
+  auto put = [&]() {
+#pragma unroll
+    for (int r = 0; r < RT; ++r)
+#pragma unroll
+      for (int t = 0; t < NT; ++t) red[((r * NT + t) * NR + (wave % NR)) * WAVE + lane] = acc[r][t];
+  };
+  if (NR < NW) {                                     // LDS holds half: the upper waves hand their sums to the lower ones first
+    if (wave >= NR) put();
+    __syncthreads();
+    if (wave < NR) {
+#pragma unroll
+      for (int r = 0; r < RT; ++r)
+#pragma unroll
+        for (int t = 0; t < NT; ++t) acc[r][t] += red[((r * NT + t) * NR + wave) * WAVE + lane];
+      put();
+    }
+  } else {
+    put();
+  }
+  __syncthreads();
+  for (int tile = wave; tile < TL::TILES; tile += NW) {
+    f32x4 v = red[tile * NR * WAVE + lane];
+#pragma unroll
+    for (int w = 1; w < NR; ++w) v += red[(tile * NR + w) * WAVE + lane];
+    const int ht = ht0 + tile / NT, t = 16 * (tile % NT) + c16;
+    if (scaled) v *= rs_lds[16 * (tile % NT) + c16];
+    if (ht >= n_half) continue;
+    if (EPI == EPI_STORE) {
+      const int nrow = 16 * ht + 4 * kg;
+      float* dst = a.y + ((size_t)split * a.T + t) * a.ldy + nrow;
+      if (t < a.T) {
+        if (nrow + 3 < a.N) {
+          *reinterpret_cast<f32x4*>(dst) = v;
+        } else {
+#pragma unroll
+          for (int j = 0; j < 4; ++j)
+            if (nrow + j < a.N) dst[j] = v[j];
+        }
+      }
+    } else {
+      // lanes 0..31 hold gate rows 4 (kg & 1) + {0..3}, lanes 32..63 the up rows of the same features: the halves trade, so
+      // that the lower lanes hold both of features 0 and 1 of the four and the upper lanes both of features 2 and 3
+      const auto e0 = __builtin_amdgcn_permlane32_swap(__float_as_uint(v[0]), __float_as_uint(v[2]), false, false);
+      const auto e1 = __builtin_amdgcn_permlane32_swap(__float_as_uint(v[1]), __float_as_uint(v[3]), false, false);
+      const float g0 = __uint_as_float(e0[0]), u0 = __uint_as_float(e0[1]);
+      const float g1 = __uint_as_float(e1[0]), u1 = __uint_as_float(e1[1]);
+      uint32_t hi, lo = 0;
+      split_pair<FMT, PL>(g0 / (1.f + __expf(-g0)) * u0, g1 / (1.f + __expf(-g1)) * u1, hi, lo);
+      if (t < a.T && 8 * ht < (a.N >> 1)) {
+        h16_t* dst = a.act + frag_act_offset(t, 8 * ht, 0, a.act_mtiles, PL) + 4 * (kg & 1) + 2 * (kg >> 1);
+        *reinterpret_cast<uint32_t*>(dst) = hi;
+        if (PL == 2) *reinterpret_cast<uint32_t*>(dst + 512) = lo;
+      }
+    }
+  }
+}
+
+template <int RT, int NT, int PL, int FMT, int EPI>
+void launch_flow_one(const GemmArgs& a, dim3 grid, hipStream_t st) {
+  static std::once_flag attr_once;                   // raise the dynamic LDS limit once per instantiation, from any thread
+  constexpr int lds = FlowTiling<RT, NT, PL>::LDS_BYTES;
+  std::call_once(attr_once, [] {
+    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_flow_kernel<RT, NT, PL, FMT, EPI>),
+                              hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+  });
+  hipLaunchKernelGGL((gemm_flow_kernel<RT, NT, PL, FMT, EPI>), grid, dim3(64 * FLOW_WAVES), lds, st, a);
+}
+template <int RT, int NT, int EPI>
+void launch_flow_fmt(const GemmArgs& a, dim3 grid, const Act& x, hipStream_t st) {
+  if (x.dtype == DT_F16) launch_flow_one<RT, NT, 1, DT_F16, EPI>(a, grid, st);
+  else launch_flow_one<RT, NT, 2, DT_BF16, EPI>(a, grid, st);
+}
+template <int RT, int EPI>
+void launch_flow(const GemmArgs& a, int splits, const Act& x, hipStream_t st) {
+  const dim3 grid((((a.N + 31) / 32) * 2 + RT - 1) / RT, splits);
+  if (a.T <= 16) launch_flow_fmt<RT, 1, EPI>(a, grid, x, st);
+  else if (a.T <= 32) launch_flow_fmt<RT, 2, EPI>(a, grid, x, st);
+  else if (a.T <= 48) launch_flow_fmt<RT, 3, EPI>(a, grid, x, st);
+  else if (a.T <= 64) launch_flow_fmt<RT, 4, EPI>(a, grid, x, st);
+  else if constexpr (RT <= FLOW_RT_MANY) {
+    if (a.T <= 96) launch_flow_fmt<RT, 6, EPI>(a, grid, x, st);
+    else if (EPI == EPI_SWIGLU || x.planes == 1) launch_flow_fmt<RT, 8, EPI>(a, grid, x, st);
+  }
+}
+
+GemmArgs flow_args(const Act& x, int N, int K, int T, int splits) {
+  GemmArgs a = {};
+  a.x = x.p; a.x_mtiles = x.mtiles(); a.x_ss = x.ss; a.x_eps = x.eps;
+  a.N = N; a.K = K; a.T = T;
+  a.ksteps_per_split = ((K / 16 + 1) / 2 + splits - 1) / splits;         // 32-wide steps
+  return a;
+}
+bool flow_format(int planes, int dtype) { return (dtype == DT_BF16 && planes == 2) || (dtype == DT_F16 && planes == 1); }
+
+// ---- store form: row tiles per workgroup and planes of K ----
+// The grid is one workgroup per compute unit at most, so the time is that of one of them: what it takes in at 45 bytes/ns, its
+// weights alone at 32 (or all of them at the card's 6.6 TB/s), its tiles' sums through LDS, and the planes that it and the kernel
+// behind it write and read.  The constants (us) were fitted to a sweep of the 4B shape's products at 1 to 128 tokens; there the
+// choice is within 4 % of the best one, or takes half the planes.
+struct FlowPlan { int rt, splits; };
+constexpr int FLOW_RT[] = {2, 4, 5, 8};
+FlowPlan plan_flow(int N, int K, int T, int max_splits, int n_units, int planes) {
+  const int row_tiles = (N + 31) / 32 * 2, steps = (K / 16 + 1) / 2;
+  const float all = (float)N * (float)K * 2.f / 6.6e6f;
+  FlowPlan best = {2, 1};
+  float best_us = 1e30f;
+  for (int rt : FLOW_RT) {
+    if (T > 64 && rt > FLOW_RT_MANY) continue;
+    const int groups = (row_tiles + rt - 1) / rt;
+    for (int s = 1; s <= max_splits; ++s) {
+      const int per = (steps + s - 1) / s;
+      if (s > 1 && ((s - 1) * per >= steps || per < FLOW_WAVES)) continue;   // no empty split, a step for every wave
+      const float rounds = (float)((groups * s + n_units - 1) / n_units);
+      const float kb = (float)((per + FLOW_WAVES - 1) / FLOW_WAVES * FLOW_WAVES) * 1.024f;   // of a row tile, or of a token tile and term
+      float us = rounds * kb * ((float)rt + (float)(planes * T) / 16.f) / 45.f;
+      const float weights = rounds * kb * (float)rt / 32.f;
+      if (us < weights) us = weights;
+      if (us < all) us = all;
+      us += rounds * 0.12f * (float)(rt * ((T + 15) / 16)) + (float)s * (0.12f + 1e-6f * (float)T * (float)N);
+      if (us < best_us) { best_us = us; best = {rt, s}; }
+    }
+  }
+  return best;
+}
+
+// SwiGLU form (K whole): the fewest row tiles per workgroup that keep the grid within one workgroup per unit (4B shape, 64 tokens:
+// 5 row tiles, 244 workgroups 25.4 us; 8, 152 30.9; 4, 304 38.4); 0: none does
+constexpr int FLOW_SWIGLU_RT[] = {2, 4, 5, 6, 8};
+int flow_swiglu_rt(int F, int T, int n_units) {
+  for (int rt : FLOW_SWIGLU_RT)
+    if ((F / 8 + rt - 1) / rt <= n_units) return T > 64 && rt > FLOW_RT_MANY ? 0 : rt;
+  return 0;
+}
+
+}  // namespace
+
+// stores of two terms: up to 96 tokens (the table above; at 97 to 128 the skinny form's two groups of 64 are as fast or faster)
+bool gemm_flow_store_form(int T, int planes, int dtype) { return flow_format(planes, dtype) && T <= (planes == 2 ? 96 : 128); }
+int gemm_flow_splits(int N, int K, int T, int max_splits, int n_units, int planes) {
+  return plan_flow(N, K, T, max_splits, n_units, planes).splits;
+}
+hipError_t gemm_flow_store(const LinearW& w, const Act& x, int T, float* y, int ldy, int max_splits, int n_units, hipStream_t st) {
+  if (!gemm_flow_store_form(T, x.planes, x.dtype) || x.pitch) return hipErrorInvalidValue;
+  const FlowPlan plan = plan_flow(w.N, w.K, T, max_splits, n_units, x.planes);
+  GemmArgs a = flow_args(x, w.N, w.K, T, plan.splits);
+  for (int i = 0; i < 3; ++i) { a.w[i] = w.seg[i]; a.w_tiles[i] = (w.rows[i] + 31) / 32; }
+  a.y = y; a.ldy = ldy;
+  if (plan.rt == 2) launch_flow<2, EPI_STORE>(a, plan.splits, x, st);
+  else if (plan.rt == 4) launch_flow<4, EPI_STORE>(a, plan.splits, x, st);
+  else if (plan.rt == 5) launch_flow<5, EPI_STORE>(a, plan.splits, x, st);
+  else launch_flow<8, EPI_STORE>(a, plan.splits, x, st);
+  return hipGetLastError();
+}
+
+bool gemm_flow_swiglu_form(int F, int T, int n_units, int planes, int dtype) {
+  return flow_format(planes, dtype) && T <= 128 && flow_swiglu_rt(F, T, n_units) > 0;
+}
+hipError_t gemm_flow_swiglu(const h16_t* w_gate_up, int F, int K, const Act& x, int T, const Act& act, int n_units, hipStream_t st) {
+  if (!gemm_flow_swiglu_form(F, T, n_units, x.planes, x.dtype) || x.pitch || act.pitch) return hipErrorInvalidValue;
+  GemmArgs a = flow_args(x, 2 * F, K, T, 1);
+  a.w[0] = w_gate_up; a.w_tiles[0] = F / 16;
+  a.act = act.p; a.act_mtiles = act.mtiles();
+  const int rt = flow_swiglu_rt(F, T, n_units);
+  if (rt == 2) launch_flow<2, EPI_SWIGLU>(a, 1, x, st);
+  else if (rt == 4) launch_flow<4, EPI_SWIGLU>(a, 1, x, st);
+  else if (rt == 5) launch_flow<5, EPI_SWIGLU>(a, 1, x, st);
+  else if (rt == 6) launch_flow<6, EPI_SWIGLU>(a, 1, x, st);
+  else launch_flow<8, EPI_SWIGLU>(a, 1, x, st);
+  return hipGetLastError();
+}
+
+}  // namespace rlx

@@ -95,6 +95,15 @@ hipError_t gemm_routed_swiglu(const h16_t* w_gate_up, int E, int F, int K, const
                               int n_pairs, int top_k, int max_rows, const Act& act, int32_t* group_off,
                               int32_t* pair_pos, hipStream_t st);
 
+// ---- gemm_flow.hip: the same products for short calls of dense policies (activations in fragment order), on bf16 as two terms
+// or fp16 as one ----
+// y[split][t][n] in gemm_flow_splits() planes, at most max_splits
+bool gemm_flow_store_form(int T, int planes, int dtype);   // whether the form is built, and the faster one, for T tokens
+int gemm_flow_splits(int N, int K, int T, int max_splits, int n_units, int planes);
+hipError_t gemm_flow_store(const LinearW& w, const Act& x, int T, float* y, int ldy, int max_splits, int n_units, hipStream_t st);
+bool gemm_flow_swiglu_form(int F, int T, int n_units, int planes, int dtype);
+hipError_t gemm_flow_swiglu(const h16_t* w_gate_up, int F, int K, const Act& x, int T, const Act& act, int n_units, hipStream_t st);
+
 // ---- gemm_long.hip: the same products for long calls on two-term bf16 activations in rows (Act::pitch) ----
 enum { LONG_512x128 = 0, LONG_128x128, LONG_512x64 };   // weight rows x tokens of a workgroup
 // y[split][t][n]: K cut into gemm_long_splits() planes, at most max_splits: the fastest number, or the largest (`finest`)

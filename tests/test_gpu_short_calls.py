@@ -1,0 +1,45 @@
+"""Products of short calls of dense policies: calls of up to 128 tokens deal K to the waves of a workgroup in 32-wide steps, on
+16-row weight tiles and 16-token tiles.  One-token sequences at the edges of the token tiles go through one layer whose widths
+reach every weight tiling of gate/up (F / 8 row tiles on 256 units: 2, 4, 5, 6 and 8 per workgroup, and the 32-row form past
+that) and K with an odd number of 16-wide steps, against the oracle on the same weights."""
+import numpy as np
+import pytest
+
+import oracle as O
+import rollout_inputs as RI
+
+pytestmark = pytest.mark.gpu
+
+TOKENS = (1, 15, 16, 17, 32, 33, 48, 49, 64, 65, 96, 97, 128)
+# Largest difference over the logits' root mean square, of nine rows in ten and of every row.  bf16 in two terms keeps 16 bits:
+# 2^-17 / sqrt(3) per product, four products in a row, 4.5 sigma: 4e-5.  A row whose cached value got the neighbouring code of an
+# element of 3 sigma moves by 2^-8 * 3 / sqrt(256) of its attention's part, times 4.5 sigma: 3.3e-3.  One fp16 term is
+# 2^-12 / sqrt(3) off: 1.3e-3, and its codes 2^-11.  Twice to four times that.
+BAR = {"bf16": (1e-4, 7e-3), "f16": (5e-3, 1e-2)}
+
+
+@pytest.mark.parametrize("fmt", ["bf16", "f16"])
+@pytest.mark.parametrize("d_model,d_ff", [(256, 688), (80, 4112), (528, 8208), (80, 9728), (80, 10256), (80, 12304), (80, 16400)])
+def test_short_calls_match_the_oracle(d_model, d_ff, fmt):
+    import paper_2604_11554_amd as pkg
+    from paper_2604_11554_amd import synthetic
+
+    s = RI.TINY_DENSE.replace(n_layers=1, d_model=d_model, d_ff=d_ff, vocab=264, qk_norm=True)
+    kw = dict(fmt="f16", activation_split=0) if fmt == "f16" else {}
+    model = synthetic.model_from_shape(s, 0, **kw)
+    toks = np.random.default_rng(d_ff).integers(0, s.vocab - 2, TOKENS[-1]).astype(np.int32)
+    want = O.forward_full(O.OracleModel(s, 0, fmt=fmt), [toks[i:i + 1] for i in range(len(toks))])
+    want = np.stack([w["logits"][-1] for w in want])
+    rms = np.sqrt((want * want).mean())
+    eng = pkg.RolloutEngine(model, n_blocks=len(toks), max_seqs=len(toks), max_chunk_tokens=len(toks), max_blocks_per_seq=1)
+    for i in range(len(toks)):
+        eng.add_sequence(i, reserve_tokens=16)
+    worst = {}
+    for n in TOKENS:
+        eng.ctx_lens.zero_()
+        out = eng.prefill(list(range(n)), [toks[i:i + 1] for i in range(n)], want_logits=True)
+        rows = np.sort(np.abs(out.logits[:n].cpu().numpy() - want[:n]).max(axis=1) / rms)
+        worst[n] = float(rows[int(0.9 * (n - 1))]), float(rows[-1])
+        print("d_model %d d_ff %d %s, %d tokens: %.2e %.2e" % (d_model, d_ff, fmt, n, *worst[n]), flush=True)
+    model.close()
+    assert all(w[0] <= BAR[fmt][0] and w[1] <= BAR[fmt][1] for w in worst.values()), worst
