@@ -284,8 +284,7 @@ int run_layers(const rlx_model* m, h16_t* pool, int64_t n_blocks, const Workspac
   // residual contribution produced by the previous sub-layer, folded into the next norm
   const float* pend_planes = nullptr; int pend_n = 0; bool pend_moe = false;
   // MoE decode batches: the gate/up GEMM reads the routing table itself and publishes the grouping (no grouping launch)
-  const int rows_per_expert = c.n_experts ? (int)(((long long)T * c.top_k + c.n_experts - 1) / c.n_experts) : 0;
-  const bool routed = c.n_experts && small && gemm_routed_form(c.n_experts, c.d_ff_expert, xb, T * c.top_k, rows_per_expert);
+  const bool routed = c.n_experts && small && gemm_routed_form(c.n_experts, xb, T * c.top_k);
   // calls of up to 256 tokens: the norm runs as four workgroups per row (256 rows of 2560: 6.4 us; in one 8.9) and leaves
   // the row's common factor to the GEMMs that read xb (q|k|v, gate/up, router), which also keeps rows that two bf16 terms
   // hold exactly (embeddings) exact; not for fp16 (unnormalised rows would strain its range) and not where the grouped
@@ -393,12 +392,12 @@ int run_layers(const rlx_model* m, h16_t* pool, int64_t n_blocks, const Workspac
                                                     T * c.top_k, c.top_k, T, act, w.group_off, w.pair_pos, st));
       else
         RLX_LAUNCH(RLX_K_GATEUP, gemm_grouped_swiglu(m->w_gate_up[l], c.n_experts, c.d_ff_expert, d, xb,
-                                                     w.sorted_token, w.group_off, T, rows_per_expert, act, st));
+                                                     w.sorted_token, w.group_off, T, T * c.top_k, act, st));
       if (lng)
         RLX_LAUNCH(RLX_K_DOWN, gemm_long_grouped_store(m->w_down[l], d, c.d_ff_expert, act, w.group_off, w.moe_y, w.items, st));
       else
         RLX_LAUNCH(RLX_K_DOWN, gemm_grouped_store(m->w_down[l], c.n_experts, d, c.d_ff_expert, act, w.group_off, T,
-                                                  rows_per_expert, w.moe_y, st));
+                                                  T * c.top_k, w.moe_y, st));
       pend_moe = true;
     }
   }

@@ -16,6 +16,8 @@
 //
 // Epilogues: plain store (q|k|v, o and down projections, expert down projection),
 // SwiGLU (gate/up), LM head with fused log-sum-exp and Gumbel-max partials per 32-row tile.
+#include <math.h>
+
 #include <atomic>
 #include <mutex>
 
@@ -287,7 +289,7 @@ __global__ __launch_bounds__(GEMM_THREADS, 2) void gemm_skinny_kernel(GemmArgs a
 // (Four groups per workgroup leave registers for 4 KB batches only, which was measured slower than one group.)
 template <int J>
 struct ExpertTiling {
-  static constexpr int KC = 16, U = 8, NBC = KC / U;
+  static constexpr int KC = 16, U = J == 1 ? 4 : 8, NBC = KC / U;
   static constexpr int BPC = J * NBC;                    // weight batches per chunk
   static constexpr int R = (BPC % 4 == 0) ? 4 : 3;       // ring depth: divides BPC, so ring slots are static
   static_assert(BPC % R == 0, "ring depth must divide the batches of a chunk");
@@ -304,7 +306,30 @@ __global__ __launch_bounds__(GEMM_THREADS) void gemm_expert_kernel(GemmArgs a) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int r32 = lane & 31, half = lane >> 5;
   const int mt0 = blockIdx.z;                       // 32-row tile of the expert's rows
-  const int e = blockIdx.y;
+  // REACHED (J == 1): only experts that have rows get workgroups.  blockIdx.x counts through those (the ids past them leave),
+  // so that the live workgroups are the first ones and spread evenly over the units; otherwise blockIdx.y is the expert.
+  constexpr bool REACHED = J == 1;
+  int e = blockIdx.y, bx = blockIdx.x;
+  int prev = -1;                                    // the expert with rows before e, or -1
+  bool last = false;                                // e is the last one with rows
+  unsigned long long has[4];                        // bit e % 64 of word e / 64: expert e has rows (uniform)
+  auto pick = [&]() -> bool {                       // e, prev and last from the workgroup's place among the live ones; false: none
+    const int rank = blockIdx.x / a.expert_wgs;
+    bx = blockIdx.x % a.expert_wgs;
+    e = -1;
+    int n = 0;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+      const int rk = n + __builtin_amdgcn_mbcnt_hi((uint32_t)(has[w] >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)has[w], 0));
+      const bool set = (has[w] >> lane) & 1ull;
+      const unsigned long long at = __ballot(set && rk == rank), before = __ballot(set && rk == rank - 1);
+      if (at) e = 64 * w + __builtin_ctzll(at);
+      if (before) prev = 64 * w + __builtin_ctzll(before);
+      n += __popcll(has[w]);
+    }
+    last = rank == n - 1;
+    return e >= 0;
+  };
   int row_base, my_pair = -1;
   if (a.route_idx) {
     // No grouping pass: the workgroup reads the routing table (a few KB, the same for every workgroup of the launch)
@@ -316,6 +341,19 @@ __global__ __launch_bounds__(GEMM_THREADS) void gemm_expert_kernel(GemmArgs a) {
     __shared__ int32_t route_rows[32];              // pairs of this workgroup's tile of the expert's rows
     const int ppt = (a.n_pairs + GEMM_THREADS - 1) / GEMM_THREADS;
     const int p0 = (int)threadIdx.x * ppt;
+    if constexpr (REACHED) {
+      __shared__ uint8_t route_has[256];
+      route_has[threadIdx.x] = 0;
+      __syncthreads();
+      for (int i = 0; i < ppt; ++i) {
+        const int idx = p0 + i < a.n_pairs ? a.route_idx[p0 + i] : -1;
+        if (idx >= 0 && idx < 256) route_has[idx] = 1;
+      }
+      __syncthreads();
+#pragma unroll
+      for (int w = 0; w < 4; ++w) has[w] = __ballot(route_has[64 * w + lane] != 0);
+      if (!pick()) return;                          // uniform over the workgroup
+    }
     int less = 0, eq = 0;
     for (int i = 0; i < ppt; ++i) {
       const int p = p0 + i;
@@ -342,7 +380,13 @@ __global__ __launch_bounds__(GEMM_THREADS) void gemm_expert_kernel(GemmArgs a) {
       n_rows += route_sum[w][1];
     }
     a.T = n_rows;
-    if (blockIdx.x == 0 && mt0 == 0 && threadIdx.x == 0) {   // also for an expert without rows
+    if constexpr (REACHED) {
+      if (bx == 0 && mt0 == 0) {                    // its own first row, that of the experts without rows before it ...
+        for (int i = prev + 1 + (int)threadIdx.x; i <= e; i += GEMM_THREADS) a.pub_group_off[i] = row_base;
+        if (last)                                   // ... and of those behind the last one
+          for (int i = e + 1 + (int)threadIdx.x; i <= a.n_experts; i += GEMM_THREADS) a.pub_group_off[i] = row_base + n_rows;
+      }
+    } else if (bx == 0 && mt0 == 0 && threadIdx.x == 0) {   // also for an expert without rows
       a.pub_group_off[e] = row_base;
       if (e == (int)gridDim.y - 1) a.pub_group_off[e + 1] = row_base + n_rows;
     }
@@ -350,17 +394,28 @@ __global__ __launch_bounds__(GEMM_THREADS) void gemm_expert_kernel(GemmArgs a) {
     int pos = before + incl - eq - mt0 * 32;        // place, inside this tile, of the thread's first match
     for (int i = 0; i < ppt; ++i) {
       const int p = p0 + i;
-      if (p < a.n_pairs && a.route_idx[p] == e) {   // second look at the same few entries: cache hits
+      if (p < a.n_pairs && a.route_idx[p] == e) {   // another look at the same few entries: cache hits
         if (pos >= 0 && pos < 32) route_rows[pos] = p;
         ++pos;
       }
     }
     __syncthreads();
     my_pair = route_rows[r32];                      // -1 past the expert's last row
-    if (blockIdx.x == 0) {
+    if (bx == 0) {
       if (threadIdx.x < 32 && my_pair >= 0) a.pub_pair_pos[my_pair] = row_base + mt0 * 32 + r32;
     }
   } else {
+    if constexpr (REACHED) {
+      int first[4], next[4];                        // all on their way before the first is used
+#pragma unroll
+      for (int w = 0; w < 4; ++w) {
+        first[w] = a.group_off[min(64 * w + lane, a.n_experts)];
+        next[w] = a.group_off[min(64 * w + lane + 1, a.n_experts)];
+      }
+#pragma unroll
+      for (int w = 0; w < 4; ++w) has[w] = __ballot(next[w] > first[w]);
+      if (!pick()) return;                          // uniform over the workgroup, before any barrier
+    }
     row_base = a.group_off[e];
     a.T = a.group_off[e + 1] - row_base;
     if (mt0 * 32 >= a.T) return;                    // uniform over the workgroup, before any barrier
@@ -369,13 +424,13 @@ __global__ __launch_bounds__(GEMM_THREADS) void gemm_expert_kernel(GemmArgs a) {
 
   const int KS = a.K >> 4;
   const int n_tiles = (a.N + 31) >> 5;
-  // tile of this wave in tile group j: (blockIdx.x * J + j) * 4 + wave; consecutive groups lie KS * W_KSTRIDE apart
-  const int nt0 = blockIdx.x * J * W_GROUP + wave;
+  // tile of this wave in tile group j: (bx * J + j) * 4 + wave; consecutive groups lie KS * W_KSTRIDE apart
+  const int nt0 = bx * J * W_GROUP + wave;
   static_assert(W_GROUP == GEMM_WAVES, "a wave owns one tile of every interleaved group");
   const h16_t* wp = wbase + packed_tile_offset(nt0, KS) + lane * 8;
   const size_t group_stride = (size_t)KS * W_KSTRIDE;
   // a tile group past the end of the matrix is read as the last one that exists (cache hits) and never stored
-  int jmax = ((n_tiles + W_GROUP - 1) / W_GROUP) - 1 - blockIdx.x * J;
+  int jmax = ((n_tiles + W_GROUP - 1) / W_GROUP) - 1 - bx * J;
   if (jmax > J - 1) jmax = J - 1;
 
   // ---- activation staging: each wave moves PT fragments of a chunk; fragment f = (k-step f / PL, plane f % PL) ----
@@ -532,10 +587,14 @@ void launch_mt(const GemmArgs& a, int n_tiles, int grid_y, int mt, const Act& x,
   else launch_fmt<4, EPI>(a, dim3(gx, grid_y, (mtiles + 3) / 4), x, st);
 }
 
-// Expert-grouped decode form (two-term bf16 only; the other formats keep the skinny form).  Tile groups per
-// workgroup: three or two, whichever divides the groups of an expert and still leaves two workgroups per compute
-// unit (measured at the 30B-A3B shape: gate/up, 12 groups, 155 us with one group per workgroup, 145 with two, 146
-// with three; down, 16 groups, 77.7 / 77.0 / 78.8); a grid that cannot fill the device anyway takes two.
+// Expert-grouped decode form (two-term bf16 only; the other formats keep the skinny form).  Tile groups per workgroup:
+//  - One, for the experts that have rows, where a batch reaches few of them.  With a workgroup of three groups for every
+//    expert the empty ones, resident for as long as it takes to find out, left some units two full ones and others
+//    none, and a batch of one put its eight experts on 32 units (30B-A3B shape, us of gate/up + down, before -> now: 1 token
+//    72 -> 31, 4 tokens 100 -> 62, 12 131 -> 114, 16 144 -> 131, 24 161 -> 160; 32 tokens, 88 % of the experts: 173, 178).
+//  - Otherwise three or two, whichever divides the groups of an expert and still leaves two workgroups per compute
+//    unit (measured at the 30B-A3B shape: gate/up, 12 groups, 155 us with one group per workgroup, 145 with two, 146
+//    with three; down, 16 groups, 77.7 / 77.0 / 78.8); a grid that cannot fill the device anyway takes two.
 template <int J, int EPI>
 void launch_expert_one(const GemmArgs& a, dim3 grid, hipStream_t st) {
   static std::once_flag attr_once;
@@ -547,22 +606,24 @@ void launch_expert_one(const GemmArgs& a, dim3 grid, hipStream_t st) {
   hipLaunchKernelGGL((gemm_expert_kernel<J, EPI, 2, DT_BF16>), grid, dim3(GEMM_THREADS), lds, st, a);
 }
 
-int expert_tile_groups(int n_tiles, int n_experts, int n_units) {
+int expert_tile_groups(int n_tiles, int n_experts, int n_pairs, int n_units) {
   const int groups = (n_tiles + W_GROUP - 1) / W_GROUP;
+  // share of the experts that a random routing of so many pairs misses
+  if (groups == 1 || powf(1.f - 1.f / (float)n_experts, (float)n_pairs) > 0.2f) return 1;
   for (int j = 3; j >= 2; --j)
     if (groups % j == 0 && (long)(groups / j) * n_experts >= 2L * n_units) return j;
-  return groups >= 2 ? 2 : 1;
+  return 2;
 }
 
 template <int EPI>
-bool launch_expert(const GemmArgs& a, int n_tiles, int n_experts, const Act& x, hipStream_t st) {
+bool launch_expert(GemmArgs a, int n_tiles, int n_experts, int n_pairs, const Act& x, hipStream_t st) {
   if (x.planes != 2 || x.dtype != DT_BF16) return false;
-  const int j = expert_tile_groups(n_tiles, n_experts, g_units.load(std::memory_order_relaxed));
-  if (j < 2) return false;
-  const int groups = (n_tiles + W_GROUP - 1) / W_GROUP;
-  const dim3 grid((groups + j - 1) / j, n_experts, (a.T + 31) / 32);
-  if (j == 2) launch_expert_one<2, EPI>(a, grid, st);
-  else launch_expert_one<3, EPI>(a, grid, st);
+  const int j = expert_tile_groups(n_tiles, n_experts, n_pairs, g_units.load(std::memory_order_relaxed));
+  const int groups = (n_tiles + W_GROUP - 1) / W_GROUP, row_tiles = (a.T + 31) / 32;
+  a.n_experts = n_experts; a.expert_wgs = (groups + j - 1) / j;
+  if (j == 1) launch_expert_one<1, EPI>(a, dim3(a.expert_wgs * (n_pairs < n_experts ? n_pairs : n_experts), 1, row_tiles), st);
+  else if (j == 2) launch_expert_one<2, EPI>(a, dim3(a.expert_wgs, n_experts, row_tiles), st);
+  else launch_expert_one<3, EPI>(a, dim3(a.expert_wgs, n_experts, row_tiles), st);
   return true;
 }
 
@@ -655,8 +716,10 @@ static int grouped_mt(int expected_rows) {
   return expected_rows <= 16 ? 1 : (expected_rows <= 40 ? 2 : 4);
 }
 
+static int rows_expected(int n_pairs, int E) { return (n_pairs + E - 1) / E; }
+
 hipError_t gemm_grouped_swiglu(const h16_t* w_gate_up, int E, int F, int K, const Act& x, const int32_t* x_rows,
-                               const int32_t* group_off, int max_rows, int expected_rows, const Act& act,
+                               const int32_t* group_off, int max_rows, int n_pairs, const Act& act,
                                hipStream_t st) {
   if (x.ss && x_rows) return hipErrorInvalidValue;   // the epilogue would need the row list to find a row's factor
   GemmArgs a = {};
@@ -667,13 +730,13 @@ hipError_t gemm_grouped_swiglu(const h16_t* w_gate_up, int E, int F, int K, cons
   a.ksteps_per_split = K / 16;
   a.act = act.p; a.act_mtiles = act.mtiles();
   a.group_off = group_off; a.w_expert_stride = packed_weight_elems(2 * F, K);
-  if (grouped_mt(expected_rows) == 1 && launch_expert<EPI_SWIGLU>(a, a.w_tiles[0], E, x, st)) return hipGetLastError();
-  launch_mt<EPI_SWIGLU>(a, a.w_tiles[0], E, grouped_mt(expected_rows), x, st);
+  if (grouped_mt(rows_expected(n_pairs, E)) == 1 && launch_expert<EPI_SWIGLU>(a, a.w_tiles[0], E, n_pairs, x, st)) return hipGetLastError();
+  launch_mt<EPI_SWIGLU>(a, a.w_tiles[0], E, grouped_mt(rows_expected(n_pairs, E)), x, st);
   return hipGetLastError();
 }
 
 hipError_t gemm_grouped_store(const h16_t* w, int E, int N, int K, const Act& x, const int32_t* group_off,
-                              int max_rows, int expected_rows, float* y, hipStream_t st) {
+                              int max_rows, int n_pairs, float* y, hipStream_t st) {
   GemmArgs a = {};
   fill_x(a, x);
   a.w[0] = w; a.w_tiles[0] = (N + 31) / 32;
@@ -681,8 +744,8 @@ hipError_t gemm_grouped_store(const h16_t* w, int E, int N, int K, const Act& x,
   a.ksteps_per_split = K / 16;
   a.y = y; a.ldy = N;
   a.group_off = group_off; a.w_expert_stride = packed_weight_elems(N, K);
-  if (grouped_mt(expected_rows) == 1 && launch_expert<EPI_STORE>(a, a.w_tiles[0], E, x, st)) return hipGetLastError();
-  launch_mt<EPI_STORE>(a, a.w_tiles[0], E, grouped_mt(expected_rows), x, st);
+  if (grouped_mt(rows_expected(n_pairs, E)) == 1 && launch_expert<EPI_STORE>(a, a.w_tiles[0], E, n_pairs, x, st)) return hipGetLastError();
+  launch_mt<EPI_STORE>(a, a.w_tiles[0], E, grouped_mt(rows_expected(n_pairs, E)), x, st);
   return hipGetLastError();
 }
 
@@ -690,10 +753,9 @@ hipError_t gemm_grouped_store(const h16_t* w, int E, int N, int K, const Act& x,
 // pairs in the routing table (route_idx[token * top_k + slot] = expert), reads the token's row of x and writes act
 // in expert order (pairs of expert 0 first, in pair order: what the counting sort produces).  The launch also
 // publishes group_off[E + 1] and pair_pos[n_pairs] of that order, which the down GEMM and the combine then read.
-bool gemm_routed_form(int E, int F, const Act& x, int n_pairs, int expected_rows) {
-  if (x.planes != 2 || x.dtype != DT_BF16 || grouped_mt(expected_rows) != 1) return false;
-  if (n_pairs > 16 * GEMM_THREADS) return false;    // at most 16 table entries per thread of a workgroup
-  return expert_tile_groups(F / 16, E, g_units.load(std::memory_order_relaxed)) >= 2;
+bool gemm_routed_form(int E, const Act& x, int n_pairs) {
+  if (x.planes != 2 || x.dtype != DT_BF16 || grouped_mt(rows_expected(n_pairs, E)) != 1) return false;
+  return n_pairs <= 16 * GEMM_THREADS;              // at most 16 table entries per thread of a workgroup
 }
 
 hipError_t gemm_routed_swiglu(const h16_t* w_gate_up, int E, int F, int K, const Act& x, const int32_t* route_idx,
@@ -708,7 +770,7 @@ hipError_t gemm_routed_swiglu(const h16_t* w_gate_up, int E, int F, int K, const
   a.w_expert_stride = packed_weight_elems(2 * F, K);
   a.route_idx = route_idx; a.n_pairs = n_pairs; a.top_k = top_k;
   a.pub_group_off = group_off; a.pub_pair_pos = pair_pos;
-  if (!launch_expert<EPI_SWIGLU>(a, a.w_tiles[0], E, x, st)) return hipErrorInvalidValue;
+  if (!launch_expert<EPI_SWIGLU>(a, a.w_tiles[0], E, n_pairs, x, st)) return hipErrorInvalidValue;
   return hipGetLastError();
 }
 

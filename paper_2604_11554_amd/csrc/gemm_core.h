@@ -33,6 +33,7 @@ struct GemmArgs {
   // expert-grouped decode form without a grouping pass: the kernel finds its expert's rows in the routing table itself
   const int32_t* route_idx;   // [n_pairs] expert of pair p = token * top_k + slot, or null (rows come from group_off)
   int n_pairs, top_k;
+  int n_experts, expert_wgs;  // expert-grouped decode form: experts, and workgroups per expert that has rows
   int32_t* pub_group_off;     // [E + 1] written by this launch: first row of every expert in expert order
   int32_t* pub_pair_pos;      // [n_pairs] written by this launch: row of every pair in expert order
   // long-call form (gemm_long.hip): x is in rows (Act::pitch), and so is act

@@ -80,17 +80,17 @@ hipError_t gemm_lmhead(const h16_t* w_lm, int V, int K, const Act& x, int T, flo
                        const uint64_t* seeds, const float* temperature, const int32_t* sample_pos,
                        const int32_t* row_seq, bool draw, hipStream_t st);
 // expert-grouped forms: rows [group_off[e], group_off[e+1]) belong to expert e = blockIdx.y; max_rows bounds the rows
-// of one expert, expected_rows (pairs / experts) picks the token-tile height
+// of one expert, n_pairs / E, the rows that one is expected to have, picks the token-tile height
 hipError_t gemm_grouped_swiglu(const h16_t* w_gate_up, int E, int F, int K, const Act& x, const int32_t* x_rows,
-                               const int32_t* group_off, int max_rows, int expected_rows, const Act& act,
+                               const int32_t* group_off, int max_rows, int n_pairs, const Act& act,
                                hipStream_t st);
 hipError_t gemm_grouped_store(const h16_t* w, int E, int N, int K, const Act& x,
-                              const int32_t* group_off, int max_rows, int expected_rows, float* y, hipStream_t st);
+                              const int32_t* group_off, int max_rows, int n_pairs, float* y, hipStream_t st);
 
 // routed form of the gate/up GEMM (decode batches, two-term bf16): the kernel finds its expert's (token, slot) pairs
 // in the routing table route_idx[n_pairs] itself, so no grouping pass runs before it; it writes act in expert order
 // and publishes group_off[E + 1] and pair_pos[n_pairs] of that order for gemm_grouped_store and the combine.
-bool gemm_routed_form(int E, int F, const Act& x, int n_pairs, int expected_rows);
+bool gemm_routed_form(int E, const Act& x, int n_pairs);
 hipError_t gemm_routed_swiglu(const h16_t* w_gate_up, int E, int F, int K, const Act& x, const int32_t* route_idx,
                               int n_pairs, int top_k, int max_rows, const Act& act, int32_t* group_off,
                               int32_t* pair_pos, hipStream_t st);
