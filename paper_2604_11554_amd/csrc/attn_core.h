@@ -89,23 +89,26 @@ __device__ __forceinline__ void qk_step(Scores<HD, NCT>& s, const h16x8 (&k0)[HD
       }
 }
 
-// Scaling, and -inf for the keys that a column does not see: a key is visible to column c when its page is valid,
+// -inf for the keys that a column does not see, and scaling: a key is visible to column c when its page is valid,
 // key < key_end and key <= pos_col[c]; all_visible (uniform over the wave) says that this holds for every key and column,
-// which all but the last steps of a run can tell.
+// which all but the last steps of a run can tell.  (Scaled behind the branch, the scores are known to be products where their
+// maximum is taken, which saves a canonicalising operation per score.)
 template <int HD, int NCT>
-__device__ __forceinline__ void scale_and_mask(Scores<HD, NCT>& s, int key_base0, int key_base1, bool ok0, bool ok1, int key_end,
+__device__ __forceinline__ void mask_and_scale(Scores<HD, NCT>& s, int key_base0, int key_base1, bool ok0, bool ok1, int key_end,
                                                const int (&pos_col)[NCT], bool all_visible, float scale, int g) {
+#pragma clang fp contract(off)          // the products are rounded on their own, not fused with the softmax's subtraction
+  if (!all_visible) {
+#pragma unroll
+    for (int c = 0; c < NCT; ++c)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int key0 = key_base0 + 4 * g + v, key1 = key_base1 + 4 * g + v;
+        if (!(ok0 && key0 < key_end && key0 <= pos_col[c])) s.a[c][v] = -INFINITY;
+        if (!(ok1 && key1 < key_end && key1 <= pos_col[c])) s.b[c][v] = -INFINITY;
+      }
+  }
 #pragma unroll
   for (int c = 0; c < NCT; ++c) { s.a[c] *= scale; s.b[c] *= scale; }
-  if (all_visible) return;
-#pragma unroll
-  for (int c = 0; c < NCT; ++c)
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const int key0 = key_base0 + 4 * g + v, key1 = key_base1 + 4 * g + v;
-      if (!(ok0 && key0 < key_end && key0 <= pos_col[c])) s.a[c][v] = -INFINITY;
-      if (!(ok1 && key1 < key_end && key1 <= pos_col[c])) s.b[c][v] = -INFINITY;
-    }
 }
 
 // The vector arithmetic of a step: per score a subtraction, the exponential, an addition and three operations for its
@@ -146,10 +149,16 @@ __device__ __forceinline__ void softmax_step(WaveState<HD, NCT>& st, const Score
   }
 }
 
-// (A branch that skips this where no maximum moved cost as many register moves as it saved products, and split the
-// step's instructions into blocks that cannot be interleaved.)
-template <int HD, int NCT>
+// LATE: past the first thousand keys most steps move no column's maximum, and a factor of 1 leaves the bits as they are.  (Before
+// that the branch, which splits the step's instructions into blocks that cannot be interleaved, costs more than it saves.)
+template <int HD, int NCT, bool LATE>
 __device__ __forceinline__ void rescale(WaveState<HD, NCT>& st, const float (&alpha)[NCT]) {
+  if (LATE) {
+    bool moved = false;
+#pragma unroll
+    for (int c = 0; c < NCT; ++c) moved |= alpha[c] != 1.f;
+    if (!__builtin_amdgcn_ballot_w64(moved)) return;
+  }
 #pragma unroll
   for (int c = 0; c < NCT; ++c)
 #pragma unroll
@@ -167,7 +176,7 @@ __device__ __forceinline__ void pv_step(WaveState<HD, NCT>& st, const h16x8 (&vf
         st.o[c][dt] = mfma_16x16x32<FMT>(vf[dt], pf[p][c], st.o[c][dt]);
 }
 
-template <int HD, int NCT, int PL, int FMT, typename QF>
+template <int HD, int NCT, int PL, int FMT, bool LATE = false, typename QF>
 __device__ __forceinline__ void pair_step(WaveState<HD, NCT>& st, const h16x8 (&k0)[HD / 32],
                                           const h16x8 (&k1)[HD / 32], const h16x8 (&vf)[HD / 16], QF qf,
                                           int key_base0, int key_base1, bool ok0, bool ok1, int key_end,
@@ -176,9 +185,9 @@ __device__ __forceinline__ void pair_step(WaveState<HD, NCT>& st, const h16x8 (&
   h16x8 pf[PL][NCT];
   float alpha[NCT];
   qk_step<HD, NCT, PL, FMT>(s, k0, k1, qf);
-  scale_and_mask<HD, NCT>(s, key_base0, key_base1, ok0, ok1, key_end, pos_col, all_visible, scale, g);
+  mask_and_scale<HD, NCT>(s, key_base0, key_base1, ok0, ok1, key_end, pos_col, all_visible, scale, g);
   softmax_step<HD, NCT, PL, FMT>(st, s, pf, alpha);
-  rescale<HD, NCT>(st, alpha);
+  rescale<HD, NCT, LATE>(st, alpha);
   pv_step<HD, NCT, PL, FMT>(st, vf, pf);
 }
 

@@ -64,6 +64,7 @@ template <int DT, int PL> __device__ __forceinline__ void split_pair(float a, fl
     if (PL == 2) lo = pack_f16(a - f16_to_f32((h16_t)(hi & 0xFFFFu)), b - f16_to_f32((h16_t)(hi >> 16)));
   } else {
     hi = pack_bf16(a, b);
+    asm("" : "+v"(hi));                 // the halves are taken from the pair, not from conversions of their own
     if (PL == 2) lo = pack_bf16(a - __uint_as_float(hi << 16), b - __uint_as_float(hi & 0xFFFF0000u));
   }
 }

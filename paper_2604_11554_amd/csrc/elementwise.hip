@@ -28,10 +28,12 @@ __global__ void meta_decode_kernel(TokenMeta m, int n, const int32_t* ctx, const
   m.sample_on[i] = live;
 }
 
-// one workgroup; sequences are walked in order so the tile list is deterministic
+// One workgroup.  The query tiles are listed by the keys they walk, the longest first (to a 1024th of the longest; equal ones in
+// any order), so that a grid in list order starts the long ones first and ends with short ones.
 __global__ void meta_prefill_kernel(TokenMeta m, int n_seqs, int total, const int32_t* cu, const int32_t* ctx,
                                     const uint8_t* sample_last) {
-  __shared__ int tile_base[1025];
+  __shared__ int bucket[1024];
+  __shared__ int longest;
   // per-token fields: binary search of the owning sequence
   for (int t = threadIdx.x; t < total; t += blockDim.x) {
     int lo = 0, hi = n_seqs - 1;
@@ -50,31 +52,36 @@ __global__ void meta_prefill_kernel(TokenMeta m, int n_seqs, int total, const in
     m.sample_pos[i] = ctx[i] + len;
     m.sample_on[i] = (sample_last && sample_last[i] && len > 0) ? 1 : 0;
   }
-  // query tiles of ATTN_QTILE positions, sequence by sequence (n_seqs <= 1024 per chunk of the scan)
+  // query tiles of ATTN_QTILE positions: a wave per sequence, a lane per tile, counted into buckets and placed from there
+  bucket[threadIdx.x] = 0;                          // 1024 threads
+  if (threadIdx.x == 0) longest = 0;
   __syncthreads();
-  int base = 0;
-  for (int s0 = 0; s0 < n_seqs; s0 += 1024) {
-    int cnt = min(1024, n_seqs - s0);
-    if (threadIdx.x == 0) {
-      int acc = base;
-      for (int i = 0; i < cnt; ++i) {
-        tile_base[i] = acc;
-        acc += (cu[s0 + i + 1] - cu[s0 + i] + ATTN_QTILE - 1) / ATTN_QTILE;
-      }
-      tile_base[cnt] = acc;
+  for (int i = threadIdx.x; i < n_seqs; i += blockDim.x)
+    if (cu[i + 1] > cu[i]) atomicMax(&longest, ctx[i] + cu[i + 1] - cu[i]);
+  __syncthreads();
+  const int shift = max(0, 22 - __clz(longest));    // longest >> shift < 1024
+  auto each_tile = [&](auto f) {
+    for (int i = threadIdx.x >> 6; i < n_seqs; i += blockDim.x >> 6) {
+      const int len = cu[i + 1] - cu[i], c = ctx[i];
+      for (int q0 = ATTN_QTILE * (threadIdx.x & 63); q0 < len; q0 += ATTN_QTILE * 64)
+        f(i, q0, 1023 - (min(c + min(q0 + ATTN_QTILE, len), longest) >> shift));
     }
+  };
+  each_tile([&](int, int, int b) { atomicAdd(&bucket[b], 1); });
+  __syncthreads();
+  for (int o = 1; o < 1024; o <<= 1) {              // inclusive prefix
+    const int v = (int)threadIdx.x >= o ? bucket[threadIdx.x - o] : 0;
     __syncthreads();
-    for (int i = threadIdx.x; i < cnt; i += blockDim.x) {
-      int nt = tile_base[i + 1] - tile_base[i];
-      for (int j = 0; j < nt; ++j) {
-        m.qtile_seq[tile_base[i] + j] = s0 + i;
-        m.qtile_q0[tile_base[i] + j] = ATTN_QTILE * j;
-      }
-    }
-    base = tile_base[cnt];
+    bucket[threadIdx.x] += v;
     __syncthreads();
   }
-  if (threadIdx.x == 0) m.n_qtiles[0] = base;
+  if (threadIdx.x == 0) m.n_qtiles[0] = bucket[1023];
+  __syncthreads();
+  each_tile([&](int i, int q0, int b) {             // from a bucket's end downwards
+    const int at = atomicSub(&bucket[b], 1) - 1;
+    m.qtile_seq[at] = i;
+    m.qtile_q0[at] = q0;
+  });
 }
 
 // grid = ceil(T / 4), a wave per token: the rotary factors of every token's position, once per call and not per

@@ -131,7 +131,7 @@ struct TokenMeta {        // per packed token, built on the device at the start 
   int32_t* sample_row;    // [n_seqs] packed index of the token whose hidden state is sampled from
   int32_t* sample_pos;    // [n_seqs] absolute position of the token to be drawn
   uint8_t* sample_on;     // [n_seqs] 1 if the row emits a token in this call
-  int32_t* qtile_seq;     // prefill attention tiles: sequence, first query index
+  int32_t* qtile_seq;     // prefill attention tiles, longest first: sequence, first query index
   int32_t* qtile_q0;
   int32_t* n_qtiles;      // [1]
   int32_t* tok_iota;      // prefill: [T] 0, 1, 2, ... (row lists of the per-token scoring pass)
@@ -205,6 +205,7 @@ struct AttnArgs {            // prefill
   const int32_t* cu_seqlens;
   const int32_t* qtile_seq; const int32_t* qtile_q0; const int32_t* n_qtiles;
   int max_qtiles;
+  int n_units;               // compute units of the device
   Act o;                     // [T, Hq*hd] in fragment order (input of the output projection)
 };
 hipError_t attention_prefill(const AttnArgs& a, hipStream_t st);

@@ -12,6 +12,10 @@ namespace rlx {
 __device__ __forceinline__ void copy_to_lds(const void* g, uint32_t lds) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds), "v"(g) : "memory", "m0");
 }
+// The same from a uniform address plus a 32-bit lane offset.
+__device__ __forceinline__ void copy_to_lds(const void* base, uint32_t offset, uint32_t lds) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(offset), "s"(base) : "memory", "m0");
+}
 #pragma clang diagnostic pop
 // Waits until at most N of this wave's copies are in flight and its LDS reads are done, then for the other waves.
 template <int N>
