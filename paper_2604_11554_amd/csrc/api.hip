@@ -105,7 +105,7 @@ struct Workspace {
   h16_t* q;         // [T, q_dim]
   h16_t* ob;        // [T, q_dim]
   float* attn_part;  // [ATTN_SHARES_MAX][2][Hq/Hkv][hd+4] decode partials of straddling (sequence, KV head) pairs
-  int32_t *attn_prefix, *attn_share_seq, *attn_hdr;   // decode attention plan
+  int32_t *attn_prefix, *attn_share_start, *attn_hdr;   // decode attention plan
   float* attn_seq_part;   // [S][Hkv][Hq/Hkv][hd+4] own part of a pair that prefix tiles precede
   float* attn_pre_part;   // [shared_prefix_max_tiles][SP_COLS][hd+4] parts of the shared-prefix tiles
   float* planes;     // split-K planes of the o / down projections
@@ -209,7 +209,7 @@ Workspace carve(const rlx_model_config& c, char* base, int S, int T, const Plane
   w.q = (h16_t*)take((size_t)PL * T * qdim * 2);
   w.ob = (h16_t*)take(act_bytes(T, qdim, lng));
   w.attn_prefix = (int32_t*)take((size_t)(S + 1) * 4);
-  w.attn_share_seq = (int32_t*)take((size_t)ATTN_SHARES_MAX * 4);
+  w.attn_share_start = (int32_t*)take((size_t)ATTN_SHARES_MAX * ATTN_SHARE_WORDS * 4);
   w.attn_hdr = (int32_t*)take(4 * 4);
   w.attn_seq_part = (float*)take((size_t)S * c.n_q_heads * (c.head_dim + 4) * 4);
   w.attn_pre_part = (float*)take((size_t)shared_prefix_max_tiles(S, c.n_kv_heads) * SP_COLS * (c.head_dim + 4) * 4);
@@ -279,7 +279,7 @@ int run_layers(const rlx_model* m, h16_t* pool, int64_t n_blocks, const Workspac
   const Act ob = call_act(c, w.ob, T, qdim, lng);
   const RowAct qb = {w.q, (size_t)T * qdim, qdim, PL, FMT};
 
-  RLX_HIP(embed_tokens(m->embed, c.vocab, d, io.tokens, io.input_embeds, T, w.h, FMT, st));
+  if (!io.decode) RLX_HIP(embed_tokens(m->embed, c.vocab, d, io.tokens, io.input_embeds, T, w.h, FMT, st));
 
   // residual contribution produced by the previous sub-layer, folded into the next norm
   const float* pend_planes = nullptr; int pend_n = 0; bool pend_moe = false;
@@ -343,7 +343,7 @@ int run_layers(const rlx_model* m, h16_t* pool, int64_t n_blocks, const Workspac
       at.q = qb; at.pool_layer = pool_layer; at.n_blocks = n_blocks;
       at.Hq = c.n_q_heads; at.Hkv = c.n_kv_heads; at.hd = c.head_dim;
       at.block_table = io.block_table; at.max_blocks = io.max_blocks; at.ctx_lens = io.ctx_lens;
-      at.n_seqs = io.n_seqs; at.unit_prefix = w.attn_prefix; at.share_seq = w.attn_share_seq; at.plan_hdr = w.attn_hdr;
+      at.n_seqs = io.n_seqs; at.unit_prefix = w.attn_prefix; at.share_start = w.attn_share_start; at.plan_hdr = w.attn_hdr;
       at.team = attn_by_team(c); at.n_wgs = m->attn_wgs; at.part = w.attn_part; at.o = ob;
       at.shared = io.shared_prefix; at.seq_part = w.attn_seq_part; at.pre_part = w.attn_pre_part;
       at.n_prefix_wgs = 2 * m->n_units;
@@ -512,9 +512,15 @@ int decode_step(const rlx_model* m, void* kv_pool, int64_t n_blocks, void* works
   if (w.bytes > workspace_bytes)
     return fail(RLX_ENOMEM, "workspace too small: need %zu bytes, have %zu", w.bytes, workspace_bytes);
   hipStream_t st = (hipStream_t)stream;
-  RLX_HIP(meta_decode(w.meta, n_seqs, ctx_lens_inout, finished_inout, m->inv_freq, m->cfg.head_dim, st));
-  RLX_HIP(attention_decode_plan(n_seqs, ctx_lens_inout, w.meta.tok_live, m->cfg.n_kv_heads, m->attn_wgs,
-                                attn_by_team(m->cfg), (const int32_t*)shared_prefix, w.attn_prefix, w.attn_share_seq, w.attn_hdr, st));
+  DecodeBeginArgs b = {};
+  b.n_seqs = n_seqs; b.Hkv = m->cfg.n_kv_heads; b.head_dim = m->cfg.head_dim;
+  b.ctx_lens = ctx_lens_inout; b.finished = finished_inout; b.block_table = block_table; b.max_blocks = max_blocks_per_seq;
+  b.meta = w.meta; b.inv_freq = m->inv_freq;
+  b.embed = m->embed; b.vocab = m->cfg.vocab; b.d_model = m->cfg.d_model; b.dtype = m->cfg.dtype;
+  b.tokens = tokens_inout; b.h = w.h;
+  b.team = attn_by_team(m->cfg); b.shared = (const int32_t*)shared_prefix;
+  b.unit_prefix = w.attn_prefix; b.share_start = w.attn_share_start; b.plan_hdr = w.attn_hdr;
+  RLX_HIP(decode_begin(b, m->attn_wgs, st));
   StepIO io = {};
   io.n_seqs = n_seqs; io.T = n_seqs; io.decode = true;
   io.tokens = tokens_inout; io.ctx_lens = ctx_lens_inout; io.ctx_lens_rw = ctx_lens_inout;

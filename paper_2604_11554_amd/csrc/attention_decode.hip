@@ -30,6 +30,7 @@
 // shared units, and the merge kernel adds the prefix parts first.
 #include "attn_core.h"
 #include "lds_copy.h"
+#include "rope.h"
 
 namespace rlx {
 namespace {
@@ -85,7 +86,25 @@ struct Run {
   bool seg_start, seg_end, valid;
 };
 
-// Walks the runs of a share: the per-sequence plan entries are held in a 64-lane register window.
+// Where a share starts, as the plan writes it (one 64-byte record, so that a share's first pages are two round trips away):
+// sequence, KV head, ctx, u0 and np of its first pair, the share's first unit counted from that pair's, the share's units
+// [u, u_end) on the line (none if u >= u_end), and the pages of its first units, two each, up to the segment's last one.
+constexpr int SHARE_WORDS = ATTN_SHARE_WORDS, SHARE_BLOCKS = 8, SHARE_FIRST_UNITS = (SHARE_WORDS - SHARE_BLOCKS) / 2;
+struct ShareStart {
+  int seq, kvh, ctx, u0, np, pb, u, u_end;
+  int32_t blocks[2 * SHARE_FIRST_UNITS];
+  __device__ __forceinline__ int pe() const { return min(np, u_end - (u - pb)); }   // end of the first segment
+};
+__device__ __forceinline__ ShareStart load_share(const int32_t* recs, int w) {
+  const int32_t* r = recs + (size_t)w * SHARE_WORDS;
+  ShareStart s = {r[0], r[1], r[2], r[3], r[4], r[5], r[6], r[7], {}};
+#pragma unroll
+  for (int i = 0; i < 2 * SHARE_FIRST_UNITS; ++i) s.blocks[i] = r[SHARE_BLOCKS + i];
+  return s;
+}
+
+// Walks the runs of a share: the per-sequence plan entries are held in a 64-lane register window.  The first run is known from
+// the share's record; the window is requested with it and read when the walk goes on.
 struct RunWalk {
   const AttnDecodeArgs& a;
   const SharedView sv;
@@ -93,9 +112,17 @@ struct RunWalk {
   int u, seq, seq0, rem_lo, rem_hi;                  // rem: rest of the current segment
   int32_t wpre, wctx, wst;
   Run seg;
-  __device__ __forceinline__ RunWalk(const AttnDecodeArgs& args, int lane_, int u_, int u_end_, int seq_)
-      : a(args), sv(shared_view(args.shared, args.n_seqs, args.Hkv)), lane(lane_), u_end(u_end_), u(u_), seq(seq_), rem_lo(0),
-        rem_hi(0), seg() {
+  __device__ __forceinline__ RunWalk(const AttnDecodeArgs& args, int lane_, const ShareStart& s, Run& r)
+      : a(args), sv(shared_view(args.shared, args.n_seqs, args.Hkv)), lane(lane_), u_end(s.u_end) {
+    seg.seq = s.seq; seg.kvh = s.kvh; seg.ctx = s.ctx; seg.np = s.np; seg.u0 = s.u0;
+    seg.pb = s.pb; seg.pe = s.pe();
+    seg.valid = true;
+    r = seg;
+    r.lo = seg.pb; r.hi = min(seg.pe, seg.pb + 64);
+    r.seg_start = true; r.seg_end = r.hi == seg.pe;
+    rem_lo = r.hi; rem_hi = seg.pe;
+    u = s.u - s.pb + seg.pe;
+    seq = s.seq + (seg.pe == seg.np && seg.kvh == a.Hkv - 1 ? 1 : 0);
     slide();
   }
   __device__ __forceinline__ void slide() {
@@ -148,17 +175,14 @@ __device__ __forceinline__ void load_window(const AttnDecodeArgs& a, const Run& 
   if (jb + 64 >= a.max_blocks) t1 = -1;
 }
 
-// Page loads of unit i of run r (table window t0/t1).  They are unconditional: a slot with no unit behind it
+// Page loads of unit i of run r, pages b0_ and b1_.  They are unconditional: a slot with no unit behind it
 // (`live` false, i clamped into the run) reads one fixed row of the pool with every lane, which costs cache
 // hits and no memory traffic.
 template <int HD>
-__device__ __forceinline__ void issue_unit(const AttnDecodeArgs& a, const Run& r, int32_t t0, int32_t t1, int i, bool live, int c16,
-                                           int g, PageRegs<HD>& pr) {
+__device__ __forceinline__ void issue_pages(const AttnDecodeArgs& a, const Run& r, int32_t b0_, int32_t b1_, int i, bool live, int c16,
+                                            int g, PageRegs<HD>& pr) {
   constexpr size_t page = (size_t)2 * 16 * HD;
-  const int rel = 2 * (i - r.lo);                    // uniform, 0 .. 126
-  const int32_t sel = rel < 64 ? t0 : t1;
-  int64_t b0 = __builtin_amdgcn_readlane(sel, rel & 63);
-  int64_t b1 = __builtin_amdgcn_readlane(sel, (rel + 1) & 63);
+  int64_t b0 = b0_, b1 = b1_;
   const bool has1 = (2 * (r.u0 + i) + 1) * 16 < r.ctx + 1;
   pr.ok0 = live && b0 >= 0 && b0 < a.n_blocks;
   pr.ok1 = live && has1 && b1 >= 0 && b1 < a.n_blocks;
@@ -178,6 +202,15 @@ __device__ __forceinline__ void issue_unit(const AttnDecodeArgs& a, const Run& r
 #pragma unroll
   for (int dt = 0; dt < HD / 16; ++dt)
     pr.vf[dt] = load_2x4_stream(vp0 + 256 * dt + voff0, vp1 + 256 * dt + voff1);
+}
+
+// The same with the pages taken from the run's table window t0/t1.
+template <int HD>
+__device__ __forceinline__ void issue_unit(const AttnDecodeArgs& a, const Run& r, int32_t t0, int32_t t1, int i, bool live, int c16,
+                                           int g, PageRegs<HD>& pr) {
+  const int rel = 2 * (i - r.lo);                    // uniform, 0 .. 126
+  const int32_t sel = rel < 64 ? t0 : t1;
+  issue_pages<HD>(a, r, __builtin_amdgcn_readlane(sel, rel & 63), __builtin_amdgcn_readlane(sel, (rel + 1) & 63), i, live, c16, g, pr);
 }
 
 // The end of a segment: final if it is a whole pair that no prefix precedes, else (o, m, l) for the merge kernel.  `share`:
@@ -213,11 +246,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   const bool col_ok = c16 < group;
   const int w = wave * gridDim.x + blockIdx.x;       // few shares spread over the units
   if (w >= ATTN_SHARES_MAX) return;
-  const Shares sh = load_shares(a.plan_hdr);
-  const int u = sh.start(w), u_end = min(sh.U, sh.start(w + 1));
-  if (u >= u_end) return;                            // uniform over the wave
+  const ShareStart share = load_share(a.share_start, w);
+  if (share.u >= share.u_end) return;                // uniform over the wave
   const float scale = rsqrtf((float)HD);
-  RunWalk walk(a, lane, u, u_end, a.share_seq[w]);
+  Run cur, nxt;
+  RunWalk walk(a, lane, share, cur);
   // The query fragments of a pair go straight into LDS, a whole run before they are read (the run generator looks one
   // run ahead anyway).  Columns past the group read some head's queries; their results are never stored.
   int qsel = 0;
@@ -232,16 +265,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   };
   auto qf = [&](int p, int, int ks) { return __builtin_bit_cast(h16x8, lds_q[wave][qsel][(p * KS + ks) * WAVE + lane]); };
 
-  Run cur, nxt;
-  walk.next(cur);
-  if (!cur.valid) return;
   int32_t tb0, tb1, tbn0, tbn1;
   load_window(a, cur, lane, tb0, tb1);
   copy_queries(cur, 0);
 
   WaveState<HD, 1> st;
   PageRegs<HD> ra, rb;
-  issue_unit<HD>(a, cur, tb0, tb1, cur.lo, true, c16, g, ra);
+  issue_pages<HD>(a, cur, share.blocks[0], share.blocks[1], cur.lo, true, c16, g, ra);
+  __builtin_amdgcn_sched_barrier(0);                 // everything that the record names is on its way before the walk goes on
   bool first_seg = true, more = false, fresh = true;
   int k = cur.lo;
   auto look_ahead = [&]() {                          // the run after cur: its table window and, for a new pair, its queries
@@ -306,11 +337,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   const int group = a.Hq / a.Hkv;
   const bool col_ok = c16 < group;
   const int w = blockIdx.x;
-  const Shares sh = load_shares(a.plan_hdr);
-  const int u = sh.start(w), u_end = min(sh.U, sh.start(w + 1));
-  if (u >= u_end) return;                            // uniform over the workgroup
+  const ShareStart share = load_share(a.share_start, w);
+  if (share.u >= share.u_end) return;                // uniform over the workgroup
   const float scale = rsqrtf((float)HD);
-  RunWalk walk(a, lane, u, u_end, a.share_seq[w]);
+  Run cur, nxt;
+  RunWalk walk(a, lane, share, cur);
   // The waves share the fetch of a segment's query fragments; they stay in LDS (registers hold two units of pages).
   // The fragments of the next run's pair are requested a whole run ahead (the run generator looks one run ahead
   // anyway) and only written to LDS at the switch, so that a new segment does not begin with a round trip.
@@ -332,19 +363,23 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   };
   auto qf = [&](int p, int, int ks) { return __builtin_bit_cast(h16x8, lds_q[(p * KS + ks) * WAVE + lane]); };
 
-  Run cur, nxt;
-  walk.next(cur);
-  if (!cur.valid) return;                            // uniform over the workgroup
   int32_t tb0, tb1, tbn0, tbn1;
   load_window(a, cur, lane, tb0, tb1);
   u32x4 qpre[QPW];
   fetch_queries(cur, qpre);
+  WaveState<HD, 1> st;
+  PageRegs<HD> ra, rb;
+  {
+    int32_t b0 = share.blocks[0], b1 = share.blocks[1];
+#pragma unroll
+    for (int i = 1; i < 4; ++i)
+      if (wave == i) { b0 = share.blocks[2 * i]; b1 = share.blocks[2 * i + 1]; }
+    issue_pages<HD>(a, cur, b0, b1, min(cur.lo + wave, cur.hi - 1), cur.lo + wave < cur.hi, c16, g, ra);
+  }
+  __builtin_amdgcn_sched_barrier(0);                 // everything that the record names is on its way before the walk goes on
   put_queries(qpre);
   __syncthreads();
 
-  WaveState<HD, 1> st;
-  PageRegs<HD> ra, rb;
-  issue_unit<HD>(a, cur, tb0, tb1, min(cur.lo + wave, cur.hi - 1), cur.lo + wave < cur.hi, c16, g, ra);
   bool first_seg = true;
 
   for (;;) {                                         // one run per iteration; uniform
@@ -616,11 +651,35 @@ __global__ __launch_bounds__(256 * GROUPS) void attn_decode_merge_kernel(AttnDec
   }
 }
 
-// One workgroup: exclusive prefix of the per-sequence unit counts, the two share sizes, and the sequence in which
-// each share starts.
-__global__ __launch_bounds__(1024) void attn_plan_kernel(int n_seqs, const int32_t* ctx, const uint8_t* live, int Hkv,
-                                                          int n_shares, bool team, const int32_t* shared, int32_t* unit_prefix,
-                                                          int32_t* share_seq, int32_t* hdr) {
+// The start of a decode step, one launch of n_seqs + 1 workgroups.  Workgroup 1 + i: metadata of row i, the rotary factors of
+// its new position (the same for every layer, so they are computed once per step and not per layer) and its token's embedding.
+// Workgroup 0, the plan of the step's attention: exclusive prefix of the per-sequence unit counts, the two share sizes, and
+// where each share starts.
+__global__ __launch_bounds__(1024) void decode_begin_kernel(DecodeBeginArgs b) {
+  const int n_seqs = b.n_seqs, Hkv = b.Hkv;
+  const int32_t* ctx = b.ctx_lens;
+  if (blockIdx.x > 0) {
+    const int i = blockIdx.x - 1, pos = ctx[i], half = b.head_dim / 2;
+    embed_row(b.embed, b.vocab, b.d_model, b.tokens[i], nullptr, b.h + (size_t)i * b.d_model, b.dtype);
+    for (int j = threadIdx.x; j < half; j += blockDim.x) {
+      float c, s;
+      rope_cos_sin(pos, b.inv_freq, true, j, c, s);
+      b.meta.rope_cs[(size_t)i * half + j] = float2{c, s};
+    }
+    if (threadIdx.x != 0) return;
+    const uint8_t live = b.finished[i] ? 0 : 1;
+    b.meta.tok_seq[i] = i;
+    b.meta.tok_pos[i] = pos;
+    b.meta.tok_live[i] = live;
+    b.meta.sample_row[i] = i;
+    b.meta.sample_pos[i] = pos + 1;
+    b.meta.sample_on[i] = live;
+    return;
+  }
+  const int n_shares = b.n_shares, max_blocks = b.max_blocks;
+  const bool team = b.team;
+  const int32_t *shared = b.shared, *block_table = b.block_table;
+  int32_t *unit_prefix = b.unit_prefix, *hdr = b.plan_hdr;
   __shared__ int sh[1024];
   __shared__ int carry, n_live;
   const int tid = threadIdx.x;
@@ -630,12 +689,13 @@ __global__ __launch_bounds__(1024) void attn_plan_kernel(int n_seqs, const int32
   for (int base = 0; base < n_seqs; base += 1024) {
     const int i = base + tid;
     // units of the sequence's own pairs: those after the ones that prefix tiles serve
-    const int v = (i < n_seqs && live[i]) ? (ctx[i] + 1 + 31) / 32 - shared_units_of(sv, i, ctx[i]) : 0;
+    const int v = (i < n_seqs && !b.finished[i]) ? (ctx[i] + 1 + 31) / 32 - shared_units_of(sv, i, ctx[i]) : 0;
     sh[tid] = v;
     const int live_here = __popcll(__ballot(v > 0));
     if ((tid & 63) == 0 && live_here) atomicAdd(&n_live, live_here);
     __syncthreads();
-    for (int o = 1; o < 1024; o <<= 1) {
+    const int count = min(1024, n_seqs - base);
+    for (int o = 1; o < count; o <<= 1) {
       const int t = tid >= o ? sh[tid - o] : 0;
       __syncthreads();
       sh[tid] += t;
@@ -643,12 +703,13 @@ __global__ __launch_bounds__(1024) void attn_plan_kernel(int n_seqs, const int32
     }
     if (i < n_seqs) unit_prefix[i] = carry + sh[tid] - v;
     __syncthreads();
-    if (tid == 1023) carry += sh[1023];
+    if (tid == 0) carry += sh[count - 1];
     __syncthreads();
   }
   const int per_head = carry;
   if (tid == 0) unit_prefix[n_seqs] = per_head;
-  __syncthreads();                                   // the prefix is read back below
+  __syncthreads();                                   // the prefix is read back below, from LDS if it is all there
+  auto prefix = [&](int i) { return n_seqs > 1024 ? unit_prefix[i] : i ? sh[i - 1] : 0; };
   const int total = per_head * Hkv;
   // Share sizes differ by at most one unit: the units of the step are dealt out evenly and the first H shares take the
   // remainder, one unit each.  A share per wave is never empty, and there are on average at most MERGE_AT_ONCE of them per
@@ -665,20 +726,37 @@ __global__ __launch_bounds__(1024) void attn_plan_kernel(int n_seqs, const int32
     int lo = 0, hi = n_seqs - 1;                     // largest s with Hkv * prefix[s] <= u0
     while (lo < hi) {
       const int mid = (lo + hi + 1) >> 1;
-      if (Hkv * unit_prefix[mid] <= u0) lo = mid; else hi = mid - 1;
+      if (Hkv * prefix(mid) <= u0) lo = mid; else hi = mid - 1;
     }
-    share_seq[w] = u0 < total ? lo : n_seqs;
+    int32_t* r = b.share_start + (size_t)w * SHARE_WORDS;
+    const int end = min(total, shr.start(w + 1));
+    if (u0 >= end) { r[6] = r[7] = 0; continue; }
+    const int base = Hkv * prefix(lo), np = prefix(lo + 1) - prefix(lo), c = ctx[lo];
+    const int kvh = (u0 - base) / np, pb = u0 - base - kvh * np, first = shared_units_of(sv, lo, c);
+    const int last = min(np, end - (u0 - pb)) - 1;   // last unit of the first segment
+    int32_t blocks[2 * SHARE_FIRST_UNITS];
+#pragma unroll
+    for (int i = 0; i < 2 * SHARE_FIRST_UNITS; ++i) {
+      const int j = 2 * (first + min(pb + i / 2, last)) + (i & 1);
+      const int32_t id = block_table[(size_t)lo * max_blocks + min(j, max_blocks - 1)];
+      blocks[i] = j < max_blocks ? id : -1;
+    }
+    typedef int32_t i32x4 __attribute__((ext_vector_type(4)));
+    static_assert(SHARE_WORDS == 16, "four stores");
+    i32x4* out = reinterpret_cast<i32x4*>(r);
+    out[0] = i32x4{lo, kvh, c, first};
+    out[1] = i32x4{np, pb, u0, end};
+    out[2] = i32x4{blocks[0], blocks[1], blocks[2], blocks[3]};
+    out[3] = i32x4{blocks[4], blocks[5], blocks[6], blocks[7]};
   }
 }
 
 }  // namespace
 
-hipError_t attention_decode_plan(int n_seqs, const int32_t* ctx_lens, const uint8_t* tok_live, int Hkv, int n_wgs, bool team,
-                                 const int32_t* shared, int32_t* unit_prefix, int32_t* share_seq, int32_t* hdr,
-                                 hipStream_t st) {
+hipError_t decode_begin(DecodeBeginArgs b, int n_wgs, hipStream_t st) {
   const int waves = 4 * n_wgs < ATTN_SHARES_MAX ? 4 * n_wgs : ATTN_SHARES_MAX;   // a larger grid leaves waves idle
-  hipLaunchKernelGGL(attn_plan_kernel, dim3(1), dim3(1024), 0, st, n_seqs, ctx_lens, tok_live, Hkv, team ? n_wgs : waves, team,
-                     shared, unit_prefix, share_seq, hdr);
+  b.n_shares = b.team ? n_wgs : waves;
+  hipLaunchKernelGGL(decode_begin_kernel, dim3(1 + b.n_seqs), dim3(1024), 0, st, b);
   return hipGetLastError();
 }
 

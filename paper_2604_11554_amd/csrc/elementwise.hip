@@ -7,27 +7,6 @@
 namespace rlx {
 namespace {
 
-// grid = n sequences, 64 threads: thread 0 writes the row's metadata, lane i < hd/2 the rotary factors of the
-// row's new position (the same for every layer, so they are computed once per step and not per layer)
-__global__ void meta_decode_kernel(TokenMeta m, int n, const int32_t* ctx, const uint8_t* fin, const double* inv_freq,
-                                   int half) {
-  const int i = blockIdx.x;
-  const int pos = ctx[i];
-  for (int j = threadIdx.x; j < half; j += blockDim.x) {
-    float c, s;
-    rope_cos_sin(pos, inv_freq, true, j, c, s);
-    m.rope_cs[(size_t)i * half + j] = float2{c, s};
-  }
-  if (threadIdx.x != 0) return;
-  uint8_t live = fin[i] ? 0 : 1;
-  m.tok_seq[i] = i;
-  m.tok_pos[i] = pos;
-  m.tok_live[i] = live;
-  m.sample_row[i] = i;
-  m.sample_pos[i] = pos + 1;
-  m.sample_on[i] = live;
-}
-
 // One workgroup.  The query tiles are listed by the keys they walk, the longest first (to a 1024th of the longest; equal ones in
 // any order), so that a grid in list order starts the long ones first and ends with short ones.
 __global__ void meta_prefill_kernel(TokenMeta m, int n_seqs, int total, const int32_t* cu, const int32_t* ctx,
@@ -97,15 +76,10 @@ __global__ __launch_bounds__(256) void rope_table_kernel(TokenMeta m, int total,
   }
 }
 
-__global__ void embed_kernel(const h16_t* embed, int vocab, int d, const int32_t* tokens, const h16_t* inj, float* h,
-                             int dtype) {
-  int t = blockIdx.x;
-  int tok = tokens[t];
-  const h16_t* src;
-  if (tok >= 0 && tok < vocab) src = embed + (size_t)tok * d;
-  else if (tok < 0 && inj) src = inj + (size_t)t * d;
-  else src = nullptr;   // out-of-range id: zero row rather than a stray read
-  for (int i = threadIdx.x; i < d; i += blockDim.x) h[(size_t)t * d + i] = src ? h16_to_f32(src[i], dtype) : 0.f;
+__global__ __launch_bounds__(256) void embed_kernel(const h16_t* embed, int vocab, int d, const int32_t* tokens, const h16_t* inj, float* h,
+                                                    int dtype) {
+  const int t = blockIdx.x;
+  embed_row(embed, vocab, d, tokens[t], inj ? inj + (size_t)t * d : nullptr, h + (size_t)t * d, dtype);
 }
 
 __device__ __forceinline__ float block_sum_256(float v, float* sh) {
@@ -602,13 +576,6 @@ __global__ void kv_copy_kernel(h16_t* pool, int64_t n_blocks, size_t block_elems
 }
 
 }  // namespace
-
-hipError_t meta_decode(const TokenMeta& m, int n_seqs, const int32_t* ctx_lens, const uint8_t* finished,
-                       const double* inv_freq, int head_dim, hipStream_t st) {
-  hipLaunchKernelGGL(meta_decode_kernel, dim3(n_seqs), dim3(64), 0, st, m, n_seqs, ctx_lens, finished, inv_freq,
-                     head_dim / 2);
-  return hipGetLastError();
-}
 
 hipError_t meta_prefill(const TokenMeta& m, int n_seqs, int total_tokens, const int32_t* cu_seqlens,
                         const int32_t* ctx_lens, const uint8_t* sample_last, const double* inv_freq, int head_dim,

@@ -137,8 +137,6 @@ struct TokenMeta {        // per packed token, built on the device at the start 
   int32_t* tok_iota;      // prefill: [T] 0, 1, 2, ... (row lists of the per-token scoring pass)
   float2* rope_cs;        // [T][hd/2] (cos, sin) of the rotary angles of each token's position
 };
-hipError_t meta_decode(const TokenMeta& m, int n_seqs, const int32_t* ctx_lens, const uint8_t* finished,
-                       const double* inv_freq, int head_dim, hipStream_t st);
 hipError_t meta_prefill(const TokenMeta& m, int n_seqs, int total_tokens, const int32_t* cu_seqlens,
                         const int32_t* ctx_lens, const uint8_t* sample_last, const double* inv_freq, int head_dim,
                         hipStream_t st);
@@ -171,7 +169,7 @@ struct RopeArgs {
   int n_planes;
   const h16_t* q_gain;      // [hd] or null
   const h16_t* k_gain;
-  const float2* rope_cs;     // [T][hd/2] (cos, sin) of each token's position (meta_decode / meta_prefill)
+  const float2* rope_cs;     // [T][hd/2] (cos, sin) of each token's position (decode_begin / meta_prefill)
   int T, Hq, Hkv, hd;
   float eps;
   const int32_t* tok_seq; const int32_t* tok_pos; const uint8_t* tok_live;
@@ -210,6 +208,7 @@ struct AttnArgs {            // prefill
 };
 hipError_t attention_prefill(const AttnArgs& a, hipStream_t st);
 
+constexpr int ATTN_SHARE_WORDS = 16;    // int32 words of a share's record in the plan
 constexpr int ATTN_SHARES_MAX = 2048;   // decode attention: four waves of two workgroups on 256 compute units
 struct AttnDecodeArgs {      // one new token per sequence: row = sequence slot
   RowAct q;                  // [planes][n_seqs, Hq*hd] rotated queries
@@ -219,9 +218,9 @@ struct AttnDecodeArgs {      // one new token per sequence: row = sequence slot
   const int32_t* block_table; int max_blocks;
   const int32_t* ctx_lens;   // cached length before this call = position of the new token
   int n_seqs;
-  // plan of the step (attention_decode_plan): 32-key units of all (sequence, KV head) pairs end to end
+  // plan of the step (decode_begin): 32-key units of all (sequence, KV head) pairs end to end
   const int32_t* unit_prefix;  // [n_seqs + 1] exclusive prefix of the per-sequence unit counts (0 for inert rows)
-  const int32_t* share_seq;    // [ATTN_SHARES_MAX] sequence in which a share starts
+  const int32_t* share_start;  // [ATTN_SHARES_MAX][ATTN_SHARE_WORDS] where a share starts
   const int32_t* plan_hdr;     // [4] units of the first H shares, total units, units of the others, H
   bool team;                   // a share of the unit sequence per workgroup (MoE policies), else per wave
   int n_wgs;                   // grid size; at most ATTN_SHARES_MAX shares
@@ -251,9 +250,21 @@ inline size_t shared_prefix_words(int n_seqs, int Hkv) {
 }
 // fills `words` (shared_prefix_words entries) from per-sequence group leaders and shared page counts (host arrays)
 void shared_prefix_build(int n_seqs, int Hq, int Hkv, const int32_t* leader, const int32_t* shared_pages, int32_t* words);
-hipError_t attention_decode_plan(int n_seqs, const int32_t* ctx_lens, const uint8_t* tok_live, int Hkv, int n_wgs, bool team,
-                                 const int32_t* shared, int32_t* unit_prefix, int32_t* share_seq, int32_t* hdr,
-                                 hipStream_t st);
+// start of a decode step: token metadata, embeddings, and the plan of the step's attention on a grid of n_wgs workgroups
+struct DecodeBeginArgs {
+  int n_seqs, Hkv, head_dim;
+  const int32_t* ctx_lens; const uint8_t* finished;
+  const int32_t* block_table; int max_blocks;
+  TokenMeta meta; const double* inv_freq;
+  const h16_t* embed; int vocab, d_model, dtype;
+  const int32_t* tokens;
+  float* h;                  // [n_seqs, d_model]
+  bool team;
+  int n_shares;              // set by decode_begin
+  const int32_t* shared;     // shared-prefix descriptor or null
+  int32_t *unit_prefix, *share_start, *plan_hdr;
+};
+hipError_t decode_begin(DecodeBeginArgs b, int n_wgs, hipStream_t st);
 hipError_t attention_decode_prefix(const AttnDecodeArgs& a, hipStream_t st);   // no-op without a descriptor
 hipError_t attention_decode(const AttnDecodeArgs& a, hipStream_t st);
 hipError_t attention_decode_merge(const AttnDecodeArgs& a, hipStream_t st);   // prefix parts, straddling pairs, inert rows
