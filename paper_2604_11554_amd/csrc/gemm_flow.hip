@@ -17,6 +17,7 @@
 //   q|k|v      9.8 ->  7.5  10.9 -> 10.4  11.5 -> 11.9  17.5 -> 15.4  (17.9 -> 19.2)   with two fifths fewer planes
 //   o          7.1 ->  5.7   9.3 ->  7.7   9.8 ->  8.6  12.8 -> 11.2  (13.4 -> 14.0)
 //   down      12.7 ->  9.8  15.4 -> 12.8  15.8 -> 14.5  24.5 -> 19.1  (25.2 -> 23.4)
+//   LM head    128 ->  115
 #include <mutex>
 
 #include "gemm_core.h"
@@ -32,7 +33,7 @@ struct FlowTiling {
   static constexpr int TILES = RT * NT, LOADS = RT + NT * PL;
   static constexpr int D = LOADS <= 4 ? 4 : 2;                             // steps loaded ahead
   static constexpr int NR = TILES <= 32 ? FLOW_WAVES : FLOW_WAVES / 2;     // waves whose sums are in LDS at a time
-  static constexpr int LDS_BYTES = TILES * NR * 1024 + 16 * NT * 4;
+  static constexpr int LDS_BYTES = TILES * NR * 1024 + 16 * NT * 16;       // and, per token, its factor or its LmRow
 };
 
 // Loads by buffer descriptor: uniform base, uniform offset of the step, 32-bit lane offset.  A lane whose offset lies past the
@@ -93,13 +94,20 @@ __global__ __launch_bounds__(64 * FLOW_WAVES, 1) void gemm_flow_kernel(GemmArgs 
   }
   // the rows' factors (Act::ss) are requested first of all and settled behind the first steps' loads
   f32x4 ssq = {1.f, 1.f, 1.f, 1.f};
-  const bool scaled = a.x_ss != nullptr;
+  const bool scaled = EPI != EPI_LMHEAD && a.x_ss != nullptr;
+  LmRow* lm_lds = reinterpret_cast<LmRow*>(lds_raw + TL::TILES * NR * 1024);
+  LmRow lm = {};                                     // LM head: of token threadIdx.x
+  if (EPI == EPI_LMHEAD) lm = lm_row(a, (int)threadIdx.x);
   if (scaled) ssq = row_ss(a, min((int)threadIdx.x, a.T - 1));
   __builtin_amdgcn_sched_barrier(0);
 
+  // Where the activations outweigh the weights the workgroups start at different steps: all of them reading the same lines of
+  // the activations at the same time made the 4B shape's step of 64 tokens 2.8 % longer (5325 -> 5175 us; 45 tokens 1.0 %, 96
+  // 1.9 %; fp16 120 2.0 %); with fewer activations (fp16 45 tokens, bf16 up to 16) nothing or 0.5 % the other way.
+  const int rot = NT * PL >= 4 && n > 0 ? (int)blockIdx.x % n : 0;
   struct Step { u32x4 w[RT], x[NT * PL]; };
   auto load = [&](int i, Step& d) {
-    const int s = s_b + wave + NW * i;
+    const int s = i < n ? s_b + wave + NW * (i + rot < n ? i + rot : i + rot - n) : s_e;
     const uint32_t gone = (s >= s_e || (2 * s + 1 >= KS && kg >= 2)) ? NOWHERE : 0u;
     const uint32_t ws = (uint32_t)s * (2 * W_KSTRIDE * 2), xs = (uint32_t)s * 2 * x_kstride;
 #pragma unroll
@@ -121,6 +129,7 @@ __global__ __launch_bounds__(64 * FLOW_WAVES, 1) void gemm_flow_kernel(GemmArgs 
   float rstd = 1.f;
   if (scaled) rstd = row_rstd(a, ssq);
   asm volatile("" : "+v"(rstd));
+  if (EPI == EPI_LMHEAD) asm volatile("" : "+v"(lm.temperature), "+v"(lm.seed), "+v"(lm.pos));
   __builtin_amdgcn_sched_barrier(0);
   for (int i = 0; i < n; i += D)
 #pragma unroll
@@ -137,6 +146,7 @@ __global__ __launch_bounds__(64 * FLOW_WAVES, 1) void gemm_flow_kernel(GemmArgs 
 
   // ---- the waves' sums, tile by tile in wave order ----
   if (scaled && (int)threadIdx.x < 16 * NT) rs_lds[threadIdx.x] = rstd;
+  if (EPI == EPI_LMHEAD && (int)threadIdx.x < 16 * NT) lm_lds[threadIdx.x] = lm;
   auto put = [&]() {
 #pragma unroll
     for (int r = 0; r < RT; ++r)
@@ -157,10 +167,36 @@ __global__ __launch_bounds__(64 * FLOW_WAVES, 1) void gemm_flow_kernel(GemmArgs 
     put();
   }
   __syncthreads();
-  for (int tile = wave; tile < TL::TILES; tile += NW) {
+  auto sum_of = [&](int tile) {
     f32x4 v = red[tile * NR * WAVE + lane];
 #pragma unroll
     for (int w = 1; w < NR; ++w) v += red[(tile * NR + w) * WAVE + lane];
+    return v;
+  };
+  if constexpr (EPI == EPI_LMHEAD) {
+    // a part is 32 vocabulary rows, two row tiles: lane = token c16 of the token tile, rows 4 kg .. 4 kg + 3 of each
+    static_assert(RT % 2 == 0, "whole parts");
+    const int n_parts = n_half / 2;
+    for (int p = wave; p < TL::TILES / 2; p += NW) {
+      const int part = ht0 / 2 + p / NT, tt = p % NT, t = 16 * tt + c16;
+      if (part >= n_parts) break;                    // uniform
+      LmSums s;
+      if (t < a.T) {
+        const LmRow row = lm_lds[t];
+#pragma unroll 1
+        for (int h = 0; h < 2; ++h) {
+          const int nrow = 32 * part + 16 * h + 4 * kg;
+          if (nrow < a.N) lm_add(a, s, sum_of((2 * (p / NT) + h) * NT + tt), t, nrow, row);
+        }
+      }
+      lm_merge_lanes(s, 16, kg & 1);
+      lm_merge_lanes(s, 32, kg >> 1);
+      if (t < a.T && kg == 0) lm_store(a, s, t, part, n_parts);
+    }
+    return;
+  }
+  for (int tile = wave; tile < TL::TILES; tile += NW) {
+    f32x4 v = sum_of(tile);
     const int ht = ht0 + tile / NT, t = 16 * (tile % NT) + c16;
     if (scaled) v *= rs_lds[16 * (tile % NT) + c16];
     if (ht >= n_half) continue;
@@ -273,13 +309,17 @@ int flow_swiglu_rt(int F, int T, int n_units) {
 
 }  // namespace
 
-// stores of two terms: up to 96 tokens (the table above; at 97 to 128 the skinny form's two groups of 64 are as fast or faster)
-bool gemm_flow_store_form(int T, int planes, int dtype) { return flow_format(planes, dtype) && T <= (planes == 2 ? 96 : 128); }
+// Stores of two terms: up to 96 tokens (at 97 to 128 the skinny form's two groups of 64 are as fast or faster), and not where four
+// full token tiles meet more rows than columns: 4B shape's q|k|v, 64 tokens, 11.9 us against 11.5 in the skinny form.
+bool gemm_flow_store_form(int N, int K, int T, int planes, int dtype) {
+  if (!flow_format(planes, dtype)) return false;
+  return planes == 1 ? T <= 128 : T <= 96 && !(T > 48 && T <= 64 && N > K);
+}
 int gemm_flow_splits(int N, int K, int T, int max_splits, int n_units, int planes) {
   return plan_flow(N, K, T, max_splits, n_units, planes).splits;
 }
 hipError_t gemm_flow_store(const LinearW& w, const Act& x, int T, float* y, int ldy, int max_splits, int n_units, hipStream_t st) {
-  if (!gemm_flow_store_form(T, x.planes, x.dtype) || x.pitch) return hipErrorInvalidValue;
+  if (!gemm_flow_store_form(w.N, w.K, T, x.planes, x.dtype) || x.pitch) return hipErrorInvalidValue;
   const FlowPlan plan = plan_flow(w.N, w.K, T, max_splits, n_units, x.planes);
   GemmArgs a = flow_args(x, w.N, w.K, T, plan.splits);
   for (int i = 0; i < 3; ++i) { a.w[i] = w.seg[i]; a.w_tiles[i] = (w.rows[i] + 31) / 32; }
@@ -305,6 +345,20 @@ hipError_t gemm_flow_swiglu(const h16_t* w_gate_up, int F, int K, const Act& x, 
   else if (rt == 5) launch_flow<5, EPI_SWIGLU>(a, 1, x, st);
   else if (rt == 6) launch_flow<6, EPI_SWIGLU>(a, 1, x, st);
   else launch_flow<8, EPI_SWIGLU>(a, 1, x, st);
+  return hipGetLastError();
+}
+
+// LM heads of one token tile (151 936 x 2560, 1 token: 128 us in the skinny form, 115 in this one; of more, where the activations
+// weigh as much as the weights and the sums through LDS more: 45 tokens in fp16 157 and 171, 64 in bf16 170 and 196)
+bool gemm_flow_lmhead_form(int T, int planes, int dtype) { return flow_format(planes, dtype) && T <= 16; }
+hipError_t gemm_flow_lmhead(const h16_t* w_lm, int V, int K, const Act& x, int T, float* logits, float* part, const uint64_t* seeds,
+                            const float* temperature, const int32_t* sample_pos, const int32_t* row_seq, bool draw, hipStream_t st) {
+  if (!gemm_flow_lmhead_form(T, x.planes, x.dtype) || x.pitch || x.ss) return hipErrorInvalidValue;
+  GemmArgs a = flow_args(x, V, K, T, 1);
+  a.w[0] = w_lm; a.w_tiles[0] = (V + 31) / 32;
+  a.logits = logits; a.part = part; a.seeds = seeds; a.temperature = temperature; a.sample_pos = sample_pos;
+  a.row_seq = row_seq; a.draw = draw ? 1 : 0;
+  launch_flow_fmt<8, 1, EPI_LMHEAD>(a, dim3(((V + 31) / 32 * 2 + 7) / 8), x, st);
   return hipGetLastError();
 }
 
