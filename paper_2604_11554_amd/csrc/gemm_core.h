@@ -160,58 +160,6 @@ __device__ __forceinline__ LmRow lm_row(const GemmArgs& a, int t) {
   if (a.draw) { r.seed = a.seeds[tc]; r.pos = (uint32_t)a.sample_pos[tc]; }
   return r;
 }
-struct LmSums { float mx = -INFINITY, se = 0.f, best = -INFINITY; int besti = 0x7FFFFFFF; };
-// four vocabulary rows nrow .. nrow + 3 (nrow a multiple of 4, below N) of token t: logits v
-__device__ __forceinline__ void lm_add(const GemmArgs& a, LmSums& s, const f32x4& v, int t, int nrow, const LmRow& row) {
-  const float temp = row.temperature, invt = temp > 0.f ? 1.f / temp : 1.f;
-  const bool draw = a.draw != 0 && temp > 0.f;                // uniform over the launch when draw == 0
-  if (a.logits) {
-    if (nrow + 3 < a.N) {
-      *reinterpret_cast<f32x4*>(a.logits + (size_t)t * a.N + nrow) = v;
-    } else {
-#pragma unroll
-      for (int j = 0; j < 4; ++j)
-        if (nrow + j < a.N) a.logits[(size_t)t * a.N + nrow + j] = v[j];
-    }
-  }
-  float z[4], sc[4];
-#pragma unroll
-  for (int j = 0; j < 4; ++j) z[j] = sc[j] = nrow + j < a.N ? v[j] * invt : -INFINITY;
-  if (a.draw) {
-    uint32_t rnd[4];                                          // one Philox block covers the four ids
-    philox4x32_10((uint32_t)(nrow >> 2), row.pos, 0u, 0u, (uint32_t)row.seed, (uint32_t)(row.seed >> 32), rnd);
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      float noise = gumbel_from_u32(rnd[j]);
-      asm volatile("" : "+v"(noise));                         // computed for all lanes: no branch per id
-      sc[j] = draw ? z[j] + noise : z[j];
-    }
-  }
-#pragma unroll
-  for (int j = 0; j < 4; ++j)
-    if (sc[j] > s.best) { s.best = sc[j]; s.besti = nrow + j; }   // ascending ids: ties keep the smaller one
-  const float nm = fmaxf(s.mx, fmaxf(fmaxf(z[0], z[1]), fmaxf(z[2], z[3])));
-  s.se = s.se * __expf(s.mx - nm) + ((__expf(z[0] - nm) + __expf(z[1] - nm)) + (__expf(z[2] - nm) + __expf(z[3] - nm)));
-  s.mx = nm;
-}
-// merge with the lane `mask` apart that holds other rows of the same token; both end up with the same bits
-__device__ __forceinline__ void lm_merge_lanes(LmSums& s, int mask, bool upper) {
-  const float omx = __shfl_xor(s.mx, mask, WAVE), ose = __shfl_xor(s.se, mask, WAVE);
-  const float obest = __shfl_xor(s.best, mask, WAVE);
-  const int obesti = __shfl_xor(s.besti, mask, WAVE);
-  if (obest > s.best || (obest == s.best && obesti < s.besti)) { s.best = obest; s.besti = obesti; }
-  const float nm = fmaxf(s.mx, omx);
-  if (nm > -INFINITY) {
-    // fixed operand order: lower lanes first
-    const float lo_m = upper ? omx : s.mx, lo_s = upper ? ose : s.se, hi_m = upper ? s.mx : omx, hi_s = upper ? s.se : ose;
-    s.se = lo_s * (lo_m == -INFINITY ? 0.f : __expf(lo_m - nm)) + hi_s * (hi_m == -INFINITY ? 0.f : __expf(hi_m - nm));
-    s.mx = nm;
-  }
-}
-__device__ __forceinline__ void lm_store(const GemmArgs& a, const LmSums& s, int t, int part, int n_parts) {
-  const f32x4 pv = {s.mx, s.se, s.best, __int_as_float(s.besti)};
-  *reinterpret_cast<f32x4*>(a.part + ((size_t)t * n_parts + part) * 4) = pv;
-}
 template <int JT, int MT>
 __device__ __forceinline__ void lmhead_epilogue(const GemmArgs& a, f32x4* scr, const f32x16 (&acc)[JT][MT], const LmRow (&row)[MT],
                                                 int nt0, int mt0, int part, int n_parts, int lane) {
@@ -227,17 +175,64 @@ __device__ __forceinline__ void lmhead_epilogue(const GemmArgs& a, f32x4* scr, c
   for (int m = 0; m < MT; ++m) {
     const int t = (mt0 + m) * 32 + r32;
     const bool ok = t < a.T;
-    LmSums s;
+    float mx = -INFINITY, se = 0.f, best = -INFINITY;
+    int besti = 0x7FFFFFFF;
     if (ok) {
+      const float temp = row[m].temperature, invt = temp > 0.f ? 1.f / temp : 1.f;
+      const bool draw = a.draw != 0 && temp > 0.f;            // uniform over the launch when draw == 0
+      const uint64_t seed = row[m].seed;
+      const uint32_t pos = row[m].pos;
 #pragma unroll 1
       for (int i = 0; i < 4 * JT; ++i) {
-        const int nrow = nt0 * 32 + 8 * i + 4 * half;
+        const int nrow = nt0 * 32 + 8 * i + 4 * half;         // multiple of 4: one Philox block covers the four ids
         if (nrow >= a.N) break;
-        lm_add(a, s, scr[(m * JT * 4 + i) * WAVE + lane], t, nrow, row[m]);
+        const f32x4 v = scr[(m * JT * 4 + i) * WAVE + lane];
+        if (a.logits) {
+          if (nrow + 3 < a.N) {
+            *reinterpret_cast<f32x4*>(a.logits + (size_t)t * a.N + nrow) = v;
+          } else {
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+              if (nrow + j < a.N) a.logits[(size_t)t * a.N + nrow + j] = v[j];
+          }
+        }
+        float z[4], sc[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) z[j] = sc[j] = nrow + j < a.N ? v[j] * invt : -INFINITY;
+        if (a.draw) {
+          uint32_t rnd[4];
+          philox4x32_10((uint32_t)(nrow >> 2), pos, 0u, 0u, (uint32_t)seed, (uint32_t)(seed >> 32), rnd);
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            float noise = gumbel_from_u32(rnd[j]);
+            asm volatile("" : "+v"(noise));                     // computed for all lanes: no branch per id
+            sc[j] = draw ? z[j] + noise : z[j];
+          }
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          if (sc[j] > best) { best = sc[j]; besti = nrow + j; }   // ascending ids: ties keep the smaller one
+        const float nm = fmaxf(mx, fmaxf(fmaxf(z[0], z[1]), fmaxf(z[2], z[3])));
+        se = se * __expf(mx - nm) + ((__expf(z[0] - nm) + __expf(z[1] - nm)) + (__expf(z[2] - nm) + __expf(z[3] - nm)));
+        mx = nm;
       }
     }
-    lm_merge_lanes(s, 32, half != 0);                 // rows 8i + 0..3 and 8i + 4..7 of the same token
-    if (ok && half == 0) lm_store(a, s, t, part, n_parts);
+    // merge the two half-waves (rows 8i+0..3 and 8i+4..7) of the same token
+    const float omx = __shfl_xor(mx, 32, WAVE), ose = __shfl_xor(se, 32, WAVE);
+    const float obest = __shfl_xor(best, 32, WAVE);
+    const int obesti = __shfl_xor(besti, 32, WAVE);
+    if (obest > best || (obest == best && obesti < besti)) { best = obest; besti = obesti; }
+    const float nm = fmaxf(mx, omx);
+    if (nm > -INFINITY) {
+      // fixed operand order (lower half first) so both half-waves compute the same bits
+      const float lo_m = half ? omx : mx, lo_s = half ? ose : se, hi_m = half ? mx : omx, hi_s = half ? se : ose;
+      se = lo_s * (lo_m == -INFINITY ? 0.f : __expf(lo_m - nm)) + hi_s * (hi_m == -INFINITY ? 0.f : __expf(hi_m - nm));
+      mx = nm;
+    }
+    if (ok && half == 0) {
+      const f32x4 pv = {mx, se, best, __int_as_float(besti)};
+      *reinterpret_cast<f32x4*>(a.part + ((size_t)t * n_parts + part) * 4) = pv;
+    }
   }
 }
 

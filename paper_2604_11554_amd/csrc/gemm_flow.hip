@@ -49,6 +49,63 @@ __device__ __forceinline__ u32x4 desc_load(Desc d, uint32_t lane, uint32_t step)
   return __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(d, (int)lane, (int)step, AUX));
 }
 
+// ---- LM head: sums of a lane's vocabulary rows ----
+// (The steps are those of lmhead_epilogue; as functions that both used they made its loop, 2 to 4 % of a long LM head, slower.)
+struct LmSums { float mx = -INFINITY, se = 0.f, best = -INFINITY; int besti = 0x7FFFFFFF; };
+__device__ __forceinline__ float lm_scale(const LmRow& r) { return r.temperature > 0.f ? 1.f / r.temperature : 1.f; }
+__device__ __forceinline__ bool lm_draws(const GemmArgs& a, const LmRow& r) { return a.draw != 0 && r.temperature > 0.f; }   // uniform over the launch when draw == 0
+// four vocabulary rows nrow .. nrow + 3 (nrow a multiple of 4, below N) of token t: logits v; invt and draw are the row's
+// lm_scale() and lm_draws()
+__device__ __forceinline__ void lm_add(const GemmArgs& a, LmSums& s, const f32x4& v, int t, int nrow, const LmRow& row, float invt,
+                                       bool draw) {
+  if (a.logits) {
+    if (nrow + 3 < a.N) {
+      *reinterpret_cast<f32x4*>(a.logits + (size_t)t * a.N + nrow) = v;
+    } else {
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        if (nrow + j < a.N) a.logits[(size_t)t * a.N + nrow + j] = v[j];
+    }
+  }
+  float z[4], sc[4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) z[j] = sc[j] = nrow + j < a.N ? v[j] * invt : -INFINITY;
+  if (a.draw) {
+    uint32_t rnd[4];                                          // one Philox block covers the four ids
+    philox4x32_10((uint32_t)(nrow >> 2), row.pos, 0u, 0u, (uint32_t)row.seed, (uint32_t)(row.seed >> 32), rnd);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      float noise = gumbel_from_u32(rnd[j]);
+      asm volatile("" : "+v"(noise));                         // computed for all lanes: no branch per id
+      sc[j] = draw ? z[j] + noise : z[j];
+    }
+  }
+#pragma unroll
+  for (int j = 0; j < 4; ++j)
+    if (sc[j] > s.best) { s.best = sc[j]; s.besti = nrow + j; }   // ascending ids: ties keep the smaller one
+  const float nm = fmaxf(s.mx, fmaxf(fmaxf(z[0], z[1]), fmaxf(z[2], z[3])));
+  s.se = s.se * __expf(s.mx - nm) + ((__expf(z[0] - nm) + __expf(z[1] - nm)) + (__expf(z[2] - nm) + __expf(z[3] - nm)));
+  s.mx = nm;
+}
+// merge with the lane `mask` apart that holds other rows of the same token; both end up with the same bits
+__device__ __forceinline__ void lm_merge_lanes(LmSums& s, int mask, bool upper) {
+  const float omx = __shfl_xor(s.mx, mask, WAVE), ose = __shfl_xor(s.se, mask, WAVE);
+  const float obest = __shfl_xor(s.best, mask, WAVE);
+  const int obesti = __shfl_xor(s.besti, mask, WAVE);
+  if (obest > s.best || (obest == s.best && obesti < s.besti)) { s.best = obest; s.besti = obesti; }
+  const float nm = fmaxf(s.mx, omx);
+  if (nm > -INFINITY) {
+    // fixed operand order: lower lanes first
+    const float lo_m = upper ? omx : s.mx, lo_s = upper ? ose : s.se, hi_m = upper ? s.mx : omx, hi_s = upper ? s.se : ose;
+    s.se = lo_s * (lo_m == -INFINITY ? 0.f : __expf(lo_m - nm)) + hi_s * (hi_m == -INFINITY ? 0.f : __expf(hi_m - nm));
+    s.mx = nm;
+  }
+}
+__device__ __forceinline__ void lm_store(const GemmArgs& a, const LmSums& s, int t, int part, int n_parts) {
+  const f32x4 pv = {s.mx, s.se, s.best, __int_as_float(s.besti)};
+  *reinterpret_cast<f32x4*>(a.part + ((size_t)t * n_parts + part) * 4) = pv;
+}
+
 template <int RT, int NT, int PL, int FMT, int EPI>
 __global__ __launch_bounds__(64 * FLOW_WAVES, 1) void gemm_flow_kernel(GemmArgs a) {
   using TL = FlowTiling<RT, NT, PL>;
@@ -183,10 +240,12 @@ __global__ __launch_bounds__(64 * FLOW_WAVES, 1) void gemm_flow_kernel(GemmArgs 
       LmSums s;
       if (t < a.T) {
         const LmRow row = lm_lds[t];
+        const float invt = lm_scale(row);
+        const bool draw = lm_draws(a, row);
 #pragma unroll 1
         for (int h = 0; h < 2; ++h) {
           const int nrow = 32 * part + 16 * h + 4 * kg;
-          if (nrow < a.N) lm_add(a, s, sum_of((2 * (p / NT) + h) * NT + tt), t, nrow, row);
+          if (nrow < a.N) lm_add(a, s, sum_of((2 * (p / NT) + h) * NT + tt), t, nrow, row, invt, draw);
         }
       }
       lm_merge_lanes(s, 16, kg & 1);

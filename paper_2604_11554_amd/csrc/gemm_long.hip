@@ -2,8 +2,8 @@
 //
 //   y[t, n] = sum_k x[t, k] * W[n, k],  x = hi + lo: two MFMA 32x32x16 per weight fragment and 32 x 32 outputs
 //
-// A workgroup of WR x WT waves computes 32 JW WR weight rows x 64 WT tokens, a wave 32 JW x 64 of them (JW weight tiles x
-// 2 token tiles: 32 JW accumulator registers).  Both operands pass through LDS, copied there by the hardware
+// A workgroup of WR x WT waves computes 32 JW WR weight rows x 32 MW WT tokens, a wave 32 JW x 32 MW of them (JW weight tiles x
+// MW token tiles: 16 JW MW accumulator registers).  Both operands pass through LDS, copied there by the hardware
 // (global_load_lds, 16 bytes per lane, no registers in between), in stages of 32 k, NB stage buffers deep.
 //  - Weights: the packed layout's fragments, 1 KB per copy, read back linearly.
 //  - Activations: rows (Act::pitch): the 32 k of a stage are one 128-byte line of a row (eight 16-byte chunks: per
@@ -24,23 +24,23 @@
 namespace rlx {
 namespace {
 
-template <int JW, int WR, int WT, int NB>
+template <int JW, int MW, int WR, int WT, int NB>
 struct LongTiling {
-  static constexpr int WAVES = WR * WT, ROWS = 32 * JW * WR, TOKENS = 64 * WT;
-  static constexpr int WFR = 2 * JW * WR, XFR = 8 * WT;            // KB of weights and of activations per stage
+  static constexpr int WAVES = WR * WT, ROWS = 32 * JW * WR, TOKENS = 32 * MW * WT;
+  static constexpr int WFR = 2 * JW * WR, XFR = 4 * MW * WT;       // KB of weights and of activations per stage
   static constexpr int STAGE = (WFR + XFR) * 1024;
-  static constexpr int PW = WFR / WAVES, PX = XFR / WAVES, P = PW + PX;   // copies per wave and stage
+  static constexpr int PW = (WFR + WAVES - 1) / WAVES, PX = XFR / WAVES, P = PW + PX;   // copies per wave and stage
   static constexpr int LDS_BYTES = NB * STAGE;
-  static_assert(WFR % WAVES == 0 && XFR % WAVES == 0, "the waves share a stage's copies evenly");
+  static_assert(XFR % WAVES == 0, "the waves share a stage's activations evenly");
 };
 
 // grid: 8 * ceil(tiles / 8) workgroups, tiles = splits x weight tiles x (token tiles, or items of the list).  The ids go
 // round robin over the eight XCDs, so XCD x takes every eighth id; each takes one contiguous eighth of the tiles, whose
 // order keeps the tiles in flight on an XCD close: `band` token tiles, then the next weight tile.
-template <int JW, int WR, int WT, int NB, int EPI>
+template <int JW, int MW, int WR, int WT, int NB, int EPI>
 __global__ __launch_bounds__(64 * WR * WT) __attribute__((amdgpu_waves_per_eu(2, 2))) void gemm_long_kernel(GemmArgs a, int n_wt,
                                                                                                            int n_tt, int band) {
-  using TL = LongTiling<JW, WR, WT, NB>;
+  using TL = LongTiling<JW, MW, WR, WT, NB>;
   constexpr int NW = TL::WAVES, STAGE = TL::STAGE, PW = TL::PW, PX = TL::PX, P = TL::P, WFR = TL::WFR;
   extern __shared__ __align__(16) unsigned char lds_raw[];
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -83,7 +83,7 @@ __global__ __launch_bounds__(64 * WR * WT) __attribute__((amdgpu_waves_per_eu(2,
   int wstep[PW];
 #pragma unroll
   for (int i = 0; i < PW; ++i) {
-    const int f = wave + NW * i, j = f % (JW * WR);
+    const int f = min(wave + NW * i, WFR - 1), j = f % (JW * WR);   // a wave short of a copy repeats the last one's bytes
     int lt = tw * JW * WR + j;
     wstep[i] = 1;
     if (lt >= n_tiles) { lt = 0; wstep[i] = 0; }     // no such tile: one cached block, its products are never stored
@@ -109,7 +109,7 @@ __global__ __launch_bounds__(64 * WR * WT) __attribute__((amdgpu_waves_per_eu(2,
     const int sc = min(s, n_cp - 1);
     const uint32_t dst = lds0 + buf * STAGE;
     if (i < PW) {
-      const int f = wave + NW * i;
+      const int f = min(wave + NW * i, WFR - 1);
       const int ks = min(ks_b + 2 * sc + f / (JW * WR), KS - 1);   // the missing half of an odd last stage: any block
       copy_to_lds(wp[i] + (size_t)(ks * wstep[i]) * W_KSTRIDE, dst + f * 1024);
     } else {
@@ -117,11 +117,11 @@ __global__ __launch_bounds__(64 * WR * WT) __attribute__((amdgpu_waves_per_eu(2,
     }
   };
 
-  f32x16 acc[JW][2];
+  f32x16 acc[JW][MW];
 #pragma unroll
   for (int j = 0; j < JW; ++j)
 #pragma unroll
-    for (int m = 0; m < 2; ++m)
+    for (int m = 0; m < MW; ++m)
 #pragma unroll
       for (int q = 0; q < 16; ++q) acc[j][m][q] = 0.f;
 
@@ -131,22 +131,22 @@ __global__ __launch_bounds__(64 * WR * WT) __attribute__((amdgpu_waves_per_eu(2,
 #pragma unroll
   for (int c = 0; c < 4; ++c) {
     const int chunk = ((c >> 1) * 2 + half) * 2 + (c & 1);
-    x_rd[c] = lds_raw + WFR * 1024 + (wt * 64 + r32) * 128 + ((chunk ^ ((r32 >> 1) & 7)) * 16);
+    x_rd[c] = lds_raw + WFR * 1024 + (wt * 32 * MW + r32) * 128 + ((chunk ^ ((r32 >> 1) & 7)) * 16);
   }
   auto read_w = [&](int buf, int kk, h16x8 (&w)[JW]) {
 #pragma unroll
     for (int j = 0; j < JW; ++j) w[j] = *reinterpret_cast<const u32x4*>(w_rd + buf * STAGE + (kk * JW * WR + j) * 1024);
   };
-  auto read_x = [&](int buf, int kk, int p, h16x8 (&x)[2]) {
+  auto read_x = [&](int buf, int kk, int p, h16x8 (&x)[MW]) {
 #pragma unroll
-    for (int m = 0; m < 2; ++m) x[m] = *reinterpret_cast<const u32x4*>(x_rd[kk * 2 + p] + buf * STAGE + m * 4096);
+    for (int m = 0; m < MW; ++m) x[m] = *reinterpret_cast<const u32x4*>(x_rd[kk * 2 + p] + buf * STAGE + m * 4096);
   };
   // half a phase: the store form swaps the operands, so that lanes run along n and registers along the tokens
-  auto products = [&](const h16x8 (&w)[JW], const h16x8 (&x)[2], int hf) {
+  auto products = [&](const h16x8 (&w)[JW], const h16x8 (&x)[MW], int hf) {
 #pragma unroll
-    for (int j = JW / 2 * hf; j < JW / 2 * (hf + 1); ++j)
+    for (int j = JW * hf / 2; j < JW * (hf + 1) / 2; ++j)
 #pragma unroll
-      for (int m = 0; m < 2; ++m)
+      for (int m = 0; m < MW; ++m)
         acc[j][m] = EPI == EPI_STORE ? mfma_32x32x16<DT_BF16>(x[m], w[j], acc[j][m]) : mfma_32x32x16<DT_BF16>(w[j], x[m], acc[j][m]);
   };
   // copies of slot k (0..5): those of the stage NB - 1 ahead, into the buffer that the last barrier released
@@ -164,7 +164,7 @@ __global__ __launch_bounds__(64 * WR * WT) __attribute__((amdgpu_waves_per_eu(2,
 #pragma unroll
     for (int i = 0; i < P; ++i) copy_one(i, s, s);
   wait_copies_and_barrier<(AHEAD - 1) * P>();
-  const int tok0 = tt * TL::TOKENS + wt * 64;        // the wave's first token (of its group)
+  const int tok0 = tt * TL::TOKENS + wt * 32 * MW;        // the wave's first token (of its group)
   int buf = 0, fbuf = AHEAD;
   if (tok0 >= a.T) {
     // all of the wave's tokens lie past the last row: it only copies, and leaves its SIMD to the waves beside it
@@ -177,7 +177,7 @@ __global__ __launch_bounds__(64 * WR * WT) __attribute__((amdgpu_waves_per_eu(2,
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     return;
   }
-  h16x8 w0[JW], w1[JW], xa[2], xb[2];
+  h16x8 w0[JW], w1[JW], xa[MW], xb[MW];
   read_w(0, 0, w0);
   read_x(0, 0, 1, xa);
   __builtin_amdgcn_sched_barrier(0);
@@ -223,17 +223,15 @@ __global__ __launch_bounds__(64 * WR * WT) __attribute__((amdgpu_waves_per_eu(2,
     products(w0, xb, 0);
     products(w0, xb, 1);
   }
-  // factors that the norm left to this kernel (Act::ss): the lane's tokens r32 and 32 + r32
-  float rs[2] = {1.f, 1.f};
-  if (EPI != EPI_LMHEAD && a.x_ss) {
+  // factors that the norm left to this kernel (Act::ss): the lane's tokens 32 m + r32
+  float rs[MW];
+  LmRow lm[MW];
 #pragma unroll
-    for (int m = 0; m < 2; ++m) {
-      const int t = tok0 + m * 32 + r32;
-      rs[m] = row_rstd(a, row_ss(a, t < a.T ? t : 0));
-    }
+  for (int m = 0; m < MW; ++m) {
+    const int t = tok0 + m * 32 + r32;
+    rs[m] = EPI != EPI_LMHEAD && a.x_ss ? row_rstd(a, row_ss(a, t < a.T ? t : 0)) : 1.f;
+    if constexpr (EPI == EPI_LMHEAD) lm[m] = lm_row(a, t);
   }
-  LmRow lm[2];
-  if constexpr (EPI == EPI_LMHEAD) { lm[0] = lm_row(a, tok0 + r32); lm[1] = lm_row(a, tok0 + 32 + r32); }
   // no copy may outlive the workgroup's LDS, and no fragment read of the last k-step the barrier of the LM head below
   asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
 
@@ -242,7 +240,7 @@ __global__ __launch_bounds__(64 * WR * WT) __attribute__((amdgpu_waves_per_eu(2,
     // lane = weight row r32 of a tile, register q = token 8 (q / 4) + 4 half + q % 4
     float* y = a.y + ((size_t)split * a.T + row_base + tok0) * a.ldy + (size_t)nt0 * 32 + r32;
 #pragma unroll
-    for (int m = 0; m < 2; ++m)
+    for (int m = 0; m < MW; ++m)
 #pragma unroll
       for (int q = 0; q < 16; ++q) {
         const int t = m * 32 + 8 * (q >> 2) + 4 * half + (q & 3);
@@ -261,7 +259,7 @@ __global__ __launch_bounds__(64 * WR * WT) __attribute__((amdgpu_waves_per_eu(2,
       const int nt = nt0 + j;
       if (nt >= n_tiles) continue;
 #pragma unroll
-      for (int m = 0; m < 2; ++m) {
+      for (int m = 0; m < MW; ++m) {
         uint32_t hi[2][2], lo[2][2];
 #pragma unroll
         for (int g = 0; g < 2; ++g) {
@@ -289,7 +287,8 @@ __global__ __launch_bounds__(64 * WR * WT) __attribute__((amdgpu_waves_per_eu(2,
         }
       }
     }
-  } else {
+  } else if constexpr (EPI == EPI_LMHEAD) {
+    static_assert(EPI != EPI_LMHEAD || (MW == 2 && JW % 2 == 0), "parts of two weight tiles");
     // every wave's copies and fragment reads are complete once it is past this barrier (waves without tokens have left; a
     // barrier counts those that run): the stage buffers become the waves' scratch, two weight tiles at a time
     asm volatile("s_barrier" ::: "memory");
@@ -303,16 +302,16 @@ __global__ __launch_bounds__(64 * WR * WT) __attribute__((amdgpu_waves_per_eu(2,
   }
 }
 
-template <int JW, int WR, int WT, int NB, int EPI>
+template <int JW, int MW, int WR, int WT, int NB, int EPI>
 void launch_form(const GemmArgs& a, int n_wt, int n_tt, int band, hipStream_t st) {
-  using TL = LongTiling<JW, WR, WT, NB>;
+  using TL = LongTiling<JW, MW, WR, WT, NB>;
   static std::once_flag attr_once;                   // raise the dynamic LDS limit once per instantiation, from any thread
   std::call_once(attr_once, [] {
-    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_long_kernel<JW, WR, WT, NB, EPI>),
+    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_long_kernel<JW, MW, WR, WT, NB, EPI>),
                               hipFuncAttributeMaxDynamicSharedMemorySize, TL::LDS_BYTES);
   });
   const long tiles = (long)n_wt * n_tt * a.splits;
-  hipLaunchKernelGGL((gemm_long_kernel<JW, WR, WT, NB, EPI>), dim3((unsigned)((tiles + 7) / 8 * 8)), dim3(64 * TL::WAVES),
+  hipLaunchKernelGGL((gemm_long_kernel<JW, MW, WR, WT, NB, EPI>), dim3((unsigned)((tiles + 7) / 8 * 8)), dim3(64 * TL::WAVES),
                      TL::LDS_BYTES, st, a, n_wt, n_tt, band);
 }
 
@@ -321,24 +320,28 @@ void launch_long(const GemmArgs& a, int form, int n_items, hipStream_t st) {
   const int n_tiles = (a.N + 31) / 32;
   auto tt = [&](int tokens) { return n_items ? n_items : (a.T + tokens - 1) / tokens; };
   auto wt = [&](int rows) { return (n_tiles * 32 + rows - 1) / rows; };
-  if (form == LONG_512x128) launch_form<4, 4, 2, 3, EPI>(a, wt(512), tt(128), 4, st);
-  else if (form == LONG_128x128) launch_form<2, 2, 2, 3, EPI>(a, wt(128), tt(128), 8, st);
-  else if constexpr (EPI != EPI_LMHEAD) launch_form<4, 4, 1, 2, EPI>(a, wt(512), tt(64), 8, st);   // grouped only
+  if (form == LONG_512x128) launch_form<4, 2, 4, 2, 3, EPI>(a, wt(512), tt(128), 4, st);
+  else if (form == LONG_128x128) launch_form<2, 2, 2, 2, 3, EPI>(a, wt(128), tt(128), 8, st);
+  else if constexpr (EPI != EPI_LMHEAD) {
+    if (form == LONG_160x128) launch_form<5, 1, 1, 4, 5, EPI>(a, wt(160), tt(128), 8, st);
+    else if (form == LONG_192x128) launch_form<6, 1, 1, 4, 5, EPI>(a, wt(192), tt(128), 8, st);
+    else launch_form<4, 2, 4, 1, 2, EPI>(a, wt(512), tt(64), 8, st);     // grouped only
+  }
 }
 
 // ---- which form, and into how many planes K is cut ----
 // 512 x 128 (eight waves, one workgroup per unit) has the better rate when the device is full many times over, 128 x 128
-// (four waves, two workgroups per unit) an eighth of its step in size, and what decides at a few hundred to a few thousand
-// tokens is how well the workgroups fit the units.  A launch of 512 x 128 takes about rounds x (10 + 1.4 stages) us,
-// rounds = ceil(workgroups / units); one of 128 x 128 3 + 0.85 stages per two workgroups on every unit, and for the rest
-// 0.44 per stage where a unit gets one of them, 0.85 where some get two; a plane more costs its write and read.  The
-// constants were fitted to a sweep over the two model shapes (N 128..19456, K 2048..9728), 260..8192 tokens and 1, 2 and
-// 4 planes, where the choice is within 10 % of the best of the sweep everywhere and 1 % behind it in the mean.  E.g.
-// 1437 tokens, N 2560, K 9728: 512 x 128 whole 324 us, 128 x 128 whole 135, 512 x 128 in four planes 122; 3000 tokens,
-// N 6144, K 2560: 512 x 128 217 us, 128 x 128 174; 8192 tokens: 375 and 428.  (256 x 128 tiles were never the best.)
+// (four waves, two workgroups per unit) an eighth of its step in size, 160 x 128 and 192 x 128 (four waves, one per unit, a wave
+// all weight rows and 32 tokens) make one even round of 129 to 512 tokens where the others fill it and a half; what decides
+// at a few hundred to a few thousand tokens is how well the workgroups fit the units.  The constants (us: start of a round, and
+// per stage) were fitted to a sweep of the products of the two model shapes (N 2048..19456, K 2048..9728), 140..8192 tokens and
+// 1 to 8 planes, where the choice is 0.1 % behind the best of the sweep in the mean and 4 % at worst.  E.g. gate/up of 256
+// tokens, N 19456, K 2560: 128 x 128 (304 workgroups) 65 us, 160 x 128 (244) 51; 1437 tokens, N 6144, K 2560: 128 x 128 in two
+// planes 96 us, 512 x 128 in three 88; 8192 tokens, N 2560, K 9728: 128 x 128 692, 512 x 128 in two planes 629.
 struct LongPlan { int form, splits; };
-// `finest`: as many planes as there may be, in the form that is faster with them.
-static LongPlan plan_long(int N, int K, int T, int max_splits, int n_units, bool finest) {
+// `finest`: as many planes as there may be, in the form that is faster with them.  `lmhead`: the forms that its
+// epilogue is built for, whose rounds it makes longer where nothing runs beside them (256 rows: 444 us in 512 x 128, 410 in 128 x 128).
+static LongPlan plan_long(int N, int K, int T, int max_splits, int n_units, bool finest, bool lmhead) {
   const int stages = (K / 16 + 1) / 2;
   LongPlan best = {LONG_512x128, 1};
   float best_us = 1e30f;
@@ -347,13 +350,21 @@ static LongPlan plan_long(int N, int K, int T, int max_splits, int n_units, bool
     if (s > 1 && ((s - 1) * per >= stages || per < 8)) continue;   // no empty split, no split of a few stages
     if (finest) best_us = 1e30f;
     const long wg_t = (long)((T + 127) / 128) * s;
-    const float planes_us = (float)(s - 1) * (float)T * (float)N * 1.1e-6f;
-    const long r512 = (wg_t * ((N + 511) / 512) + n_units - 1) / n_units;
-    const float t512 = (float)r512 * (10.f + 1.4f * (float)per) + planes_us;
-    if (t512 < best_us) { best_us = t512; best = {LONG_512x128, s}; }
+    const float planes_us = (float)(s - 1) * (float)T * (float)N * 0.94e-6f;
+    auto alone = [&](int form, int rows, float start, float stage) {   // one workgroup per unit; a last round that is not full is a little shorter
+      const long w = wg_t * ((N + rows - 1) / rows), rounds = (w + n_units - 1) / n_units;
+      const float full = (float)(w - (rounds - 1) * n_units) / (float)n_units;
+      const float us = (float)rounds * (start + stage * (float)per) - 0.1f * (1.f - full) * stage * (float)per + planes_us;
+      if (us < best_us) { best_us = us; best = {form, s}; }
+    };
+    alone(LONG_512x128, 512, lmhead ? 10.f : 5.0f, lmhead ? 1.4f : 1.29f);
+    if (!lmhead) {
+      alone(LONG_160x128, 160, 3.8f, 0.67f);
+      alone(LONG_192x128, 192, 3.2f, 0.785f);
+    }
     const long w128 = wg_t * ((N + 127) / 128), full = w128 / (2 * n_units), rest = w128 % (2 * n_units);
-    float t128 = 3.f + (float)full * (3.f + 0.85f * (float)per) + planes_us;
-    if (rest) t128 += 3.f + (rest <= n_units ? 0.44f : 0.85f) * (float)per;
+    float t128 = (float)full * (3.5f + 0.79f * (float)per) + planes_us;
+    if (rest) t128 += 3.5f + (rest <= n_units ? 0.464f : 0.79f) * (float)per;
     if (t128 < best_us) { best_us = t128; best = {LONG_128x128, s}; }
   }
   return best;
@@ -369,7 +380,7 @@ static int grouped_form(int tile_rows) { return tile_rows == 64 ? LONG_512x64 : 
 int gemm_long_item_rows(int expected_rows) { return expected_rows <= 48 ? 64 : 128; }
 
 int gemm_long_splits(int N, int K, int T, int max_splits, int n_units, bool finest) {
-  return plan_long(N, K, T, max_splits, n_units, finest).splits;
+  return plan_long(N, K, T, max_splits, n_units, finest, false).splits;
 }
 
 static void fill_long(GemmArgs& a, const Act& x, int N, int K, int T) {
@@ -381,7 +392,7 @@ static void fill_long(GemmArgs& a, const Act& x, int N, int K, int T) {
 
 hipError_t gemm_long_store(const LinearW& w, const Act& x, int T, float* y, int ldy, int max_splits, int n_units, bool finest,
                            hipStream_t st) {
-  const LongPlan plan = plan_long(w.N, w.K, T, max_splits, n_units, finest);
+  const LongPlan plan = plan_long(w.N, w.K, T, max_splits, n_units, finest, false);
   GemmArgs a = {};
   fill_long(a, x, w.N, w.K, T);
   for (int i = 0; i < 3; ++i) { a.w[i] = w.seg[i]; a.w_tiles[i] = (w.rows[i] + 31) / 32; }
@@ -398,7 +409,7 @@ hipError_t gemm_long_swiglu(const h16_t* w_gate_up, int F, int K, const Act& x, 
   fill_long(a, x, 2 * F, K, T);
   a.w[0] = w_gate_up; a.w_tiles[0] = F / 16;
   a.act = act.p; a.act_pitch = act.pitch;
-  launch_long<EPI_SWIGLU>(a, plan_long(2 * F, K, T, 1, n_units, false).form, 0, st);
+  launch_long<EPI_SWIGLU>(a, plan_long(2 * F, K, T, 1, n_units, false, false).form, 0, st);
   return hipGetLastError();
 }
 
@@ -433,7 +444,7 @@ hipError_t gemm_long_lmhead(const h16_t* w_lm, int V, int K, const Act& x, int T
   a.w[0] = w_lm; a.w_tiles[0] = (V + 31) / 32;
   a.logits = logits; a.part = part; a.seeds = seeds; a.temperature = temperature; a.sample_pos = sample_pos;
   a.row_seq = row_seq; a.draw = draw ? 1 : 0;
-  launch_long<EPI_LMHEAD>(a, plan_long(V, K, T, 1, n_units, false).form, 0, st);
+  launch_long<EPI_LMHEAD>(a, plan_long(V, K, T, 1, n_units, false, true).form, 0, st);
   return hipGetLastError();
 }
 

@@ -109,7 +109,7 @@ hipError_t gemm_flow_lmhead(const h16_t* w_lm, int V, int K, const Act& x, int T
                             const float* temperature, const int32_t* sample_pos, const int32_t* row_seq, bool draw, hipStream_t st);
 
 // ---- gemm_long.hip: the same products for long calls on two-term bf16 activations in rows (Act::pitch) ----
-enum { LONG_512x128 = 0, LONG_128x128, LONG_512x64 };   // weight rows x tokens of a workgroup
+enum { LONG_512x128 = 0, LONG_128x128, LONG_512x64, LONG_160x128, LONG_192x128 };   // weight rows x tokens of a workgroup
 // y[split][t][n]: K cut into gemm_long_splits() planes, at most max_splits: the fastest number, or the largest (`finest`)
 int gemm_long_splits(int N, int K, int T, int max_splits, int n_units, bool finest);
 hipError_t gemm_long_store(const LinearW& w, const Act& x, int T, float* y, int ldy, int max_splits, int n_units, bool finest,

@@ -18,16 +18,29 @@ TOKENS = (1, 15, 16, 17, 32, 33, 48, 49, 64, 65, 96, 97, 128)
 BAR = {"bf16": (1e-4, 7e-3), "f16": (5e-3, 1e-2)}
 
 
+# ... and where the long-call form begins: gate/up in tiles of 160 (9728) and of 192 (11008) weight rows
+LONG = (129, 200, 256, 257, 300)
+
+
+@pytest.mark.parametrize("d_model,d_ff", [(528, 9728), (528, 11008), (80, 9744)])
+def test_calls_just_above_match_the_oracle(d_model, d_ff):
+    _compare(d_model, d_ff, "bf16", LONG)
+
+
 @pytest.mark.parametrize("fmt", ["bf16", "f16"])
 @pytest.mark.parametrize("d_model,d_ff", [(256, 688), (80, 4112), (528, 8208), (80, 9728), (80, 10256), (80, 12304), (80, 16400)])
 def test_short_calls_match_the_oracle(d_model, d_ff, fmt):
+    _compare(d_model, d_ff, fmt, TOKENS)
+
+
+def _compare(d_model, d_ff, fmt, tokens):
     import paper_2604_11554_amd as pkg
     from paper_2604_11554_amd import synthetic
 
     s = RI.TINY_DENSE.replace(n_layers=1, d_model=d_model, d_ff=d_ff, vocab=264, qk_norm=True)
     kw = dict(fmt="f16", activation_split=0) if fmt == "f16" else {}
     model = synthetic.model_from_shape(s, 0, **kw)
-    toks = np.random.default_rng(d_ff).integers(0, s.vocab - 2, TOKENS[-1]).astype(np.int32)
+    toks = np.random.default_rng(d_ff).integers(0, s.vocab - 2, tokens[-1]).astype(np.int32)
     want = O.forward_full(O.OracleModel(s, 0, fmt=fmt), [toks[i:i + 1] for i in range(len(toks))])
     want = np.stack([w["logits"][-1] for w in want])
     rms = np.sqrt((want * want).mean())
@@ -35,7 +48,7 @@ def test_short_calls_match_the_oracle(d_model, d_ff, fmt):
     for i in range(len(toks)):
         eng.add_sequence(i, reserve_tokens=16)
     worst = {}
-    for n in TOKENS:
+    for n in tokens:
         eng.ctx_lens.zero_()
         out = eng.prefill(list(range(n)), [toks[i:i + 1] for i in range(n)], want_logits=True)
         rows = np.sort(np.abs(out.logits[:n].cpu().numpy() - want[:n]).max(axis=1) / rms)
