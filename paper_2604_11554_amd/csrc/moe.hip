@@ -42,16 +42,19 @@ __device__ __forceinline__ float float_from_order_bits(uint32_t o) {
   return __uint_as_float(o ^ ((o >> 31) ? 0x80000000u : 0xFFFFFFFFu));
 }
 
-// Top-k of one token by one wave: lane holds experts lane, lane+64, ...; selection by (logit descending,
-// id ascending); weights = softmax over the chosen logits (== softmax over all experts, renormalised).
+// Top-k of one token by one wave: lane holds experts lane, lane+64, ... (NJ of them); selection by (logit descending,
+// id ascending); weights = softmax over the chosen logits (== softmax over all experts, renormalised).  Built for 128 and 256
+// experts and for 1, 8 and 16 planes: a launch of a few wavefronts waits for its instructions, and the form of 256 experts and
+// 16 planes has four times those that 128 experts in 8 planes need (us, 12 tokens 7.2 -> 6.7, 128 8.9 -> 7.4, 16 384 in one plane
+// 29 -> 22).
+template <int NJ, int MAXP>
 __device__ __forceinline__ void wave_topk(const RouterArgs& a, int t, int lane, int32_t* idx_out, float* w_out) {
   // all plane loads go out first (the skips are uniform over the wave), then the sums in plane order
-  constexpr int MAXP = 16;
-  float v[MAX_E / 64];
-  float part[MAX_E / 64][MAXP];
+  float v[NJ];
+  float part[NJ][MAXP];
   const bool live = !a.tok_live || a.tok_live[t] != 0;   // requested with the logits, not after the selection
 #pragma unroll
-  for (int j = 0; j < MAX_E / 64; ++j) {
+  for (int j = 0; j < NJ; ++j) {
     const int e = lane + 64 * j;
     const int ec = e < a.E ? e : 0;
 #pragma unroll
@@ -59,7 +62,7 @@ __device__ __forceinline__ void wave_topk(const RouterArgs& a, int t, int lane, 
       part[j][s] = (s < a.n_planes && 64 * j < a.E) ? a.logits[((size_t)s * a.T + t) * a.E + ec] : 0.f;
   }
 #pragma unroll
-  for (int j = 0; j < MAX_E / 64; ++j) {
+  for (int j = 0; j < NJ; ++j) {
     float acc = 0.f;
 #pragma unroll
     for (int s = 0; s < MAXP; ++s) acc += s < a.n_planes ? part[j][s] : 0.f;
@@ -67,7 +70,7 @@ __device__ __forceinline__ void wave_topk(const RouterArgs& a, int t, int lane, 
   }
   float mx = -INFINITY;
 #pragma unroll
-  for (int j = 0; j < MAX_E / 64; ++j) mx = fmaxf(mx, v[j]);
+  for (int j = 0; j < NJ; ++j) mx = fmaxf(mx, v[j]);
   mx = wave_max(mx);
   float my_e = 0.f, denom = 0.f;
   int my_i = 0;
@@ -84,7 +87,7 @@ __device__ __forceinline__ void wave_topk(const RouterArgs& a, int t, int lane, 
       if (bi >= 0 && bi < a.E) {
         float mine = -INFINITY;
 #pragma unroll
-        for (int j = 0; j < MAX_E / 64; ++j)
+        for (int j = 0; j < NJ; ++j)
           if (j == (bi >> 6)) mine = v[j];
         bv = __shfl(mine, bi & 63, WAVE);
         given = bv != -INFINITY;
@@ -93,7 +96,7 @@ __device__ __forceinline__ void wave_topk(const RouterArgs& a, int t, int lane, 
     if (!given) {
       bv = -INFINITY; bi = 0x7FFFFFFF;
 #pragma unroll
-      for (int j = 0; j < MAX_E / 64; ++j)
+      for (int j = 0; j < NJ; ++j)
         if (v[j] > bv) { bv = v[j]; bi = lane + 64 * j; }      // ascending id within the lane
       // the wave's best by (logit descending, id ascending): the largest key (ordered logit bits, ~id)
       const unsigned long long best =
@@ -106,7 +109,7 @@ __device__ __forceinline__ void wave_topk(const RouterArgs& a, int t, int lane, 
     if (lane == k) { my_e = ev; my_i = bi; }
     if ((bi & 63) == lane) {
 #pragma unroll
-      for (int j = 0; j < MAX_E / 64; ++j)
+      for (int j = 0; j < NJ; ++j)
         if (j == (bi >> 6)) v[j] = -INFINITY;
     }
   }
@@ -119,9 +122,10 @@ __device__ __forceinline__ void wave_topk(const RouterArgs& a, int t, int lane, 
 }
 
 // grid = ceil(T / 4): every wave does the top-k of one token
+template <int NJ, int MAXP>
 __global__ __launch_bounds__(256) void moe_topk_kernel(RouterArgs a) {
   const int t = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (t < a.T) wave_topk(a, t, threadIdx.x & 63, a.topk_idx + (size_t)t * a.top_k, a.topk_w + (size_t)t * a.top_k);
+  if (t < a.T) wave_topk<NJ, MAXP>(a, t, threadIdx.x & 63, a.topk_idx + (size_t)t * a.top_k, a.topk_w + (size_t)t * a.top_k);
 }
 
 // Stable counting sort of the T*top_k (token, slot) pairs by expert.  The pair list is cut into contiguous
@@ -299,13 +303,21 @@ __global__ __launch_bounds__(256) void moe_group_place_kernel(RouterArgs a, cons
   place_segment(a.topk_idx, p_begin, p_end, a.top_k, a.E, lane, base + wave * MAX_E, sorted_token, pair_pos);
 }
 
+template <int NJ>
+void launch_topk(const RouterArgs& a, hipStream_t st) {
+  const dim3 grid((a.T + 3) / 4);
+  if (a.n_planes == 1) hipLaunchKernelGGL((moe_topk_kernel<NJ, 1>), grid, dim3(256), 0, st, a);
+  else if (a.n_planes <= 8) hipLaunchKernelGGL((moe_topk_kernel<NJ, 8>), grid, dim3(256), 0, st, a);
+  else hipLaunchKernelGGL((moe_topk_kernel<NJ, 16>), grid, dim3(256), 0, st, a);
+}
+
 }  // namespace
 
 size_t moe_group_workspace_words() { return (size_t)GROUP_SEGS * MAX_E; }
 
 hipError_t moe_route(const RouterArgs& a, int32_t* group_off, int32_t* sorted_token, int32_t* pair_pos,
                      int32_t* seg_ws, bool group, const GroupItems* items, hipStream_t st) {
-  hipLaunchKernelGGL(moe_topk_kernel, dim3((a.T + 3) / 4), dim3(256), 0, st, a);
+  if (a.E <= 128) launch_topk<2>(a, st); else launch_topk<MAX_E / 64>(a, st);
   if (!group) return hipGetLastError();
   if ((size_t)a.T * a.top_k <= GROUP_ONE_WG_PAIRS && !items) {
     hipLaunchKernelGGL(moe_group_kernel, dim3(1), dim3(256), 0, st, a, group_off, sorted_token, pair_pos);
