@@ -293,7 +293,7 @@ int run_layers(const rlx_model* m, h16_t* pool, int64_t n_blocks, const Workspac
   // y = x W^T into `y`: split-K planes that the next kernel adds.  q|k|v of long calls of up to 256 tokens (decode batches) comes
   // in all the planes it may have: keys and values are rounded to 16 bits right after, and with longer sums more of them
   // get the neighbouring code (K 2560, of six million values 1908 with the two planes that are fastest, 1573 with four, 1490
-  // in short calls; logits of 256 rows, four layers: 2.5e-5 of their norm off a 64-bit computation with two, 2.3e-5 with
+  // in calls of 64 tokens; logits of 256 rows, four layers: 2.5e-5 of their norm off a 64-bit computation with two, 2.3e-5 with
   // four and in the short form; eight layers, 129 rows: 1500 -> 1520 us a step, 256 rows 1910 both).
   const bool fine_qkv = T <= 256;
   // dense policies only: MoE decode keeps its sums in the order that its routing was recorded with
