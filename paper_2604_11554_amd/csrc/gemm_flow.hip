@@ -19,6 +19,7 @@
 //   down      12.7 ->  9.8  15.4 -> 12.8  15.8 -> 14.5  24.5 -> 19.1  (25.2 -> 23.4)
 //   LM head    128 ->  115
 #include <mutex>
+#include <type_traits>
 
 #include "gemm_core.h"
 
@@ -28,12 +29,14 @@ namespace {
 constexpr int FLOW_WAVES = 4;
 constexpr int FLOW_RT_MANY = 5;                      // row tiles per workgroup at most beside more than four token tiles (registers)
 
-template <int RT, int NT, int PL>
+template <int RT, int NT, int PL, int EPI>
 struct FlowTiling {
   static constexpr int TILES = RT * NT, LOADS = RT + NT * PL;
   static constexpr int D = LOADS <= 4 ? 4 : 2;                             // steps loaded ahead
   static constexpr int NR = TILES <= 32 ? FLOW_WAVES : FLOW_WAVES / 2;     // waves whose sums are in LDS at a time
-  static constexpr int LDS_BYTES = TILES * NR * 1024 + 16 * NT * 16;       // and, per token, its factor or its LmRow
+  typedef std::conditional_t<EPI == EPI_LMHEAD, LmRow, float> PerToken;    // behind the sums: what the epilogue knows of a token
+  static constexpr int SUM_BYTES = TILES * NR * 1024, LDS_BYTES = SUM_BYTES + 16 * NT * (int)sizeof(PerToken);
+  static_assert(SUM_BYTES % alignof(PerToken) == 0 && LDS_BYTES <= 160 * 1024, "LDS of a workgroup");
 };
 
 // Loads by buffer descriptor: uniform base, uniform offset of the step, 32-bit lane offset.  A lane whose offset lies past the
@@ -108,11 +111,11 @@ __device__ __forceinline__ void lm_store(const GemmArgs& a, const LmSums& s, int
 
 template <int RT, int NT, int PL, int FMT, int EPI>
 __global__ __launch_bounds__(64 * FLOW_WAVES, 1) void gemm_flow_kernel(GemmArgs a) {
-  using TL = FlowTiling<RT, NT, PL>;
+  using TL = FlowTiling<RT, NT, PL, EPI>;
   constexpr int D = TL::D, NW = FLOW_WAVES, NR = TL::NR, NONTEMPORAL = 2;
   extern __shared__ __align__(16) unsigned char lds_raw[];
   f32x4* red = reinterpret_cast<f32x4*>(lds_raw);    // [tile][NR][lane]
-  float* rs_lds = reinterpret_cast<float*>(lds_raw + TL::TILES * NR * 1024);
+  typename TL::PerToken* tok_lds = reinterpret_cast<typename TL::PerToken*>(lds_raw + TL::SUM_BYTES);   // [16 NT]
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int c16 = lane & 15, kg = lane >> 4;
   const int split = blockIdx.y;
@@ -152,7 +155,6 @@ __global__ __launch_bounds__(64 * FLOW_WAVES, 1) void gemm_flow_kernel(GemmArgs 
   // the rows' factors (Act::ss) are requested first of all and settled behind the first steps' loads
   f32x4 ssq = {1.f, 1.f, 1.f, 1.f};
   const bool scaled = EPI != EPI_LMHEAD && a.x_ss != nullptr;
-  LmRow* lm_lds = reinterpret_cast<LmRow*>(lds_raw + TL::TILES * NR * 1024);
   LmRow lm = {};                                     // LM head: of token threadIdx.x
   if (EPI == EPI_LMHEAD) lm = lm_row(a, (int)threadIdx.x);
   if (scaled) ssq = row_ss(a, min((int)threadIdx.x, a.T - 1));
@@ -202,8 +204,10 @@ __global__ __launch_bounds__(64 * FLOW_WAVES, 1) void gemm_flow_kernel(GemmArgs 
     }
 
   // ---- the waves' sums, tile by tile in wave order ----
-  if (scaled && (int)threadIdx.x < 16 * NT) rs_lds[threadIdx.x] = rstd;
-  if (EPI == EPI_LMHEAD && (int)threadIdx.x < 16 * NT) lm_lds[threadIdx.x] = lm;
+  if ((int)threadIdx.x < 16 * NT) {
+    if constexpr (EPI == EPI_LMHEAD) tok_lds[threadIdx.x] = lm;
+    else if (scaled) tok_lds[threadIdx.x] = rstd;
+  }
   auto put = [&]() {
 #pragma unroll
     for (int r = 0; r < RT; ++r)
@@ -239,7 +243,7 @@ __global__ __launch_bounds__(64 * FLOW_WAVES, 1) void gemm_flow_kernel(GemmArgs 
       if (part >= n_parts) break;                    // uniform
       LmSums s;
       if (t < a.T) {
-        const LmRow row = lm_lds[t];
+        const LmRow row = tok_lds[t];
         const float invt = lm_scale(row);
         const bool draw = lm_draws(a, row);
 #pragma unroll 1
@@ -257,7 +261,9 @@ __global__ __launch_bounds__(64 * FLOW_WAVES, 1) void gemm_flow_kernel(GemmArgs 
   for (int tile = wave; tile < TL::TILES; tile += NW) {
     f32x4 v = sum_of(tile);
     const int ht = ht0 + tile / NT, t = 16 * (tile % NT) + c16;
-    if (scaled) v *= rs_lds[16 * (tile % NT) + c16];
+    if constexpr (EPI != EPI_LMHEAD) {
+      if (scaled) v *= tok_lds[16 * (tile % NT) + c16];
+    }
     if (ht >= n_half) continue;
     if (EPI == EPI_STORE) {
       const int nrow = 16 * ht + 4 * kg;
@@ -292,7 +298,7 @@ __global__ __launch_bounds__(64 * FLOW_WAVES, 1) void gemm_flow_kernel(GemmArgs 
 template <int RT, int NT, int PL, int FMT, int EPI>
 void launch_flow_one(const GemmArgs& a, dim3 grid, hipStream_t st) {
   static std::once_flag attr_once;                   // raise the dynamic LDS limit once per instantiation, from any thread
-  constexpr int lds = FlowTiling<RT, NT, PL>::LDS_BYTES;
+  constexpr int lds = FlowTiling<RT, NT, PL, EPI>::LDS_BYTES;
   std::call_once(attr_once, [] {
     (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_flow_kernel<RT, NT, PL, FMT, EPI>),
                               hipFuncAttributeMaxDynamicSharedMemorySize, lds);

@@ -59,3 +59,43 @@ def _compare(d_model, d_ff, fmt, tokens):
         print("d_model %d d_ff %d %s, %d tokens: %.2e %.2e" % (d_model, d_ff, fmt, n, *worst[n]), flush=True)
     model.close()
     assert all(w[0] <= BAR[fmt][0] and w[1] <= BAR[fmt][1] for w in worst.values()), worst
+
+
+# rows of LM heads: one token tile (the last of whose rows hold their temperature, seed and position at its very end), and two
+# rows more, which take the form that stages the activations
+@pytest.mark.parametrize("fmt", ["bf16", "f16"])
+@pytest.mark.parametrize("d_model,vocab", [(256, 2056), (272, 35)])
+def test_draws_of_few_rows_match_the_oracle(d_model, vocab, fmt):
+    """Draws and log-probabilities of 1 to 18 dense rows, each with its own temperature (greedy ones among them) and seed; the
+    rows of a call are the first ones of the next, so both forms of the LM head are held to the same oracle on the same rows."""
+    import paper_2604_11554_amd as pkg
+    from paper_2604_11554_amd import synthetic
+
+    s = RI.TINY_DENSE.replace(n_layers=1, d_model=d_model, vocab=vocab)
+    model = synthetic.model_from_shape(s, 0, **(dict(fmt="f16", activation_split=0) if fmt == "f16" else {}))
+    rng = np.random.default_rng(vocab)
+    toks = rng.integers(0, s.vocab - 2, 18).astype(np.int32)
+    temps = np.array([0.0, 1.0, 0.5, 1.7, 0.8, 0.0, 1.2, 0.6, 2.0, 1.0, 0.7, 0.5, 1.5, 0.0, 0.9, 1.3, 0.5, 0.0])
+    seeds = [int(x) for x in rng.integers(1, 1 << 62, 18)]
+    z = np.stack([w["logits"][-1] for w in O.forward_full(O.OracleModel(s, 0, fmt=fmt), [toks[i:i + 1] for i in range(18)])])
+    z = z.astype(np.float64)
+    # a logit is off by the second bar at most (above), a difference of two logits or of one and the log-sum-exp by twice that
+    bar = 2 * BAR[fmt][1] * np.sqrt((z * z).mean())
+    eng = pkg.RolloutEngine(model, n_blocks=18, max_seqs=18, max_chunk_tokens=18, max_blocks_per_seq=1)
+    for i in range(18):
+        eng.add_sequence(seeds[i], temperature=float(temps[i]), reserve_tokens=16)
+    drawn = 0
+    for n in (1, 10, 11, 12, 15, 16, 17, 18):
+        eng.ctx_lens.zero_()
+        out = eng.prefill(list(range(n)), [toks[i:i + 1] for i in range(n)], want_sampled=True)
+        got, lp = out.sampled.cpu().numpy(), out.logprobs.cpu().numpy()
+        for i in range(n):
+            t = temps[i] if temps[i] > 0 else 1.0
+            score = z[i] / t + (O.gumbel_noise(seeds[i], 1, vocab) if temps[i] > 0 else 0.0)
+            want = z[i][got[i]] / t - np.log(np.exp(z[i] / t).sum())
+            tag = "%d rows, row %d, temperature %.1f" % (n, i, temps[i])
+            assert score[got[i]] >= score.max() - bar / t, tag
+            assert abs(float(lp[i]) - want) <= bar / t, tag
+            drawn += int(got[i] != int(np.argmax(score)))
+    assert drawn <= 4, drawn                     # of 100 draws and 16 greedy picks: scores closer than the bar are rare
+    model.close()
