@@ -352,7 +352,12 @@ __global__ __launch_bounds__(GEMM_THREADS) void gemm_expert_kernel(GemmArgs a) {
       __syncthreads();
 #pragma unroll
       for (int w = 0; w < 4; ++w) has[w] = __ballot(route_has[64 * w + lane] != 0);
-      if (!pick()) return;                          // uniform over the workgroup
+      if (!pick()) {                                // uniform over the workgroup
+        // no expert has rows: the table that the next kernels index with is still published, all empty
+        if (!(has[0] | has[1] | has[2] | has[3]) && blockIdx.x == 0 && mt0 == 0)
+          for (int i = threadIdx.x; i <= a.n_experts; i += GEMM_THREADS) a.pub_group_off[i] = 0;
+        return;
+      }
     }
     int less = 0, eq = 0;
     for (int i = 0; i < ppt; ++i) {

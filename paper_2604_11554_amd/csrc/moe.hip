@@ -3,6 +3,7 @@
 // capture of the chosen expert ids (the record Rollout Routing Replay consumes,
 // paper Sec. 5.5), and a stable, deterministic grouping of (token, slot) pairs by expert.
 #include "kernels.h"
+#include "topk_rule.h"
 
 namespace rlx {
 namespace {
@@ -33,24 +34,16 @@ __device__ __forceinline__ unsigned long long wave_max_key(unsigned long long ke
   const uint32_t rlo = (uint32_t)__builtin_amdgcn_readlane((int)lo, 63), rhi = (uint32_t)__builtin_amdgcn_readlane((int)hi, 63);
   return ((unsigned long long)rhi << 32) | rlo;
 }
-// floats as unsigned integers of the same order, and back
-__device__ __forceinline__ uint32_t float_order_bits(float f) {
-  const uint32_t u = __float_as_uint(f);
-  return u ^ ((u >> 31) ? 0xFFFFFFFFu : 0x80000000u);
-}
-__device__ __forceinline__ float float_from_order_bits(uint32_t o) {
-  return __uint_as_float(o ^ ((o >> 31) ? 0x80000000u : 0xFFFFFFFFu));
-}
 
 // Top-k of one token by one wave: lane holds experts lane, lane+64, ... (NJ of them); selection by (logit descending,
-// id ascending); weights = softmax over the chosen logits (== softmax over all experts, renormalised).  Built for 128 and 256
-// experts and for 1, 8 and 16 planes: a launch of a few wavefronts waits for its instructions, and the form of 256 experts and
+// id ascending; topk_rule.h); weights = softmax over the chosen logits (== softmax over all experts, renormalised).  Built
+// for 128 and 256 experts and for 1, 8 and 16 planes: a launch of a few wavefronts waits for its instructions, and the form of 256 experts and
 // 16 planes has four times those that 128 experts in 8 planes need (us, 12 tokens 7.2 -> 6.7, 128 8.9 -> 7.4, 16 384 in one plane
 // 29 -> 22).
 template <int NJ, int MAXP>
 __device__ __forceinline__ void wave_topk(const RouterArgs& a, int t, int lane, int32_t* idx_out, float* w_out) {
   // all plane loads go out first (the skips are uniform over the wave), then the sums in plane order
-  float v[NJ];
+  float v[NJ], rank[NJ];
   float part[NJ][MAXP];
   const bool live = !a.tok_live || a.tok_live[t] != 0;   // requested with the logits, not after the selection
 #pragma unroll
@@ -67,6 +60,7 @@ __device__ __forceinline__ void wave_topk(const RouterArgs& a, int t, int lane, 
 #pragma unroll
     for (int s = 0; s < MAXP; ++s) acc += s < a.n_planes ? part[j][s] : 0.f;
     v[j] = (lane + 64 * j) < a.E ? acc : -INFINITY;
+    rank[j] = (lane + 64 * j) < a.E ? topk_rank(acc) : TOPK_GONE;
   }
   float mx = -INFINITY;
 #pragma unroll
@@ -76,33 +70,27 @@ __device__ __forceinline__ void wave_topk(const RouterArgs& a, int t, int lane, 
   int my_i = 0;
   const int32_t* replay = a.replay_idx ? a.replay_idx + ((size_t)t * a.n_layers + a.layer) * a.top_k : nullptr;
   for (int k = 0; k < a.top_k; ++k) {
-    float bv = -INFINITY; int bi = 0x7FFFFFFF;
+    float bv = -INFINITY; int bi = -1;
     bool given = false;                                        // uniform over the wave
     if (replay) {
       // routing replay (paper Sec. 5.5): the expert is given; its weight still comes from this layer's own gate
-      // logits, renormalised over the replayed set.  An id outside [0, E), or one already taken by an earlier
-      // slot of this token (its entry of v is -inf by then), is not used: the slot falls back to the layer's own
+      // logits, renormalised over the replayed set.  An id outside [0, E), one already taken by an earlier
+      // slot of this token, or one whose logit is minus infinity is not used: the slot falls back to the layer's own
       // best expert not yet taken, so that a token never reaches an expert twice.
       bi = replay[k];
       if (bi >= 0 && bi < a.E) {
         float mine = -INFINITY;
 #pragma unroll
         for (int j = 0; j < NJ; ++j)
-          if (j == (bi >> 6)) mine = v[j];
+          if (j == (bi >> 6) && rank[j] != TOPK_GONE) mine = v[j];
         bv = __shfl(mine, bi & 63, WAVE);
         given = bv != -INFINITY;
       }
     }
     if (!given) {
-      bv = -INFINITY; bi = 0x7FFFFFFF;
-#pragma unroll
-      for (int j = 0; j < NJ; ++j)
-        if (v[j] > bv) { bv = v[j]; bi = lane + 64 * j; }      // ascending id within the lane
-      // the wave's best by (logit descending, id ascending): the largest key (ordered logit bits, ~id)
-      const unsigned long long best =
-          wave_max_key(((unsigned long long)float_order_bits(bv) << 32) | (uint32_t)(0xFFFFFFFFu - (uint32_t)bi));
-      bv = float_from_order_bits((uint32_t)(best >> 32));
-      bi = (int)(0xFFFFFFFFu - (uint32_t)best);
+      const unsigned long long best = wave_max_key(topk_lane_key<NJ>(rank, lane));
+      bv = topk_key_rank(best);
+      bi = topk_key_id(best);
     }
     const float ev = __expf(bv - mx);
     denom += ev;
@@ -110,7 +98,7 @@ __device__ __forceinline__ void wave_topk(const RouterArgs& a, int t, int lane, 
     if ((bi & 63) == lane) {
 #pragma unroll
       for (int j = 0; j < NJ; ++j)
-        if (j == (bi >> 6)) v[j] = -INFINITY;
+        if (j == (bi >> 6)) rank[j] = TOPK_GONE;
     }
   }
   if (lane < a.top_k) {

@@ -42,3 +42,76 @@ def test_few_tokens_reach_few_experts(n_experts, top_k, d_ff_expert):
             assert d <= BAR
             np.testing.assert_array_equal(got.cpu().numpy().reshape(r.shape), r)
     model.close()
+
+
+@pytest.mark.parametrize("n", [1, 2, 5, 33, 300])
+def test_rows_that_are_not_numbers_stay_with_themselves(n):
+    """Injected embeddings that are NaN, in every row or in one: their router logits are NaN, their experts the first ones, their
+    logits NaN; the other rows are what they are beside an ordinary row, and so is the next call."""
+    import paper_2604_11554_amd as pkg
+    from paper_2604_11554_amd import synthetic
+
+    s = RI.TINY_MOE.replace(n_layers=2, vocab=264)
+    model = synthetic.model_from_shape(s, 0)
+    eng = pkg.RolloutEngine(model, n_blocks=n, max_seqs=n, max_chunk_tokens=n, max_blocks_per_seq=1)
+    for i in range(n):
+        eng.add_sequence(i, reserve_tokens=16)
+    toks = np.random.default_rng(n).integers(0, s.vocab - 2, (n, 1)).astype(np.int32)
+
+    def call(nan_rows):
+        eng.ctx_lens.zero_()
+        eng.kv_pool.zero_()
+        t, e = toks.copy(), [None] * n
+        for i in nan_rows:
+            t[i] = -1
+            e[i] = np.full((1, s.d_model), 0x7FC0, np.uint16)
+        out = eng.prefill(list(range(n)), list(t), e, forced=[5] * n, want_logits=True, want_routing=True)
+        return out.logits.cpu().numpy(), out.routing.cpu().numpy()
+
+    want, routing = call([])
+    for nan_rows in (range(n), [n // 2]):
+        got, routed = call(nan_rows)
+        for i in range(n):
+            if i in nan_rows:
+                assert np.isnan(got[i]).all()
+                np.testing.assert_array_equal(routed[i], np.broadcast_to(np.arange(s.top_k), routed[i].shape))
+            else:
+                np.testing.assert_array_equal(got[i], want[i])
+                np.testing.assert_array_equal(routed[i], routing[i])
+    again, routed = call([])
+    np.testing.assert_array_equal(again, want)
+    np.testing.assert_array_equal(routed, routing)
+    model.close()
+
+
+@pytest.mark.parametrize("n_experts", [32, 200])
+def test_experts_whose_logits_are_not_numbers_come_last(n_experts):
+    """Three router rows are numbers, fewer than a token has experts: those come first, by their logits, then the smallest ids of
+    the others, whose weight is zero."""
+    import paper_2604_11554_amd as pkg
+    from paper_2604_11554_amd import synthetic
+
+    s = RI.TINY_MOE.replace(n_layers=1, n_experts=n_experts, vocab=264)
+    numbers = [5, 9, n_experts - 1]
+
+    def tensor(layer, name):
+        t = RI.tensor_bits(s, 0, layer, name)
+        if name == "w_router":
+            keep = t[numbers].copy()
+            t = np.full_like(t, 0x7FC0)
+            t[numbers] = keep
+        return t
+
+    model = pkg.RolloutModel(synthetic.config_from_shape(s), tensor)
+    rest = [e for e in range(n_experts) if e not in numbers][:s.top_k - 3]
+    for n in (1, 7, 40, 300):
+        eng = pkg.RolloutEngine(model, n_blocks=n, max_seqs=n, max_chunk_tokens=n, max_blocks_per_seq=1)
+        for i in range(n):
+            eng.add_sequence(i, reserve_tokens=16)
+        toks = np.random.default_rng(n).integers(0, s.vocab - 2, (n, 1)).astype(np.int32)
+        out = eng.prefill(list(range(n)), list(toks), forced=[5] * n, want_logits=True, want_routing=True)
+        routed = out.routing.cpu().numpy()[:, 0]
+        np.testing.assert_array_equal(np.sort(routed[:, :3]), np.broadcast_to(numbers, (n, 3)))
+        np.testing.assert_array_equal(routed[:, 3:], np.broadcast_to(rest, (n, s.top_k - 3)))
+        assert np.isfinite(out.logits.cpu().numpy()).all()
+    model.close()
