@@ -209,7 +209,6 @@ Workspace carve(const rlx_model_config& c, char* base, int S, int T, const Plane
   w.q = (h16_t*)take((size_t)PL * T * qdim * 2);
   w.ob = (h16_t*)take(act_bytes(T, qdim, lng));
   w.attn_prefix = (int32_t*)take((size_t)(S + 1) * 4);
-  w.attn_share_start = (int32_t*)take((size_t)ATTN_SHARES_MAX * ATTN_SHARE_WORDS * 4);
   w.attn_hdr = (int32_t*)take(4 * 4);
   w.attn_seq_part = (float*)take((size_t)S * c.n_q_heads * (c.head_dim + 4) * 4);
   w.attn_pre_part = (float*)take((size_t)shared_prefix_max_tiles(S, c.n_kv_heads) * SP_COLS * (c.head_dim + 4) * 4);
@@ -240,11 +239,16 @@ Workspace carve(const rlx_model_config& c, char* base, int S, int T, const Plane
   } else {
     w.act = (h16_t*)take(act_bytes(T, c.d_ff, lng));
   }
+  // Behind the layers: rows and partials of the LM head.  A decode step has the records of its attention shares there, which its
+  // first launch writes and its last layer reads, before the final norm writes the rows.
+  const size_t lm_at = off;
+  w.attn_share_start = base ? (int32_t*)(base + lm_at) : nullptr;
   const int score_rows = score_rows_max(T), lm_rows = S > score_rows ? S : score_rows;   // sampled rows, or a block of scored ones
   w.x_lm = (h16_t*)take(act_bytes(lm_rows, c.d_model, rows_lmhead(c, lm_rows)));
   // a part per 64 ids in the form of many rows, per 32 in that of up to 64: there are at least 256 rows here
   w.lm_part = (float*)take((size_t)lm_rows * (two_term(c) ? (c.vocab + 63) / 64 : (c.vocab + 31) / 32) * 4 * 4);
-  w.bytes = off;
+  const size_t shares_end = lm_at + align_up((size_t)ATTN_SHARES_MAX * ATTN_SHARE_WORDS * 4);
+  w.bytes = off > shares_end ? off : shares_end;
   return w;
 }
 

@@ -80,6 +80,21 @@ def _fits(B, model, n):
     return e.value.code == B.RLX_EINVAL
 
 
+# ... and at commit 98e1273, whose plans of a step's attention were smaller than a share's record is now
+@pytest.mark.parametrize("shape,kw,took", [
+    (RI.TINY_DENSE, {}, 4212), (RI.TINY_DENSE, {"fmt": "f16"}, 4905), (RI.TINY_MOE, {}, 3904),
+    (RI.TINY_MOE, {"activation_split": 0}, 4488), (RI.TINY_DENSE.replace(vocab=35, d_model=128), {}, 4659),
+    (FIXED["mid_dense"][0], {}, 1427), (FIXED["mid_moe"][0], {"fmt": "f16"}, 1604), (FIXED["hd128"][0], {}, 1850)])
+def test_the_fixed_array_takes_what_it_took(shape, kw, took):
+    from paper_2604_11554_amd import binding as B
+    from paper_2604_11554_amd import synthetic
+
+    model = synthetic.device_random_model(shape, **kw)
+    assert all(_fits(B, model, n) for n in (1, 171, 172, 256, 257, took // 2, took - 1, took))
+    assert not _fits(B, model, took + 200)
+    model.close()
+
+
 @pytest.mark.parametrize("name", sorted(FIXED))
 def test_the_largest_step_on_the_fixed_array(name):
     """What the fixed array took it still takes, and the largest step that it takes today equals the step on a workspace."""
