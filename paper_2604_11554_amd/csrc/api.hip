@@ -301,14 +301,14 @@ int run_layers(const rlx_model* m, h16_t* pool, int64_t n_blocks, const Workspac
   // four and in the short form; eight layers, 129 rows: 1500 -> 1520 us a step, 256 rows 1910 both).
   const bool fine_qkv = T <= 256;
   // dense policies only: MoE decode keeps its sums in the order that its routing was recorded with
-  auto flow = [&](int N, int K) { return small && c.n_experts == 0 && gemm_flow_store_form(N, K, T, PL, FMT); };
+  auto flow = [&](int N) { return small && c.n_experts == 0 && gemm_flow_store_form(N, T, m->n_units, PL, FMT); };
   auto planes_of = [&](int N, int K, bool wide) {
-    if (flow(N, K)) return gemm_flow_splits(N, K, T, gemm_max_splits(), m->n_units, PL);
+    if (flow(N)) return gemm_flow_splits(N, K, T, gemm_max_splits(), m->n_units, PL);
     if (small) return gemm_plan_splits(N, K, T, gemm_max_splits(), m->n_units, PL, FMT);
     return lng ? gemm_long_splits(N, K, T, long_planes(c, T, wide, io.lean), m->n_units, wide && fine_qkv) : 1;
   };
   auto store = [&](const LinearW& lw, const Act& x, float* y, int splits, bool wide) {
-    if (flow(lw.N, lw.K)) return gemm_flow_store(lw, x, T, y, lw.N, gemm_max_splits(), m->n_units, st);
+    if (flow(lw.N)) return gemm_flow_store(lw, x, T, y, lw.N, gemm_max_splits(), m->n_units, st);
     return lng ? gemm_long_store(lw, x, T, y, lw.N, long_planes(c, T, wide, io.lean), m->n_units, wide && fine_qkv, st)
                : gemm_store(lw, x, T, y, lw.N, splits, st);
   };

@@ -374,17 +374,21 @@ int flow_swiglu_rt(int F, int T, int n_units) {
 
 }  // namespace
 
-// Stores of two terms: up to 96 tokens (at 97 to 128 the skinny form's two groups of 64 are as fast or faster), and not where four
-// full token tiles meet more rows than columns: 4B shape's q|k|v, 64 tokens, 11.9 us against 11.5 in the skinny form.
-bool gemm_flow_store_form(int N, int K, int T, int planes, int dtype) {
+// Stores of two terms: up to 96 tokens (at 97 to 128 the skinny form's two groups of 64 are as fast or faster).  Of 49 to 64 tokens,
+// the skinny form's own tile, only the narrower ones: what this form saves there are planes of K, of which the skinny form needs
+// n_units / (N / 128) to fill the device.  Where five or fewer do, the two are even (us, skinny -> this form, 64 tokens, N x K
+// 6144 x 2560 11.4 -> 11.8, 6144 x 4096 15.4 -> 15.9, 7168 x 5120 19.3 -> 19.3, 9216 x 4096 21.6 -> 20.9); with more this one is
+// faster (5120 x 2048 9.6 -> 8.8, 3072 x 2048 7.7 -> 7.3, 1536 x 1024 6.5 -> 4.5, 768 x 256 6.2 -> 3.9; 2560 x 9728 15.8 -> 14.7).
+bool gemm_flow_store_form(int N, int T, int n_units, int planes, int dtype) {
   if (!flow_format(planes, dtype)) return false;
-  return planes == 1 ? T <= 128 : T <= 96 && !(T > 48 && T <= 64 && N > K);
+  if (planes == 1) return T <= 128;
+  return T <= 48 || (T <= 64 ? n_units / ((N + 127) / 128) > 5 : T <= 96);
 }
 int gemm_flow_splits(int N, int K, int T, int max_splits, int n_units, int planes) {
   return plan_flow(N, K, T, max_splits, n_units, planes).splits;
 }
 hipError_t gemm_flow_store(const LinearW& w, const Act& x, int T, float* y, int ldy, int max_splits, int n_units, hipStream_t st) {
-  if (!gemm_flow_store_form(w.N, w.K, T, x.planes, x.dtype) || x.pitch) return hipErrorInvalidValue;
+  if (!gemm_flow_store_form(w.N, T, n_units, x.planes, x.dtype) || x.pitch) return hipErrorInvalidValue;
   const FlowPlan plan = plan_flow(w.N, w.K, T, max_splits, n_units, x.planes);
   GemmArgs a = flow_args(x, w.N, w.K, T, plan.splits);
   for (int i = 0; i < 3; ++i) { a.w[i] = w.seg[i]; a.w_tiles[i] = (w.rows[i] + 31) / 32; }
