@@ -319,7 +319,8 @@ void launch_flow(const GemmArgs& a, int splits, const Act& x, hipStream_t st) {
   else if (a.T <= 64) launch_flow_fmt<RT, 4, EPI>(a, grid, x, st);
   else if constexpr (RT <= FLOW_RT_MANY) {
     if (a.T <= 96) launch_flow_fmt<RT, 6, EPI>(a, grid, x, st);
-    else if (EPI == EPI_SWIGLU || x.planes == 1) launch_flow_fmt<RT, 8, EPI>(a, grid, x, st);
+    else if constexpr (EPI == EPI_SWIGLU) launch_flow_fmt<RT, 8, EPI>(a, grid, x, st);
+    else launch_flow_one<RT, 8, 1, DT_F16, EPI>(a, grid, st);   // stores of two terms end at 96 tokens
   }
 }
 
