@@ -300,18 +300,24 @@ int run_layers(const rlx_model* m, h16_t* pool, int64_t n_blocks, const Workspac
   // in calls of 64 tokens; logits of 256 rows, four layers: 2.5e-5 of their norm off a 64-bit computation with two, 2.3e-5 with
   // four and in the short form; eight layers, 129 rows: 1500 -> 1520 us a step, 256 rows 1910 both).
   const bool fine_qkv = T <= 256;
-  // dense policies only: MoE decode keeps its sums in the order that its routing was recorded with
-  auto flow = [&](int N) { return small && c.n_experts == 0 && gemm_flow_store_form(N, T, m->n_units, PL, FMT); };
-  auto planes_of = [&](int N, int K, bool wide) {
-    if (flow(N)) return gemm_flow_splits(N, K, T, gemm_max_splits(), m->n_units, PL);
-    if (small) return gemm_plan_splits(N, K, T, gemm_max_splits(), m->n_units, PL, FMT);
-    return lng ? gemm_long_splits(N, K, T, long_planes(c, T, wide, io.lean), m->n_units, wide && fine_qkv) : 1;
+  // Form and planes of a product are the same in every layer: settled once per call (the search over 64 cuts of a short call's
+  // product is 0.3 us of host time, six of them a layer).  Short-call form in dense policies only: MoE decode keeps its
+  // sums in the order that its routing was recorded with.
+  struct Plan { bool is_flow; FlowPlan flow; LongPlan lng; int planes; };
+  auto plan_of = [&](int N, int K, bool wide) {
+    Plan p = {small && c.n_experts == 0 && gemm_flow_store_form(N, T, m->n_units, PL, FMT), {}, {}, 1};
+    if (p.is_flow) { p.flow = flow_store_plan(N, K, T, gemm_max_splits(), m->n_units, PL); p.planes = p.flow.splits; }
+    else if (small) p.planes = gemm_plan_splits(N, K, T, gemm_max_splits(), m->n_units, PL, FMT);
+    else if (lng) { p.lng = gemm_long_plan(N, K, T, long_planes(c, T, wide, io.lean), m->n_units, wide && fine_qkv); p.planes = p.lng.splits; }
+    return p;
   };
-  auto store = [&](const LinearW& lw, const Act& x, float* y, int splits, bool wide) {
-    if (flow(lw.N)) return gemm_flow_store(lw, x, T, y, lw.N, gemm_max_splits(), m->n_units, st);
-    return lng ? gemm_long_store(lw, x, T, y, lw.N, long_planes(c, T, wide, io.lean), m->n_units, wide && fine_qkv, st)
-               : gemm_store(lw, x, T, y, lw.N, splits, st);
+  auto store = [&](const LinearW& lw, const Act& x, float* y, const Plan& p) {
+    return p.is_flow ? gemm_flow_store(lw, x, T, y, lw.N, p.flow, st)
+           : lng     ? gemm_long_store(lw, x, T, y, lw.N, p.lng, st)
+                     : gemm_store(lw, x, T, y, lw.N, p.planes, st);
   };
+  const Plan p_qkv = plan_of(qkv_dim, d, true), p_o = plan_of(d, qdim, false);
+  const Plan p_ffn = c.n_experts ? plan_of(c.n_experts, d, false) : plan_of(d, c.d_ff, false);   // router, or down
   auto norm = [&](const h16_t* gain, const int32_t* rows, int n_rows, const Act& x, float* xf) -> hipError_t {
     NormArgs a = {};
     a.h = w.h; a.gain = gain; a.d = d; a.T = n_rows; a.T_total = T; a.eps = c.rms_eps; a.rows = rows;
@@ -329,12 +335,11 @@ int run_layers(const rlx_model* m, h16_t* pool, int64_t n_blocks, const Workspac
     wqkv.seg[1] = m->wk[l]; wqkv.rows[1] = kvdim;
     wqkv.seg[2] = m->wv[l]; wqkv.rows[2] = kvdim;
     wqkv.N = qkv_dim; wqkv.K = d;
-    const int s_qkv = planes_of(qkv_dim, d, true);
-    RLX_LAUNCH(RLX_K_QKV, store(wqkv, xb, w.qkv, s_qkv, true));
+    RLX_LAUNCH(RLX_K_QKV, store(wqkv, xb, w.qkv, p_qkv));
 
     h16_t* pool_layer = pool + (size_t)l * n_blocks * block_elems(c);
     RopeArgs r = {};
-    r.qkv = w.qkv; r.n_planes = s_qkv;
+    r.qkv = w.qkv; r.n_planes = p_qkv.planes;
     r.q_gain = c.qk_norm ? m->q_norm[l] : nullptr; r.k_gain = c.qk_norm ? m->k_norm[l] : nullptr;
     r.rope_cs = w.meta.rope_cs;
     r.T = T; r.Hq = c.n_q_heads; r.Hkv = c.n_kv_heads; r.hd = c.head_dim;
@@ -364,9 +369,8 @@ int run_layers(const rlx_model* m, h16_t* pool, int64_t n_blocks, const Workspac
       RLX_LAUNCH(RLX_K_ATTN, attention_prefill(at, st));
     }
 
-    const int s_o = planes_of(d, qdim, false);
-    RLX_LAUNCH(RLX_K_OPROJ, store(linear1(m->wo[l], d, qdim), ob, w.planes, s_o, false));
-    pend_planes = w.planes; pend_n = s_o;
+    RLX_LAUNCH(RLX_K_OPROJ, store(linear1(m->wo[l], d, qdim), ob, w.planes, p_o));
+    pend_planes = w.planes; pend_n = p_o.planes;
 
     RLX_LAUNCH(RLX_K_NORM, norm(m->ffn_norm[l], nullptr, T, xb, nullptr));
     if (c.n_experts == 0) {
@@ -375,14 +379,12 @@ int run_layers(const rlx_model* m, h16_t* pool, int64_t n_blocks, const Workspac
                                : gemm_flow_swiglu_form(c.d_ff, T, m->n_units, PL, FMT)
                                    ? gemm_flow_swiglu(m->w_gate_up[l], c.d_ff, d, xb, T, act, m->n_units, st)
                                    : gemm_swiglu(m->w_gate_up[l], c.d_ff, d, xb, T, act, st));
-      const int s_d = planes_of(d, c.d_ff, false);
-      RLX_LAUNCH(RLX_K_DOWN, store(linear1(m->w_down[l], d, c.d_ff), act, w.planes, s_d, false));
-      pend_planes = w.planes; pend_n = s_d;
+      RLX_LAUNCH(RLX_K_DOWN, store(linear1(m->w_down[l], d, c.d_ff), act, w.planes, p_ffn));
+      pend_planes = w.planes; pend_n = p_ffn.planes;
     } else {
-      const int s_r = planes_of(c.n_experts, d, false);
-      RLX_LAUNCH(RLX_K_ROUTER, store(linear1(m->w_router[l], c.n_experts, d), xb, w.router, s_r, false));
+      RLX_LAUNCH(RLX_K_ROUTER, store(linear1(m->w_router[l], c.n_experts, d), xb, w.router, p_ffn));
       RouterArgs ra = {};
-      ra.logits = w.router; ra.n_planes = s_r; ra.T = T; ra.E = c.n_experts; ra.top_k = c.top_k;
+      ra.logits = w.router; ra.n_planes = p_ffn.planes; ra.T = T; ra.E = c.n_experts; ra.top_k = c.top_k;
       ra.topk_idx = w.topk_idx; ra.topk_w = w.topk_w; ra.routing_out = io.out_routing; ra.layer = l;
       ra.n_layers = c.n_layers; ra.tok_live = w.meta.tok_live; ra.replay_idx = io.replay_routing;
       RLX_LAUNCH(RLX_K_GROUP, moe_route(ra, w.group_off, w.sorted_token, w.pair_pos, w.group_ws, !routed,

@@ -26,9 +26,6 @@
 namespace rlx {
 namespace {
 
-constexpr int FLOW_WAVES = 4;
-constexpr int FLOW_RT_MANY = 5;                      // row tiles per workgroup at most beside more than four token tiles (registers)
-
 template <int RT, int NT, int PL, int EPI>
 struct FlowTiling {
   static constexpr int TILES = RT * NT, LOADS = RT + NT * PL;
@@ -333,71 +330,22 @@ GemmArgs flow_args(const Act& x, int N, int K, int T, int splits) {
 }
 bool flow_format(int planes, int dtype) { return (dtype == DT_BF16 && planes == 2) || (dtype == DT_F16 && planes == 1); }
 
-// ---- store form: row tiles per workgroup and planes of K ----
-// The grid is one workgroup per compute unit at most, so the time is that of one of them: what it takes in at 45 bytes/ns, its
-// weights alone at 32 (or all of them at the card's 6.6 TB/s), its tiles' sums through LDS, and the planes that it and the kernel
-// behind it write and read.  The constants (us) were fitted to a sweep of the 4B shape's products at 1 to 128 tokens; there the
-// choice is within 4 % of the best one, or takes half the planes.
-struct FlowPlan { int rt, splits; };
-constexpr int FLOW_RT[] = {2, 4, 5, 8};
-FlowPlan plan_flow(int N, int K, int T, int max_splits, int n_units, int planes) {
-  const int row_tiles = (N + 31) / 32 * 2, steps = (K / 16 + 1) / 2;
-  const float all = (float)N * (float)K * 2.f / 6.6e6f;
-  FlowPlan best = {2, 1};
-  float best_us = 1e30f;
-  for (int rt : FLOW_RT) {
-    if (T > 64 && rt > FLOW_RT_MANY) continue;
-    const int groups = (row_tiles + rt - 1) / rt;
-    for (int s = 1; s <= max_splits; ++s) {
-      const int per = (steps + s - 1) / s;
-      if (s > 1 && ((s - 1) * per >= steps || per < FLOW_WAVES)) continue;   // no empty split, a step for every wave
-      const float rounds = (float)((groups * s + n_units - 1) / n_units);
-      const float kb = (float)((per + FLOW_WAVES - 1) / FLOW_WAVES * FLOW_WAVES) * 1.024f;   // of a row tile, or of a token tile and term
-      float us = rounds * kb * ((float)rt + (float)(planes * T) / 16.f) / 45.f;
-      const float weights = rounds * kb * (float)rt / 32.f;
-      if (us < weights) us = weights;
-      if (us < all) us = all;
-      us += rounds * 0.12f * (float)(rt * ((T + 15) / 16)) + (float)s * (0.12f + 1e-6f * (float)T * (float)N);
-      if (us < best_us) { best_us = us; best = {rt, s}; }
-    }
-  }
-  return best;
-}
-
-// SwiGLU form (K whole): the fewest row tiles per workgroup that keep the grid within one workgroup per unit (4B shape, 64 tokens:
-// 5 row tiles, 244 workgroups 25.4 us; 8, 152 30.9; 4, 304 38.4); 0: none does
-constexpr int FLOW_SWIGLU_RT[] = {2, 4, 5, 6, 8};
-int flow_swiglu_rt(int F, int T, int n_units) {
-  for (int rt : FLOW_SWIGLU_RT)
-    if ((F / 8 + rt - 1) / rt <= n_units) return T > 64 && rt > FLOW_RT_MANY ? 0 : rt;
-  return 0;
-}
-
 }  // namespace
 
-// Stores of two terms: up to 96 tokens (at 97 to 128 the skinny form's two groups of 64 are as fast or faster).  Of 49 to 64 tokens,
-// the skinny form's own tile, only the narrower ones: what this form saves there are planes of K, of which the skinny form needs
-// n_units / (N / 128) to fill the device.  Where five or fewer do, the two are even (us, skinny -> this form, 64 tokens, N x K
-// 6144 x 2560 11.4 -> 11.8, 6144 x 4096 15.4 -> 15.9, 7168 x 5120 19.3 -> 19.3, 9216 x 4096 21.6 -> 20.9); with more this one is
-// faster (5120 x 2048 9.6 -> 8.8, 3072 x 2048 7.7 -> 7.3, 1536 x 1024 6.5 -> 4.5, 768 x 256 6.2 -> 3.9; 2560 x 9728 15.8 -> 14.7).
 bool gemm_flow_store_form(int N, int T, int n_units, int planes, int dtype) {
-  if (!flow_format(planes, dtype)) return false;
-  if (planes == 1) return T <= 128;
-  return T <= 48 || (T <= 64 ? n_units / ((N + 127) / 128) > 5 : T <= 96);
+  return flow_format(planes, dtype) && flow_store_form(N, T, n_units, planes);
 }
-int gemm_flow_splits(int N, int K, int T, int max_splits, int n_units, int planes) {
-  return plan_flow(N, K, T, max_splits, n_units, planes).splits;
-}
-hipError_t gemm_flow_store(const LinearW& w, const Act& x, int T, float* y, int ldy, int max_splits, int n_units, hipStream_t st) {
-  if (!gemm_flow_store_form(w.N, T, n_units, x.planes, x.dtype) || x.pitch) return hipErrorInvalidValue;
-  const FlowPlan plan = plan_flow(w.N, w.K, T, max_splits, n_units, x.planes);
+hipError_t gemm_flow_store(const LinearW& w, const Act& x, int T, float* y, int ldy, const FlowPlan& plan, hipStream_t st) {
+  if (!flow_format(x.planes, x.dtype) || x.pitch || T > (x.planes == 1 ? 128 : 96) || (T > 64 && plan.rt > FLOW_RT_MANY))
+    return hipErrorInvalidValue;
   GemmArgs a = flow_args(x, w.N, w.K, T, plan.splits);
   for (int i = 0; i < 3; ++i) { a.w[i] = w.seg[i]; a.w_tiles[i] = (w.rows[i] + 31) / 32; }
   a.y = y; a.ldy = ldy;
   if (plan.rt == 2) launch_flow<2, EPI_STORE>(a, plan.splits, x, st);
   else if (plan.rt == 4) launch_flow<4, EPI_STORE>(a, plan.splits, x, st);
   else if (plan.rt == 5) launch_flow<5, EPI_STORE>(a, plan.splits, x, st);
-  else launch_flow<8, EPI_STORE>(a, plan.splits, x, st);
+  else if (plan.rt == 8) launch_flow<8, EPI_STORE>(a, plan.splits, x, st);
+  else return hipErrorInvalidValue;
   return hipGetLastError();
 }
 

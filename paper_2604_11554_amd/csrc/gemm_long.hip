@@ -338,7 +338,6 @@ void launch_long(const GemmArgs& a, int form, int n_items, hipStream_t st) {
 // 1 to 8 planes, where the choice is 0.1 % behind the best of the sweep in the mean and 4 % at worst.  E.g. gate/up of 256
 // tokens, N 19456, K 2560: 128 x 128 (304 workgroups) 65 us, 160 x 128 (244) 51; 1437 tokens, N 6144, K 2560: 128 x 128 in two
 // planes 96 us, 512 x 128 in three 88; 8192 tokens, N 2560, K 9728: 128 x 128 692, 512 x 128 in two planes 629.
-struct LongPlan { int form, splits; };
 // `finest`: as many planes as there may be, in the form that is faster with them.  `lmhead`: the forms that its
 // epilogue is built for, whose rounds it makes longer where nothing runs beside them (256 rows: 444 us in 512 x 128, 410 in 128 x 128).
 static LongPlan plan_long(int N, int K, int T, int max_splits, int n_units, bool finest, bool lmhead) {
@@ -379,8 +378,8 @@ static int grouped_form(int tile_rows) { return tile_rows == 64 ? LONG_512x64 : 
 
 int gemm_long_item_rows(int expected_rows) { return expected_rows <= 48 ? 64 : 128; }
 
-int gemm_long_splits(int N, int K, int T, int max_splits, int n_units, bool finest) {
-  return plan_long(N, K, T, max_splits, n_units, finest, false).splits;
+LongPlan gemm_long_plan(int N, int K, int T, int max_splits, int n_units, bool finest) {
+  return plan_long(N, K, T, max_splits, n_units, finest, false);
 }
 
 static void fill_long(GemmArgs& a, const Act& x, int N, int K, int T) {
@@ -390,9 +389,7 @@ static void fill_long(GemmArgs& a, const Act& x, int N, int K, int T) {
   a.splits = 1;
 }
 
-hipError_t gemm_long_store(const LinearW& w, const Act& x, int T, float* y, int ldy, int max_splits, int n_units, bool finest,
-                           hipStream_t st) {
-  const LongPlan plan = plan_long(w.N, w.K, T, max_splits, n_units, finest, false);
+hipError_t gemm_long_store(const LinearW& w, const Act& x, int T, float* y, int ldy, const LongPlan& plan, hipStream_t st) {
   GemmArgs a = {};
   fill_long(a, x, w.N, w.K, T);
   for (int i = 0; i < 3; ++i) { a.w[i] = w.seg[i]; a.w_tiles[i] = (w.rows[i] + 31) / 32; }

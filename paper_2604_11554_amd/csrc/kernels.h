@@ -2,6 +2,7 @@
 // the given stream and returns hipGetLastError(); shapes are validated by the caller.
 #pragma once
 #include "common.h"
+#include "flow_plan.h"
 
 namespace rlx {
 
@@ -97,10 +98,9 @@ hipError_t gemm_routed_swiglu(const h16_t* w_gate_up, int E, int F, int K, const
 
 // ---- gemm_flow.hip: the same products for short calls of dense policies (activations in fragment order), on bf16 as two terms
 // or fp16 as one ----
-// y[split][t][n] in gemm_flow_splits() planes, at most max_splits
+// y[split][t][n] in the planes of `plan` (flow_store_plan)
 bool gemm_flow_store_form(int N, int T, int n_units, int planes, int dtype);   // whether the form is built, and the faster one
-int gemm_flow_splits(int N, int K, int T, int max_splits, int n_units, int planes);
-hipError_t gemm_flow_store(const LinearW& w, const Act& x, int T, float* y, int ldy, int max_splits, int n_units, hipStream_t st);
+hipError_t gemm_flow_store(const LinearW& w, const Act& x, int T, float* y, int ldy, const FlowPlan& plan, hipStream_t st);
 bool gemm_flow_swiglu_form(int F, int T, int n_units, int planes, int dtype);
 hipError_t gemm_flow_swiglu(const h16_t* w_gate_up, int F, int K, const Act& x, int T, const Act& act, int n_units, hipStream_t st);
 
@@ -110,10 +110,10 @@ hipError_t gemm_flow_lmhead(const h16_t* w_lm, int V, int K, const Act& x, int T
 
 // ---- gemm_long.hip: the same products for long calls on two-term bf16 activations in rows (Act::pitch) ----
 enum { LONG_512x128 = 0, LONG_128x128, LONG_512x64, LONG_160x128, LONG_192x128 };   // weight rows x tokens of a workgroup
-// y[split][t][n]: K cut into gemm_long_splits() planes, at most max_splits: the fastest number, or the largest (`finest`)
-int gemm_long_splits(int N, int K, int T, int max_splits, int n_units, bool finest);
-hipError_t gemm_long_store(const LinearW& w, const Act& x, int T, float* y, int ldy, int max_splits, int n_units, bool finest,
-                           hipStream_t st);
+// y[split][t][n]: form, and K cut into at most max_splits planes: the fastest number, or the largest (`finest`)
+struct LongPlan { int form, splits; };
+LongPlan gemm_long_plan(int N, int K, int T, int max_splits, int n_units, bool finest);
+hipError_t gemm_long_store(const LinearW& w, const Act& x, int T, float* y, int ldy, const LongPlan& plan, hipStream_t st);
 hipError_t gemm_long_swiglu(const h16_t* w_gate_up, int F, int K, const Act& x, int T, const Act& act, int n_units,
                             hipStream_t st);
 // list of (expert, tile of tile_rows of the expert's rows) items that moe_route writes; count is on the device
