@@ -51,8 +51,12 @@ inline int flow_swiglu_rt(int F, int T, int n_units) {
 // n_units / (N / 128) to fill the device.  Where five or fewer do, the two are even (us, skinny -> this form, 64 tokens, N x K
 // 6144 x 2560 11.4 -> 11.8, 6144 x 4096 15.4 -> 15.9, 7168 x 5120 19.3 -> 19.3, 9216 x 4096 21.6 -> 20.9); with more this one is
 // faster (5120 x 2048 9.6 -> 8.8, 3072 x 2048 7.7 -> 7.3, 1536 x 1024 6.5 -> 4.5, 768 x 256 6.2 -> 3.9; 2560 x 9728 15.8 -> 14.7).
+// And only where the activations stay in an XCD's 4 MB of L2, from where the workgroups read them again and again: N x K 8192 x
+// 22016, 80 tokens (7.0 MB) 119 -> 134 us, 96 (8.5 MB) 117 -> 150, fp16 128 (5.6 MB) 96 -> 114; while 5120 x 13824, 96 tokens
+// (5.3 MB) 51.8 -> 52.4, 80 (4.4 MB) 52.9 -> 41.6, 4096 x 12288, 96 (4.7 MB) 36.6 -> 33.9.
 // planes: activations as two bf16 terms or one fp16 term.
-inline bool flow_store_form(int N, int T, int n_units, int planes) {
+inline bool flow_store_form(int N, int K, int T, int n_units, int planes) {
+  if ((long)planes * T * K * 2 > 5L << 20) return false;
   if (planes == 1) return T <= 128;
   return T <= 48 || (T <= 64 ? n_units / ((N + 127) / 128) > 5 : T <= 96);
 }

@@ -332,8 +332,8 @@ bool flow_format(int planes, int dtype) { return (dtype == DT_BF16 && planes == 
 
 }  // namespace
 
-bool gemm_flow_store_form(int N, int T, int n_units, int planes, int dtype) {
-  return flow_format(planes, dtype) && flow_store_form(N, T, n_units, planes);
+bool gemm_flow_store_form(int N, int K, int T, int n_units, int planes, int dtype) {
+  return flow_format(planes, dtype) && flow_store_form(N, K, T, n_units, planes);
 }
 hipError_t gemm_flow_store(const LinearW& w, const Act& x, int T, float* y, int ldy, const FlowPlan& plan, hipStream_t st) {
   if (!flow_format(x.planes, x.dtype) || x.pitch || T > (x.planes == 1 ? 128 : 96) || (T > 64 && plan.rt > FLOW_RT_MANY))

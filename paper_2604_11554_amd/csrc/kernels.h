@@ -99,7 +99,7 @@ hipError_t gemm_routed_swiglu(const h16_t* w_gate_up, int E, int F, int K, const
 // ---- gemm_flow.hip: the same products for short calls of dense policies (activations in fragment order), on bf16 as two terms
 // or fp16 as one ----
 // y[split][t][n] in the planes of `plan` (flow_store_plan)
-bool gemm_flow_store_form(int N, int T, int n_units, int planes, int dtype);   // whether the form is built, and the faster one
+bool gemm_flow_store_form(int N, int K, int T, int n_units, int planes, int dtype);   // whether the form is built, and the faster one
 hipError_t gemm_flow_store(const LinearW& w, const Act& x, int T, float* y, int ldy, const FlowPlan& plan, hipStream_t st);
 bool gemm_flow_swiglu_form(int F, int T, int n_units, int planes, int dtype);
 hipError_t gemm_flow_swiglu(const h16_t* w_gate_up, int F, int K, const Act& x, int T, const Act& act, int n_units, hipStream_t st);

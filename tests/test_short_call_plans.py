@@ -16,7 +16,7 @@ extern "C" int store_plan(int N, int K, int T, int units, int planes) {
   const rlx::FlowPlan p = rlx::flow_store_plan(N, K, T, 16, units, planes);
   return p.rt * 100 + p.splits;
 }
-extern "C" int store_form(int N, int T, int units, int planes) { return rlx::flow_store_form(N, T, units, planes); }
+extern "C" int store_form(int N, int K, int T, int units, int planes) { return rlx::flow_store_form(N, K, T, units, planes); }
 """
 
 
@@ -45,10 +45,13 @@ def test_every_plan_covers_k_once_with_a_kernel_that_is_built(lib):
 
 def test_the_form_of_a_store(lib):
     # fp16 in one term: up to 128 tokens, whatever the widths
-    assert [lib.store_form(6144, t, 256, 1) for t in (1, 49, 64, 65, 128, 129)] == [1, 1, 1, 1, 1, 0]
+    assert [lib.store_form(6144, 2560, t, 256, 1) for t in (1, 49, 64, 65, 128, 129)] == [1, 1, 1, 1, 1, 0]
     # bf16 in two: up to 96 but for 49 to 64 where the other form cuts K in five or fewer: 256 // 43 = 5, 256 // 42 = 6
     for rows, narrow in ((1, 1), (2560, 1), (128 * 42, 1), (128 * 42 + 1, 0), (6144, 0), (40000, 0)):
-        assert [lib.store_form(rows, t, 256, 2) for t in (1, 48, 49, 64, 65, 96, 97, 128)] == [1, 1, narrow, narrow, 1, 1, 0, 0]
+        assert [lib.store_form(rows, 2560, t, 256, 2) for t in (1, 48, 49, 64, 65, 96, 97, 128)] == [1, 1, narrow, narrow, 1, 1, 0, 0]
+    # activations of more than 5 MiB: 96 tokens of 13 653 columns in two terms, of 27 306 in one
+    assert [lib.store_form(5120, k, 96, 256, 2) for k in (13648, 13664)] == [1, 0]
+    assert [lib.store_form(5120, k, 96, 256, 1) for k in (27296, 27312)] == [1, 0]
 
 
 @pytest.mark.parametrize("fmt", ["bf16", "f16"])
@@ -59,7 +62,7 @@ def test_the_compared_products_reach_every_tiling(lib, fmt):
         for t in G.WIDE_TOKENS:
             token_tiles = next(n for n in (1, 2, 3, 4, 6, 8) if t <= 16 * n)
             for N, K in ((s.q_dim + 2 * s.kv_dim, s.d_model), (s.d_model, s.q_dim), (s.d_model, s.d_ff)):
-                if lib.store_form(N, t, 256, planes):
+                if lib.store_form(N, K, t, 256, planes):
                     stores.add((lib.store_plan(N, K, t, 256, planes) // 100, token_tiles))
     # all (row tiles, token tiles) that any product of up to 16 384 x 12 288 takes
     want = {(rt, n) for rt in (2, 4, 5) for n in (1, 2, 3, 4, 6)} | {(8, n) for n in (2, 3, 4)}
