@@ -80,10 +80,12 @@ __global__ __launch_bounds__(64 * WR * WT) __attribute__((amdgpu_waves_per_eu(2,
   const int n_cp = (ks_e - ks_b + 1) >> 1;           // stages to copy
   const uint32_t lds0 = lds_address(lds_raw);
   const h16_t* wp[PW];
+  // a wave short of a copy repeats the last one's bytes
+  auto weight_copy = [&](int i) { return WFR % NW == 0 ? wave + NW * i : min(wave + NW * i, WFR - 1); };
   int wstep[PW];
 #pragma unroll
   for (int i = 0; i < PW; ++i) {
-    const int f = min(wave + NW * i, WFR - 1), j = f % (JW * WR);   // a wave short of a copy repeats the last one's bytes
+    const int f = weight_copy(i), j = f % (JW * WR);
     int lt = tw * JW * WR + j;
     wstep[i] = 1;
     if (lt >= n_tiles) { lt = 0; wstep[i] = 0; }     // no such tile: one cached block, its products are never stored
@@ -109,7 +111,7 @@ __global__ __launch_bounds__(64 * WR * WT) __attribute__((amdgpu_waves_per_eu(2,
     const int sc = min(s, n_cp - 1);
     const uint32_t dst = lds0 + buf * STAGE;
     if (i < PW) {
-      const int f = min(wave + NW * i, WFR - 1);
+      const int f = weight_copy(i);
       const int ks = min(ks_b + 2 * sc + f / (JW * WR), KS - 1);   // the missing half of an odd last stage: any block
       copy_to_lds(wp[i] + (size_t)(ks * wstep[i]) * W_KSTRIDE, dst + f * 1024);
     } else {
@@ -227,10 +229,16 @@ __global__ __launch_bounds__(64 * WR * WT) __attribute__((amdgpu_waves_per_eu(2,
   float rs[MW];
   LmRow lm[MW];
 #pragma unroll
-  for (int m = 0; m < MW; ++m) {
-    const int t = tok0 + m * 32 + r32;
-    rs[m] = EPI != EPI_LMHEAD && a.x_ss ? row_rstd(a, row_ss(a, t < a.T ? t : 0)) : 1.f;
-    if constexpr (EPI == EPI_LMHEAD) lm[m] = lm_row(a, t);
+  for (int m = 0; m < MW; ++m) rs[m] = 1.f;
+  if constexpr (EPI == EPI_LMHEAD) {
+#pragma unroll
+    for (int m = 0; m < MW; ++m) lm[m] = lm_row(a, tok0 + m * 32 + r32);
+  } else if (a.x_ss) {
+    f32x4 ss[MW];                                    // all on their way before the first is used
+#pragma unroll
+    for (int m = 0; m < MW; ++m) ss[m] = row_ss(a, tok0 + m * 32 + r32 < a.T ? tok0 + m * 32 + r32 : 0);
+#pragma unroll
+    for (int m = 0; m < MW; ++m) rs[m] = row_rstd(a, ss[m]);
   }
   // no copy may outlive the workgroup's LDS, and no fragment read of the last k-step the barrier of the LM head below
   asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
