@@ -306,9 +306,15 @@ int run_layers(const rlx_model* m, h16_t* pool, int64_t n_blocks, const Workspac
   struct Plan { bool is_flow; FlowPlan flow; LongPlan lng; int planes; };
   auto plan_of = [&](int N, int K, bool wide) {
     Plan p = {small && c.n_experts == 0 && gemm_flow_store_form(N, K, T, m->n_units, PL, FMT), {}, {}, 1};
-    if (p.is_flow) { p.flow = flow_store_plan(N, K, T, gemm_max_splits(), m->n_units, PL); p.planes = p.flow.splits; }
-    else if (small) p.planes = gemm_plan_splits(N, K, T, gemm_max_splits(), m->n_units, PL, FMT);
-    else if (lng) { p.lng = gemm_long_plan(N, K, T, long_planes(c, T, wide, io.lean), m->n_units, wide && fine_qkv); p.planes = p.lng.splits; }
+    if (p.is_flow) {
+      p.flow = flow_store_plan(N, K, T, gemm_max_splits(), m->n_units, PL);
+      p.planes = p.flow.splits;
+    } else if (small) {
+      p.planes = gemm_plan_splits(N, K, T, gemm_max_splits(), m->n_units, PL, FMT);
+    } else if (lng) {
+      p.lng = gemm_long_plan(N, K, T, long_planes(c, T, wide, io.lean), m->n_units, wide && fine_qkv);
+      p.planes = p.lng.splits;
+    }
     return p;
   };
   auto store = [&](const LinearW& lw, const Act& x, float* y, const Plan& p) {

@@ -29,6 +29,7 @@
 // responses of a prompt at the 4B shape) instead of once per sequence; the per-sequence kernel starts after the
 // shared units, and the merge kernel adds the prefix parts first.
 #include "attn_core.h"
+#include "embed.h"
 #include "lds_copy.h"
 #include "rope.h"
 
@@ -874,7 +875,8 @@ static void launch_merge(const AttnDecodeArgs& a, hipStream_t st) {
   auto lds = [&](int groups) { return (size_t)(groups - 1) * slices * 10 * sizeof(float); };
   if (a.team) hipLaunchKernelGGL((attn_decode_merge_kernel<HD, 1>), grid, dim3(threads), lds(1), st, a);
   else if ((int)grid.x >= MERGE_MANY) hipLaunchKernelGGL((attn_decode_merge_kernel<HD, 2>), grid, dim3(threads * 2), lds(2), st, a);
-  else hipLaunchKernelGGL((attn_decode_merge_kernel<HD, MERGE_GROUPS_MAX>), grid, dim3(threads * MERGE_GROUPS_MAX), lds(MERGE_GROUPS_MAX), st, a);
+  else hipLaunchKernelGGL((attn_decode_merge_kernel<HD, MERGE_GROUPS_MAX>), grid, dim3(threads * MERGE_GROUPS_MAX),
+                          lds(MERGE_GROUPS_MAX), st, a);
 }
 
 hipError_t attention_decode_merge(const AttnDecodeArgs& a, hipStream_t st) {

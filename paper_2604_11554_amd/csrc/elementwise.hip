@@ -2,6 +2,7 @@
 // (residual add / split-K reduce / MoE combine) + RMSNorm, fused per-head q/k
 // RMSNorm + rotary embedding + paged KV append, KV page copy.
 #include "kernels.h"
+#include "embed.h"
 #include "rope.h"
 
 namespace rlx {

@@ -7,10 +7,11 @@ constexpr int FLOW_WAVES = 4;
 constexpr int FLOW_RT_MANY = 5;                      // row tiles per workgroup at most beside more than four token tiles (registers)
 
 // ---- store form: row tiles per workgroup and planes of K ----
-// The grid is one workgroup per compute unit at most, so the time is that of one of them: what it takes in at 45 bytes/ns, its
-// weights alone at 32 (or all of them at the card's 6.6 TB/s), its tiles' sums through LDS, and the planes that it and the kernel
-// behind it write and read.  The constants (us) were fitted to a sweep of the 4B shape's products at 1 to 128 tokens; there the
-// choice is within 4 % of the best one, or takes half the planes.
+// A grid runs in `rounds` of one workgroup per compute unit, usually one (wide outputs take more), so the time is that of so many
+// workgroups: what one takes in at 45 bytes/ns, its weights alone at 32 (or all of them at the card's 6.6 TB/s), its tiles' sums
+// through LDS, and the planes that it and the kernel behind it write and read.  The constants (us) were fitted to a sweep of the
+// 4B shape's products at 1 to 128 tokens; there the choice is within 4 % of the best one, or takes half the planes.  Against the
+// skinny form, over nineteen products of 256 x 688 to 12 288 x 8192 and both formats: 0.53 to 1.04 of its time.
 struct FlowPlan { int rt, splits; };   // row tiles of a workgroup, planes
 constexpr int FLOW_RT[] = {2, 4, 5, 8};
 inline FlowPlan flow_store_plan(int N, int K, int T, int max_splits, int n_units, int planes) {

@@ -543,7 +543,8 @@ __global__ __launch_bounds__(GEMM_THREADS) void gemm_expert_kernel(GemmArgs a) {
 #pragma unroll
   for (int j = 0; j < J; ++j) {
     const int nt = nt0 + j * W_GROUP;
-    if (nt < n_tiles) tile_epilogue<1, EPI, PL, FMT>(a, reinterpret_cast<const f32x16(&)[1]>(acc[j]), nt, n_tiles, mt0, 0, row_base, lane, rs);
+    if (nt < n_tiles)
+      tile_epilogue<1, EPI, PL, FMT>(a, reinterpret_cast<const f32x16(&)[1]>(acc[j]), nt, n_tiles, mt0, 0, row_base, lane, rs);
   }
 }
 

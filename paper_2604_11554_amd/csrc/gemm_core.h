@@ -170,7 +170,8 @@ __device__ __forceinline__ void lmhead_epilogue(const GemmArgs& a, f32x4* scr, c
     for (int j = 0; j < JT; ++j)
 #pragma unroll
       for (int q = 0; q < 4; ++q)
-        scr[((m * JT + j) * 4 + q) * WAVE + lane] = f32x4{acc[j][m][4 * q], acc[j][m][4 * q + 1], acc[j][m][4 * q + 2], acc[j][m][4 * q + 3]};
+        scr[((m * JT + j) * 4 + q) * WAVE + lane] =
+            f32x4{acc[j][m][4 * q], acc[j][m][4 * q + 1], acc[j][m][4 * q + 2], acc[j][m][4 * q + 3]};
 #pragma unroll
   for (int m = 0; m < MT; ++m) {
     const int t = (mt0 + m) * 32 + r32;

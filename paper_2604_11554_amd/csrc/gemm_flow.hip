@@ -50,10 +50,12 @@ __device__ __forceinline__ u32x4 desc_load(Desc d, uint32_t lane, uint32_t step)
 }
 
 // ---- LM head: sums of a lane's vocabulary rows ----
-// (The steps are those of lmhead_epilogue; as functions that both used they made its loop, 2 to 4 % of a long LM head, slower.)
+// (The steps are those of lmhead_epilogue; as functions that both used they made its loop, 2 to 4 % of a long LM head, slower.  A
+// change of one is made in both: the tests hold 1 to 18 rows, in one form and the other, to the same draws.)
 struct LmSums { float mx = -INFINITY, se = 0.f, best = -INFINITY; int besti = 0x7FFFFFFF; };
 __device__ __forceinline__ float lm_scale(const LmRow& r) { return r.temperature > 0.f ? 1.f / r.temperature : 1.f; }
-__device__ __forceinline__ bool lm_draws(const GemmArgs& a, const LmRow& r) { return a.draw != 0 && r.temperature > 0.f; }   // uniform over the launch when draw == 0
+// uniform over the launch when draw == 0
+__device__ __forceinline__ bool lm_draws(const GemmArgs& a, const LmRow& r) { return a.draw != 0 && r.temperature > 0.f; }
 // four vocabulary rows nrow .. nrow + 3 (nrow a multiple of 4, below N) of token t: logits v; invt and draw are the row's
 // lm_scale() and lm_draws()
 __device__ __forceinline__ void lm_add(const GemmArgs& a, LmSums& s, const f32x4& v, int t, int nrow, const LmRow& row, float invt,

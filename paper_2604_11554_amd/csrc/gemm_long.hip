@@ -306,7 +306,8 @@ __global__ __launch_bounds__(64 * WR * WT) __attribute__((amdgpu_waves_per_eu(2,
 #pragma unroll
     for (int j = 0; j < JW; j += 2)
       if (nt0 + j < n_tiles)
-        lmhead_epilogue<2, 2>(a, scr, reinterpret_cast<const f32x16(&)[2][2]>(acc[j]), lm, nt0 + j, tok0 >> 5, (nt0 + j) >> 1, n_parts, lane);
+        lmhead_epilogue<2, 2>(a, scr, reinterpret_cast<const f32x16(&)[2][2]>(acc[j]), lm, nt0 + j, tok0 >> 5, (nt0 + j) >> 1, n_parts,
+                              lane);
   }
 }
 
@@ -343,7 +344,8 @@ void launch_long(const GemmArgs& a, int form, int n_items, hipStream_t st) {
 // all weight rows and 32 tokens) make one even round of 129 to 512 tokens where the others fill it and a half; what decides
 // at a few hundred to a few thousand tokens is how well the workgroups fit the units.  The constants (us: start of a round, and
 // per stage) were fitted to a sweep of the products of the two model shapes (N 2048..19456, K 2048..9728), 140..8192 tokens and
-// 1 to 8 planes, where the choice is 0.1 % behind the best of the sweep in the mean and 4 % at worst.  E.g. gate/up of 256
+// 1 to 8 planes, where the choice is 0.1 % behind the best of the sweep in the mean and 4 % at worst (6 % in a second sweep at other
+// token counts: N 5120, K 2048, 1700 tokens 83 us in 128 x 128, 88 in the chosen 512 x 128).  E.g. gate/up of 256
 // tokens, N 19456, K 2560: 128 x 128 (304 workgroups) 65 us, 160 x 128 (244) 51; 1437 tokens, N 6144, K 2560: 128 x 128 in two
 // planes 96 us, 512 x 128 in three 88; 8192 tokens, N 2560, K 9728: 128 x 128 692, 512 x 128 in two planes 629.
 // `finest`: as many planes as there may be, in the form that is faster with them.  `lmhead`: the forms that its
@@ -358,7 +360,8 @@ static LongPlan plan_long(int N, int K, int T, int max_splits, int n_units, bool
     if (finest) best_us = 1e30f;
     const long wg_t = (long)((T + 127) / 128) * s;
     const float planes_us = (float)(s - 1) * (float)T * (float)N * 0.94e-6f;
-    auto alone = [&](int form, int rows, float start, float stage) {   // one workgroup per unit; a last round that is not full is a little shorter
+    // one workgroup per unit; a last round that is not full is a little shorter
+    auto alone = [&](int form, int rows, float start, float stage) {
       const long w = wg_t * ((N + rows - 1) / rows), rounds = (w + n_units - 1) / n_units;
       const float full = (float)(w - (rounds - 1) * n_units) / (float)n_units;
       const float us = (float)rounds * (start + stage * (float)per) - 0.1f * (1.f - full) * stage * (float)per + planes_us;

@@ -80,8 +80,9 @@ inline int lmhead_parts(int vocab, const Act& x) { return x.pitch ? (vocab + 63)
 hipError_t gemm_lmhead(const h16_t* w_lm, int V, int K, const Act& x, int T, float* logits, float* part,
                        const uint64_t* seeds, const float* temperature, const int32_t* sample_pos,
                        const int32_t* row_seq, bool draw, hipStream_t st);
-// expert-grouped forms: rows [group_off[e], group_off[e+1]) belong to expert e = blockIdx.y; max_rows bounds the rows
-// of one expert, n_pairs / E, the rows that one is expected to have, picks the token-tile height
+// expert-grouped forms: rows [group_off[e], group_off[e+1]) belong to expert e: blockIdx.y, or, where few tokens reach few experts,
+// the one that the workgroup's place among the experts with rows says (gemm_expert_kernel); max_rows bounds the rows of
+// one expert, n_pairs / E, the rows that one is expected to have, picks the token-tile height
 hipError_t gemm_grouped_swiglu(const h16_t* w_gate_up, int E, int F, int K, const Act& x, const int32_t* x_rows,
                                const int32_t* group_off, int max_rows, int n_pairs, const Act& act,
                                hipStream_t st);

@@ -37,9 +37,9 @@ __device__ __forceinline__ unsigned long long wave_max_key(unsigned long long ke
 
 // Top-k of one token by one wave: lane holds experts lane, lane+64, ... (NJ of them); selection by (logit descending,
 // id ascending; topk_rule.h); weights = softmax over the chosen logits (== softmax over all experts, renormalised).  Built
-// for 128 and 256 experts and for 1, 8 and 16 planes: a launch of a few wavefronts waits for its instructions, and the form of 256 experts and
-// 16 planes has four times those that 128 experts in 8 planes need (us, 12 tokens 7.2 -> 6.7, 128 8.9 -> 7.4, 16 384 in one plane
-// 29 -> 22).
+// for 128 and 256 experts and for 1, 8 and 16 planes: a launch of a few wavefronts waits for its instructions, and the form of
+// 256 experts and 16 planes has four times those that 128 experts in 8 planes need (us, 12 tokens 7.2 -> 6.7, 128 8.9 -> 7.4,
+// 16 384 in one plane 29 -> 22).
 template <int NJ, int MAXP>
 __device__ __forceinline__ void wave_topk(const RouterArgs& a, int t, int lane, int32_t* idx_out, float* w_out) {
   // all plane loads go out first (the skips are uniform over the wave), then the sums in plane order
