@@ -4,6 +4,7 @@
 #include "kernels.h"
 #include "embed.h"
 #include "rope.h"
+#include "tile_order.h"
 
 namespace rlx {
 namespace {
@@ -12,7 +13,7 @@ namespace {
 // any order), so that a grid in list order starts the long ones first and ends with short ones.
 __global__ void meta_prefill_kernel(TokenMeta m, int n_seqs, int total, const int32_t* cu, const int32_t* ctx,
                                     const uint8_t* sample_last) {
-  __shared__ int bucket[1024];
+  __shared__ int bucket[TILE_BUCKETS];
   __shared__ int longest;
   // per-token fields: binary search of the owning sequence
   for (int t = threadIdx.x; t < total; t += blockDim.x) {
@@ -33,29 +34,29 @@ __global__ void meta_prefill_kernel(TokenMeta m, int n_seqs, int total, const in
     m.sample_on[i] = (sample_last && sample_last[i] && len > 0) ? 1 : 0;
   }
   // query tiles of ATTN_QTILE positions: a wave per sequence, a lane per tile, counted into buckets and placed from there
-  bucket[threadIdx.x] = 0;                          // 1024 threads
+  bucket[threadIdx.x] = 0;                          // TILE_BUCKETS threads
   if (threadIdx.x == 0) longest = 0;
   __syncthreads();
   for (int i = threadIdx.x; i < n_seqs; i += blockDim.x)
     if (cu[i + 1] > cu[i]) atomicMax(&longest, ctx[i] + cu[i + 1] - cu[i]);
   __syncthreads();
-  const int shift = max(0, 22 - __clz(longest));    // longest >> shift < 1024
+  const int shift = tile_shift(longest);
   auto each_tile = [&](auto f) {
     for (int i = threadIdx.x >> 6; i < n_seqs; i += blockDim.x >> 6) {
       const int len = cu[i + 1] - cu[i], c = ctx[i];
       for (int q0 = ATTN_QTILE * (threadIdx.x & 63); q0 < len; q0 += ATTN_QTILE * 64)
-        f(i, q0, 1023 - (min(c + min(q0 + ATTN_QTILE, len), longest) >> shift));
+        f(i, q0, tile_bucket(c + min(q0 + ATTN_QTILE, len), longest, shift));
     }
   };
   each_tile([&](int, int, int b) { atomicAdd(&bucket[b], 1); });
   __syncthreads();
-  for (int o = 1; o < 1024; o <<= 1) {              // inclusive prefix
+  for (int o = 1; o < TILE_BUCKETS; o <<= 1) {      // inclusive prefix
     const int v = (int)threadIdx.x >= o ? bucket[threadIdx.x - o] : 0;
     __syncthreads();
     bucket[threadIdx.x] += v;
     __syncthreads();
   }
-  if (threadIdx.x == 0) m.n_qtiles[0] = bucket[1023];
+  if (threadIdx.x == 0) m.n_qtiles[0] = bucket[TILE_BUCKETS - 1];
   __syncthreads();
   each_tile([&](int i, int q0, int b) {             // from a bucket's end downwards
     const int at = atomicSub(&bucket[b], 1) - 1;
