@@ -317,16 +317,17 @@ int run_layers(const rlx_model* m, h16_t* pool, int64_t n_blocks, const Workspac
     }
     return p;
   };
-  auto store = [&](const LinearW& lw, const Act& x, float* y, const Plan& p) {
-    return p.is_flow ? gemm_flow_store(lw, x, T, y, lw.N, p.flow, st)
+  auto store = [&](const LinearW& lw, const Act& x, float* y, const Plan& p, const FlowNorm* nm = nullptr) {
+    return p.is_flow ? gemm_flow_store(lw, x, T, y, lw.N, p.flow, st, nm)
            : lng     ? gemm_long_store(lw, x, T, y, lw.N, p.lng, st)
                      : gemm_store(lw, x, T, y, lw.N, p.planes, st);
   };
   const Plan p_qkv = plan_of(qkv_dim, d, true), p_o = plan_of(d, qdim, false);
   const Plan p_ffn = c.n_experts ? plan_of(c.n_experts, d, false) : plan_of(d, c.d_ff, false);   // router, or down
+  float* h_at = w.h;                                  // where the residual stream is
   auto norm = [&](const h16_t* gain, const int32_t* rows, int n_rows, const Act& x, float* xf) -> hipError_t {
     NormArgs a = {};
-    a.h = w.h; a.gain = gain; a.d = d; a.T = n_rows; a.T_total = T; a.eps = c.rms_eps; a.rows = rows;
+    a.h = h_at; a.gain = gain; a.d = d; a.T = n_rows; a.T_total = T; a.eps = c.rms_eps; a.rows = rows;
     a.add = pend_planes; a.n_planes = pend_n;
     if (pend_moe) { a.moe_y = w.moe_y; a.pair_pos = w.pair_pos; a.topk_w = w.topk_w; a.top_k = c.top_k; }
     a.x = x; a.xf = xf;
@@ -334,14 +335,27 @@ int run_layers(const rlx_model* m, h16_t* pool, int64_t n_blocks, const Workspac
     return rmsnorm(a, st);
   };
 
+  // Calls of few tokens: the products that read normalised rows make them themselves.  The residual stream then changes its place
+  // with every addition, between w.h and the activation matrix that nothing else uses here (32 rows of 4 bytes per element, or of
+  // two; at most sixteen rows of four are put there).
+  const bool norm_inside = p_qkv.is_flow && gemm_flow_norm_form(T, d) && gemm_flow_swiglu_form(c.d_ff, T, m->n_units, PL, FMT);
+  auto inner_norm = [&](const h16_t* gain) {
+    FlowNorm f = {h_at, nullptr, pend_planes, pend_n, gain, c.rms_eps, nullptr};
+    if (pend_planes) h_at = f.h_out = h_at == w.h ? (float*)w.xb : w.h;
+    pend_planes = nullptr; pend_n = 0;
+    return f;
+  };
+
   for (int l = 0; l < c.n_layers; ++l) {
-    RLX_LAUNCH(RLX_K_NORM, norm(m->attn_norm[l], nullptr, T, xb, nullptr));
+    FlowNorm nm = {};
+    if (norm_inside) nm = inner_norm(m->attn_norm[l]);
+    else RLX_LAUNCH(RLX_K_NORM, norm(m->attn_norm[l], nullptr, T, xb, nullptr));
     LinearW wqkv = {};
     wqkv.seg[0] = m->wq[l]; wqkv.rows[0] = qdim;
     wqkv.seg[1] = m->wk[l]; wqkv.rows[1] = kvdim;
     wqkv.seg[2] = m->wv[l]; wqkv.rows[2] = kvdim;
     wqkv.N = qkv_dim; wqkv.K = d;
-    RLX_LAUNCH(RLX_K_QKV, store(wqkv, xb, w.qkv, p_qkv));
+    RLX_LAUNCH(RLX_K_QKV, store(wqkv, xb, w.qkv, p_qkv, norm_inside ? &nm : nullptr));
 
     h16_t* pool_layer = pool + (size_t)l * n_blocks * block_elems(c);
     RopeArgs r = {};
@@ -378,12 +392,13 @@ int run_layers(const rlx_model* m, h16_t* pool, int64_t n_blocks, const Workspac
     RLX_LAUNCH(RLX_K_OPROJ, store(linear1(m->wo[l], d, qdim), ob, w.planes, p_o));
     pend_planes = w.planes; pend_n = p_o.planes;
 
-    RLX_LAUNCH(RLX_K_NORM, norm(m->ffn_norm[l], nullptr, T, xb, nullptr));
+    if (norm_inside) nm = inner_norm(m->ffn_norm[l]);
+    else RLX_LAUNCH(RLX_K_NORM, norm(m->ffn_norm[l], nullptr, T, xb, nullptr));
     if (c.n_experts == 0) {
       const Act act = call_act(c, w.act, T, c.d_ff, lng);
       RLX_LAUNCH(RLX_K_GATEUP, lng ? gemm_long_swiglu(m->w_gate_up[l], c.d_ff, d, xb, T, act, m->n_units, st)
                                : gemm_flow_swiglu_form(c.d_ff, T, m->n_units, PL, FMT)
-                                   ? gemm_flow_swiglu(m->w_gate_up[l], c.d_ff, d, xb, T, act, m->n_units, st)
+                                   ? gemm_flow_swiglu(m->w_gate_up[l], c.d_ff, d, xb, T, act, m->n_units, st, norm_inside ? &nm : nullptr)
                                    : gemm_swiglu(m->w_gate_up[l], c.d_ff, d, xb, T, act, st));
       RLX_LAUNCH(RLX_K_DOWN, store(linear1(m->w_down[l], d, c.d_ff), act, w.planes, p_ffn));
       pend_planes = w.planes; pend_n = p_ffn.planes;
@@ -415,9 +430,10 @@ int run_layers(const rlx_model* m, h16_t* pool, int64_t n_blocks, const Workspac
   }
 
   auto lmhead = [&](const Act& x, int rows, float* logits, const uint64_t* seeds, const int32_t* sample_pos,
-                    const int32_t* row_seq, bool draw) {
+                    const int32_t* row_seq, bool draw, const FlowNorm* nm = nullptr) {
     if (c.n_experts == 0 && !x.pitch && gemm_flow_lmhead_form(rows, PL, FMT))
-      return gemm_flow_lmhead(m->lm_head, c.vocab, d, x, rows, logits, w.lm_part, seeds, io.temperature, sample_pos, row_seq, draw, st);
+      return gemm_flow_lmhead(m->lm_head, c.vocab, d, x, rows, logits, w.lm_part, seeds, io.temperature, sample_pos, row_seq, draw, st,
+                              nm);
     return x.pitch ? gemm_long_lmhead(m->lm_head, c.vocab, d, x, rows, logits, w.lm_part, seeds, io.temperature, sample_pos,
                                       row_seq, draw, m->n_units, st)
                    : gemm_lmhead(m->lm_head, c.vocab, d, x, rows, logits, w.lm_part, seeds, io.temperature, sample_pos, row_seq,
@@ -449,8 +465,11 @@ int run_layers(const rlx_model* m, h16_t* pool, int64_t n_blocks, const Workspac
   // final norm of the rows that emit a token, LM head with fused log-sum-exp / Gumbel-max partials
   const int S = io.n_seqs;
   const Act x_lm = call_act(c, w.x_lm, S, d, rows_lmhead(c, S));
-  RLX_HIP(norm(m->final_norm, w.meta.sample_row, S, x_lm, nullptr));
-  RLX_LAUNCH(RLX_K_LMHEAD, lmhead(x_lm, S, io.out_logits, io.seeds, w.meta.sample_pos, nullptr, true));
+  FlowNorm nm = {};
+  const bool last_inside = norm_inside && io.decode;   // rows and tokens are the same (and gemm_flow_lmhead_form holds: T <= 16)
+  if (last_inside) nm = inner_norm(m->final_norm);
+  else RLX_HIP(norm(m->final_norm, w.meta.sample_row, S, x_lm, nullptr));
+  RLX_LAUNCH(RLX_K_LMHEAD, lmhead(x_lm, S, io.out_logits, io.seeds, w.meta.sample_pos, nullptr, true, last_inside ? &nm : nullptr));
   FinalizeArgs f = {};
   f.n_rows = S; f.n_parts = lmhead_parts(c.vocab, x_lm); f.vocab = c.vocab; f.d = d;
   f.part = w.lm_part; f.x = x_lm; f.w_lm = m->lm_head;

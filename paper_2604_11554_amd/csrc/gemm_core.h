@@ -42,6 +42,9 @@ struct GemmArgs {
   const int32_t* item_expert; // grouped: expert and row tile of every item, and the number of items (GroupItems)
   const int32_t* item_tile;
   const int32_t* n_items;
+  // calls of few tokens (gemm_flow.hip): the kernel makes its rows from the residual stream itself (FlowNorm)
+  FlowNorm norm;
+  int lds_split;              // where the tokens' entries begin in LDS
 };
 
 enum { EPI_STORE = 0, EPI_SWIGLU = 1, EPI_LMHEAD = 2 };

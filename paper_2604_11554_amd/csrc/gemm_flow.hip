@@ -18,6 +18,7 @@
 //   o          7.1 ->  5.7   9.3 ->  7.7   9.8 ->  8.6  12.8 -> 11.2  (13.4 -> 14.0)
 //   down      12.7 ->  9.8  15.4 -> 12.8  15.8 -> 14.5  24.5 -> 19.1  (25.2 -> 23.4)
 //   LM head    128 ->  115
+// Calls of few tokens (NORM) make their rows themselves, see below.
 #include <mutex>
 #include <type_traits>
 
@@ -108,13 +109,126 @@ __device__ __forceinline__ void lm_store(const GemmArgs& a, const LmSums& s, int
   *reinterpret_cast<f32x4*>(a.part + ((size_t)t * n_parts + part) * 4) = pv;
 }
 
-template <int RT, int NT, int PL, int FMT, int EPI>
+// ---- the norm of the rows, where a call has so few of them that every workgroup can make them all (NORM) ----
+// A norm kernel costs its launch, a round trip for its row and another for the product's workgroups that wait for it: 3.9 us
+// before a product of 8 to 18 at one token.  Here the row's residual and planes (40 KB at the 4B shape) are asked for first and the
+// first weights right behind them, so that the norm passes in the shadow of the weights' latency; the rows stay in LDS, one
+// 16-byte read per lane, step and term.  The price is the rows once per workgroup, which is what bounds the number of tokens: up to
+// NV float4 slices of them per thread, five at most (a step of eight layers of the 4B shape, us: 1 token, three slices 638 -> 594;
+// 2, five 670 -> 643; 3, eight 690 -> 700; 4, ten 693 -> 722; the two-layer policy, 4 tokens 92 -> 79).
+constexpr int FLOW_NORM_NV = 5;
+template <int PL, int EPI>
+struct FlowRows {
+  // rows that keep their common factor out (Act::ss) but for LM heads, whose rows are read again, and one fp16 term, whose range
+  // unnormalised rows would strain
+  static constexpr bool LATE_FACTOR = EPI != EPI_LMHEAD && PL == 2;
+  __host__ __device__ static int pitch(int K) { return (K + 31) / 32 * 32 + 8; }   // elements; 16 bytes past the banks' period
+  __host__ __device__ static int x_bytes(int T, int K) { return PL * T * pitch(K) * 2; }
+  __host__ __device__ static int bytes(int T, int K) { return x_bytes(T, K) + T * (K / 4) * 4 + 16 * 4; }   // + squares of the slices, + factors
+};
+template <int NV, int PL, int FMT, int EPI>
+__device__ __forceinline__ void flow_rows_load(const GemmArgs& a, f32x4 (&v)[NV], u32x2 (&gain)[NV]) {
+  constexpr int PR = 4, NG = NV;                   // planes per round, slices in flight with them
+  const int nv = a.K >> 2, total = a.T * nv, tid = (int)threadIdx.x;
+  const FlowNorm& m = a.norm;
+#pragma unroll
+  for (int j0 = 0; j0 < NV; j0 += NG) {
+    if (256 * j0 >= total) break;                               // uniform
+    int f[NG];
+#pragma unroll
+    for (int j = 0; j < NG; ++j) {
+      f[j] = min(256 * (j0 + j) + tid, total - 1);              // a slice past the end repeats the last one and is never stored
+      v[j0 + j] = *reinterpret_cast<const f32x4*>(m.h + 4 * (size_t)f[j]);
+      gain[j0 + j] = *reinterpret_cast<const u32x2*>(m.gain + 4 * (f[j] % nv));
+    }
+    if (m.add)
+      for (int s0 = 0; s0 < m.n_planes; s0 += PR) {             // in plane order
+        f32x4 p[PR][NG];
+#pragma unroll
+        for (int q = 0; q < PR; ++q) {
+          const size_t plane = (size_t)min(s0 + q, m.n_planes - 1) * a.T * a.K;
+#pragma unroll
+          for (int j = 0; j < NG; ++j) p[q][j] = *reinterpret_cast<const f32x4*>(m.add + plane + 4 * (size_t)f[j]);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int q = 0; q < PR; ++q)
+          if (s0 + q < m.n_planes) {
+#pragma unroll
+            for (int j = 0; j < NG; ++j) v[j0 + j] += p[q][j];
+          }
+      }
+  }
+}
+// the rows into LDS as 16-bit terms [term][row][pitch], zeros behind K; the factors that are left out go to `late`
+template <int NV, int PL, int FMT, int EPI>
+__device__ __forceinline__ void flow_rows_finish(const GemmArgs& a, const f32x4 (&v)[NV], const u32x2 (&gain)[NV], unsigned char* lds,
+                                                 float* late, int wg, int n_wgs) {
+  using FR = FlowRows<PL, EPI>;
+  const int nv = a.K >> 2, total = a.T * nv, tid = (int)threadIdx.x, lane = tid & 63, wave = tid >> 6, pitch = FR::pitch(a.K);
+  h16_t* x = reinterpret_cast<h16_t*>(lds);
+  float* sq = reinterpret_cast<float*>(lds + FR::x_bytes(a.T, a.K));
+  float* factor = FR::LATE_FACTOR ? late : sq + total;
+  const FlowNorm& m = a.norm;
+#pragma unroll
+  for (int j = 0; j < NV; ++j) {
+    const int f = 256 * j + tid;
+    if (f >= total) continue;
+    sq[f] = v[j][0] * v[j][0] + v[j][1] * v[j][1] + v[j][2] * v[j][2] + v[j][3] * v[j][3];
+    if (m.add && m.h_out && j % n_wgs == wg) *reinterpret_cast<f32x4*>(m.h_out + 4 * (size_t)f) = v[j];
+  }
+  for (int i = tid; i < PL * a.T * (pitch - a.K) / 2; i += 256) {   // zeros behind the rows' ends
+    const int w = (pitch - a.K) / 2;
+    reinterpret_cast<uint32_t*>(x + (size_t)(i / w) * pitch + a.K)[i % w] = 0u;
+  }
+  auto put = [&]() {
+#pragma unroll
+    for (int j = 0; j < NV; ++j) {
+      const int f = 256 * j + tid;
+      if (f >= total) continue;
+      const int t = f / nv, k = 4 * (f - t * nv);
+      const float r = FR::LATE_FACTOR ? 1.f : factor[t];
+      float o[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const float g = h16_to_f32<FMT>((h16_t)((gain[j][e >> 1] >> (16 * (e & 1))) & 0xFFFFu));
+        o[e] = FR::LATE_FACTOR ? v[j][e] * g : v[j][e] * r * g;
+      }
+      uint32_t hi[2], lo[2] = {0u, 0u};
+#pragma unroll
+      for (int e = 0; e < 2; ++e) split_pair<FMT, PL>(o[2 * e], o[2 * e + 1], hi[e], lo[e]);
+      *reinterpret_cast<u32x2*>(x + (size_t)t * pitch + k) = u32x2{hi[0], hi[1]};
+      if (PL == 2) *reinterpret_cast<u32x2*>(x + (size_t)(a.T + t) * pitch + k) = u32x2{lo[0], lo[1]};
+      if (EPI == EPI_LMHEAD && j % n_wgs == wg) {
+        h16_t* dst = m.x_out + frag_act_offset(t, k & ~7, 0, a.x_mtiles, PL) + (k & 7);
+        *reinterpret_cast<u32x2*>(dst) = u32x2{hi[0], hi[1]};
+        if (PL == 2) *reinterpret_cast<u32x2*>(dst + 512) = u32x2{lo[0], lo[1]};
+      }
+    }
+  };
+  if (FR::LATE_FACTOR) put();
+  __syncthreads();
+  for (int t = wave; t < a.T; t += FLOW_WAVES) {
+    float s = 0.f;
+    for (int i = lane; i < nv; i += 64) s += sq[t * nv + i];
+    s = wave_sum(s);
+    if (lane == 0) factor[t] = 1.0f / sqrtf(s / (float)a.K + m.eps);
+  }
+  if (!FR::LATE_FACTOR) {
+    __syncthreads();
+    put();
+    __syncthreads();
+  }
+}
+
+template <int RT, int NT, int PL, int FMT, int EPI, int NORM = 0>
 __global__ __launch_bounds__(64 * FLOW_WAVES, 1) void gemm_flow_kernel(GemmArgs a) {
   using TL = FlowTiling<RT, NT, PL, EPI>;
+  static_assert(!NORM || NT == 1, "few tokens");
   constexpr int D = TL::D, NW = FLOW_WAVES, NR = TL::NR, NONTEMPORAL = 2;
   extern __shared__ __align__(16) unsigned char lds_raw[];
   f32x4* red = reinterpret_cast<f32x4*>(lds_raw);    // [tile][NR][lane]
-  typename TL::PerToken* tok_lds = reinterpret_cast<typename TL::PerToken*>(lds_raw + TL::SUM_BYTES);   // [16 NT]
+  typename TL::PerToken* tok_lds = reinterpret_cast<typename TL::PerToken*>(lds_raw + (NORM ? a.lds_split : TL::SUM_BYTES));   // [16 NT]
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int c16 = lane & 15, kg = lane >> 4;
   const int split = blockIdx.y;
@@ -151,27 +265,32 @@ __global__ __launch_bounds__(64 * FLOW_WAVES, 1) void gemm_flow_kernel(GemmArgs 
     x_lane[t] = (uint32_t)(tok >> 5) * (PL * 1024) + (uint32_t)((tok & 31) + 32 * (kg & 1)) * 16 + (uint32_t)(kg >> 1) * x_kstride;
     if (tok >= a.T) x_lane[t] = NOWHERE;
   }
+  f32x4 row_v[NORM ? NORM : 1];
+  u32x2 row_gain[NORM ? NORM : 1];
+  if constexpr (NORM) flow_rows_load<NORM, PL, FMT, EPI>(a, row_v, row_gain);
   // the rows' factors (Act::ss) are requested first of all and settled behind the first steps' loads
   f32x4 ssq = {1.f, 1.f, 1.f, 1.f};
-  const bool scaled = EPI != EPI_LMHEAD && a.x_ss != nullptr;
+  const bool scaled = NORM ? FlowRows<PL, EPI>::LATE_FACTOR : EPI != EPI_LMHEAD && a.x_ss != nullptr;
   LmRow lm = {};                                     // LM head: of token threadIdx.x
   if (EPI == EPI_LMHEAD) lm = lm_row(a, (int)threadIdx.x);
-  if (scaled) ssq = row_ss(a, min((int)threadIdx.x, a.T - 1));
+  if (!NORM && scaled) ssq = row_ss(a, min((int)threadIdx.x, a.T - 1));
   __builtin_amdgcn_sched_barrier(0);
 
   // Where the activations outweigh the weights the workgroups start at different steps: all of them reading the same lines of
   // the activations at the same time made the 4B shape's step of 64 tokens 2.8 % longer (5325 -> 5175 us; 45 tokens 1.0 %, 96
   // 1.9 %; fp16 120 2.0 %); with fewer activations (fp16 45 tokens, bf16 up to 16) nothing or 0.5 % the other way.
   const int rot = NT * PL >= 4 && n > 0 ? (int)blockIdx.x % n : 0;
-  struct Step { u32x4 w[RT], x[NT * PL]; };
+  struct Step { u32x4 w[RT], x[NORM ? 1 : NT * PL]; };
   auto load = [&](int i, Step& d) {
     const int s = i < n ? s_b + wave + NW * (i + rot < n ? i + rot : i + rot - n) : s_e;
     const uint32_t gone = (s >= s_e || (2 * s + 1 >= KS && kg >= 2)) ? NOWHERE : 0u;
     const uint32_t ws = (uint32_t)s * (2 * W_KSTRIDE * 2), xs = (uint32_t)s * 2 * x_kstride;
+    if constexpr (!NORM) {
 #pragma unroll
-    for (int t = 0; t < NT; ++t)
+      for (int t = 0; t < NT; ++t)
 #pragma unroll
-      for (int p = 0; p < PL; ++p) d.x[t * PL + p] = desc_load<0>(xd, x_lane[t] | gone, xs + p * 1024);
+        for (int p = 0; p < PL; ++p) d.x[t * PL + p] = desc_load<0>(xd, x_lane[t] | gone, xs + p * 1024);
+    }
 #pragma unroll
     for (int r = 0; r < RT; ++r) d.w[r] = desc_load<NONTEMPORAL>(wd[r], w_lane | gone, ws);
     __builtin_amdgcn_sched_barrier(0);
@@ -185,27 +304,51 @@ __global__ __launch_bounds__(64 * FLOW_WAVES, 1) void gemm_flow_kernel(GemmArgs 
 #pragma unroll
   for (int d = 0; d < D; ++d) load(d, st[d]);
   float rstd = 1.f;
-  if (scaled) rstd = row_rstd(a, ssq);
+  if constexpr (NORM)
+    flow_rows_finish<NORM, PL, FMT, EPI>(a, row_v, row_gain, lds_raw, reinterpret_cast<float*>(tok_lds), (int)(blockIdx.x + gridDim.x * blockIdx.y),
+                                         (int)(gridDim.x * gridDim.y));
+  else if (scaled) rstd = row_rstd(a, ssq);
   asm volatile("" : "+v"(rstd));
   if (EPI == EPI_LMHEAD) asm volatile("" : "+v"(lm.temperature), "+v"(lm.seed), "+v"(lm.pos));
   __builtin_amdgcn_sched_barrier(0);
+  // NORM: the lane's token row and features in LDS (lanes past the last token repeat it: their columns are never stored)
+  const int x_pitch = NORM ? FlowRows<PL, EPI>::pitch(a.K) : 0;
+  const h16_t* x_lds = reinterpret_cast<const h16_t*>(lds_raw) + (NORM ? min(c16, a.T - 1) * x_pitch + 8 * kg : 0);
   for (int i = 0; i < n; i += D)
 #pragma unroll
     for (int d = 0; d < D; ++d) {
+      if constexpr (NORM) {
+        const bool in = i + d < n;                   // past the end the weights are zeros and so are the rows
+        const int s = in ? s_b + wave + NW * (i + d) : 0;
+        u32x4 x[PL];
+#pragma unroll
+        for (int p = 0; p < PL; ++p) {
+          x[p] = *reinterpret_cast<const u32x4*>(x_lds + (size_t)p * a.T * x_pitch + 32 * s);
+          if (!in) x[p] = u32x4{0u, 0u, 0u, 0u};
+        }
+#pragma unroll
+        for (int p = PL - 1; p >= 0; --p)
+#pragma unroll
+          for (int r = 0; r < RT; ++r) acc[r][0] = mfma_16x16x32<FMT>(st[d].w[r], x[p], acc[r][0]);
+        __builtin_amdgcn_sched_barrier(0);
+        load(i + D + d, st[d]);
+        continue;
+      }
 #pragma unroll
       for (int p = PL - 1; p >= 0; --p)              // small term first
 #pragma unroll
         for (int r = 0; r < RT; ++r)
 #pragma unroll
-          for (int t = 0; t < NT; ++t) acc[r][t] = mfma_16x16x32<FMT>(st[d].w[r], st[d].x[t * PL + p], acc[r][t]);
+          for (int t = 0; t < NT; ++t) acc[r][t] = mfma_16x16x32<FMT>(st[d].w[r], st[d].x[NORM ? 0 : t * PL + p], acc[r][t]);
       __builtin_amdgcn_sched_barrier(0);
       load(i + D + d, st[d]);
     }
 
   // ---- the waves' sums, tile by tile in wave order ----
+  if constexpr (NORM) __syncthreads();               // the sums lie where the rows were
   if ((int)threadIdx.x < 16 * NT) {
     if constexpr (EPI == EPI_LMHEAD) tok_lds[threadIdx.x] = lm;
-    else if (scaled) tok_lds[threadIdx.x] = rstd;
+    else if (scaled && !NORM) tok_lds[threadIdx.x] = rstd;
   }
   auto put = [&]() {
 #pragma unroll
@@ -304,8 +447,30 @@ void launch_flow_one(const GemmArgs& a, dim3 grid, hipStream_t st) {
   });
   hipLaunchKernelGGL((gemm_flow_kernel<RT, NT, PL, FMT, EPI>), grid, dim3(64 * FLOW_WAVES), lds, st, a);
 }
+template <int RT, int PL, int FMT, int EPI, int NORM>
+void launch_flow_norm(GemmArgs a, dim3 grid, hipStream_t st) {
+  static std::once_flag attr_once;
+  using TL = FlowTiling<RT, 1, PL, EPI>;
+  constexpr int most = 64 * 1024;                     // of rows and sums; at most 10 KB of float4 slices go with 41 KB of terms
+  std::call_once(attr_once, [] {
+    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_flow_kernel<RT, 1, PL, FMT, EPI, NORM>),
+                              hipFuncAttributeMaxDynamicSharedMemorySize, most + TL::LDS_BYTES - TL::SUM_BYTES);
+  });
+  const int rows = (FlowRows<PL, EPI>::bytes(a.T, a.K) + 15) / 16 * 16;
+  a.lds_split = rows > TL::SUM_BYTES ? rows : TL::SUM_BYTES;
+  hipLaunchKernelGGL((gemm_flow_kernel<RT, 1, PL, FMT, EPI, NORM>), grid, dim3(64 * FLOW_WAVES),
+                     a.lds_split + TL::LDS_BYTES - TL::SUM_BYTES, st, a);
+}
 template <int RT, int NT, int EPI>
 void launch_flow_fmt(const GemmArgs& a, dim3 grid, const Act& x, hipStream_t st) {
+  if constexpr (NT == 1) {
+    if (a.norm.h) {
+      const bool few = a.T * (a.K / 4) <= 3 * 256;
+      if (x.dtype == DT_F16) few ? launch_flow_norm<RT, 1, DT_F16, EPI, 3>(a, grid, st) : launch_flow_norm<RT, 1, DT_F16, EPI, FLOW_NORM_NV>(a, grid, st);
+      else few ? launch_flow_norm<RT, 2, DT_BF16, EPI, 3>(a, grid, st) : launch_flow_norm<RT, 2, DT_BF16, EPI, FLOW_NORM_NV>(a, grid, st);
+      return;
+    }
+  }
   if (x.dtype == DT_F16) launch_flow_one<RT, NT, 1, DT_F16, EPI>(a, grid, st);
   else launch_flow_one<RT, NT, 2, DT_BF16, EPI>(a, grid, st);
 }
@@ -334,15 +499,21 @@ bool flow_format(int planes, int dtype) { return (dtype == DT_BF16 && planes == 
 
 }  // namespace
 
+bool gemm_flow_norm_form(int T, int K) { return T <= 16 && (long)T * (K / 4) <= FLOW_NORM_NV * 256L; }
+static bool norm_fits(const FlowNorm* norm, int T, int K) { return !norm || gemm_flow_norm_form(T, K); }
+
 bool gemm_flow_store_form(int N, int K, int T, int n_units, int planes, int dtype) {
   return flow_format(planes, dtype) && flow_store_form(N, K, T, n_units, planes);
 }
-hipError_t gemm_flow_store(const LinearW& w, const Act& x, int T, float* y, int ldy, const FlowPlan& plan, hipStream_t st) {
+hipError_t gemm_flow_store(const LinearW& w, const Act& x, int T, float* y, int ldy, const FlowPlan& plan, hipStream_t st,
+                           const FlowNorm* norm) {
+  if (!norm_fits(norm, T, w.K)) return hipErrorInvalidValue;
   if (!flow_format(x.planes, x.dtype) || x.pitch || T > (x.planes == 1 ? 128 : 96) || (T > 64 && plan.rt > FLOW_RT_MANY))
     return hipErrorInvalidValue;
   GemmArgs a = flow_args(x, w.N, w.K, T, plan.splits);
   for (int i = 0; i < 3; ++i) { a.w[i] = w.seg[i]; a.w_tiles[i] = (w.rows[i] + 31) / 32; }
   a.y = y; a.ldy = ldy;
+  if (norm) a.norm = *norm;
   if (plan.rt == 2) launch_flow<2, EPI_STORE>(a, plan.splits, x, st);
   else if (plan.rt == 4) launch_flow<4, EPI_STORE>(a, plan.splits, x, st);
   else if (plan.rt == 5) launch_flow<5, EPI_STORE>(a, plan.splits, x, st);
@@ -354,11 +525,14 @@ hipError_t gemm_flow_store(const LinearW& w, const Act& x, int T, float* y, int 
 bool gemm_flow_swiglu_form(int F, int T, int n_units, int planes, int dtype) {
   return flow_format(planes, dtype) && T <= 128 && flow_swiglu_rt(F, T, n_units) > 0;
 }
-hipError_t gemm_flow_swiglu(const h16_t* w_gate_up, int F, int K, const Act& x, int T, const Act& act, int n_units, hipStream_t st) {
+hipError_t gemm_flow_swiglu(const h16_t* w_gate_up, int F, int K, const Act& x, int T, const Act& act, int n_units, hipStream_t st,
+                            const FlowNorm* norm) {
+  if (!norm_fits(norm, T, K)) return hipErrorInvalidValue;
   if (!gemm_flow_swiglu_form(F, T, n_units, x.planes, x.dtype) || x.pitch || act.pitch) return hipErrorInvalidValue;
   GemmArgs a = flow_args(x, 2 * F, K, T, 1);
   a.w[0] = w_gate_up; a.w_tiles[0] = F / 16;
   a.act = act.p; a.act_mtiles = act.mtiles();
+  if (norm) a.norm = *norm;
   const int rt = flow_swiglu_rt(F, T, n_units);
   if (rt == 2) launch_flow<2, EPI_SWIGLU>(a, 1, x, st);
   else if (rt == 4) launch_flow<4, EPI_SWIGLU>(a, 1, x, st);
@@ -372,12 +546,15 @@ hipError_t gemm_flow_swiglu(const h16_t* w_gate_up, int F, int K, const Act& x, 
 // weigh as much as the weights and the sums through LDS more: 45 tokens in fp16 157 and 171, 64 in bf16 170 and 196)
 bool gemm_flow_lmhead_form(int T, int planes, int dtype) { return flow_format(planes, dtype) && T <= 16; }
 hipError_t gemm_flow_lmhead(const h16_t* w_lm, int V, int K, const Act& x, int T, float* logits, float* part, const uint64_t* seeds,
-                            const float* temperature, const int32_t* sample_pos, const int32_t* row_seq, bool draw, hipStream_t st) {
+                            const float* temperature, const int32_t* sample_pos, const int32_t* row_seq, bool draw, hipStream_t st,
+                            const FlowNorm* norm) {
+  if (!norm_fits(norm, T, K)) return hipErrorInvalidValue;
   if (!gemm_flow_lmhead_form(T, x.planes, x.dtype) || x.pitch || x.ss) return hipErrorInvalidValue;
   GemmArgs a = flow_args(x, V, K, T, 1);
   a.w[0] = w_lm; a.w_tiles[0] = (V + 31) / 32;
   a.logits = logits; a.part = part; a.seeds = seeds; a.temperature = temperature; a.sample_pos = sample_pos;
   a.row_seq = row_seq; a.draw = draw ? 1 : 0;
+  if (norm) { a.norm = *norm; a.norm.x_out = x.p; }
   launch_flow_fmt<8, 1, EPI_LMHEAD>(a, dim3(((V + 31) / 32 * 2 + 7) / 8), x, st);
   return hipGetLastError();
 }

@@ -97,17 +97,34 @@ hipError_t gemm_routed_swiglu(const h16_t* w_gate_up, int E, int F, int K, const
                               int n_pairs, int top_k, int max_rows, const Act& act, int32_t* group_off,
                               int32_t* pair_pos, hipStream_t st);
 
+// ---- the norm before a product, done by the product's own workgroups (calls of few tokens, gemm_flow.hip) ----
+// Row t is h[t] + the n_planes planes add[s][t], s ascending, then RMS-normalised with `gain`; every workgroup makes all rows for
+// itself and the launch writes the sums to h_out (another array than h: other workgroups still read that) where planes were added.
+struct FlowNorm {
+  const float* h;             // [T, K]; null: no norm, the rows are in the activation matrix
+  float* h_out;
+  const float* add;           // [n_planes][T, K] or null
+  int n_planes;
+  const h16_t* gain;
+  float eps;
+  h16_t* x_out;               // optional (LM head): the normalised rows, in fragment order
+};
 // ---- gemm_flow.hip: the same products for short calls of dense policies (activations in fragment order), on bf16 as two terms
 // or fp16 as one ----
 // y[split][t][n] in the planes of `plan` (flow_store_plan)
 bool gemm_flow_store_form(int N, int K, int T, int n_units, int planes, int dtype);   // whether the form is built, and the faster one
-hipError_t gemm_flow_store(const LinearW& w, const Act& x, int T, float* y, int ldy, const FlowPlan& plan, hipStream_t st);
+// (x.p is not read where `norm` gives the rows)
+bool gemm_flow_norm_form(int T, int K);              // whether the norm goes into the products of T rows of K
+hipError_t gemm_flow_store(const LinearW& w, const Act& x, int T, float* y, int ldy, const FlowPlan& plan, hipStream_t st,
+                           const FlowNorm* norm = nullptr);
 bool gemm_flow_swiglu_form(int F, int T, int n_units, int planes, int dtype);
-hipError_t gemm_flow_swiglu(const h16_t* w_gate_up, int F, int K, const Act& x, int T, const Act& act, int n_units, hipStream_t st);
+hipError_t gemm_flow_swiglu(const h16_t* w_gate_up, int F, int K, const Act& x, int T, const Act& act, int n_units, hipStream_t st,
+                            const FlowNorm* norm = nullptr);
 
 bool gemm_flow_lmhead_form(int T, int planes, int dtype);
 hipError_t gemm_flow_lmhead(const h16_t* w_lm, int V, int K, const Act& x, int T, float* logits, float* part, const uint64_t* seeds,
-                            const float* temperature, const int32_t* sample_pos, const int32_t* row_seq, bool draw, hipStream_t st);
+                            const float* temperature, const int32_t* sample_pos, const int32_t* row_seq, bool draw, hipStream_t st,
+                            const FlowNorm* norm = nullptr);
 
 // ---- gemm_long.hip: the same products for long calls on two-term bf16 activations in rows (Act::pitch) ----
 enum { LONG_512x128 = 0, LONG_128x128, LONG_512x64, LONG_160x128, LONG_192x128 };   // weight rows x tokens of a workgroup
