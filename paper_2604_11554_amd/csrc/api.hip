@@ -130,7 +130,7 @@ constexpr int ATTN_WGS_MAX = 1024;   // decode attention grid limit
 bool two_term(const rlx_model_config& c) { return c.activation_split && c.dtype == RLX_DTYPE_BF16; }
 int short_tokens(const rlx_model_config& c) { return two_term(c) && !c.n_experts ? 128 : 256; }   // of the calls that split K in up to 16
 bool long_call(const rlx_model_config& c, int T) { return T > short_tokens(c) && two_term(c); }
-// ... and so do LM heads of more than 64 rows (151 936 x 2560, one draw per row: 96 rows 234 -> 211 us, 256 rows 509 -> 396;
+// ... and so do LM heads of more than 64 rows (151 936 x 2560, one draw per row: 96 rows 234 -> 209 us, 256 rows 509 -> 435;
 // 64 rows 153 in the short form, 161 at best in long ones)
 bool rows_lmhead(const rlx_model_config& c, int rows) { return rows > 64 && two_term(c); }
 // Decode attention of MoE policies keeps a share of the keys per workgroup: in a share per wave the sums come in another
@@ -245,7 +245,7 @@ Workspace carve(const rlx_model_config& c, char* base, int S, int T, const Plane
   w.attn_share_start = base ? (int32_t*)(base + lm_at) : nullptr;
   const int score_rows = score_rows_max(T), lm_rows = S > score_rows ? S : score_rows;   // sampled rows, or a block of scored ones
   w.x_lm = (h16_t*)take(act_bytes(lm_rows, c.d_model, rows_lmhead(c, lm_rows)));
-  // a part per 64 ids in the form of many rows, per 32 in that of up to 64: there are at least 256 rows here
+  // a part per 64 ids or more in the forms of many rows, per 32 in that of up to 64: there are at least 256 rows here
   w.lm_part = (float*)take((size_t)lm_rows * (two_term(c) ? (c.vocab + 63) / 64 : (c.vocab + 31) / 32) * 4 * 4);
   const size_t shares_end = lm_at + align_up((size_t)ATTN_SHARES_MAX * ATTN_SHARE_WORDS * 4);
   w.bytes = off > shares_end ? off : shares_end;

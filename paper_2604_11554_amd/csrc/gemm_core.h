@@ -152,8 +152,8 @@ __device__ __forceinline__ void tile_epilogue(const GemmArgs& a, const f32x16 (&
 
 // LM-head epilogue of a wave: per token, its 32 JT vocabulary rows (tiles nt0 ..) are reduced to (max, sumexp, best
 // score, its id), record `part` of `n_parts` of the token's row.  The accumulators go through a scratch area in LDS
-// (`scr`: JT * MT * 4 KB of the wave's own), which lets the work on them run as a loop: written out over the registers it
-// was up to 50 KB of straight code per form.  The parts' order of sums differs from a sum id by id, not their precision.
+// (`scr`: JT * 4 KB of the wave's own, one token tile at a time), which lets the work on them run as a loop: written out
+// over the registers it was up to 50 KB of straight code per form.  The parts' order of sums differs from a sum id by id, not their precision.
 // What it needs to know of the lane's row is passed in, so that the caller can ask for it early (three dependent fetches
 // at the end of a kernel are three round trips).
 struct LmRow { float temperature; uint64_t seed; uint32_t pos; };
@@ -168,15 +168,12 @@ __device__ __forceinline__ void lmhead_epilogue(const GemmArgs& a, f32x4* scr, c
                                                 int nt0, int mt0, int part, int n_parts, int lane) {
   const int r32 = lane & 31, half = lane >> 5;
 #pragma unroll
-  for (int m = 0; m < MT; ++m)
+  for (int m = 0; m < MT; ++m) {
 #pragma unroll
     for (int j = 0; j < JT; ++j)
 #pragma unroll
       for (int q = 0; q < 4; ++q)
-        scr[((m * JT + j) * 4 + q) * WAVE + lane] =
-            f32x4{acc[j][m][4 * q], acc[j][m][4 * q + 1], acc[j][m][4 * q + 2], acc[j][m][4 * q + 3]};
-#pragma unroll
-  for (int m = 0; m < MT; ++m) {
+        scr[(j * 4 + q) * WAVE + lane] = f32x4{acc[j][m][4 * q], acc[j][m][4 * q + 1], acc[j][m][4 * q + 2], acc[j][m][4 * q + 3]};
     const int t = (mt0 + m) * 32 + r32;
     const bool ok = t < a.T;
     float mx = -INFINITY, se = 0.f, best = -INFINITY;
@@ -190,7 +187,7 @@ __device__ __forceinline__ void lmhead_epilogue(const GemmArgs& a, f32x4* scr, c
       for (int i = 0; i < 4 * JT; ++i) {
         const int nrow = nt0 * 32 + 8 * i + 4 * half;         // multiple of 4: one Philox block covers the four ids
         if (nrow >= a.N) break;
-        const f32x4 v = scr[(m * JT * 4 + i) * WAVE + lane];
+        const f32x4 v = scr[i * WAVE + lane];
         if (a.logits) {
           if (nrow + 3 < a.N) {
             *reinterpret_cast<f32x4*>(a.logits + (size_t)t * a.N + nrow) = v;

@@ -30,7 +30,8 @@ struct LongTiling {
   static constexpr int WFR = 2 * JW * WR, XFR = 4 * MW * WT;       // KB of weights and of activations per stage
   static constexpr int STAGE = (WFR + XFR) * 1024;
   static constexpr int PW = (WFR + WAVES - 1) / WAVES, PX = XFR / WAVES, P = PW + PX;   // copies per wave and stage
-  static constexpr int LDS_BYTES = NB * STAGE;
+  static constexpr int LM_TILES = JW % 2 ? JW : 2;                 // weight tiles of an LM head's part
+  static constexpr int LDS_BYTES = NB * STAGE, LM_SCRATCH = WAVES * LM_TILES * 4096;
   static_assert(XFR % WAVES == 0, "the waves share a stage's activations evenly");
 };
 
@@ -296,18 +297,17 @@ __global__ __launch_bounds__(64 * WR * WT) __attribute__((amdgpu_waves_per_eu(2,
       }
     }
   } else if constexpr (EPI == EPI_LMHEAD) {
-    static_assert(EPI != EPI_LMHEAD || (MW == 2 && JW % 2 == 0), "parts of two weight tiles");
     // every wave's copies and fragment reads are complete once it is past this barrier (waves without tokens have left; a
-    // barrier counts those that run): the stage buffers become the waves' scratch, two weight tiles at a time
+    // barrier counts those that run): the stage buffers become the waves' scratch, a part's weight tiles at a time
     asm volatile("s_barrier" ::: "memory");
-    f32x4* scr = reinterpret_cast<f32x4*>(lds_raw) + wave * 2 * 2 * 4 * WAVE;
-    static_assert(EPI != EPI_LMHEAD || TL::LDS_BYTES >= NW * 16 * 1024, "the waves' scratch fits");
-    const int n_parts = (n_tiles + 1) / 2;
+    constexpr int JT = TL::LM_TILES;
+    f32x4* scr = reinterpret_cast<f32x4*>(lds_raw) + wave * JT * 4 * WAVE;
+    const int n_parts = (n_tiles + JT - 1) / JT;
 #pragma unroll
-    for (int j = 0; j < JW; j += 2)
+    for (int j = 0; j < JW; j += JT)
       if (nt0 + j < n_tiles)
-        lmhead_epilogue<2, 2>(a, scr, reinterpret_cast<const f32x16(&)[2][2]>(acc[j]), lm, nt0 + j, tok0 >> 5, (nt0 + j) >> 1, n_parts,
-                              lane);
+        lmhead_epilogue<JT, MW>(a, scr, reinterpret_cast<const f32x16(&)[JT][MW]>(acc[j]), lm, nt0 + j, tok0 >> 5, (nt0 + j) / JT,
+                                n_parts, lane);
   }
 }
 
@@ -315,13 +315,15 @@ template <int JW, int MW, int WR, int WT, int NB, int EPI>
 void launch_form(const GemmArgs& a, int n_wt, int n_tt, int band, hipStream_t st) {
   using TL = LongTiling<JW, MW, WR, WT, NB>;
   static std::once_flag attr_once;                   // raise the dynamic LDS limit once per instantiation, from any thread
+  constexpr int lds = EPI == EPI_LMHEAD && TL::LM_SCRATCH > TL::LDS_BYTES ? TL::LM_SCRATCH : TL::LDS_BYTES;
+  static_assert(lds <= 160 * 1024, "LDS of a workgroup");
   std::call_once(attr_once, [] {
     (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_long_kernel<JW, MW, WR, WT, NB, EPI>),
-                              hipFuncAttributeMaxDynamicSharedMemorySize, TL::LDS_BYTES);
+                              hipFuncAttributeMaxDynamicSharedMemorySize, lds);
   });
   const long tiles = (long)n_wt * n_tt * a.splits;
   hipLaunchKernelGGL((gemm_long_kernel<JW, MW, WR, WT, NB, EPI>), dim3((unsigned)((tiles + 7) / 8 * 8)), dim3(64 * TL::WAVES),
-                     TL::LDS_BYTES, st, a, n_wt, n_tt, band);
+                     lds, st, a, n_wt, n_tt, band);
 }
 
 template <int EPI>
@@ -335,6 +337,9 @@ void launch_long(const GemmArgs& a, int form, int n_items, hipStream_t st) {
     if (form == LONG_160x128) launch_form<5, 1, 1, 4, 5, EPI>(a, wt(160), tt(128), 8, st);
     else if (form == LONG_192x128) launch_form<6, 1, 1, 4, 5, EPI>(a, wt(192), tt(128), 8, st);
     else launch_form<4, 2, 4, 1, 2, EPI>(a, wt(512), tt(64), 8, st);     // grouped only
+  } else {
+    if (form == LONG_320x128) launch_form<5, 1, 2, 4, 4, EPI>(a, wt(320), tt(128), 2, st);
+    else launch_form<5, 2, 2, 4, 3, EPI>(a, wt(320), tt(256), 1, st);
   }
 }
 
@@ -444,6 +449,11 @@ hipError_t gemm_long_grouped_store(const h16_t* w, int N, int K, const Act& x, c
   return hipGetLastError();
 }
 
+// Up to LM_FEW_ROWS rows: tiles of 320 vocabulary rows by all tokens (eight waves), which read the weights once and make 475 tiles of
+// 151 936 rows, nearly two even rounds on 256 units; a wave's 160 rows are a part.  us before (128 x 128) -> now, one draw per row:
+// K 2560, 96 rows 233 -> 211, 128 250 -> 227, 129 384 -> 341, 256 455 -> 435; K 2048, 128 rows 217 -> 196, 256 379 -> 355; the
+// parts' merge 10 -> 8.5.  (Of 64 rows and fewer tiles of 160 to 320 rows, one or two workgroups per unit, gave what the short
+// forms give.)
 hipError_t gemm_long_lmhead(const h16_t* w_lm, int V, int K, const Act& x, int T, float* logits, float* part,
                             const uint64_t* seeds, const float* temperature, const int32_t* sample_pos,
                             const int32_t* row_seq, bool draw, int n_units, hipStream_t st) {
@@ -452,7 +462,8 @@ hipError_t gemm_long_lmhead(const h16_t* w_lm, int V, int K, const Act& x, int T
   a.w[0] = w_lm; a.w_tiles[0] = (V + 31) / 32;
   a.logits = logits; a.part = part; a.seeds = seeds; a.temperature = temperature; a.sample_pos = sample_pos;
   a.row_seq = row_seq; a.draw = draw ? 1 : 0;
-  launch_long<EPI_LMHEAD>(a, plan_long(V, K, T, 1, n_units, false, true).form, 0, st);
+  const int form = T > LM_FEW_ROWS ? plan_long(V, K, T, 1, n_units, false, true).form : T <= 128 ? LONG_320x128 : LONG_320x256;
+  launch_long<EPI_LMHEAD>(a, form, 0, st);
   return hipGetLastError();
 }
 

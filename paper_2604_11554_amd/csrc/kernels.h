@@ -73,9 +73,13 @@ int gemm_plan_splits(int N, int K, int T, int max_splits, int n_units, int plane
 hipError_t gemm_store(const LinearW& w, const Act& x, int T, float* y, int ldy, int splits, hipStream_t st);
 // act[t][f] = silu(x Wg^T) * (x Wu^T); w_gate_up is the interleaved packed pair (pack_gate_up)
 hipError_t gemm_swiglu(const h16_t* w_gate_up, int F, int K, const Act& x, int T, const Act& act, hipStream_t st);
-// LM head with fused log-sum-exp and Gumbel-max partials: part[t][lmhead_parts()][4], a part per 32 vocabulary rows, or
-// per 64 in the long-call form
-inline int lmhead_parts(int vocab, const Act& x) { return x.pitch ? (vocab + 63) / 64 : (vocab + 31) / 32; }
+// LM head with fused log-sum-exp and Gumbel-max partials: part[t][lmhead_parts()][4], a part per 32 vocabulary rows, in the
+// long-call forms per 160 (calls of up to LM_FEW_ROWS rows) or 64
+constexpr int LM_FEW_ROWS = 256;
+inline int lmhead_parts(int vocab, const Act& x) {
+  const int tiles = (vocab + 31) / 32, per = !x.pitch ? 1 : x.T <= LM_FEW_ROWS ? 5 : 2;
+  return (tiles + per - 1) / per;
+}
 // row_seq (optional): row t reads temperature[row_seq[t]]; draw = false skips the Gumbel-max draw (scoring)
 hipError_t gemm_lmhead(const h16_t* w_lm, int V, int K, const Act& x, int T, float* logits, float* part,
                        const uint64_t* seeds, const float* temperature, const int32_t* sample_pos,
@@ -127,7 +131,8 @@ hipError_t gemm_flow_lmhead(const h16_t* w_lm, int V, int K, const Act& x, int T
                             const FlowNorm* norm = nullptr);
 
 // ---- gemm_long.hip: the same products for long calls on two-term bf16 activations in rows (Act::pitch) ----
-enum { LONG_512x128 = 0, LONG_128x128, LONG_512x64, LONG_160x128, LONG_192x128 };   // weight rows x tokens of a workgroup
+enum { LONG_512x128 = 0, LONG_128x128, LONG_512x64, LONG_160x128, LONG_192x128,   // weight rows x tokens of a workgroup
+       LONG_320x128, LONG_320x256 };                                              // ... of LM heads of few rows
 // y[split][t][n]: form, and K cut into at most max_splits planes: the fastest number, or the largest (`finest`)
 struct LongPlan { int form, splits; };
 LongPlan gemm_long_plan(int N, int K, int T, int max_splits, int n_units, bool finest);
