@@ -96,6 +96,8 @@ struct rlx_model {
 
 namespace {
 
+int prefix_wgs(const rlx_model* m) { return 2 * m->n_units; }   // workgroups of the prefix tiles: all resident
+
 struct Workspace {
   TokenMeta meta;
   float* h;          // [T, d]
@@ -375,7 +377,7 @@ int run_layers(const rlx_model* m, h16_t* pool, int64_t n_blocks, const Workspac
       at.n_seqs = io.n_seqs; at.unit_prefix = w.attn_prefix; at.share_start = w.attn_share_start; at.plan_hdr = w.attn_hdr;
       at.team = attn_by_team(c); at.n_wgs = m->attn_wgs; at.part = w.attn_part; at.o = ob;
       at.shared = io.shared_prefix; at.seq_part = w.attn_seq_part; at.pre_part = w.attn_pre_part;
-      at.n_prefix_wgs = 2 * m->n_units;
+      at.n_prefix_wgs = prefix_wgs(m);
       RLX_LAUNCH(RLX_K_ATTN_PREFIX, attention_decode_prefix(at, st));
       RLX_LAUNCH(RLX_K_ATTN, attention_decode(at, st));
       RLX_LAUNCH(RLX_K_ATTN_MERGE, attention_decode_merge(at, st));
@@ -816,7 +818,7 @@ int rlx_shared_prefix_build(const rlx_model* m, int32_t n_seqs, const int32_t* l
       return fail(RLX_EINVAL, "rlx_shared_prefix_build: sequence %d: leader %d (0..%d) / shared_pages %d", i, leader[i],
                   i, shared_pages[i]);
   std::vector<int32_t> host(words);
-  shared_prefix_build(n_seqs, m->cfg.n_q_heads, m->cfg.n_kv_heads, leader, shared_pages, host.data());
+  shared_prefix_build(n_seqs, m->cfg.n_q_heads, m->cfg.n_kv_heads, leader, shared_pages, attn_by_team(m->cfg) ? 0 : prefix_wgs(m), host.data());
   hipStream_t st = (hipStream_t)stream;
   RLX_HIP(hipMemcpyAsync(desc, host.data(), words * 4, hipMemcpyHostToDevice, st));
   RLX_HIP(hipStreamSynchronize(st));      // the staging vector dies with this call

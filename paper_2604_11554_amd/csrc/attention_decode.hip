@@ -28,6 +28,11 @@
 // are the query heads of all its member sequences, so the shared pages are read once per subgroup (the eight
 // responses of a prompt at the 4B shape) instead of once per sequence; the per-sequence kernel starts after the
 // shared units, and the merge kernel adds the prefix parts first.
+#include <algorithm>
+#include <mutex>
+#include <type_traits>
+#include <vector>
+
 #include "attn_core.h"
 #include "embed.h"
 #include "lds_copy.h"
@@ -45,16 +50,20 @@ struct PageRegs {
 // Views into the shared-prefix descriptor (kernels.h); `on` is false when there is none or it was built for
 // another batch size, and every index read from it is clamped by its user.
 struct SharedView {
-  bool on;
+  bool on, again;                                    // again: some pages are read by more than one tile
   int n_tiles, max_tiles;
   const int32_t *start_unit, *tile0, *n_chunks, *col0, *t_row, *t_kvh, *t_lo, *t_hi, *t_mem;
 };
 __device__ __forceinline__ SharedView shared_view(const int32_t* sp, int n_seqs, int Hkv) {
   SharedView v = {};
-  v.on = sp != nullptr && sp[0] == n_seqs;
+  if (sp == nullptr) return v;
+  typedef int32_t i32x4 __attribute__((ext_vector_type(4)));
+  const i32x4 head = *reinterpret_cast<const i32x4*>(sp);     // at once: one round trip before anything else is read
+  v.on = head[0] == n_seqs;
   if (!v.on) return v;
   v.max_tiles = shared_prefix_max_tiles(n_seqs, Hkv);
-  v.n_tiles = min(max(sp[1], 0), v.max_tiles);
+  v.n_tiles = min(max(head[1], 0), v.max_tiles);
+  v.again = head[3] != 0;
   const int32_t* p = sp + SP_HDR;
   v.start_unit = p; v.tile0 = p + n_seqs; v.n_chunks = p + 2 * n_seqs; v.col0 = p + 3 * n_seqs;
   p += 4 * (size_t)n_seqs;
@@ -443,72 +452,162 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 // the KV head's group); every key of the tile's units is visible to every member (the pages are full and shared).
 // The four waves take units round-robin and are merged through LDS; (o, m, l) of all columns go to pre_part.  The
 // query fragments of a tile sit in LDS (with two column tiles they would take half the register file).
+// What bounds it: latency.  A wave has two to four units of a tile, and without registers for a second set of pages it waited for
+// every one of them from the block table on.  The hardware now copies a unit's pages into the wave's part of LDS while the wave works
+// on the one before, whose fragments are in registers by then (chunks permuted as in prefill attention: no bank conflicts); a tile's
+// description, members and block-table entries are requested a tile ahead, and its queries behind its first pages.  Pages that one
+// tile alone reads are copied with the streaming mark; tiles are as many as there are workgroups where chunks can be longer instead.
+// us a layer of the 4B shape, before / copies / longest tiles first / one round of tiles / streaming mark: 32 groups of eight with prompts
+// of 517 to 2048 positions 50.6 / 48.3 / 47.1 / 45.8 / 41.4 (168 MB, 4.1 TB/s); fp16, 32 of four, 400 to 1500, 38 / 35 / 34 / 32 / 29;
+// 16 groups of sixteen, whose pages two tiles read, 42 / - / - / - / 34.  Short prompts (200 to 600) 21 before and now: the start, four
+// round trips from the header to the pages, and the merge.
+template <int HD, int NCT, int PL>
+struct PrefixLds {
+  static constexpr int UNIT = 4 * 16 * HD;           // elements of two pages of a KV head
+  static constexpr int Q_BYTES = PL * NCT * (HD / 32) * WAVE * 16, PAGES_BYTES = 4 * UNIT * 2;
+  static constexpr int O_BYTES = 2 * NCT * (HD / 16) * WAVE * 16, ML_BYTES = 2 * NCT * 2 * WAVE * 4;   // of the merge, over the pages
+  static constexpr int BYTES = Q_BYTES + PAGES_BYTES;
+  static_assert(O_BYTES + ML_BYTES <= PAGES_BYTES && BYTES <= 80 * 1024, "two workgroups per unit");
+};
 template <int HD, int PL, int FMT, int NCT>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_decode_prefix_kernel(AttnDecodeArgs a) {
-  constexpr int DT = HD / 16, KS = HD / 32, PS = HD + 4, NQ = PL * NCT * KS;
-  __shared__ f32x4 lds_o[2 * NCT * DT * WAVE];
-  __shared__ float lds_ml[2 * NCT * 2 * WAVE];
-  __shared__ u32x4 lds_q[NQ * WAVE];                 // fragment (p, c, ks) at ((p * NCT + c) * KS + ks) * 64 + lane
+  constexpr int DT = HD / 16, KS = HD / 32, PS = HD + 4, NQ = PL * NCT * KS, RCH = HD / 8;
+  constexpr int PAGE = 2 * 16 * HD, COPIES = PAGE * 2 / 1024;   // elements of a page, 1 KB copies of one
+  typedef PrefixLds<HD, NCT, PL> L;
+  extern __shared__ __align__(16) unsigned char prefix_lds[];
+  u32x4* lds_q = reinterpret_cast<u32x4*>(prefix_lds);          // fragment (p, c, ks) at ((p * NCT + c) * KS + ks) * 64 + lane
   const SharedView sv = shared_view(a.shared, a.n_seqs, a.Hkv);
-  if (!sv.on) return;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  if (!sv.on || (int)blockIdx.x >= sv.n_tiles) return;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int c16 = lane & 15, g = lane >> 4;
   const int group = a.Hq / a.Hkv;
   const float scale = rsqrtf((float)HD);
-  const size_t page = (size_t)2 * 16 * HD;
-  for (int t = blockIdx.x; t < sv.n_tiles; t += gridDim.x) {
-    const int row = min(max(sv.t_row[t], 0), a.n_seqs - 1);
-    const int kvh = min(max(sv.t_kvh[t], 0), a.Hkv - 1);
-    const int lo = max(sv.t_lo[t], 0), hi = min(sv.t_hi[t], a.max_blocks / 2);
+  h16_t* my_pages = reinterpret_cast<h16_t*>(prefix_lds + L::Q_BYTES) + wave * L::UNIT;
+  f32x4* lds_o = reinterpret_cast<f32x4*>(prefix_lds + L::Q_BYTES);
+  float* lds_ml = reinterpret_cast<float*>(prefix_lds + L::Q_BYTES + L::O_BYTES);
+  const uint32_t pages_at = lds_address(my_pages);
+
+  // ---- what the tiles are ----
+  struct Tile { int row, kvh, lo, hi, mem[NCT]; };   // all but the members uniform; mem: sequence of the lane's column, or out of range
+  auto load_tile = [&](int t) {                      // requested, to be settled by `tile`
+    Tile d;
+    d.row = sv.t_row[t]; d.kvh = sv.t_kvh[t]; d.lo = sv.t_lo[t]; d.hi = sv.t_hi[t];
+#pragma unroll
+    for (int c = 0; c < NCT; ++c) {
+      const int mi = (16 * c + c16) / group;
+      d.mem[c] = sv.t_mem[(size_t)t * 16 + min(mi, 15)];
+      if (mi > 15) d.mem[c] = -1;
+    }
+    return d;
+  };
+  auto tile = [&](Tile d) {
+    d.row = min(max(__builtin_amdgcn_readfirstlane(d.row), 0), a.n_seqs - 1);
+    d.kvh = min(max(__builtin_amdgcn_readfirstlane(d.kvh), 0), a.Hkv - 1);
+    d.lo = max(__builtin_amdgcn_readfirstlane(d.lo), 0);
+    d.hi = min(__builtin_amdgcn_readfirstlane(d.hi), a.max_blocks / 2);
+    return d;
+  };
+  // entries of the 32 units from unit `first` on: lane i holds block 2 first + i
+  auto load_window = [&](const Tile& d, int first) {
+    return a.block_table[(size_t)d.row * a.max_blocks + min(2 * first + lane, a.max_blocks - 1)];
+  };
+
+  // ---- copies of a unit: chunk (16 bytes) i * 64 + lane of a page comes from byte offset ... of it ----
+  uint32_t k_off[COPIES / 2], v_off;                 // K rows' chunks permuted; V^T, 16 features at a time: the first chunks
+#pragma unroll                                       // (tokens 0..7) of their rows, then the second
+  for (int i = 0; i < COPIES / 2; ++i) {
+    const int chunk = 64 * i + lane, row = chunk / RCH;
+    k_off[i] = (uint32_t)(row * RCH + ((chunk % RCH) ^ (RCH == 16 ? row : (row >> 1) & 7))) * 16;
+  }
+  v_off = (uint32_t)(16 * RCH + ((lane >> 5) * 16 + (lane & 15)) * 2 + ((lane >> 4) & 1)) * 16;
+  bool ok0 = false, ok1 = false;                     // of the unit in the wave's part of LDS
+  auto copy_unit = [&](const Tile& d, int32_t window, int rel) {   // rel: unit counted from the window's first
+    const int64_t n0 = __builtin_amdgcn_readlane(window, 2 * rel), n1 = __builtin_amdgcn_readlane(window, 2 * rel + 1);
+    ok0 = n0 >= 0 && n0 < a.n_blocks;
+    ok1 = n1 >= 0 && n1 < a.n_blocks;
+    const int64_t b0 = ok0 ? n0 : 0, b1 = ok1 ? n1 : b0;   // keep the copies in bounds; scores are masked
+#pragma unroll
+    for (int half = 0; half < 2; ++half) {
+      const unsigned char* page = reinterpret_cast<const unsigned char*>(a.pool_layer + ((size_t)(half ? b1 : b0) * a.Hkv + d.kvh) * PAGE);
+      const uint32_t dst = pages_at + half * PAGE * 2;
+      auto copy = [&](auto again) {
+        auto one = [&](const unsigned char* p, uint32_t off, uint32_t to) {
+          if constexpr (decltype(again)::value) copy_to_lds(p, off, to);
+          else copy_to_lds_stream(p, off, to);
+        };
+#pragma unroll
+        for (int i = 0; i < COPIES / 2; ++i) one(page, k_off[i], dst + i * 1024);
+#pragma unroll
+        for (int i = 0; i < COPIES / 2; ++i) one(page + i * 1024, v_off, dst + (COPIES / 2 + i) * 1024);
+      };
+      if (sv.again) copy(std::true_type());
+      else copy(std::false_type());
+    }
+  };
+
+  // tiles of a workgroup: the list comes longest first and is walked to and fro, so that who begins with a long tile goes on
+  // with a short one
+  auto tile_of = [&](int k) { return k * (int)gridDim.x + (k & 1 ? (int)gridDim.x - 1 - (int)blockIdx.x : (int)blockIdx.x); };
+  Tile d = tile(load_tile(blockIdx.x));
+  int32_t window = load_window(d, d.lo);
+  for (int k = 0; tile_of(k) < sv.n_tiles; ++k) {
+    const int t = tile_of(k);
+    int wlo = d.lo;                                  // first unit of the window
+    if (d.lo + wave < d.hi) copy_unit(d, window, wave);
     // the waves share the fetch of the tile's query fragments
 #pragma unroll
     for (int i = 0; i < (NQ + 3) / 4; ++i) {
       const int f = wave + 4 * i;
       if (f < NQ) {
         const int p = f / (NCT * KS), c = (f / KS) % NCT, ks = f % KS;
-        const int col = 16 * c + c16, mi = col / group;
-        const int mem = mi < 16 ? sv.t_mem[(size_t)t * 16 + mi] : -1;
+        int mem = d.mem[0];
+#pragma unroll
+        for (int cc = 1; cc < NCT; ++cc) mem = c == cc ? d.mem[cc] : mem;
         const bool col_ok = mem >= 0 && mem < a.n_seqs;
-        const int head = kvh * group + col % group;
-        const u32x4 z = {0u, 0u, 0u, 0u};
-        u32x4 q = z;
+        const int head = d.kvh * group + (16 * c + c16) % group;
+        u32x4 q = {0u, 0u, 0u, 0u};
         if (col_ok)
           q = *reinterpret_cast<const u32x4*>(a.q.p + p * a.q.plane + ((size_t)mem * a.Hq + head) * HD + 32 * ks + 8 * g);
         lds_q[f * WAVE + lane] = q;
       }
     }
+    const Tile next = load_tile(min(tile_of(k + 1), sv.n_tiles - 1));
     __syncthreads();
     auto qf = [&](int p, int c, int ks) {
       return __builtin_bit_cast(h16x8, lds_q[((p * NCT + c) * KS + ks) * WAVE + lane]);
     };
     WaveState<HD, NCT> st;
     st.reset();
-    const int32_t* table = a.block_table + (size_t)row * a.max_blocks;
     int pos_col[NCT];
 #pragma unroll
     for (int c = 0; c < NCT; ++c) pos_col[c] = 0x7FFFFFFF;
-    for (int i = lo + wave; i < hi; i += 4) {          // 2 i + 1 < max_blocks by the clamp of hi
-      int64_t b0 = table[2 * i], b1 = table[2 * i + 1];
-      const bool ok0 = b0 >= 0 && b0 < a.n_blocks, ok1 = b1 >= 0 && b1 < a.n_blocks;
-      if (!ok0) b0 = 0;                                // keep the loads in bounds; scores are masked
-      if (!ok1) b1 = b0;
-      const h16_t* kp0 = a.pool_layer + ((size_t)b0 * a.Hkv + kvh) * page;
-      const h16_t* kp1 = a.pool_layer + ((size_t)b1 * a.Hkv + kvh) * page;
+    for (int i = d.lo + wave; i < d.hi; i += 4) {    // 2 i + 1 < max_blocks by the clamp of hi
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the unit's pages are in LDS
       h16x8 k0[KS], k1[KS], vf[DT];
 #pragma unroll
       for (int ks = 0; ks < KS; ++ks) {
-        k0[ks] = load_h16x8(kp0 + c16 * HD + 32 * ks + 8 * g);     // the tiles of a group read these pages again:
-        k1[ks] = load_h16x8(kp1 + c16 * HD + 32 * ks + 8 * g);     // ordinary loads (the streaming mark cost 25 % here)
+        const int off = c16 * HD + ((4 * ks + g) ^ (RCH == 16 ? c16 : (c16 >> 1) & 7)) * 8;
+        k0[ks] = load_h16x8(my_pages + off);
+        k1[ks] = load_h16x8(my_pages + PAGE + off);
       }
 #pragma unroll
-      for (int dt = 0; dt < DT; ++dt)
-        vf[dt] = load_2x4(kp0 + 16 * HD + (size_t)(16 * dt + c16) * 16 + 4 * g,
-                          kp1 + 16 * HD + (size_t)(16 * dt + c16) * 16 + 4 * g);
-      asm volatile("" ::: "memory");                   // query fragments are re-read from LDS, not kept in registers
-      pair_step<HD, NCT, PL, FMT>(st, k0, k1, vf, qf, 32 * i, 32 * i + 16, ok0, ok1, 0x7FFFFFFF, pos_col, ok0 && ok1,
-                                  scale, g);
+      for (int dt = 0; dt < DT; ++dt) {
+        const int off = 16 * HD + dt * 256 + (g >> 1) * 128 + c16 * 8 + (g & 1) * 4;
+        vf[dt] = load_2x4(my_pages + off, my_pages + PAGE + off);
+      }
+      const bool o0 = ok0, o1 = ok1;
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // ... and in registers: the next one's may overwrite them
+      if (i + 4 < d.hi) {
+        if (i + 4 >= wlo + 32) { wlo += 32; window = load_window(d, wlo); }
+        copy_unit(d, window, i + 4 - wlo);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      pair_step<HD, NCT, PL, FMT>(st, k0, k1, vf, qf, 32 * i, 32 * i + 16, o0, o1, 0x7FFFFFFF, pos_col, o0 && o1, scale, g);
     }
+    d = tile(next);
+    window = load_window(d, d.lo);
     st.finish_denominators();
+    __syncthreads();                                   // the pages' place is the merge's now
     merge_waves<HD, NCT>(st, lds_o, lds_ml, wave, lane);
     if (wave == 0) {
 #pragma unroll
@@ -764,7 +863,7 @@ hipError_t decode_begin(DecodeBeginArgs b, int n_wgs, hipStream_t st) {
 // Host side of the descriptor.  A group is a run of consecutive sequences with the same leader (the first of them);
 // its shared units are the smallest shared page count of its members, halved.  Groups of one, groups that share
 // less than one unit, and models whose 32 columns hold a single sequence get no tiles.
-void shared_prefix_build(int n_seqs, int Hq, int Hkv, const int32_t* leader, const int32_t* shared_pages, int32_t* words) {
+void shared_prefix_build(int n_seqs, int Hq, int Hkv, const int32_t* leader, const int32_t* shared_pages, int most_tiles, int32_t* words) {
   const int group = Hq / Hkv, MS = shared_prefix_members(group);
   const int max_tiles = shared_prefix_max_tiles(n_seqs, Hkv);
   const size_t n_words = shared_prefix_words(n_seqs, Hkv);
@@ -789,43 +888,69 @@ void shared_prefix_build(int n_seqs, int Hq, int Hkv, const int32_t* leader, con
     }
     int chunks_cap = n_sub_total ? max_tiles / (n_sub_total * Hkv) : 0;
     if (chunks_cap > SP_MAX_CHUNKS) chunks_cap = SP_MAX_CHUNKS;
+    // the longest prefixes first: a workgroup's second tile comes from the other end of the list (PrefixOrder)
+    struct Group { int b, e, units; };
+    std::vector<Group> groups;
     for (int b = 0; b < n_seqs && chunks_cap >= 1;) {
       int e = b + 1;
       while (e < n_seqs && leader[e] == b && leader[b] == b) ++e;
       int units = 0x7FFFFFFF;
       for (int i = b; i < e; ++i) units = shared_pages[i] / 2 < units ? shared_pages[i] / 2 : units;
-      if (e - b >= 2 && units > 0) {
-        int nc = (units + 7) / 8;                      // at least eight units (256 keys) per chunk
-        if (nc > chunks_cap) nc = chunks_cap;
-        const int per = (units + nc - 1) / nc;
-        nc = (units + per - 1) / per;                  // no empty chunk
-        for (int sb = b; sb < e; sb += MS) {
-          const int se = sb + MS < e ? sb + MS : e;
-          for (int i = sb; i < se; ++i) {
-            start_unit[i] = units; tile0[i] = n_tiles; n_chunks[i] = nc; col0[i] = (i - sb) * group;
-          }
-          for (int c = 0; c < nc; ++c)
-            for (int h = 0; h < Hkv; ++h) {
-              const int t = n_tiles + c * Hkv + h;
-              t_row[t] = b; t_kvh[t] = h; t_lo[t] = c * per; t_hi[t] = (c + 1) * per < units ? (c + 1) * per : units;
-              for (int i = sb; i < se; ++i) t_mem[t * 16 + (i - sb)] = i;
-            }
-          n_tiles += nc * Hkv;
-        }
-      }
+      if (e - b >= 2 && units > 0) groups.push_back({b, e, units});
       b = e;
+    }
+    std::stable_sort(groups.begin(), groups.end(), [](const Group& x, const Group& y) { return x.units > y.units; });
+    // at least eight units (256 keys) per chunk, and more where the tiles would be more than there are workgroups at once
+    int least = 8;
+    auto chunks = [&](const Group& gr) { return std::min((gr.units + least - 1) / least, chunks_cap); };
+    for (bool more = most_tiles > 0; more;) {
+      int64_t tiles = 0;
+      more = false;
+      for (const Group& gr : groups) {
+        tiles += (int64_t)((gr.e - gr.b + MS - 1) / MS) * Hkv * chunks(gr);
+        more |= chunks(gr) > 1;
+      }
+      more &= tiles > most_tiles;
+      if (more) ++least;
+    }
+    for (const Group& gr : groups) {
+      int nc = chunks(gr);
+      const int per = (gr.units + nc - 1) / nc;
+      nc = (gr.units + per - 1) / per;                 // no empty chunk
+      if (gr.e - gr.b > MS) words[3] = 1;              // several tiles read these pages
+      for (int sb = gr.b; sb < gr.e; sb += MS) {
+        const int se = sb + MS < gr.e ? sb + MS : gr.e;
+        for (int i = sb; i < se; ++i) {
+          start_unit[i] = gr.units; tile0[i] = n_tiles; n_chunks[i] = nc; col0[i] = (i - sb) * group;
+        }
+        for (int c = 0; c < nc; ++c)
+          for (int h = 0; h < Hkv; ++h) {
+            const int t = n_tiles + c * Hkv + h;
+            t_row[t] = gr.b; t_kvh[t] = h; t_lo[t] = c * per; t_hi[t] = (c + 1) * per < gr.units ? (c + 1) * per : gr.units;
+            for (int i = sb; i < se; ++i) t_mem[t * 16 + (i - sb)] = i;
+          }
+        n_tiles += nc * Hkv;
+      }
     }
   }
   words[1] = n_tiles;
 }
 
+template <int HD, int PL, int FMT, int NCT>
+static void launch_prefix_columns(const AttnDecodeArgs& a, dim3 grid, hipStream_t st) {
+  static std::once_flag raised;                      // above the default limit of 64 KB per workgroup
+  constexpr int lds = PrefixLds<HD, NCT, PL>::BYTES;
+  std::call_once(raised, [] {
+    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_decode_prefix_kernel<HD, PL, FMT, NCT>),
+                              hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+  });
+  hipLaunchKernelGGL((attn_decode_prefix_kernel<HD, PL, FMT, NCT>), grid, dim3(256), lds, st, a);
+}
 template <int HD, int PL, int FMT>
 static void launch_prefix(const AttnDecodeArgs& a, dim3 grid, hipStream_t st) {
   // one column tile holds all members when there is one query head per KV head; two otherwise
-  if (shared_prefix_members(a.Hq / a.Hkv) * (a.Hq / a.Hkv) <= 16)
-    hipLaunchKernelGGL((attn_decode_prefix_kernel<HD, PL, FMT, 1>), grid, dim3(256), 0, st, a);
-  else
-    hipLaunchKernelGGL((attn_decode_prefix_kernel<HD, PL, FMT, 2>), grid, dim3(256), 0, st, a);
+  if (shared_prefix_members(a.Hq / a.Hkv) * (a.Hq / a.Hkv) <= 16) launch_prefix_columns<HD, PL, FMT, 1>(a, grid, st);
+  else launch_prefix_columns<HD, PL, FMT, 2>(a, grid, st);
 }
 
 hipError_t attention_decode_prefix(const AttnDecodeArgs& a, hipStream_t st) {

@@ -16,6 +16,10 @@ __device__ __forceinline__ void copy_to_lds(const void* g, uint32_t lds) {
 __device__ __forceinline__ void copy_to_lds(const void* base, uint32_t offset, uint32_t lds) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(offset), "s"(base) : "memory", "m0");
 }
+// ... for data that the launch reads once (load_stream_16)
+__device__ __forceinline__ void copy_to_lds_stream(const void* base, uint32_t offset, uint32_t lds) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt" ::"s"(lds), "v"(offset), "s"(base) : "memory", "m0");
+}
 #pragma clang diagnostic pop
 // Waits until at most N of this wave's copies are in flight and its LDS reads are done, then for the other waves.
 template <int N>
