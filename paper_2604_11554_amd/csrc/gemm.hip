@@ -267,7 +267,7 @@ __global__ __launch_bounds__(GEMM_THREADS, 2) void gemm_skinny_kernel(GemmArgs a
   if (!have_tile) return;
   if (PL != 2) fetch_lm_rows();
   if constexpr (EPI == EPI_LMHEAD)                   // past the last barrier: the activation chunks are dead
-    lmhead_epilogue<1, MT>(a, reinterpret_cast<f32x4*>(lds) + wave * 4 * WAVE, reinterpret_cast<const f32x16(&)[1][MT]>(acc),
+    lmhead_epilogue<1, MT, true>(a, reinterpret_cast<f32x4*>(lds) + wave * 4 * WAVE, reinterpret_cast<const f32x16(&)[1][MT]>(acc),
                            lm, nt, mt0, nt, n_tiles, lane);
   else
     tile_epilogue<MT, EPI, PL, FMT>(a, acc, nt, n_tiles, mt0, split, row_base, lane, rs);

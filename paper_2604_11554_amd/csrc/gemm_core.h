@@ -163,7 +163,12 @@ __device__ __forceinline__ LmRow lm_row(const GemmArgs& a, int t) {
   if (a.draw) { r.seed = a.seeds[tc]; r.pos = (uint32_t)a.sample_pos[tc]; }
   return r;
 }
-template <int JT, int MT>
+// LINES: how the logits leave (if they are asked for).  In lines of a row, past the caches, eight lanes a line, or by each lane its own
+// 16 bytes of a row per instruction, of rows that lie a vocabulary apart.  What the caches hold back they write while other
+// workgroups' weights stream: 45 rows of 151 936 ids, K 2560, 174 us -> 158, fp16 157 -> 146 (whole lines alone 171 and 154; no
+// logits 157 and 133).  The long-call forms have no other workgroup on the unit that would use the time and pay for the passes through
+// LDS: 128 rows of the MoE batch 1535 us a step by lanes, 1541 by lines.
+template <int JT, int MT, bool LINES>
 __device__ __forceinline__ void lmhead_epilogue(const GemmArgs& a, f32x4* scr, const f32x16 (&acc)[JT][MT], const LmRow (&row)[MT],
                                                 int nt0, int mt0, int part, int n_parts, int lane) {
   const int r32 = lane & 31, half = lane >> 5;
@@ -173,7 +178,29 @@ __device__ __forceinline__ void lmhead_epilogue(const GemmArgs& a, f32x4* scr, c
     for (int j = 0; j < JT; ++j)
 #pragma unroll
       for (int q = 0; q < 4; ++q)
-        scr[(j * 4 + q) * WAVE + lane] = f32x4{acc[j][m][4 * q], acc[j][m][4 * q + 1], acc[j][m][4 * q + 2], acc[j][m][4 * q + 3]};
+        scr[(j * 4 + q) * WAVE + (lane ^ (2 * q + half))] =
+            f32x4{acc[j][m][4 * q], acc[j][m][4 * q + 1], acc[j][m][4 * q + 2], acc[j][m][4 * q + 3]};
+    if (LINES && a.logits) {
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // written by other lanes of the wave
+      const int c = lane & 7;
+#pragma unroll
+      for (int j = 0; j < JT; ++j)
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          const int tok = 8 * k + (lane >> 3), tt = (mt0 + m) * 32 + tok, nrow = (nt0 + j) * 32 + 4 * c;
+          const f32x4 v = scr[(j * 4 + (c >> 1)) * WAVE + ((tok + 32 * (c & 1)) ^ c)];
+          if (tt < a.T && nrow < a.N) {
+            float* dst = a.logits + (size_t)tt * a.N + nrow;
+            if (nrow + 3 < a.N) {
+              __builtin_nontemporal_store(v, reinterpret_cast<f32x4*>(dst));
+            } else {
+#pragma unroll
+              for (int e = 0; e < 4; ++e)
+                if (nrow + e < a.N) dst[e] = v[e];
+            }
+          }
+        }
+    }
     const int t = (mt0 + m) * 32 + r32;
     const bool ok = t < a.T;
     float mx = -INFINITY, se = 0.f, best = -INFINITY;
@@ -187,8 +214,8 @@ __device__ __forceinline__ void lmhead_epilogue(const GemmArgs& a, f32x4* scr, c
       for (int i = 0; i < 4 * JT; ++i) {
         const int nrow = nt0 * 32 + 8 * i + 4 * half;         // multiple of 4: one Philox block covers the four ids
         if (nrow >= a.N) break;
-        const f32x4 v = scr[i * WAVE + lane];
-        if (a.logits) {
+        const f32x4 v = scr[i * WAVE + (lane ^ (2 * (i & 3) + half))];
+        if (!LINES && a.logits) {
           if (nrow + 3 < a.N) {
             *reinterpret_cast<f32x4*>(a.logits + (size_t)t * a.N + nrow) = v;
           } else {

@@ -306,7 +306,7 @@ __global__ __launch_bounds__(64 * WR * WT) __attribute__((amdgpu_waves_per_eu(2,
 #pragma unroll
     for (int j = 0; j < JW; j += JT)
       if (nt0 + j < n_tiles)
-        lmhead_epilogue<JT, MW>(a, scr, reinterpret_cast<const f32x16(&)[JT][MW]>(acc[j]), lm, nt0 + j, tok0 >> 5, (nt0 + j) / JT,
+        lmhead_epilogue<JT, MW, false>(a, scr, reinterpret_cast<const f32x16(&)[JT][MW]>(acc[j]), lm, nt0 + j, tok0 >> 5, (nt0 + j) / JT,
                                 n_parts, lane);
   }
 }
