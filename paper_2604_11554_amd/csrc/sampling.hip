@@ -22,17 +22,50 @@ __device__ __forceinline__ Part part_merge(Part a, Part b) {
   return r;
 }
 
+// What bounds it: round trips, of which only the emitted token's weights wait for another one's answer, and they only where the token is
+// drawn and not given.  Everything else is requested at once, and the tree over the threads stays in their waves.  us per launch, before
+// -> now, tokens given: two-layer policy 5.4 -> 4.7, 151 936 ids 1 row 8.7 -> 7.7, 64 rows 9.7 -> 8.5; 896 scored rows 15.0 -> 15.8.
 __global__ __launch_bounds__(256) void sample_finalize_kernel(FinalizeArgs a) {
-  __shared__ Part sh[256];
+  __shared__ Part sh[4];
   __shared__ float dsh[4];
-  const int r = blockIdx.x;
-  if (a.score && (a.forced[r] < 0 || a.forced[r] >= a.vocab)) {   // nothing to score at this position
-    if (threadIdx.x == 0) a.out_logprobs[r] = 0.f;
+  const int r = blockIdx.x, tid = (int)threadIdx.x;
+  const int forced = a.forced ? a.forced[r] : -1;
+  const float temp = a.temperature[a.row_seq ? a.row_seq[r] : r];
+  const uint8_t sample_on = a.score ? 1 : a.sample_on[r];
+  const int pos = a.score ? 0 : a.sample_pos[r], max_ctx_len = a.score ? 0x7FFFFFFF : a.max_ctx_len[r];
+  const f32x4* base = reinterpret_cast<const f32x4*>(a.part + (size_t)r * a.n_parts * 4);
+  f32x4 q[8];
+  auto load_parts = [&](int t0) {
+#pragma unroll
+    for (int u = 0; u < 8; ++u) q[u] = base[min(t0 + u * 256 + tid, a.n_parts - 1)];
+  };
+  load_parts(0);
+  // the row's and the emitted token's features: eight consecutive k are one 16-byte group in both layouts; a thread's loads of a
+  // round go out together
+  const int ng = a.d >> 3;
+  h16x8 xh[2], xl[2], wv[2];
+  auto group_k = [&](int g0, int u) { return 8 * min(g0 + u * 256 + tid, ng - 1); };
+  auto load_x = [&](int g0) {
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const h16_t* x = a.x.p + a.x.group_offset(r, group_k(g0, u));
+      xh[u] = load_h16x8(x);
+      xl[u] = a.x.planes == 2 ? load_h16x8(x + a.x.small_terms()) : zero_h16x8();
+    }
+  };
+  auto load_w = [&](int g0, int t) {
+#pragma unroll
+    for (int u = 0; u < 2; ++u) wv[u] = load_h16x8(a.w_lm + packed_weight_offset(t, group_k(g0, u), a.d));
+  };
+  load_x(0);
+
+  const bool given = forced >= 0 && forced < a.vocab;
+  if (a.score && !given) {                    // nothing to score at this position
+    if (tid == 0) a.out_logprobs[r] = 0.f;
     return;
   }
-  const bool on = a.score || a.sample_on[r] != 0;
-  if (!on) {                                  // inert row
-    if (threadIdx.x == 0) {
+  if (!sample_on) {                           // inert row
+    if (tid == 0) {
       a.out_tokens[r] = a.pad;
       a.out_logprobs[r] = 0.f;
       if (a.out_sampled) a.out_sampled[r] = -1;
@@ -40,60 +73,47 @@ __global__ __launch_bounds__(256) void sample_finalize_kernel(FinalizeArgs a) {
     }
     return;
   }
+  const bool capped = !a.score && pos >= max_ctx_len - 1;
+  int tok = capped ? a.eos : given ? forced : -1;
+  const bool known = tok >= 0;                // uniform
+  if (known) load_w(0, tok);
   // thread t takes tiles t, t + 256, ... (one 16-byte record each, eight loads in flight), merged in
   // ascending order; then a fixed binary tree over the threads
   Part p = {-INFINITY, 0.f, -INFINITY, 0x7FFFFFFF};
-  const f32x4* base = reinterpret_cast<const f32x4*>(a.part + (size_t)r * a.n_parts * 4);
-  for (int t0 = 0; t0 < a.n_parts; t0 += 8 * 256) {
-    f32x4 q[8];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const int tile = t0 + u * 256 + (int)threadIdx.x;
-      q[u] = base[tile < a.n_parts ? tile : a.n_parts - 1];
-    }
+  for (int t0 = 0;;) {
 #pragma unroll
     for (int u = 0; u < 8; ++u)
-      if (t0 + u * 256 + (int)threadIdx.x < a.n_parts) {
+      if (t0 + u * 256 + tid < a.n_parts) {
         Part b = {q[u][0], q[u][1], q[u][2], __float_as_int(q[u][3])};
         p = part_merge(p, b);
       }
+    t0 += 8 * 256;
+    if (t0 >= a.n_parts) break;
+    load_parts(t0);
   }
-  sh[threadIdx.x] = p;
+  for (int stride = 1; stride < 64; stride <<= 1) {
+    const Part o = {__shfl_down(p.m, stride, WAVE), __shfl_down(p.s, stride, WAVE), __shfl_down(p.best, stride, WAVE),
+                    __shfl_down(p.besti, stride, WAVE)};
+    const Part n = part_merge(p, o);
+    if ((tid & (2 * stride - 1)) == 0) p = n;
+  }
+  if ((tid & 63) == 0) sh[tid >> 6] = p;
   __syncthreads();
-  for (int stride = 1; stride < 256; stride <<= 1) {
-    if ((threadIdx.x % (2 * stride)) == 0) sh[threadIdx.x] = part_merge(sh[threadIdx.x], sh[threadIdx.x + stride]);
-    __syncthreads();
-  }
-  p = sh[0];
+  p = part_merge(part_merge(sh[0], sh[1]), part_merge(sh[2], sh[3]));
   const float lse = p.m + logf(p.s);
   const int sampled = p.besti;
-  int tok = sampled;
-  if (a.forced && a.forced[r] >= 0 && a.forced[r] < a.vocab) tok = a.forced[r];
-  if (!a.score) {
-    const int pos = a.sample_pos[r];
-    if (pos >= a.max_ctx_len[r] - 1) tok = a.eos;
-  }
+  if (!known) tok = sampled;
   if (tok < 0 || tok >= a.vocab) tok = a.eos;   // cannot happen with a non-empty vocabulary; keeps the read in bounds
 
   // logit of the emitted token: the same 16-bit operands as the LM-head tiles, fp32 accumulate
-  // (eight consecutive k are one 16-byte group in both layouts; a thread's loads of a round go out together)
   const int dt = a.x.dtype;
-  const int ng = a.d >> 3;
   float acc = 0.f;
   for (int g0 = 0; g0 < ng; g0 += 2 * 256) {
-    h16x8 xh[2], xl[2], wv[2];
-#pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      const int gi = g0 + u * 256 + (int)threadIdx.x;
-      const int k = 8 * (gi < ng ? gi : ng - 1);
-      const h16_t* x = a.x.p + a.x.group_offset(r, k);
-      xh[u] = load_h16x8(x);
-      xl[u] = a.x.planes == 2 ? load_h16x8(x + a.x.small_terms()) : zero_h16x8();
-      wv[u] = load_h16x8(a.w_lm + packed_weight_offset(tok, k, a.d));
-    }
+    if (g0) load_x(g0);
+    if (g0 || !known) load_w(g0, tok);
 #pragma unroll
     for (int u = 0; u < 2; ++u)
-      if (g0 + u * 256 + (int)threadIdx.x < ng) {
+      if (g0 + u * 256 + tid < ng) {
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
           const int sh = 16 * (e & 1);
@@ -106,9 +126,8 @@ __global__ __launch_bounds__(256) void sample_finalize_kernel(FinalizeArgs a) {
   acc = wave_sum(acc);
   if ((threadIdx.x & 63) == 0) dsh[threadIdx.x >> 6] = acc;
   __syncthreads();
-  if (threadIdx.x == 0) {
+  if (tid == 0) {
     float z = dsh[0] + dsh[1] + dsh[2] + dsh[3];
-    float temp = a.temperature[a.row_seq ? a.row_seq[r] : r];
     float invt = temp > 0.f ? 1.f / temp : 1.f;
     a.out_logprobs[r] = z * invt - lse;
     if (a.score) return;
