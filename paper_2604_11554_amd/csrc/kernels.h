@@ -264,7 +264,8 @@ struct AttnDecodeArgs {      // one new token per sequence: row = sequence slot
 //   [0] n_seqs it was built for, [1] n_tiles, [2] members per tile MS = min(16, SP_COLS / (Hq/Hkv)),
 //   [3] 1 if a group has more members than that, so that several tiles read its pages, [4..7] 0
 //   per sequence (4 arrays of n_seqs): start_unit, tile0 (first tile of its subgroup), n_chunks, col0 (its first column)
-//   per tile (arrays of max_tiles; groups of the longest prefixes first): row (sequence whose block-table row lists the pages), kvh, unit lo, unit hi,
+//   per tile (arrays of max_tiles; groups of the longest prefixes first): row (sequence whose block-table row lists the pages), kvh,
+//   unit lo, unit hi,
 //   then members [max_tiles][16] (-1 = none).  Tile of (subgroup, chunk c, kvh) = tile0 + c * Hkv + kvh.
 constexpr int SP_HDR = 8;
 constexpr int SP_MAX_CHUNKS = 4;
