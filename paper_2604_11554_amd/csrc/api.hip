@@ -314,7 +314,7 @@ int run_layers(const rlx_model* m, h16_t* pool, int64_t n_blocks, const Workspac
     } else if (small) {
       p.planes = gemm_plan_splits(N, K, T, gemm_max_splits(), m->n_units, PL, FMT);
     } else if (lng) {
-      p.lng = gemm_long_plan(N, K, T, long_planes(c, T, wide, io.lean), m->n_units, wide && fine_qkv);
+      p.lng = long_plan(N, K, T, long_planes(c, T, wide, io.lean), m->n_units, wide && fine_qkv);
       p.planes = p.lng.splits;
     }
     return p;
@@ -455,7 +455,7 @@ int run_layers(const rlx_model* m, h16_t* pool, int64_t n_blocks, const Workspac
       RLX_HIP(norm(m->final_norm, w.meta.tok_iota + r0, n, x_lm, nullptr));
       RLX_LAUNCH(RLX_K_LMHEAD, lmhead(x_lm, n, nullptr, nullptr, nullptr, w.meta.tok_seq + r0, false));
       FinalizeArgs f = {};
-      f.n_rows = n; f.n_parts = lmhead_parts(c.vocab, x_lm); f.vocab = c.vocab; f.d = d;
+      f.n_rows = n; f.n_parts = lmhead_parts(c.vocab, x_lm, m->n_units); f.vocab = c.vocab; f.d = d;
       f.part = w.lm_part; f.x = x_lm; f.w_lm = m->lm_head;
       f.temperature = io.temperature; f.forced = io.score_targets + r0; f.row_seq = w.meta.tok_seq + r0;
       f.eos = c.eos_token_id; f.pad = c.pad_token_id; f.out_logprobs = io.score_logprobs + r0; f.score = 1;
@@ -473,7 +473,7 @@ int run_layers(const rlx_model* m, h16_t* pool, int64_t n_blocks, const Workspac
   else RLX_HIP(norm(m->final_norm, w.meta.sample_row, S, x_lm, nullptr));
   RLX_LAUNCH(RLX_K_LMHEAD, lmhead(x_lm, S, io.out_logits, io.seeds, w.meta.sample_pos, nullptr, true, last_inside ? &nm : nullptr));
   FinalizeArgs f = {};
-  f.n_rows = S; f.n_parts = lmhead_parts(c.vocab, x_lm); f.vocab = c.vocab; f.d = d;
+  f.n_rows = S; f.n_parts = lmhead_parts(c.vocab, x_lm, m->n_units); f.vocab = c.vocab; f.d = d;
   f.part = w.lm_part; f.x = x_lm; f.w_lm = m->lm_head;
   f.temperature = io.temperature; f.max_ctx_len = io.max_ctx_len; f.forced = io.forced;
   f.sample_pos = w.meta.sample_pos; f.sample_on = w.meta.sample_on;

@@ -343,48 +343,6 @@ void launch_long(const GemmArgs& a, int form, int n_items, hipStream_t st) {
   }
 }
 
-// ---- which form, and into how many planes K is cut ----
-// 512 x 128 (eight waves, one workgroup per unit) has the better rate when the device is full many times over, 128 x 128
-// (four waves, two workgroups per unit) an eighth of its step in size, 160 x 128 and 192 x 128 (four waves, one per unit, a wave
-// all weight rows and 32 tokens) make one even round of 129 to 512 tokens where the others fill it and a half; what decides
-// at a few hundred to a few thousand tokens is how well the workgroups fit the units.  The constants (us: start of a round, and
-// per stage) were fitted to a sweep of the products of the two model shapes (N 2048..19456, K 2048..9728), 140..8192 tokens and
-// 1 to 8 planes, where the choice is 0.1 % behind the best of the sweep in the mean and 4 % at worst (6 % in a second sweep at other
-// token counts: N 5120, K 2048, 1700 tokens 83 us in 128 x 128, 88 in the chosen 512 x 128).  E.g. gate/up of 256
-// tokens, N 19456, K 2560: 128 x 128 (304 workgroups) 65 us, 160 x 128 (244) 51; 1437 tokens, N 6144, K 2560: 128 x 128 in two
-// planes 96 us, 512 x 128 in three 88; 8192 tokens, N 2560, K 9728: 128 x 128 692, 512 x 128 in two planes 629.
-// `finest`: as many planes as there may be, in the form that is faster with them.  `lmhead`: the forms that its
-// epilogue is built for, whose rounds it makes longer where nothing runs beside them (256 rows: 444 us in 512 x 128, 410 in 128 x 128).
-static LongPlan plan_long(int N, int K, int T, int max_splits, int n_units, bool finest, bool lmhead) {
-  const int stages = (K / 16 + 1) / 2;
-  LongPlan best = {LONG_512x128, 1};
-  float best_us = 1e30f;
-  for (int s = 1; s <= max_splits; ++s) {
-    const int per = (stages + s - 1) / s;
-    if (s > 1 && ((s - 1) * per >= stages || per < 8)) continue;   // no empty split, no split of a few stages
-    if (finest) best_us = 1e30f;
-    const long wg_t = (long)((T + 127) / 128) * s;
-    const float planes_us = (float)(s - 1) * (float)T * (float)N * 0.94e-6f;
-    // one workgroup per unit; a last round that is not full is a little shorter
-    auto alone = [&](int form, int rows, float start, float stage) {
-      const long w = wg_t * ((N + rows - 1) / rows), rounds = (w + n_units - 1) / n_units;
-      const float full = (float)(w - (rounds - 1) * n_units) / (float)n_units;
-      const float us = (float)rounds * (start + stage * (float)per) - 0.1f * (1.f - full) * stage * (float)per + planes_us;
-      if (us < best_us) { best_us = us; best = {form, s}; }
-    };
-    alone(LONG_512x128, 512, lmhead ? 10.f : 5.0f, lmhead ? 1.4f : 1.29f);
-    if (!lmhead) {
-      alone(LONG_160x128, 160, 3.8f, 0.67f);
-      alone(LONG_192x128, 192, 3.2f, 0.785f);
-    }
-    const long w128 = wg_t * ((N + 127) / 128), full = w128 / (2 * n_units), rest = w128 % (2 * n_units);
-    float t128 = (float)full * (3.5f + 0.79f * (float)per) + planes_us;
-    if (rest) t128 += 3.5f + (rest <= n_units ? 0.464f : 0.79f) * (float)per;
-    if (t128 < best_us) { best_us = t128; best = {LONG_128x128, s}; }
-  }
-  return best;
-}
-
 // Expert-grouped products: 128 rows per tile, or 64 where an expert is not expected to get more than 48 (30B-A3B shape,
 // gate/up + down: 32 rows per expert 250 us with tiles of 128, 235 with 64; 64 rows 293 / 350; 1024 rows 2255 / 2476).
 // Over the same list, tiles of 128 or 256 weight rows took up to 25 % longer than those of 512 nearly everywhere.
@@ -393,10 +351,6 @@ static int grouped_form(int tile_rows) { return tile_rows == 64 ? LONG_512x64 : 
 }  // namespace
 
 int gemm_long_item_rows(int expected_rows) { return expected_rows <= 48 ? 64 : 128; }
-
-LongPlan gemm_long_plan(int N, int K, int T, int max_splits, int n_units, bool finest) {
-  return plan_long(N, K, T, max_splits, n_units, finest, false);
-}
 
 static void fill_long(GemmArgs& a, const Act& x, int N, int K, int T) {
   a.x = x.p; a.x_pitch = x.pitch; a.x_ss = x.ss; a.x_eps = x.eps;
@@ -422,7 +376,7 @@ hipError_t gemm_long_swiglu(const h16_t* w_gate_up, int F, int K, const Act& x, 
   fill_long(a, x, 2 * F, K, T);
   a.w[0] = w_gate_up; a.w_tiles[0] = F / 16;
   a.act = act.p; a.act_pitch = act.pitch;
-  launch_long<EPI_SWIGLU>(a, plan_long(2 * F, K, T, 1, n_units, false, false).form, 0, st);
+  launch_long<EPI_SWIGLU>(a, long_plan(2 * F, K, T, 1, n_units, false).form, 0, st);
   return hipGetLastError();
 }
 
@@ -449,11 +403,9 @@ hipError_t gemm_long_grouped_store(const h16_t* w, int N, int K, const Act& x, c
   return hipGetLastError();
 }
 
-// Up to LM_FEW_ROWS rows: tiles of 320 vocabulary rows by all tokens (eight waves), which read the weights once and make 475 tiles of
-// 151 936 rows, nearly two even rounds on 256 units; a wave's 160 rows are a part.  us before (128 x 128) -> now, one draw per row:
-// K 2560, 96 rows 233 -> 211, 128 250 -> 227, 129 384 -> 341, 256 455 -> 435; K 2048, 128 rows 217 -> 196, 256 379 -> 355; the
-// parts' merge 10 -> 8.5.  (Of 64 rows and fewer tiles of 160 to 320 rows, one or two workgroups per unit, gave what the short
-// forms give.)
+// The form is long_lmhead_form's.  With 320 x 128 or 320 x 256 in place of 128 x 128, 151 936 ids, one draw per row, us: K 2560, 96 rows
+// 229 -> 207, 128 238 -> 224, 129 359 -> 310, 256 407 -> 374; K 2048, 256 rows 339 -> 316; of it the parts' merge 10 -> 8.5.  (Of 64 rows and
+// fewer tiles of 160 to 320 rows, one or two workgroups per unit, gave what the short forms give.)
 hipError_t gemm_long_lmhead(const h16_t* w_lm, int V, int K, const Act& x, int T, float* logits, float* part,
                             const uint64_t* seeds, const float* temperature, const int32_t* sample_pos,
                             const int32_t* row_seq, bool draw, int n_units, hipStream_t st) {
@@ -462,8 +414,7 @@ hipError_t gemm_long_lmhead(const h16_t* w_lm, int V, int K, const Act& x, int T
   a.w[0] = w_lm; a.w_tiles[0] = (V + 31) / 32;
   a.logits = logits; a.part = part; a.seeds = seeds; a.temperature = temperature; a.sample_pos = sample_pos;
   a.row_seq = row_seq; a.draw = draw ? 1 : 0;
-  const int form = T > LM_FEW_ROWS ? plan_long(V, K, T, 1, n_units, false, true).form : T <= 128 ? LONG_320x128 : LONG_320x256;
-  launch_long<EPI_LMHEAD>(a, form, 0, st);
+  launch_long<EPI_LMHEAD>(a, long_lmhead_form(V, K, T, n_units), 0, st);
   return hipGetLastError();
 }
 

@@ -3,6 +3,7 @@
 #pragma once
 #include "common.h"
 #include "flow_plan.h"
+#include "long_plan.h"
 
 namespace rlx {
 
@@ -74,10 +75,9 @@ hipError_t gemm_store(const LinearW& w, const Act& x, int T, float* y, int ldy, 
 // act[t][f] = silu(x Wg^T) * (x Wu^T); w_gate_up is the interleaved packed pair (pack_gate_up)
 hipError_t gemm_swiglu(const h16_t* w_gate_up, int F, int K, const Act& x, int T, const Act& act, hipStream_t st);
 // LM head with fused log-sum-exp and Gumbel-max partials: part[t][lmhead_parts()][4], a part per 32 vocabulary rows, in the
-// long-call forms per 160 (calls of up to LM_FEW_ROWS rows) or 64
-constexpr int LM_FEW_ROWS = 256;
-inline int lmhead_parts(int vocab, const Act& x) {
-  const int tiles = (vocab + 31) / 32, per = !x.pitch ? 1 : x.T <= LM_FEW_ROWS ? 5 : 2;
+// long-call forms as many weight tiles of 32 as their tiles have it (long_lmhead_form)
+inline int lmhead_parts(int vocab, const Act& x, int n_units) {
+  const int tiles = (vocab + 31) / 32, per = x.pitch ? long_lmhead_part_tiles(long_lmhead_form(vocab, x.K, x.T, n_units)) : 1;
   return (tiles + per - 1) / per;
 }
 // row_seq (optional): row t reads temperature[row_seq[t]]; draw = false skips the Gumbel-max draw (scoring)
@@ -131,11 +131,7 @@ hipError_t gemm_flow_lmhead(const h16_t* w_lm, int V, int K, const Act& x, int T
                             const FlowNorm* norm = nullptr);
 
 // ---- gemm_long.hip: the same products for long calls on two-term bf16 activations in rows (Act::pitch) ----
-enum { LONG_512x128 = 0, LONG_128x128, LONG_512x64, LONG_160x128, LONG_192x128,   // weight rows x tokens of a workgroup
-       LONG_320x128, LONG_320x256 };                                              // ... of LM heads of few rows
-// y[split][t][n]: form, and K cut into at most max_splits planes: the fastest number, or the largest (`finest`)
-struct LongPlan { int form, splits; };
-LongPlan gemm_long_plan(int N, int K, int T, int max_splits, int n_units, bool finest);
+// y[split][t][n] in the planes of `plan` (long_plan)
 hipError_t gemm_long_store(const LinearW& w, const Act& x, int T, float* y, int ldy, const LongPlan& plan, hipStream_t st);
 hipError_t gemm_long_swiglu(const h16_t* w_gate_up, int F, int K, const Act& x, int T, const Act& act, int n_units,
                             hipStream_t st);

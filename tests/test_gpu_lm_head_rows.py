@@ -1,5 +1,6 @@
-"""LM heads of 65 to 256 rows take tiles of 320 vocabulary rows: draws and log-probabilities against the logits that come with them,
-and those against calls of at most 64 rows, whose LM head has the short form."""
+"""LM heads of 65 to 256 rows: draws and log-probabilities against the logits that come with them, and those against calls of at most 64
+rows, whose LM head has the short form.  Small vocabularies take tiles of 128 x 128; tiles of 320 vocabulary rows by 128 or 256
+tokens take over where their rounds fit the vocabulary better (test_lm_head_plan.py holds these calls to it)."""
 import numpy as np
 import pytest
 
@@ -21,6 +22,20 @@ def _engine(pkg, model, n, lens):
 @pytest.mark.parametrize("vocab,d_model", [(353, 80), (705, 48), (161, 272)])
 @pytest.mark.parametrize("n_rows", [96, 200, 256])
 def test_draws_of_65_to_256_rows(n_rows, vocab, d_model):
+    _draws(n_rows, vocab, d_model, 1)
+
+
+# rows, vocabulary, d_model; 81 793 = 255 x 320 + 160 + 33: the last tile's second wave has one id past a weight tile; 81 665 = 255 x 320 +
+# 65: the second wave has none, the first one's third weight tile one; d_model 272 ends inside a stage
+WIDE_TILES = [(96, 81793, 272), (128, 81665, 272), (129, 81665, 272), (256, 81793, 272)]
+
+
+@pytest.mark.parametrize("n_rows,vocab,d_model", WIDE_TILES)
+def test_draws_in_tiles_of_320(n_rows, vocab, d_model):
+    _draws(n_rows, vocab, d_model, 7)
+
+
+def _draws(n_rows, vocab, d_model, every):
     import paper_2604_11554_amd as pkg
     from paper_2604_11554_amd import synthetic
 
@@ -29,7 +44,7 @@ def test_draws_of_65_to_256_rows(n_rows, vocab, d_model):
     out = _engine(pkg, model, n_rows, [1] * n_rows).prefill(list(range(n_rows)), toks, want_sampled=True, want_logits=True)
     z, drawn, lp = (x.cpu().numpy() for x in (out.logits, out.sampled, out.logprobs))
     from oracle import gumbel_noise
-    for i in range(n_rows):
+    for i in sorted({*range(0, n_rows, every), n_rows - 1}):
         t = 0.7 if i % 3 else 1.0
         row = z[i].astype(np.float64) / t
         score = row + (gumbel_noise(7000 + i, 1, vocab) if i % 3 else 0.0)
