@@ -28,10 +28,8 @@
 // are the query heads of all its member sequences, so the shared pages are read once per subgroup (the eight
 // responses of a prompt at the 4B shape) instead of once per sequence; the per-sequence kernel starts after the
 // shared units, and the merge kernel adds the prefix parts first.
-#include <algorithm>
 #include <mutex>
 #include <type_traits>
-#include <vector>
 
 #include "attn_core.h"
 #include "embed.h"
@@ -448,8 +446,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   }
 }
 
-// Prefix tiles: workgroup t, t + grid, ... takes tile t of the descriptor.  The NCT x 16 columns are (member, head of
-// the KV head's group); every key of the tile's units is visible to every member (the pages are full and shared).
+// Prefix tiles: the workgroups walk the descriptor's tiles (tile_of).  The NCT x 16 columns are (member, head of the KV
+// head's group); every key of the tile's units is visible to every member (the pages are full and shared).
 // The four waves take units round-robin and are merged through LDS; (o, m, l) of all columns go to pre_part.  The
 // query fragments of a tile sit in LDS (with two column tiles they would take half the register file).
 // What bounds it: latency.  A wave has two to four units of a tile, and without registers for a second set of pages it waited for
@@ -858,82 +856,6 @@ hipError_t decode_begin(DecodeBeginArgs b, int n_wgs, hipStream_t st) {
   b.n_shares = b.team ? n_wgs : waves;
   hipLaunchKernelGGL(decode_begin_kernel, dim3(1 + b.n_seqs), dim3(1024), 0, st, b);
   return hipGetLastError();
-}
-
-// Host side of the descriptor.  A group is a run of consecutive sequences with the same leader (the first of them);
-// its shared units are the smallest shared page count of its members, halved.  Groups of one, groups that share
-// less than one unit, and models whose 32 columns hold a single sequence get no tiles.
-void shared_prefix_build(int n_seqs, int Hq, int Hkv, const int32_t* leader, const int32_t* shared_pages, int most_tiles, int32_t* words) {
-  const int group = Hq / Hkv, MS = shared_prefix_members(group);
-  const int max_tiles = shared_prefix_max_tiles(n_seqs, Hkv);
-  const size_t n_words = shared_prefix_words(n_seqs, Hkv);
-  for (size_t i = 0; i < n_words; ++i) words[i] = 0;
-  int32_t* start_unit = words + SP_HDR;
-  int32_t *tile0 = start_unit + n_seqs, *n_chunks = tile0 + n_seqs, *col0 = n_chunks + n_seqs;
-  int32_t* t_row = col0 + n_seqs;
-  int32_t *t_kvh = t_row + max_tiles, *t_lo = t_kvh + max_tiles, *t_hi = t_lo + max_tiles, *t_mem = t_hi + max_tiles;
-  for (int i = 0; i < max_tiles * 16; ++i) t_mem[i] = -1;
-  words[0] = n_seqs; words[2] = MS;
-  int n_tiles = 0;
-  if (MS >= 2) {
-    // first pass: groups and their subgroup count, to size the chunks so that the tiles fit
-    int n_sub_total = 0;
-    for (int b = 0; b < n_seqs;) {
-      int e = b + 1;
-      while (e < n_seqs && leader[e] == b && leader[b] == b) ++e;
-      int units = 0x7FFFFFFF;
-      for (int i = b; i < e; ++i) units = shared_pages[i] / 2 < units ? shared_pages[i] / 2 : units;
-      if (e - b >= 2 && units > 0) n_sub_total += (e - b + MS - 1) / MS;
-      b = e;
-    }
-    int chunks_cap = n_sub_total ? max_tiles / (n_sub_total * Hkv) : 0;
-    if (chunks_cap > SP_MAX_CHUNKS) chunks_cap = SP_MAX_CHUNKS;
-    // the longest prefixes first: a workgroup's second tile comes from the other end of the list (PrefixOrder)
-    struct Group { int b, e, units; };
-    std::vector<Group> groups;
-    for (int b = 0; b < n_seqs && chunks_cap >= 1;) {
-      int e = b + 1;
-      while (e < n_seqs && leader[e] == b && leader[b] == b) ++e;
-      int units = 0x7FFFFFFF;
-      for (int i = b; i < e; ++i) units = shared_pages[i] / 2 < units ? shared_pages[i] / 2 : units;
-      if (e - b >= 2 && units > 0) groups.push_back({b, e, units});
-      b = e;
-    }
-    std::stable_sort(groups.begin(), groups.end(), [](const Group& x, const Group& y) { return x.units > y.units; });
-    // at least eight units (256 keys) per chunk, and more where the tiles would be more than there are workgroups at once
-    int least = 8;
-    auto chunks = [&](const Group& gr) { return std::min((gr.units + least - 1) / least, chunks_cap); };
-    for (bool more = most_tiles > 0; more;) {
-      int64_t tiles = 0;
-      more = false;
-      for (const Group& gr : groups) {
-        tiles += (int64_t)((gr.e - gr.b + MS - 1) / MS) * Hkv * chunks(gr);
-        more |= chunks(gr) > 1;
-      }
-      more &= tiles > most_tiles;
-      if (more) ++least;
-    }
-    for (const Group& gr : groups) {
-      int nc = chunks(gr);
-      const int per = (gr.units + nc - 1) / nc;
-      nc = (gr.units + per - 1) / per;                 // no empty chunk
-      if (gr.e - gr.b > MS) words[3] = 1;              // several tiles read these pages
-      for (int sb = gr.b; sb < gr.e; sb += MS) {
-        const int se = sb + MS < gr.e ? sb + MS : gr.e;
-        for (int i = sb; i < se; ++i) {
-          start_unit[i] = gr.units; tile0[i] = n_tiles; n_chunks[i] = nc; col0[i] = (i - sb) * group;
-        }
-        for (int c = 0; c < nc; ++c)
-          for (int h = 0; h < Hkv; ++h) {
-            const int t = n_tiles + c * Hkv + h;
-            t_row[t] = gr.b; t_kvh[t] = h; t_lo[t] = c * per; t_hi[t] = (c + 1) * per < gr.units ? (c + 1) * per : gr.units;
-            for (int i = sb; i < se; ++i) t_mem[t * 16 + (i - sb)] = i;
-          }
-        n_tiles += nc * Hkv;
-      }
-    }
-  }
-  words[1] = n_tiles;
 }
 
 template <int HD, int PL, int FMT, int NCT>

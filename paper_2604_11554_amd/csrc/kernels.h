@@ -4,6 +4,7 @@
 #include "common.h"
 #include "flow_plan.h"
 #include "long_plan.h"
+#include "prefix_plan.h"
 
 namespace rlx {
 
@@ -256,26 +257,6 @@ struct AttnDecodeArgs {      // one new token per sequence: row = sequence slot
   float* pre_part;           // [shared_prefix_max_tiles][SP_COLS][hd+4] partials of the prefix tiles
   int n_prefix_wgs;          // grid of the prefix kernel
 };
-// Descriptor of the shared prefixes of a batch, int32 words (built on the host, read by the kernels):
-//   [0] n_seqs it was built for, [1] n_tiles, [2] members per tile MS = min(16, SP_COLS / (Hq/Hkv)),
-//   [3] 1 if a group has more members than that, so that several tiles read its pages, [4..7] 0
-//   per sequence (4 arrays of n_seqs): start_unit, tile0 (first tile of its subgroup), n_chunks, col0 (its first column)
-//   per tile (arrays of max_tiles; groups of the longest prefixes first): row (sequence whose block-table row lists the pages), kvh,
-//   unit lo, unit hi,
-//   then members [max_tiles][16] (-1 = none).  Tile of (subgroup, chunk c, kvh) = tile0 + c * Hkv + kvh.
-constexpr int SP_HDR = 8;
-constexpr int SP_MAX_CHUNKS = 4;
-constexpr int SP_COLS = 32;          // columns of a prefix tile: two matrix-core column tiles of 16
-__host__ __device__ inline int shared_prefix_members(int group) { return group > 0 && SP_COLS / group < 16 ? SP_COLS / group : 16; }
-// a subgroup has at least two members wherever the groups have, and at most one more subgroup per group than
-// members / 2: tiles = subgroups x chunks x Hkv fit with at least one chunk each
-__host__ __device__ inline int shared_prefix_max_tiles(int n_seqs, int Hkv) { return n_seqs * Hkv; }
-inline size_t shared_prefix_words(int n_seqs, int Hkv) {
-  return (size_t)SP_HDR + 4 * (size_t)n_seqs + (size_t)shared_prefix_max_tiles(n_seqs, Hkv) * (4 + 16);
-}
-// fills `words` (shared_prefix_words entries) from per-sequence group leaders and shared page counts (host arrays)
-// most_tiles: chunks get longer rather than the tiles more than that (0: as many as there are)
-void shared_prefix_build(int n_seqs, int Hq, int Hkv, const int32_t* leader, const int32_t* shared_pages, int most_tiles, int32_t* words);
 // start of a decode step: token metadata, embeddings, and the plan of the step's attention on a grid of n_wgs workgroups
 struct DecodeBeginArgs {
   int n_seqs, Hkv, head_dim;

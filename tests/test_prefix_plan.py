@@ -1,0 +1,127 @@
+"""How the shared prefixes of a decode batch are cut into tiles (csrc/prefix_plan.h), compiled for the host: every shared unit of every
+member is in one tile per KV head, and no tile is the time of the whole launch."""
+import ctypes
+import random
+import subprocess
+
+import numpy as np
+import pytest
+
+from paper_2604_11554_amd import build
+
+SOURCE = """
+#include "prefix_plan.h"
+extern "C" int64_t words(int n, int Hkv) { return (int64_t)rlx::shared_prefix_words(n, Hkv); }
+extern "C" void fill(int n, int Hq, int Hkv, const int32_t* leader, const int32_t* pages, int most_tiles, int32_t* out) {
+  rlx::shared_prefix_build(n, Hq, Hkv, leader, pages, most_tiles, out);
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def lib(tmp_path_factory):
+    d = tmp_path_factory.mktemp("prefix")
+    (d / "plan.cpp").write_text(SOURCE)
+    subprocess.run(["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-ftrapv", "-I", build.CSRC, str(d / "plan.cpp"), "-o",
+                    str(d / "plan.so")], check=True, capture_output=True)
+    l = ctypes.CDLL(str(d / "plan.so"))
+    l.words.restype = ctypes.c_int64
+    return l
+
+
+def _tiles(lib, groups, Hq, Hkv, most_tiles):
+    """groups: (members, pages of every member) -> header, per-sequence arrays, tiles (row, kvh, lo, hi, members)"""
+    leader, pages = [], []
+    for p in groups:
+        leader += [len(pages)] * len(p)
+        pages += p
+    n, m = len(pages), len(pages) * Hkv
+    out = np.full(lib.words(n, Hkv) + 4, -99, np.int32)
+    a, b = np.array(leader, np.int32), np.array(pages, np.int32)
+    lib.fill(n, Hq, Hkv, a.ctypes.data_as(ctypes.c_void_p), b.ctypes.data_as(ctypes.c_void_p), most_tiles,
+             out.ctypes.data_as(ctypes.c_void_p))
+    assert (out[-4:] == -99).all()
+    out = out[:-4]
+    assert out[0] == n and out[1] <= m
+    start, tile0, chunks, col0 = out[8:8 + 4 * n].reshape(4, n)
+    t = out[8 + 4 * n:8 + 4 * n + 4 * m].reshape(4, m)
+    mem = out[8 + 4 * n + 4 * m:].reshape(m, 16)
+    return out[:8], start, tile0, chunks, col0, [(*t[:, i].tolist(), mem[i].tolist()) for i in range(out[1])]
+
+
+@pytest.mark.parametrize("Hq,Hkv", [(32, 8), (4, 2), (16, 1), (32, 4), (2, 2)])
+@pytest.mark.parametrize("most_tiles", [0, 16, 512])
+def test_every_shared_unit_of_every_member_is_in_one_tile(lib, Hq, Hkv, most_tiles):
+    rng = random.Random(Hq * 1000 + Hkv * 10 + most_tiles)
+    group = Hq // Hkv
+    MS = min(16, 32 // group)
+    for _ in range(60):
+        groups = [[rng.choice([0, 1, 2, 3, 17, rng.randint(0, 400)]) for _ in range(rng.choice([1, 1, 2, 5, 9, 33]))]
+                  for _ in range(rng.randint(1, 60))]
+        head, start, tile0, chunks, col0, tiles = _tiles(lib, groups, Hq, Hkv, most_tiles)
+        n, seen = 0, set()
+        for p in groups:
+            units = min(p) // 2 if len(p) > 1 else 0
+            for j in range(len(p)):
+                i = n + j
+                assert start[i] == units
+                if not units:
+                    assert chunks[i] == 0
+                    continue
+                first = n + j // MS * MS
+                assert col0[i] == (i - first) * group and 1 <= chunks[i] <= 4
+                for h in range(Hkv):
+                    at = 0
+                    for c in range(chunks[i]):
+                        row, kvh, lo, hi, mem = tiles[tile0[i] + c * Hkv + h]
+                        assert (row, kvh, lo) == (n, h, at) and hi > lo and mem[i - first] == i
+                        assert [x for x in mem if x >= 0] == list(range(first, min(first + MS, n + len(p))))
+                        seen.add(tile0[i] + c * Hkv + h)
+                        at = hi
+                    assert at == units
+            n += len(p)
+        assert seen == set(range(len(tiles)))
+        assert head[3] == int(any(len(p) > MS and min(p) >= 2 for p in groups))
+        longest = [0] * (len(tiles) + 1)                      # of the tiles of a run of chunks: the list comes longest first
+        firsts = sorted({tile0[i] for i in range(n) if chunks[i]})
+        longest = [max(t[3] - t[2] for t in tiles[a:b]) for a, b in zip(firsts, firsts[1:] + [len(tiles)])]
+        assert longest == sorted(longest, reverse=True)
+
+
+def _lengths(lib, units, members=8, most_tiles=512):
+    _, _, _, _, _, tiles = _tiles(lib, [[2 * u] * members for u in units], 32, 8, most_tiles)
+    return len(tiles), max(t[3] - t[2] for t in tiles)
+
+
+def test_a_long_prefix_among_short_ones_is_split(lib):
+    # 32 query and 8 KV heads on 512 workgroups: as many groups as one chunk each fills the device with, and more than that
+    assert _lengths(lib, [40] * 63 + [937]) == (63 * 8 + 4 * 8, 235)
+    assert _lengths(lib, [40] * 64 + [937]) == (64 * 8 + 4 * 8, 235)
+    assert _lengths(lib, [8] * 96 + [937], members=2) == (96 * 8 + 2 * 8, 469)     # pairs: the descriptor has room for two chunks each
+    n, longest = _lengths(lib, [16 + 48 * i // 69 for i in range(70)] + [500, 500])
+    assert longest <= 125 and n <= 80 * 8
+    # no longer than twice an even deal, or a quarter of the prefix
+    rng = random.Random(3)
+    for _ in range(200):
+        units = [rng.choice([1, 9, rng.randint(1, 100), rng.randint(1, 3000)]) for _ in range(rng.randint(1, 150))]
+        even = -(-sum(units) * 8 // 512)
+        n, longest = _lengths(lib, units)
+        assert longest <= max(8, 2 * even, max(-(-u // 4) for u in units))
+
+
+def test_chunks_are_as_many_as_one_round_takes(lib):
+    # even prefixes: the shortest chunks that fit 512 workgroups, one each where nothing shorter does
+    assert _lengths(lib, [64] * 16) == (512, 16) and _lengths(lib, [64] * 32) == (512, 32) and _lengths(lib, [64] * 33) == (264, 64)
+    assert _lengths(lib, [40] * 65) == (520, 40) and _lengths(lib, [40] * 128) == (1024, 40)
+    # MoE policies: the same chunks whatever the number of tiles is
+    assert _lengths(lib, [40] * 128, most_tiles=0) == (4096, 10) and _lengths(lib, [17] * 8, most_tiles=0) == (192, 6)
+
+
+@pytest.mark.timeout(20)
+def test_page_counts_of_any_size(lib):
+    # the search halves its range: 256 groups of the largest counts there are take no longer than others, and nothing overflows
+    top = 2 ** 31 - 1
+    assert _lengths(lib, [top // 2] * 256, members=4) == (2048, top // 2)
+    assert _lengths(lib, [3] * 255 + [top // 2], members=4) == (255 * 8 + 32, -(-(top // 2) // 4))
+    _, start, _, _, _, tiles = _tiles(lib, [[top] * 2] * 8, 32, 8, 512)
+    assert start[0] == top // 2 and max(t[3] for t in tiles) == top // 2
