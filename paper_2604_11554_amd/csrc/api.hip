@@ -340,7 +340,8 @@ int run_layers(const rlx_model* m, h16_t* pool, int64_t n_blocks, const Workspac
   // Calls of few tokens: the products that read normalised rows make them themselves.  The residual stream then changes its place
   // with every addition, between w.h and the activation matrix that nothing else uses here (32 rows of 4 bytes per element, or of
   // two; at most sixteen rows of four are put there).
-  const bool norm_inside = p_qkv.is_flow && gemm_flow_norm_form(T, d) && gemm_flow_swiglu_form(c.d_ff, T, m->n_units, PL, FMT);
+  const bool norm_inside = p_qkv.is_flow && flow_norm_form(T, d, p_o.planes, p_ffn.planes) &&
+                           gemm_flow_swiglu_form(c.d_ff, T, m->n_units, PL, FMT);
   auto inner_norm = [&](const h16_t* gain) {
     FlowNorm f = {h_at, nullptr, pend_planes, pend_n, gain, c.rms_eps, nullptr};
     if (pend_planes) h_at = f.h_out = h_at == w.h ? (float*)w.xb : w.h;

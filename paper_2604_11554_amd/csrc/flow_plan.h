@@ -62,4 +62,23 @@ inline bool flow_store_form(int N, int K, int T, int n_units, int planes) {
   return T <= 48 || (T <= 64 ? n_units / ((N + 127) / 128) > 5 : T <= 96);
 }
 
+// ---- the norm of the rows inside the products that read them: every workgroup makes all rows ----
+// What the kernels are built for: float4 slices of the rows per thread of 256, and rows of a token tile.
+constexpr int FLOW_NORM_NV = 5, FLOW_NORM_ROWS = 16;
+inline bool flow_norm_fits(int T, int K) { return T <= FLOW_NORM_ROWS && (long)T * (K / 4) <= FLOW_NORM_NV * 256L; }
+// Where it pays.  A norm kernel before a product costs 3 to 4 us (its launch, a round trip for its row and another for the product's
+// workgroups that wait for it); inside, a workgroup takes in the residual and the planes of the product before, which count
+// as many times as there are planes, and adds up every row's squares: a row costs as much as 10 KB.  us a layer (two norms) saved in
+// decode steps of two (d_model 256) or eight layers, bf16 / fp16, by the KB per product and the rows:
+//   d_model 256    28 KB,  8 rows 1.4 / 1.9   35, 10  0.1 / 0.4   42, 12 -0.3 / 0.1   49, 14 -2.7 / -2.8   56, 16 -2.9 / -2.9
+//           512    48,     4      2.2 / 2.7   72,  6  1.1 / 1.3   96,  8 -0.9 / -0.6  120, 10 -1.9 / -2.0
+//          1024    56,     2      3.5 / 3.3   84,  3  2.3 / 3.2  112,  4 -0.1 / 0.6   140,  5 -0.9 / -2.1
+//          1536    66,     2      2.9 / 4.4   99,  3  0.7 / 1.8
+//    2048, 2560    80,     2      1.6 / 3.1, 2.0 / 4.6           2560 120, 3 -1.2      4096  48, 1 3.0 / 5.8
+// The line is 145 KB per product: what it takes saves something everywhere, what it turns down would have saved 0.6 us at most.
+inline bool flow_norm_form(int T, int K, int planes_o, int planes_down) {
+  const long kb = (long)T * K * 4 * (2 + planes_o + planes_down) / 1024;   // of both products of a layer
+  return flow_norm_fits(T, K) && kb + 20L * T <= 290;
+}
+
 }  // namespace rlx

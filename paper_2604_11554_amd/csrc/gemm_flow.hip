@@ -113,10 +113,9 @@ __device__ __forceinline__ void lm_store(const GemmArgs& a, const LmSums& s, int
 // A norm kernel costs its launch, a round trip for its row and another for the product's workgroups that wait for it: 3.9 us
 // before a product of 8 to 18 at one token.  Here the row's residual and planes (40 KB at the 4B shape) are asked for first and the
 // first weights right behind them, so that the norm passes in the shadow of the weights' latency; the rows stay in LDS, one
-// 16-byte read per lane, step and term.  The price is the rows once per workgroup, which is what bounds the number of tokens: up to
-// NV float4 slices of them per thread, five at most (a step of eight layers of the 4B shape, us: 1 token, three slices 638 -> 594;
-// 2, five 670 -> 643; 3, eight 690 -> 700; 4, ten 693 -> 722; the two-layer policy, 4 tokens 92 -> 79).
-constexpr int FLOW_NORM_NV = 5;
+// 16-byte read per lane, step and term.  The price is the rows and planes once per workgroup, which is what bounds the number of tokens
+// (flow_norm_form): up to NV float4 slices of the rows per thread (a step of eight layers of the 4B shape, us: 1 token, three slices
+// 638 -> 594; 2, five 670 -> 643; 3, eight 690 -> 700; 4, ten 693 -> 722; the two-layer policy, 4 tokens 92 -> 79).
 template <int PL, int EPI>
 struct FlowRows {
   // rows that keep their common factor out (Act::ss) but for LM heads, whose rows are read again, and one fp16 term, whose range
@@ -499,8 +498,7 @@ bool flow_format(int planes, int dtype) { return (dtype == DT_BF16 && planes == 
 
 }  // namespace
 
-bool gemm_flow_norm_form(int T, int K) { return T <= 16 && (long)T * (K / 4) <= FLOW_NORM_NV * 256L; }
-static bool norm_fits(const FlowNorm* norm, int T, int K) { return !norm || gemm_flow_norm_form(T, K); }
+static bool norm_fits(const FlowNorm* norm, int T, int K) { return !norm || flow_norm_fits(T, K); }
 
 bool gemm_flow_store_form(int N, int K, int T, int n_units, int planes, int dtype) {
   return flow_format(planes, dtype) && flow_store_form(N, K, T, n_units, planes);

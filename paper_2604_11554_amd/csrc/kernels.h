@@ -118,8 +118,7 @@ struct FlowNorm {
 // or fp16 as one ----
 // y[split][t][n] in the planes of `plan` (flow_store_plan)
 bool gemm_flow_store_form(int N, int K, int T, int n_units, int planes, int dtype);   // whether the form is built, and the faster one
-// (x.p is not read where `norm` gives the rows)
-bool gemm_flow_norm_form(int T, int K);              // whether the norm goes into the products of T rows of K
+// (x.p is not read where `norm` gives the rows: flow_norm_fits)
 hipError_t gemm_flow_store(const LinearW& w, const Act& x, int T, float* y, int ldy, const FlowPlan& plan, hipStream_t st,
                            const FlowNorm* norm = nullptr);
 bool gemm_flow_swiglu_form(int F, int T, int n_units, int planes, int dtype);

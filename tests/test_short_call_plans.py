@@ -8,6 +8,8 @@ import pytest
 
 from paper_2604_11554_amd import build
 
+import rollout_inputs as RI
+import test_gpu_norm_inside as GN
 import test_gpu_short_calls as G
 
 SOURCE = """
@@ -17,6 +19,8 @@ extern "C" int store_plan(int N, int K, int T, int units, int planes) {
   return p.rt * 100 + p.splits;
 }
 extern "C" int store_form(int N, int K, int T, int units, int planes) { return rlx::flow_store_form(N, K, T, units, planes); }
+extern "C" int norm_fits(int T, int K) { return rlx::flow_norm_fits(T, K); }
+extern "C" int norm_form(int T, int K, int planes_o, int planes_down) { return rlx::flow_norm_form(T, K, planes_o, planes_down); }
 """
 
 
@@ -68,3 +72,28 @@ def test_the_compared_products_reach_every_tiling(lib, fmt):
     want = {(rt, n) for rt in (2, 4, 5) for n in (1, 2, 3, 4, 6)} | {(8, n) for n in (2, 3, 4)}
     want |= {(8, 1)} if planes == 2 else {(rt, 8) for rt in (2, 4, 5)}
     assert stores == want, stores ^ want
+
+
+def test_where_the_norm_goes_into_the_products(lib):
+    s = RI.TINY_DENSE
+
+    def inside(T, d, q_dim, d_ff, planes):
+        o, down = (lib.store_plan(d, k, T, 256, planes) % 100 for k in (q_dim, d_ff))
+        return lib.norm_form(T, d, o, down)
+
+    # the compared calls: all but the last ones, on either side of three slices per thread
+    last = {80: 13, 512: 8, 1024: 5, 2544: 2, 5120: 1}
+    for planes in (1, 2):
+        for d, d_ff, rows in GN.SHAPES:
+            assert [inside(T, d, s.q_dim, d_ff, planes) for T in rows] == [int(T <= last[d]) for T in rows], (planes, d)
+            assert last[d] in rows and last[d] + 1 in rows
+        # measured: d_model, width of the attention output, d_ff: rows that gain, rows that lose (or gain 0.6 us a layer at most)
+        for d, q_dim, d_ff, yes, no in ((256, 256, 688, 10, 12), (512, 512, 1536, 6, 8), (1024, 2048, 3072, 3, 4), (1536, 1536, 8960, 3, 4),
+                                        (2048, 2048, 6144, 2, 3), (2560, 4096, 9728, 2, 3), (4096, 4096, 12288, 1, 2)):
+            assert [inside(T, d, q_dim, d_ff, planes) for T in (yes, no)] == [1, 0], (planes, d)
+    # more planes, fewer rows; never past what the kernels are built for
+    assert [lib.norm_form(4, 512, p, p) for p in (2, 6, 12, 13, 16)] == [1, 1, 1, 0, 0]
+    for T in range(1, 40):
+        for d in (16, 48, 256, 1024, 5120, 5136, 20480):
+            assert lib.norm_fits(T, d) == int(T <= 16 and T * d <= 5120)
+            assert lib.norm_form(T, d, 1, 1) <= lib.norm_fits(T, d)
