@@ -23,16 +23,26 @@ __device__ __forceinline__ Part part_merge(Part a, Part b) {
 }
 
 // What bounds it: round trips, of which only the emitted token's weights wait for another one's answer, and they only where the token is
-// drawn and not given.  Everything else is requested at once, and the tree over the threads stays in their waves.  us per launch, before
-// -> now, tokens given: two-layer policy 5.4 -> 4.7, 151 936 ids 1 row 8.7 -> 7.7, 64 rows 9.7 -> 8.5; 896 scored rows 15.0 -> 15.8.
+// drawn and not given.  Everything else is requested at once, and the tree over the threads stays in their waves.  us per launch, each
+// load where it was first used -> now: two-layer policy, tokens given 5.4 -> 4.2, drawn 5.3 -> 4.3; 151 936 ids, 1 row 8.5 -> 7.2 and
+// 8.5 -> 7.7, 64 rows 10.7 -> 9.0 and 9.9 -> 9.1, 256 rows 11.9 -> 9.4 and 11.6 -> 9.4.
+// SCORE: many rows, some with nothing to score, which leave before they ask for anything; row and weights come behind the parts.  us for
+// 896 scored rows, 608, and the same with a third of them scored: each load where it was first used 15.0, 12.8, 9.7, 9.2; everything at
+// once 15.8, 13.8, 12.6, 10.8; now 15.7, 12.7, 10.0, 9.5.
+template <bool SCORE>
 __global__ __launch_bounds__(256) void sample_finalize_kernel(FinalizeArgs a) {
   __shared__ Part sh[4];
   __shared__ float dsh[4];
   const int r = blockIdx.x, tid = (int)threadIdx.x;
   const int forced = a.forced ? a.forced[r] : -1;
+  const bool given = forced >= 0 && forced < a.vocab;
+  if (SCORE && !given) {                    // nothing to score at this position
+    if (tid == 0) a.out_logprobs[r] = 0.f;
+    return;
+  }
   const float temp = a.temperature[a.row_seq ? a.row_seq[r] : r];
-  const uint8_t sample_on = a.score ? 1 : a.sample_on[r];
-  const int pos = a.score ? 0 : a.sample_pos[r], max_ctx_len = a.score ? 0x7FFFFFFF : a.max_ctx_len[r];
+  const uint8_t sample_on = SCORE ? 1 : a.sample_on[r];
+  const int pos = SCORE ? 0 : a.sample_pos[r], max_ctx_len = SCORE ? 0x7FFFFFFF : a.max_ctx_len[r];
   const f32x4* base = reinterpret_cast<const f32x4*>(a.part + (size_t)r * a.n_parts * 4);
   f32x4 q[8];
   auto load_parts = [&](int t0) {
@@ -57,13 +67,8 @@ __global__ __launch_bounds__(256) void sample_finalize_kernel(FinalizeArgs a) {
 #pragma unroll
     for (int u = 0; u < 2; ++u) wv[u] = load_h16x8(a.w_lm + packed_weight_offset(t, group_k(g0, u), a.d));
   };
-  load_x(0);
+  if (!SCORE) load_x(0);
 
-  const bool given = forced >= 0 && forced < a.vocab;
-  if (a.score && !given) {                    // nothing to score at this position
-    if (tid == 0) a.out_logprobs[r] = 0.f;
-    return;
-  }
   if (!sample_on) {                           // inert row
     if (tid == 0) {
       a.out_tokens[r] = a.pad;
@@ -73,10 +78,10 @@ __global__ __launch_bounds__(256) void sample_finalize_kernel(FinalizeArgs a) {
     }
     return;
   }
-  const bool capped = !a.score && pos >= max_ctx_len - 1;
+  const bool capped = !SCORE && pos >= max_ctx_len - 1;
   int tok = capped ? a.eos : given ? forced : -1;
   const bool known = tok >= 0;                // uniform
-  if (known) load_w(0, tok);
+  if (!SCORE && known) load_w(0, tok);
   // thread t takes tiles t, t + 256, ... (one 16-byte record each, eight loads in flight), merged in
   // ascending order; then a fixed binary tree over the threads
   Part p = {-INFINITY, 0.f, -INFINITY, 0x7FFFFFFF};
@@ -109,8 +114,8 @@ __global__ __launch_bounds__(256) void sample_finalize_kernel(FinalizeArgs a) {
   const int dt = a.x.dtype;
   float acc = 0.f;
   for (int g0 = 0; g0 < ng; g0 += 2 * 256) {
-    if (g0) load_x(g0);
-    if (g0 || !known) load_w(g0, tok);
+    if (g0 || SCORE) load_x(g0);
+    if (g0 || SCORE || !known) load_w(g0, tok);
 #pragma unroll
     for (int u = 0; u < 2; ++u)
       if (g0 + u * 256 + tid < ng) {
@@ -130,7 +135,7 @@ __global__ __launch_bounds__(256) void sample_finalize_kernel(FinalizeArgs a) {
     float z = dsh[0] + dsh[1] + dsh[2] + dsh[3];
     float invt = temp > 0.f ? 1.f / temp : 1.f;
     a.out_logprobs[r] = z * invt - lse;
-    if (a.score) return;
+    if (SCORE) return;
     a.out_tokens[r] = tok;
     if (a.out_sampled) a.out_sampled[r] = sampled;
     uint8_t fin = (tok == a.eos) ? 1 : 0;
@@ -146,7 +151,8 @@ __global__ __launch_bounds__(256) void sample_finalize_kernel(FinalizeArgs a) {
 }  // namespace
 
 hipError_t sample_finalize(const FinalizeArgs& a, hipStream_t st) {
-  hipLaunchKernelGGL(sample_finalize_kernel, dim3(a.n_rows), dim3(256), 0, st, a);
+  if (a.score) hipLaunchKernelGGL(sample_finalize_kernel<true>, dim3(a.n_rows), dim3(256), 0, st, a);
+  else hipLaunchKernelGGL(sample_finalize_kernel<false>, dim3(a.n_rows), dim3(256), 0, st, a);
   return hipGetLastError();
 }
 

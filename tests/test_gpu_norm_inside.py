@@ -22,7 +22,8 @@ TYPICAL = {"bf16": 1e-4 * LAYERS, "f16": 5e-3 * LAYERS}      # half of the rows,
 
 # d_model, d_ff, rows (test_short_call_plans.py holds the first ones of each to the form and the last ones to the other): 512 has 128
 # slices a row, so 6 rows fill three per thread and 8 four; 5 rows of 1024 and one of 5120 fill five
-SHAPES = [(80, 688, (1, 13, 14, 16, 17)), (512, 1024, (1, 6, 7, 8, 9, 10, 11)), (1024, 1024, (4, 5, 6)), (2544, 688, (1, 2, 3)), (5120, 688, (1, 2))]
+SHAPES = [(80, 688, (1, 13, 14, 16, 17)), (512, 1024, (1, 6, 7, 8, 9, 10, 11)), (1024, 1024, (4, 5, 6)), (2544, 688, (1, 2, 3)),
+          (5120, 688, (1, 2))]
 
 
 @pytest.mark.parametrize("fmt", ["bf16", "f16"])
