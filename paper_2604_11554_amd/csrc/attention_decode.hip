@@ -501,8 +501,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   auto tile = [&](Tile d) {
     d.row = min(max(__builtin_amdgcn_readfirstlane(d.row), 0), a.n_seqs - 1);
     d.kvh = min(max(__builtin_amdgcn_readfirstlane(d.kvh), 0), a.Hkv - 1);
-    d.lo = max(__builtin_amdgcn_readfirstlane(d.lo), 0);
-    d.hi = min(__builtin_amdgcn_readfirstlane(d.hi), a.max_blocks / 2);
+    const PrefixRange r = prefix_range(__builtin_amdgcn_readfirstlane(d.lo), __builtin_amdgcn_readfirstlane(d.hi), a.max_blocks);
+    d.lo = r.lo; d.hi = r.hi;
     return d;
   };
   // entries of the 32 units from unit `first` on: lane i holds block 2 first + i

@@ -26,6 +26,13 @@ constexpr int shared_prefix_max_tiles(int n_seqs, int Hkv) { return n_seqs * Hkv
 inline size_t shared_prefix_words(int n_seqs, int Hkv) {
   return (size_t)SP_HDR + 4 * (size_t)n_seqs + (size_t)shared_prefix_max_tiles(n_seqs, Hkv) * (4 + 16);
 }
+// The units of a tile as its kernel walks them, whatever the words hold: 0 <= lo <= hi, unit hi - 1 in a block-table row of max_blocks
+// entries (and, lo being no further than that, block 2 lo is an index that does not overflow).
+struct PrefixRange { int lo, hi; };
+constexpr PrefixRange prefix_range(int lo, int hi, int max_blocks) {
+  const int most = hi < max_blocks / 2 ? hi : max_blocks / 2, end = most > 0 ? most : 0;
+  return {lo < 0 ? 0 : lo < end ? lo : end, end};
+}
 
 // Groups that share something: sequences b .. e - 1, `units` of 32 keys.  A group is a run of consecutive sequences with the same
 // leader (the first of them); its shared units are the smallest shared page count of its members, halved.

@@ -12,6 +12,10 @@ from paper_2604_11554_amd import build
 SOURCE = """
 #include "prefix_plan.h"
 extern "C" int64_t words(int n, int Hkv) { return (int64_t)rlx::shared_prefix_words(n, Hkv); }
+extern "C" void range(int lo, int hi, int max_blocks, int* out) {
+  const rlx::PrefixRange r = rlx::prefix_range(lo, hi, max_blocks);
+  out[0] = r.lo; out[1] = r.hi;
+}
 extern "C" void fill(int n, int Hq, int Hkv, const int32_t* leader, const int32_t* pages, int most_tiles, int32_t* out) {
   rlx::shared_prefix_build(n, Hq, Hkv, leader, pages, most_tiles, out);
 }
@@ -125,3 +129,17 @@ def test_page_counts_of_any_size(lib):
     assert _lengths(lib, [3] * 255 + [top // 2], members=4) == (255 * 8 + 32, -(-(top // 2) // 4))
     _, start, _, _, _, tiles = _tiles(lib, [[top] * 2] * 8, 32, 8, 512)
     assert start[0] == top // 2 and max(t[3] for t in tiles) == top // 2
+
+
+def test_a_tiles_units_are_in_the_block_table_whatever_the_words_hold(lib):
+    # what the kernel does with them: entries 2 lo + 0 .. 63, capped at the last one, then units lo + wave .. hi - 1
+    out, top = (ctypes.c_int * 2)(), 2 ** 31 - 1
+    words = [-top - 1, -1, 0, 1, 3, 7, 8, 9, 2 ** 30 - 1, 2 ** 30, top - 3, top]
+    for lo in words:
+        for hi in words:
+            for max_blocks in (1, 2, 15, 16, 1 << 20):
+                lib.range(lo, hi, max_blocks, out)
+                assert 0 <= out[0] <= out[1] <= max_blocks // 2, (lo, hi, max_blocks)
+                assert 2 * out[0] + 63 <= top and (out[0] == out[1] or 2 * (out[1] - 1) + 1 < max_blocks)
+                if 0 <= lo < hi <= max_blocks // 2:
+                    assert (out[0], out[1]) == (lo, hi)
