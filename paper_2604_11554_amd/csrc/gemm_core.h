@@ -200,6 +200,7 @@ __device__ __forceinline__ void lmhead_epilogue(const GemmArgs& a, f32x4* scr, c
             }
           }
         }
+      asm volatile("" ::: "memory");                       // the next token tile's writes stay behind the other lanes' reads
     }
     const int t = (mt0 + m) * 32 + r32;
     const bool ok = t < a.T;
