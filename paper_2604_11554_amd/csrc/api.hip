@@ -818,10 +818,15 @@ int rlx_shared_prefix_build(const rlx_model* m, int32_t n_seqs, const int32_t* l
     if (leader[i] < 0 || leader[i] > i || shared_pages[i] < 0)
       return fail(RLX_EINVAL, "rlx_shared_prefix_build: sequence %d: leader %d (0..%d) / shared_pages %d", i, leader[i],
                   i, shared_pages[i]);
-  std::vector<int32_t> host(words);
-  // MoE policies keep the order of their sums: the same chunks however many tiles that makes
-  shared_prefix_build(n_seqs, m->cfg.n_q_heads, m->cfg.n_kv_heads, leader, shared_pages, attn_by_team(m->cfg) ? 0 : prefix_wgs(m),
-                      host.data());
+  std::vector<int32_t> host;
+  try {                                               // the groups' list and the staging copy: no exception leaves a C entry
+    host.resize(words);
+    // MoE policies keep the order of their sums: the same chunks however many tiles that makes
+    shared_prefix_build(n_seqs, m->cfg.n_q_heads, m->cfg.n_kv_heads, leader, shared_pages, attn_by_team(m->cfg) ? 0 : prefix_wgs(m),
+                        host.data());
+  } catch (const std::bad_alloc&) {
+    return fail(RLX_ENOMEM, "rlx_shared_prefix_build: host allocation failed");
+  }
   hipStream_t st = (hipStream_t)stream;
   RLX_HIP(hipMemcpyAsync(desc, host.data(), words * 4, hipMemcpyHostToDevice, st));
   RLX_HIP(hipStreamSynchronize(st));      // the staging vector dies with this call

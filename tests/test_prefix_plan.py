@@ -3,6 +3,7 @@ member is in one tile per KV head, and no tile is the time of the whole launch."
 import ctypes
 import random
 import subprocess
+import sys
 
 import numpy as np
 import pytest
@@ -143,3 +144,25 @@ def test_a_tiles_units_are_in_the_block_table_whatever_the_words_hold(lib):
                 assert 2 * out[0] + 63 <= top and (out[0] == out[1] or 2 * (out[1] - 1) + 1 < max_blocks)
                 if 0 <= lo < hi <= max_blocks // 2:
                     assert (out[0], out[1]) == (lo, hi)
+
+
+# the entry with the descriptor of 65 536 rows and 64 KV heads to stage (320 MB) in a process that may have 64 MB more than it has; of the
+# model it looks at the configuration that a handle begins with, and it returns before it touches a device
+OUT_OF_MEMORY = """
+import ctypes as C, resource
+from paper_2604_11554_amd import binding as B
+l = B.lib()
+n, model = 65536, (C.c_char * 65536)()
+cfg = B.ModelConfig.from_buffer(model)
+cfg.n_q_heads, cfg.n_kv_heads = 64, 64
+leader, pages = (C.c_int32 * n)(), (C.c_int32 * n)(*[4] * n)
+have = int(open("/proc/self/statm").read().split()[0]) * resource.getpagesize()
+resource.setrlimit(resource.RLIMIT_AS, (have + (64 << 20),) * 2)
+rc = l.rlx_shared_prefix_build(C.addressof(model), n, leader, pages, 4096, 1 << 40, None)
+print(rc, l.rlx_last_error().decode())
+"""
+
+
+def test_no_exception_leaves_the_entry():
+    r = subprocess.run([sys.executable, "-c", OUT_OF_MEMORY], cwd=build.HERE + "/..", capture_output=True, text=True)
+    assert r.returncode == 0 and r.stdout.split(" ", 1)[0] == "-2" and "host allocation failed" in r.stdout, (r.returncode, r.stdout, r.stderr)
