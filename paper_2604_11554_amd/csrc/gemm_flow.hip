@@ -123,39 +123,38 @@ struct FlowRows {
   static constexpr bool LATE_FACTOR = EPI != EPI_LMHEAD && PL == 2;
   __host__ __device__ static int pitch(int K) { return (K + 31) / 32 * 32 + 8; }   // elements; 16 bytes past the banks' period
   __host__ __device__ static int x_bytes(int T, int K) { return PL * T * pitch(K) * 2; }
-  __host__ __device__ static int bytes(int T, int K) { return x_bytes(T, K) + T * (K / 4) * 4 + 16 * 4; }   // + squares of the slices, + factors
+  // + squares of the slices, + factors
+  __host__ __device__ static int bytes(int T, int K) { return x_bytes(T, K) + T * (K / 4) * 4 + FLOW_NORM_ROWS * 4; }
+  // ... at most, of calls that fit (flow_norm_fits): so many slices of four elements, and rows that end inside a 32-wide step
+  static constexpr int SLICES = FLOW_NORM_NV * 256, MOST = PL * (4 * SLICES + FLOW_NORM_ROWS * 24) * 2 + SLICES * 4 + FLOW_NORM_ROWS * 4;
 };
 template <int NV, int PL, int FMT, int EPI>
 __device__ __forceinline__ void flow_rows_load(const GemmArgs& a, f32x4 (&v)[NV], u32x2 (&gain)[NV]) {
-  constexpr int PR = 4, NG = NV;                   // planes per round, slices in flight with them
+  constexpr int PR = 4;                              // planes per round
   const int nv = a.K >> 2, total = a.T * nv, tid = (int)threadIdx.x;
   const FlowNorm& m = a.norm;
+  int f[NV];
 #pragma unroll
-  for (int j0 = 0; j0 < NV; j0 += NG) {
-    if (256 * j0 >= total) break;                               // uniform
-    int f[NG];
+  for (int j = 0; j < NV; ++j) {
+    f[j] = min(256 * j + tid, total - 1);            // a slice past the end repeats the last one and is never stored
+    v[j] = *reinterpret_cast<const f32x4*>(m.h + 4 * (size_t)f[j]);
+    gain[j] = *reinterpret_cast<const u32x2*>(m.gain + 4 * (f[j] % nv));
+  }
+  if (!m.add) return;
+  for (int s0 = 0; s0 < m.n_planes; s0 += PR) {      // in plane order
+    f32x4 p[PR][NV];
 #pragma unroll
-    for (int j = 0; j < NG; ++j) {
-      f[j] = min(256 * (j0 + j) + tid, total - 1);              // a slice past the end repeats the last one and is never stored
-      v[j0 + j] = *reinterpret_cast<const f32x4*>(m.h + 4 * (size_t)f[j]);
-      gain[j0 + j] = *reinterpret_cast<const u32x2*>(m.gain + 4 * (f[j] % nv));
+    for (int q = 0; q < PR; ++q) {
+      const size_t plane = (size_t)min(s0 + q, m.n_planes - 1) * a.T * a.K;
+#pragma unroll
+      for (int j = 0; j < NV; ++j) p[q][j] = *reinterpret_cast<const f32x4*>(m.add + plane + 4 * (size_t)f[j]);
     }
-    if (m.add)
-      for (int s0 = 0; s0 < m.n_planes; s0 += PR) {             // in plane order
-        f32x4 p[PR][NG];
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int q = 0; q < PR; ++q) {
-          const size_t plane = (size_t)min(s0 + q, m.n_planes - 1) * a.T * a.K;
+    for (int q = 0; q < PR; ++q)
+      if (s0 + q < m.n_planes) {
 #pragma unroll
-          for (int j = 0; j < NG; ++j) p[q][j] = *reinterpret_cast<const f32x4*>(m.add + plane + 4 * (size_t)f[j]);
-        }
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int q = 0; q < PR; ++q)
-          if (s0 + q < m.n_planes) {
-#pragma unroll
-            for (int j = 0; j < NG; ++j) v[j0 + j] += p[q][j];
-          }
+        for (int j = 0; j < NV; ++j) v[j] += p[q][j];
       }
   }
 }
@@ -448,13 +447,8 @@ void launch_flow_one(const GemmArgs& a, dim3 grid, hipStream_t st) {
 }
 template <int RT, int PL, int FMT, int EPI, int NORM>
 void launch_flow_norm(GemmArgs a, dim3 grid, hipStream_t st) {
-  static std::once_flag attr_once;
   using TL = FlowTiling<RT, 1, PL, EPI>;
-  constexpr int most = 64 * 1024;                     // of rows and sums; at most 10 KB of float4 slices go with 41 KB of terms
-  std::call_once(attr_once, [] {
-    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_flow_kernel<RT, 1, PL, FMT, EPI, NORM>),
-                              hipFuncAttributeMaxDynamicSharedMemorySize, most + TL::LDS_BYTES - TL::SUM_BYTES);
-  });
+  static_assert(FlowRows<PL, EPI>::MOST + 16 <= 60 * 1024 && TL::LDS_BYTES <= 60 * 1024, "below the limit that has to be raised");
   const int rows = (FlowRows<PL, EPI>::bytes(a.T, a.K) + 15) / 16 * 16;
   a.lds_split = rows > TL::SUM_BYTES ? rows : TL::SUM_BYTES;
   hipLaunchKernelGGL((gemm_flow_kernel<RT, 1, PL, FMT, EPI, NORM>), grid, dim3(64 * FLOW_WAVES),

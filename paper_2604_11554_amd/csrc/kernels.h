@@ -112,7 +112,7 @@ struct FlowNorm {
   int n_planes;
   const h16_t* gain;
   float eps;
-  h16_t* x_out;               // optional (LM head): the normalised rows, in fragment order
+  h16_t* x_out;               // LM head: where its launch leaves the normalised rows, in fragment order (set by gemm_flow_lmhead)
 };
 // ---- gemm_flow.hip: the same products for short calls of dense policies (activations in fragment order), on bf16 as two terms
 // or fp16 as one ----
