@@ -167,7 +167,8 @@ __device__ __forceinline__ LmRow lm_row(const GemmArgs& a, int t) {
 // 16 bytes of a row per instruction, of rows that lie a vocabulary apart.  What the caches hold back they write while other
 // workgroups' weights stream: 45 rows of 151 936 ids, K 2560, 174 us -> 158, fp16 157 -> 146 (whole lines alone 171 and 154; no
 // logits 157 and 133).  The long-call forms have no other workgroup on the unit that would use the time and pay for the passes through
-// LDS: 128 rows of the MoE batch 1535 us a step by lanes, 1541 by lines.
+// LDS: as fast by lanes (151 936 ids with logits, two runs, 5 % apart at most, lanes / lines: K 2560, 128 rows 231, 225 / 223, 228,
+// 256 rows 446, 424 / 436, 435; K 2048, 128 rows 198, 187 / 199, 187) or faster (96 rows 168, 167 / 179, 185).
 template <int JT, int MT, bool LINES>
 __device__ __forceinline__ void lmhead_epilogue(const GemmArgs& a, f32x4* scr, const f32x16 (&acc)[JT][MT], const LmRow (&row)[MT],
                                                 int nt0, int mt0, int part, int n_parts, int lane) {

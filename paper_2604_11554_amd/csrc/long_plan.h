@@ -58,15 +58,19 @@ inline LongPlan long_plan(int N, int K, int T, int max_splits, int n_units, bool
 
 // The LM head, whose epilogue makes the rounds longer where nothing runs beside them.  Up to LM_FEW_ROWS rows there are two forms
 // more, 320 vocabulary rows by 128 or 256 tokens (eight waves, one workgroup per unit): they read the weights once for all rows and
-// a wave's 160 ids are one part of the partials, but a workgroup takes five eighths of a 512 x 128 tile's time or more, so that what
-// decides is how well the rounds fit the vocabulary.  us of the launch and the merge of its parts, 512 x 128 / 128 x 128 / 320 x 128 /
-// 320 x 256, K 2560:   vocabulary      32 000                 100 352                128 256                151 936
-//             128 rows  122 /  56 /  83 /  99  150 / 183 / 198 / 216  187 / 204 / 210 / 226  300 / 238 / 224 / 237
-//             256 rows  131 /  91 /  95 / 161  323 / 287 / 282 / 342  330 / 346 / 372 / 358  452 / 407 / 386 / 374
-// The constants (us: start of a round, per stage, share of a last round's time that goes with its fill, share of a stage's that goes
-// with the fill of the token tiles) were fitted to a sweep of 8192 to 200 064 ids, K 1024 to 4096 and 65 to 256 rows: 0.5 % behind the
-// best of the four forms in the mean, 14 % at worst, and 2.2 % ahead of the first two alone (4 % behind at worst); in a second sweep
-// at other sizes (20 000 to 170 000 ids, K 64 to 3072) 1.2 % behind and 2.4 % ahead.  Past 256 rows those two are within 2 % of the others.
+// a wave's 160 ids are one part of the partials, but a workgroup takes two thirds of a 512 x 128 tile's time or more, so that what
+// decides is how well the rounds fit the vocabulary.  us that a decode step takes longer than with the fastest, 512 x 128 / 128 x 128 /
+// 320 x 128 / 320 x 256, K 2560 (one draw per row, no logits):
+//   vocabulary        32 000              100 352              128 256              151 936
+//      96 rows   55 /   0 /  23 /  43    0 /  27 /  40 /  71    0 /  18 /  28 /  60   73 /  26 /   0 /  30
+//     128 rows   53 /   0 /  17 /  34    0 /  24 /  50 /  69    0 /  14 /  34 /  49   68 /   8 /   0 /  16
+//     256 rows   33 /   0 /   1 /  60    0 /   5 /   1 /  55    0 /  20 /  62 /  38   50 /  35 /  18 /   0
+// and K 2048, 151 936 ids, 96, 128, 256 rows:  67 /  14 /   0 /  22,  61 /   0 /   6 /   5,  45 /  23 /  18 /   0.
+// The constants (us: start of a round, per stage, share of a last round's time that goes with its fill -- of 128 x 128, share that a round
+// of one workgroup per unit takes --, share of a stage's that goes with the waves that have tokens) were fitted to 472 decode steps
+// of two or three layers, 16 000 to 200 064 ids, K 256 to 4096, 65 to 256 rows.  In the mean the choice is 1.0 % of the LM head's time
+// behind the best of the four, where the first two forms alone were 5.3 % and 320 rows at any vocabulary 43 %; where one of the first
+// two is best it is 3 % behind at worst.  Past 256 rows those two are within 2 % of the others.
 constexpr int LM_FEW_ROWS = 256;
 inline int long_lmhead_form(int V, int K, int T, int n_units) {
   const int per = (K / 16 + 1) / 2;
@@ -76,18 +80,20 @@ inline int long_lmhead_form(int V, int K, int T, int n_units) {
                ? LONG_512x128 : LONG_128x128;
   int best = LONG_512x128;
   float best_us = 1e30f;
-  auto take = [&](int form, int rows, int tokens, int at_once, float start, float stage, float last, float empty) {
+  // `wave`: tokens of a wave, `at_once`: workgroups of a round
+  auto take = [&](int form, int rows, int tokens, int wave, int at_once, float start, float stage, float last, float empty) {
     const long w = workgroups(rows, tokens), full = w / at_once, rest = w % at_once;
-    const float round = start + stage * (float)per * (1.f - empty * (1.f - (float)T / (float)((T + tokens - 1) / tokens * tokens)));
+    const float live = (float)((T + wave - 1) / wave * wave) / (float)((T + tokens - 1) / tokens * tokens);
+    const float round = start + stage * (float)per * (1.f - empty * (1.f - live));
     float us = (float)full * round;
     if (rest) us += form != LONG_128x128 ? round * (1.f - last * (1.f - (float)rest / (float)at_once))
-                                         : round * (rest <= n_units ? 1.f - last : 1.f);   // one per unit is no slower by fill
+                                         : round * (rest <= n_units ? last : 1.f);   // one per unit is no slower by fill
     if (us < best_us) { best_us = us; best = form; }
   };
-  take(LONG_512x128, 512, 128, n_units, 31.4f, 1.66f, 0.31f, 0.19f);
-  take(LONG_128x128, 128, 128, 2 * n_units, 15.1f, 0.89f, 0.42f, 0.28f);
-  take(LONG_320x128, 320, 128, n_units, 25.4f, 0.99f, 0.27f, 0.33f);
-  take(LONG_320x256, 320, 256, n_units, 38.6f, 2.01f, 0.18f, 0.51f);
+  take(LONG_512x128, 512, 128, 64, n_units, 28.5f, 1.46f, 0.30f, 0.43f);
+  take(LONG_128x128, 128, 128, 64, 2 * n_units, 10.3f, 0.86f, 0.57f, 0.74f);
+  take(LONG_320x128, 320, 128, 32, n_units, 16.7f, 1.09f, 0.31f, 0.52f);
+  take(LONG_320x256, 320, 256, 64, n_units, 26.3f, 1.97f, 0.21f, 0.76f);
   return best;
 }
 // weight tiles (32 vocabulary rows each) of a part of an LM head's partials
