@@ -132,6 +132,7 @@ template <int NV, int PL, int FMT, int EPI>
 __device__ __forceinline__ void flow_rows_load(const GemmArgs& a, f32x4 (&v)[NV], u32x2 (&gain)[NV]) {
   constexpr int PR = 4;                              // planes per round
   const int nv = a.K >> 2, total = a.T * nv, tid = (int)threadIdx.x;
+  __builtin_assume(total > 0);                       // offsets that are not negative: fewer instructions before the first load
   const FlowNorm& m = a.norm;
   int f[NV];
 #pragma unroll
