@@ -455,10 +455,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 // on the one before, whose fragments are in registers by then (chunks permuted as in prefill attention: no bank conflicts); a tile's
 // description, members and block-table entries are requested a tile ahead, and its queries behind its first pages.  Pages that one
 // tile alone reads are copied with the streaming mark; tiles are as many as there are workgroups where chunks can be longer instead.
-// us a layer of the 4B shape, before / copies / longest prefixes first / one round of tiles / streaming mark / longest tiles first: 32
-// groups of eight with prompts of 517 to 2048 positions 50.6 / 48.3 / 47.1 / 45.8 / 41.4 / 38.7 (168 MB, 4.3 TB/s); fp16, 32 of four, 400 to
-// 1500, 38 / 35 / 34 / 32 / 29 / -; 16 groups of sixteen, whose pages two tiles read, 42 / - / - / - / 34 / -.  Short prompts (200 to 600) 21 before and now: the start, four
-// round trips from the header to the pages, and the merge.
+// us a layer of the 4B shape, before / copies / longest prefixes first / one round of tiles / streaming mark / longest tiles first:
+// 32 groups of eight with prompts of 517 to 2048 positions 50.6 / 48.3 / 47.1 / 45.8 / 41.4 / 38.7 (168 MB, 4.3 TB/s); fp16, 32 of
+// four, 400 to 1500, 38 / 35 / 34 / 32 / 29 / -; 16 groups of sixteen, whose pages two tiles read, 42 / - / - / - / 34 / -.  Short
+// prompts (200 to 600) 21 before and now: the start, four round trips from the header to the pages, and the merge.
 template <int HD, int NCT, int PL>
 struct PrefixLds {
   static constexpr int UNIT = 4 * 16 * HD;           // elements of two pages of a KV head

@@ -153,7 +153,8 @@ __device__ __forceinline__ void tile_epilogue(const GemmArgs& a, const f32x16 (&
 // LM-head epilogue of a wave: per token, its 32 JT vocabulary rows (tiles nt0 ..) are reduced to (max, sumexp, best
 // score, its id), record `part` of `n_parts` of the token's row.  The accumulators go through a scratch area in LDS
 // (`scr`: JT * 4 KB of the wave's own, one token tile at a time), which lets the work on them run as a loop: written out
-// over the registers it was up to 50 KB of straight code per form.  The parts' order of sums differs from a sum id by id, not their precision.
+// over the registers it was up to 50 KB of straight code per form.  The parts' order of sums differs from a sum id by id, not their
+// precision.
 // What it needs to know of the lane's row is passed in, so that the caller can ask for it early (three dependent fetches
 // at the end of a kernel are three round trips).
 struct LmRow { float temperature; uint64_t seed; uint32_t pos; };

@@ -403,9 +403,9 @@ hipError_t gemm_long_grouped_store(const h16_t* w, int N, int K, const Act& x, c
   return hipGetLastError();
 }
 
-// The form is long_lmhead_form's.  With 320 x 128 or 320 x 256 in place of 128 x 128, 151 936 ids, one draw per row, us: K 2560, 96 rows
-// 229 -> 207, 128 238 -> 224, 129 359 -> 310, 256 407 -> 374; K 2048, 256 rows 339 -> 316; of it the parts' merge 10 -> 8.5.  (Of 64 rows and
-// fewer tiles of 160 to 320 rows, one or two workgroups per unit, gave what the short forms give.)
+// The form is long_lmhead_form's.  With 320 x 128 or 320 x 256 in place of 128 x 128, 151 936 ids, one draw per row, us with the
+// parts' merge (10 -> 8.5 of it): K 2560, 96 rows 229 -> 207, 128 238 -> 224, 129 359 -> 310, 256 407 -> 374; K 2048, 256 rows 339 -> 316.
+// (Of 64 rows and fewer tiles of 160 to 320 rows, one or two workgroups per unit, gave what the short forms give.)
 hipError_t gemm_long_lmhead(const h16_t* w_lm, int V, int K, const Act& x, int T, float* logits, float* part,
                             const uint64_t* seeds, const float* temperature, const int32_t* sample_pos,
                             const int32_t* row_seq, bool draw, int n_units, hipStream_t st) {
