@@ -17,8 +17,8 @@ def _engine(pkg, model, n, lens):
     return eng
 
 
-# 353 = 320 + 33 ids: one row past a weight tile in the second tile's first wave; 705 = 640 + 65 leaves that wave's second half
-# empty; 161: the second wave of the only tile has one id
+# the last tile of 128 ids, two waves of 64: 353 = 2 x 128 + 64 + 33, one id past a weight tile in the second wave; 705 = 5 x 128 + 65: the
+# second wave has one id; 161 = 128 + 33: it has none, and the first one's second weight tile one
 @pytest.mark.parametrize("vocab,d_model", [(353, 80), (705, 48), (161, 272)])
 @pytest.mark.parametrize("n_rows", [96, 200, 256])
 def test_draws_of_65_to_256_rows(n_rows, vocab, d_model):
