@@ -11,7 +11,7 @@ namespace rlx {
 
 // int32 words (built on the host, read by the kernels):
 //   [0] n_seqs it was built for, [1] n_tiles, [2] members per tile MS = min(16, SP_COLS / (Hq/Hkv)),
-//   [3] 1 if the tiles' pages are copied without the streaming mark (shared_prefix_plain), [4..7] 0
+//   [3] 1 if a group has more members than that, so that several tiles read its pages, [4..7] 0
 //   per sequence (4 arrays of n_seqs): start_unit, tile0 (first tile of its subgroup), n_chunks, col0 (its first column)
 //   per tile (arrays of max_tiles; groups of the longest chunks first): row (sequence whose block-table row lists the pages), kvh,
 //   unit lo, unit hi,
@@ -88,19 +88,6 @@ inline void shared_prefix_cut(std::vector<PrefixGroup>& groups, int MS, int Hkv,
   }
 }
 
-// Whether pages are copied without the streaming mark: where a group has more members than a tile holds, so that several tiles
-// read its pages, and where there are few rows and few pages.  us a step, 4B shape, eight layers, with the mark / without, prefixes of
-// half to all of so many positions: 4 groups of eight, 320 523.5 / 520.2, 2560 543.3 / 537.7; 16 of two, 1000 546.2 / 541.5, but 2560
-// (7700 units x KV heads) 600 / 611; 24 of four, 320 788.3 / 786.4, 12 of four, 2560 (5800) 653 / 664; 256 rows in groups of eight,
-// 320 1298 / 1308.
-constexpr int SP_PLAIN_UNITS = 3072, SP_PLAIN_ROWS = 128;
-inline bool shared_prefix_plain(const std::vector<PrefixGroup>& groups, int n_seqs, int MS, int Hkv) {
-  int64_t units = 0;
-  bool again = false;
-  for (const PrefixGroup& g : groups) { units += (int64_t)g.units * Hkv; again |= g.e - g.b > MS; }
-  return again || (n_seqs <= SP_PLAIN_ROWS && units <= SP_PLAIN_UNITS);
-}
-
 // fills `words` (shared_prefix_words entries) from per-sequence group leaders and shared page counts.  Groups of one, groups that
 // share less than one unit, and models whose 32 columns hold a single sequence get no tiles.
 inline void shared_prefix_build(int n_seqs, int Hq, int Hkv, const int32_t* leader, const int32_t* shared_pages, int most_tiles,
@@ -124,9 +111,9 @@ inline void shared_prefix_build(int n_seqs, int Hq, int Hkv, const int32_t* lead
   shared_prefix_cut(groups, MS, Hkv, most_chunks, most_tiles);
   // the longest tiles first: a workgroup's second one comes from the other end of the list
   std::stable_sort(groups.begin(), groups.end(), [](const PrefixGroup& x, const PrefixGroup& y) { return x.per > y.per; });
-  words[3] = shared_prefix_plain(groups, n_seqs, MS, Hkv);
   int n_tiles = 0;
   for (const PrefixGroup& g : groups) {
+    if (g.e - g.b > MS) words[3] = 1;                  // several tiles read these pages
     for (int sb = g.b; sb < g.e; sb += MS) {
       const int se = sb + MS < g.e ? sb + MS : g.e;
       for (int i = sb; i < se; ++i) {

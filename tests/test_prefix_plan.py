@@ -86,9 +86,7 @@ def test_every_shared_unit_of_every_member_is_in_one_tile(lib, Hq, Hkv, most_til
                     assert at == units
             n += len(p)
         assert seen == set(range(len(tiles)))
-        shared = [p for p in groups if len(p) > 1 and min(p) >= 2]
-        few = n <= 128 and sum(min(p) // 2 for p in shared) * Hkv <= 3072
-        assert head[3] == int(len(shared) > 0 and (few or any(len(p) > MS for p in shared)))
+        assert head[3] == int(any(len(p) > MS and min(p) >= 2 for p in groups))
         longest = [0] * (len(tiles) + 1)                      # of the tiles of a run of chunks: the list comes longest first
         firsts = sorted({tile0[i] for i in range(n) if chunks[i]})
         longest = [max(t[3] - t[2] for t in tiles[a:b]) for a, b in zip(firsts, firsts[1:] + [len(tiles)])]
