@@ -823,7 +823,7 @@ int rlx_shared_prefix_build(const rlx_model* m, int32_t n_seqs, const int32_t* l
     host.resize(words);
     // MoE policies keep the order of their sums: the same chunks however many tiles that makes
     shared_prefix_build(n_seqs, m->cfg.n_q_heads, m->cfg.n_kv_heads, leader, shared_pages, attn_by_team(m->cfg) ? 0 : prefix_wgs(m),
-                        host.data());
+                        shared_prefix_plain_units(m->cfg.head_dim, m->cfg.n_layers), host.data());
   } catch (const std::bad_alloc&) {
     return fail(RLX_ENOMEM, "rlx_shared_prefix_build: host allocation failed");
   }

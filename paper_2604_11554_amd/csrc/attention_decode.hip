@@ -48,7 +48,7 @@ struct PageRegs {
 // Views into the shared-prefix descriptor (kernels.h); `on` is false when there is none or it was built for
 // another batch size, and every index read from it is clamped by its user.
 struct SharedView {
-  bool on, again;                                    // again: some pages are read by more than one tile
+  bool on, plain;                                    // plain: pages are copied without the streaming mark
   int n_tiles, max_tiles;
   const int32_t *start_unit, *tile0, *n_chunks, *col0, *t_row, *t_kvh, *t_lo, *t_hi, *t_mem;
 };
@@ -61,7 +61,7 @@ __device__ __forceinline__ SharedView shared_view(const int32_t* sp, int n_seqs,
   if (!v.on) return v;
   v.max_tiles = shared_prefix_max_tiles(n_seqs, Hkv);
   v.n_tiles = min(max(head[1], 0), v.max_tiles);
-  v.again = head[3] != 0;
+  v.plain = head[3] != 0;
   const int32_t* p = sp + SP_HDR;
   v.start_unit = p; v.tile0 = p + n_seqs; v.n_chunks = p + 2 * n_seqs; v.col0 = p + 3 * n_seqs;
   p += 4 * (size_t)n_seqs;
@@ -454,7 +454,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 // every one of them from the block table on.  The hardware now copies a unit's pages into the wave's part of LDS while the wave works
 // on the one before, whose fragments are in registers by then (chunks permuted as in prefill attention: no bank conflicts); a tile's
 // description, members and block-table entries are requested a tile ahead, and its queries behind its first pages.  Pages that one
-// tile alone reads are copied with the streaming mark; tiles are as many as there are workgroups where chunks can be longer instead.
+// tile alone reads are copied with the streaming mark, but for few of them (shared_prefix_plain); tiles are as many as there are
+// workgroups where chunks can be longer instead.
 // us a layer of the 4B shape, before / copies / longest prefixes first / one round of tiles / streaming mark / longest tiles first:
 // 32 groups of eight with prompts of 517 to 2048 positions 50.6 / 48.3 / 47.1 / 45.8 / 41.4 / 38.7 (168 MB, 4.3 TB/s); fp16, 32 of
 // four, 400 to 1500, 38 / 35 / 34 / 32 / 29 / -; 16 groups of sixteen, whose pages two tiles read, 42 / - / - / - / 34 / -.  Short
@@ -528,9 +529,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     for (int half = 0; half < 2; ++half) {
       const unsigned char* page = reinterpret_cast<const unsigned char*>(a.pool_layer + ((size_t)(half ? b1 : b0) * a.Hkv + d.kvh) * PAGE);
       const uint32_t dst = pages_at + half * PAGE * 2;
-      auto copy = [&](auto again) {
+      auto copy = [&](auto plain) {
         auto one = [&](const unsigned char* p, uint32_t off, uint32_t to) {
-          if constexpr (decltype(again)::value) copy_to_lds(p, off, to);
+          if constexpr (decltype(plain)::value) copy_to_lds(p, off, to);
           else copy_to_lds_stream(p, off, to);
         };
 #pragma unroll
@@ -538,7 +539,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 #pragma unroll
         for (int i = 0; i < COPIES / 2; ++i) one(page + i * 1024, v_off, dst + (COPIES / 2 + i) * 1024);
       };
-      if (sv.again) copy(std::true_type());
+      if (sv.plain) copy(std::true_type());
       else copy(std::false_type());
     }
   };

@@ -11,7 +11,7 @@ namespace rlx {
 
 // int32 words (built on the host, read by the kernels):
 //   [0] n_seqs it was built for, [1] n_tiles, [2] members per tile MS = min(16, SP_COLS / (Hq/Hkv)),
-//   [3] 1 if a group has more members than that, so that several tiles read its pages, [4..7] 0
+//   [3] 1 if the tiles' pages are copied without the streaming mark (shared_prefix_plain), [4..7] 0
 //   per sequence (4 arrays of n_seqs): start_unit, tile0 (first tile of its subgroup), n_chunks, col0 (its first column)
 //   per tile (arrays of max_tiles; groups of the longest chunks first): row (sequence whose block-table row lists the pages), kvh,
 //   unit lo, unit hi,
@@ -88,10 +88,24 @@ inline void shared_prefix_cut(std::vector<PrefixGroup>& groups, int MS, int Hkv,
   }
 }
 
+// Whether pages are copied without the streaming mark: where a group has more members than a tile holds, so that several tiles
+// read its pages, and where the shared pages of all layers stay in the card's 256 MB memory-side cache from one step to the next, which
+// the mark keeps them out of.  us a step, 4B shape at full depth (36 layers, 590 KB a unit and KV head), with the mark / without,
+// prefixes of half to all of so many positions: groups of eight, 320: one 2779 / 2767, two 2991 / 2981, four (140 MB) 3384 / 3349,
+// eight (283 MB) 4175 / 4175, fp16 3862 / 3915; 16 groups of two, 320 (566 MB) 3404 / 3468; four of eight, 1000 (440 MB) 3400 / 3467.
+constexpr int64_t SP_PLAIN_BYTES = 160ll << 20;
+inline int64_t shared_prefix_plain_units(int hd, int n_layers) { return SP_PLAIN_BYTES / ((int64_t)128 * hd * n_layers); }
+inline bool shared_prefix_plain(const std::vector<PrefixGroup>& groups, int MS, int Hkv, int64_t plain_units) {
+  int64_t units = 0;
+  bool again = false;
+  for (const PrefixGroup& g : groups) { units += (int64_t)g.units * Hkv; again |= g.e - g.b > MS; }
+  return again || units <= plain_units;
+}
+
 // fills `words` (shared_prefix_words entries) from per-sequence group leaders and shared page counts.  Groups of one, groups that
 // share less than one unit, and models whose 32 columns hold a single sequence get no tiles.
 inline void shared_prefix_build(int n_seqs, int Hq, int Hkv, const int32_t* leader, const int32_t* shared_pages, int most_tiles,
-                                int32_t* words) {
+                                int64_t plain_units, int32_t* words) {
   const int group = Hq / Hkv, MS = shared_prefix_members(group);
   const int max_tiles = shared_prefix_max_tiles(n_seqs, Hkv);
   const size_t n_words = shared_prefix_words(n_seqs, Hkv);
@@ -111,9 +125,9 @@ inline void shared_prefix_build(int n_seqs, int Hq, int Hkv, const int32_t* lead
   shared_prefix_cut(groups, MS, Hkv, most_chunks, most_tiles);
   // the longest tiles first: a workgroup's second one comes from the other end of the list
   std::stable_sort(groups.begin(), groups.end(), [](const PrefixGroup& x, const PrefixGroup& y) { return x.per > y.per; });
+  words[3] = shared_prefix_plain(groups, MS, Hkv, plain_units);
   int n_tiles = 0;
   for (const PrefixGroup& g : groups) {
-    if (g.e - g.b > MS) words[3] = 1;                  // several tiles read these pages
     for (int sb = g.b; sb < g.e; sb += MS) {
       const int se = sb + MS < g.e ? sb + MS : g.e;
       for (int i = sb; i < se; ++i) {

@@ -12,11 +12,13 @@ pytestmark = pytest.mark.gpu
 # groups, members, pages of the shared prefix (16 positions each) per group in turn: 260 groups x 2 KV heads are 520 tiles of one
 # chunk, more than the 512 workgroups, of 35 and of 3 units; 70 groups: chunks of up to a quarter of 40 units; 9 members of a
 # head group of four, 20 of one of two: more than a tile's columns; 290 pages: chunks of 37 units; 257 groups: more tiles than workgroups
-# at one chunk each, and prefixes of 65 units in four chunks among others of three
+# at one chunk each, and prefixes of 65 units in four chunks among others of three; the last two: more pages than are copied without the
+# streaming mark (both layers' 344 and 281 MB)
 @pytest.mark.parametrize("heads,groups,members,pages,fmt", [((4, 2, 64), 260, 2, (70, 7), "bf16"), ((4, 2, 64), 70, 3, (80, 33, 5), "f16"),
                                                             ((4, 1, 128), 3, 9, (21, 40), "bf16"), ((4, 2, 128), 2, 20, (9, 66), "f16"),
                                                             ((16, 1, 64), 2, 3, (290, 18), "bf16"),
-                                                            ((4, 2, 64), 257, 4, (6,) * 64 + (130,), "bf16")])
+                                                            ((4, 2, 64), 257, 4, (6,) * 64 + (130,), "bf16"),
+                                                            ((4, 2, 64), 300, 2, (70,), "bf16"), ((4, 2, 128), 130, 2, (66,), "f16")])
 def test_prefix_tiles_match_attention_by_row(heads, groups, members, pages, fmt):
     import paper_2604_11554_amd as pkg
     from paper_2604_11554_amd import synthetic

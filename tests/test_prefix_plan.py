@@ -13,12 +13,14 @@ from paper_2604_11554_amd import build
 SOURCE = """
 #include "prefix_plan.h"
 extern "C" int64_t words(int n, int Hkv) { return (int64_t)rlx::shared_prefix_words(n, Hkv); }
+extern "C" int64_t plain_units(int hd, int n_layers) { return rlx::shared_prefix_plain_units(hd, n_layers); }
 extern "C" void range(int lo, int hi, int max_blocks, int* out) {
   const rlx::PrefixRange r = rlx::prefix_range(lo, hi, max_blocks);
   out[0] = r.lo; out[1] = r.hi;
 }
-extern "C" void fill(int n, int Hq, int Hkv, const int32_t* leader, const int32_t* pages, int most_tiles, int32_t* out) {
-  rlx::shared_prefix_build(n, Hq, Hkv, leader, pages, most_tiles, out);
+extern "C" void fill(int n, int Hq, int Hkv, const int32_t* leader, const int32_t* pages, int most_tiles, int64_t plain_units,
+                     int32_t* out) {
+  rlx::shared_prefix_build(n, Hq, Hkv, leader, pages, most_tiles, plain_units, out);
 }
 """
 
@@ -30,11 +32,11 @@ def lib(tmp_path_factory):
     subprocess.run(["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-ftrapv", "-I", build.CSRC, str(d / "plan.cpp"), "-o",
                     str(d / "plan.so")], check=True, capture_output=True)
     l = ctypes.CDLL(str(d / "plan.so"))
-    l.words.restype = ctypes.c_int64
+    l.words.restype = l.plain_units.restype = ctypes.c_int64
     return l
 
 
-def _tiles(lib, groups, Hq, Hkv, most_tiles):
+def _tiles(lib, groups, Hq, Hkv, most_tiles, plain_units=284):
     """groups: (members, pages of every member) -> header, per-sequence arrays, tiles (row, kvh, lo, hi, members)"""
     leader, pages = [], []
     for p in groups:
@@ -43,7 +45,7 @@ def _tiles(lib, groups, Hq, Hkv, most_tiles):
     n, m = len(pages), len(pages) * Hkv
     out = np.full(lib.words(n, Hkv) + 4, -99, np.int32)
     a, b = np.array(leader, np.int32), np.array(pages, np.int32)
-    lib.fill(n, Hq, Hkv, a.ctypes.data_as(ctypes.c_void_p), b.ctypes.data_as(ctypes.c_void_p), most_tiles,
+    lib.fill(n, Hq, Hkv, a.ctypes.data_as(ctypes.c_void_p), b.ctypes.data_as(ctypes.c_void_p), most_tiles, ctypes.c_int64(plain_units),
              out.ctypes.data_as(ctypes.c_void_p))
     assert (out[-4:] == -99).all()
     out = out[:-4]
@@ -86,7 +88,9 @@ def test_every_shared_unit_of_every_member_is_in_one_tile(lib, Hq, Hkv, most_til
                     assert at == units
             n += len(p)
         assert seen == set(range(len(tiles)))
-        assert head[3] == int(any(len(p) > MS and min(p) >= 2 for p in groups))
+        shared = [p for p in groups if len(p) > 1 and min(p) >= 2]
+        few = sum(min(p) // 2 for p in shared) * Hkv <= 284
+        assert head[3] == int(len(shared) > 0 and (few or any(len(p) > MS for p in shared)))
         longest = [0] * (len(tiles) + 1)                      # of the tiles of a run of chunks: the list comes longest first
         firsts = sorted({tile0[i] for i in range(n) if chunks[i]})
         longest = [max(t[3] - t[2] for t in tiles[a:b]) for a, b in zip(firsts, firsts[1:] + [len(tiles)])]
@@ -165,4 +169,14 @@ print(rc, l.rlx_last_error().decode())
 
 def test_no_exception_leaves_the_entry():
     r = subprocess.run([sys.executable, "-c", OUT_OF_MEMORY], cwd=build.HERE + "/..", capture_output=True, text=True)
-    assert r.returncode == 0 and r.stdout.split(" ", 1)[0] == "-2" and "host allocation failed" in r.stdout, (r.returncode, r.stdout, r.stderr)
+    assert r.returncode == 0, (r.returncode, r.stderr)
+    assert r.stdout.split(" ", 1)[0] == "-2" and "host allocation failed" in r.stdout, r.stdout
+
+
+def test_which_pages_are_copied_without_the_streaming_mark(lib):
+    # 160 MB of a unit's 16 KB (heads of 128, 8 KB of 64) per KV head and layer
+    assert [lib.plain_units(hd, n) for hd, n in ((128, 36), (128, 48), (128, 2), (64, 2), (128, 100000))] == [284, 213, 5120, 10240, 0]
+    flag = lambda groups, units: _tiles(lib, groups, 32, 8, 512, units)[0][3]  # noqa: E731
+    assert [flag([[2 * 17] * 8] * 2, u) for u in (271, 272)] == [0, 1]          # 34 units of eight KV heads
+    assert flag([[2 * 17] * 9], 0) == 1                                          # nine members: two tiles read the pages
+    assert flag([[0] * 8], 1000) == 0
