@@ -87,12 +87,12 @@ def test_where_the_norm_goes_into_the_products(lib):
         for d, d_ff, rows in GN.SHAPES:
             assert [inside(T, d, s.q_dim, d_ff, planes) for T in rows] == [int(T <= last[d]) for T in rows], (planes, d)
             assert last[d] in rows and last[d] + 1 in rows
-        # measured: d_model, width of the attention output, d_ff: rows that gain, rows that lose (or gain 0.6 us a layer at most)
-        for d, q_dim, d_ff, yes, no in ((256, 256, 688, 10, 12), (512, 512, 1536, 6, 8), (1024, 2048, 3072, 3, 4), (1536, 1536, 8960, 3, 4),
+        # measured: d_model, width of the attention output, d_ff: rows that gain, rows that lose (or are even)
+        for d, q_dim, d_ff, yes, no in ((256, 256, 688, 10, 12), (512, 512, 1536, 6, 8), (1024, 2048, 3072, 4, 5), (1536, 1536, 8960, 3, 4),
                                         (2048, 2048, 6144, 2, 3), (2560, 4096, 9728, 2, 3), (4096, 4096, 12288, 1, 2)):
             assert [inside(T, d, q_dim, d_ff, planes) for T in (yes, no)] == [1, 0], (planes, d)
     # more planes, fewer rows; never past what the kernels are built for
-    assert [lib.norm_form(4, 512, p, p) for p in (2, 6, 12, 13, 16)] == [1, 1, 1, 0, 0]
+    assert [lib.norm_form(4, 512, p, p) for p in (2, 6, 13, 14, 16)] == [1, 1, 1, 0, 0]
     for T in range(1, 40):
         for d in (16, 48, 256, 1024, 5120, 5136, 20480):
             assert lib.norm_fits(T, d) == int(T <= 16 and T * d <= 5120)
