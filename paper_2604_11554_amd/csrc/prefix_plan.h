@@ -58,8 +58,8 @@ inline std::vector<PrefixGroup> shared_prefix_groups(int n_seqs, const int32_t* 
 // 64 prefixes of 40 units and one of 937: 392 / 129 / 169; 63 and one: 388 / 129 / 161; 70 of 16 to 64 and two of 500: 234 / 99 / 131; 39
 // of 20 and one of 400: 58 / 58 / 59; 32 of 16 to 64: 38 / 38 / 41; 65 of 40: 80 / 80 / 81; 128 of 16 to 64: 118 / 119 / 144; 96 pairs of 8
 // units and one of 937: 369 / 197 / 198.
-// A step at full depth (36 layers), us, one round of tiles at any price / this: pairs, 64 prefixes of 640 positions and one of 15 000 13 290 /
-// 10 140; groups of four, 70 of 256 to 1024 and two of 8000 13 380 / 11 070; groups of eight, 32 of 517 to 2048 9 270 / 9 200.
+// A step at full depth (36 layers), us, one round of tiles at any price / this: pairs, 64 prefixes of 640 positions and one of 15 000
+// 13 290 / 10 140; groups of four, 70 of 256 to 1024 and two of 8000 13 380 / 11 070; groups of eight, 32 of 517 to 2048 9 270 / 9 200.
 inline void shared_prefix_cut(std::vector<PrefixGroup>& groups, int MS, int Hkv, int most_chunks, int most_tiles) {
   constexpr int LEAST = 8;
   auto subgroups = [&](const PrefixGroup& g) { return (int64_t)((g.e - g.b + MS - 1) / MS); };
